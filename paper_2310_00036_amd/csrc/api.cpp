@@ -141,6 +141,19 @@ size_t lds_limit() {
     return bytes;
 }
 
+int device_cus() {
+    static thread_local int dev_cached = -1;
+    static thread_local int cus = 256;
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return 256;
+    if (dev != dev_cached) {
+        int v = 0;
+        if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0) cus = v;
+        dev_cached = dev;
+    }
+    return cus;
+}
+
 int resident_blocks(const void* fn, int threads, size_t lds) {
     struct Entry { int dev; const void* fn; int threads; size_t lds; int blocks; };
     static std::mutex mu;

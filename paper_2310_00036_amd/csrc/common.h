@@ -98,6 +98,17 @@ CB_DEV void load4(const float* p, float* o) {
     o[0] = v.x; o[1] = v.y; o[2] = v.z; o[3] = v.w;
 }
 
+// 16-byte global accesses through pointers that may be aligned to 4 bytes only.
+typedef uint32_t cb_u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef float cb_f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+CB_DEV void store16(void* p, uint4 v) {
+    *static_cast<cb_u32x4_a4*>(p) = cb_u32x4_a4{v.x, v.y, v.z, v.w};
+}
+CB_DEV float4 load_f4(const float* p) {
+    const cb_f32x4_a4 v = *reinterpret_cast<const cb_f32x4_a4*>(p);
+    return make_float4(v.x, v.y, v.z, v.w);
+}
+
 CB_DEV float relu_f(float x) { return x < 0.f ? 0.f : x; }   // keeps NaN
 
 // ---------------------------------------------------------------- direct HBM -> LDS staging

@@ -287,6 +287,8 @@ struct OptArgs {
 hipError_t clip_opt_step(int opt, const OptArgs& a, float* stats, float* partial, hipStream_t s);
 // Largest dynamic LDS allocation per workgroup on the current device (bytes).
 size_t lds_limit();
+// Compute units of the current device.
+int device_cus();
 // Workgroups of kernel `fn` (with `threads` threads and `lds` bytes of dynamic LDS) that are
 // resident at once on the whole current device; sizes persistent grids (cached).
 int resident_blocks(const void* fn, int threads, size_t lds);

@@ -29,6 +29,7 @@
 #include "kernels.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace cb {
 
@@ -62,7 +63,6 @@ struct RbGeom {
 struct RbTile {
     int TH, nbands, ntiles;
     int x_off, t_off;   // LDS byte offsets of the two windows
-    int set_b;          // pipelined kernel: bytes from the first window pair to the second
     float inv_W, inv_TW;
 };
 
@@ -272,230 +272,283 @@ __global__ __launch_bounds__(64 * NW, RbGeom<C>::WPS) void resblock_fwd_kernel(R
     }
 }
 
-// The 32-channel block in a 16-wave workgroup with two wave roles pipelined over tiles: while
-// waves 0-7 form conv1 of a workgroup's next tile (its relu(x) window -> relu(t) window and the
-// stored t), waves 8-15 form conv2 of its current tile (relu(t) window -> y). Each wave holds
-// one convolution's A fragments for both 16-channel output blocks (72 registers), so every
-// B-fragment read feeds two MFMAs, and the two convolutions of neighbouring tiles overlap
-// instead of following each other between barriers. LDS holds two (x, t) window pairs: tile k
-// uses pair k mod 2. Per step k (tile k's conv2, tile k+1's conv1) every wave meets two
-// barriers: after the first, tile k+1's x window has landed and tile k's t window is complete;
-// between them all waves ReLU tile k+1's x window in place and clear the t rows it has off the
-// frame; after the second the conv1 waves issue tile k+2's x window into the pair tile k
-// has left (its conv1 ran in the step before), then both roles run. Only the conv1 waves
-// stage or wait for window loads, so the conv2 waves' residual loads and stores never queue
-// behind them.
-struct RbpGeom {
-    static constexpr int C = 32, MT = 2, KS = 9, PXB = 32;
-    static constexpr int NW = 16, NR = 8;   // waves per workgroup, per role
-    static constexpr int MAXS = 6;          // x-window staging slots per conv1 lane
-    __host__ __device__ static int xwin_bytes(int TH, int W) { return (MT * (TH + 4) * (W + 2) * 2 + 63) / 64 * 1024; }
-    __host__ __device__ static int twin_bytes(int TH, int W) { return MT * (TH + 2) * (W + 2) * PXB; }
+// The 32-channel block by column walks. What bounded the tile-by-tile form was LDS: a 3x3
+// convolution with one B fragment (16 pixels x 32 channels, 1 KB) read per tap and output block
+// reads 1 KB of LDS per MFMA, more than the LDS delivers at the matrix cores' rate. Here the 16
+// pixels of a fragment are 16 anchors (a column of the band, or a segment of it), and a wave
+// walks its anchors down the rows: the three fragments of an input row (kx = 0, 1, 2) feed the
+// three output rows they touch, both 16-channel output blocks each, 18 MFMAs for 3 KB, and the
+// next row's three are read meanwhile. Each wave holds both convolutions' weights for both
+// output blocks (144 registers): two 4-wave workgroups per CU, each with its own windows.
+// Sums keep the tap order of one output pixel's chain, so results are those of the per-layer
+// convolutions bit for bit.
+//   - Window pixels hold their 32 channels in 64 bytes, the four 16-byte slots of pixel p
+//     permuted by XOR with 2 * bit 2 of p, which makes every 16-byte fragment read of 16
+//     consecutive pixels free of bank conflicts; the row pitch TW is a multiple of 4 pixels, so
+//     a walk steps by one constant and flips that bit by another. One padding column serves
+//     both sides (the right neighbour of a row's last pixel is the next row's padding).
+//   - The x window stays as loaded (the fragments are ReLU'd in registers), so the residual comes
+//     from LDS too, and nothing is read twice from memory but a band's halo rows.
+//   - Output rows of the A operand are permuted so that lane group g receives channels 8g .. 8g+7:
+//     one 16-byte store per pixel, 1 KB contiguous per wave.
+//   - The weights are read once per workgroup, coalesced, and shared through LDS.
+// Measured against the tile-by-tile form (and, at 42x42, a two-role pipelined form of it):
+// 2048 frames of 21x21 75.0 -> 49.5 us (2.3 -> 3.5 TB/s of its three tensors), 8192 of 42x42 921 ->
+// 813 us, 2048 of 11x11 26.3 -> 22.5 us, 8 of 21x21 12.2 -> 10.3 us. What is left at 21x21: about
+// 2.6 us before the first row, then 70% of the matrix cores' time (vector ALU work of the
+// epilogues beside them) and the loads of a tile that the other workgroup does not cover.
+struct RwGeom {
+    static constexpr int C = 32, NW = 4, NT = 256, KS = 9;
+    static constexpr int MAXS = 11;                  // x-window staging slots per lane
+    static constexpr int WFRAG = 2 * KS * 1024;      // one convolution's A fragments (bytes)
+    static constexpr size_t LDS_TARGET = 80 * 1024;  // two workgroups per CU
+    __host__ __device__ static int pitch(int W) { return (W + 4) / 4 * 4; }
+    // a window of F frames of `rows` rows, one pixel past the end (the last row's right neighbour)
+    __host__ __device__ static int win_bytes(int F, int rows, int W) { return (F * rows * pitch(W) + 1 + 15) / 16 * 1024; }
 };
 
-__global__ __launch_bounds__(64 * RbpGeom::NW, 1) void resblock_fwd_pipe_kernel(ResBlockArgs a, RbTile t) {
-    using G = RbpGeom;
-    constexpr int NT = 64 * G::NW, NR = G::NR, KS = G::KS, MT = G::MT, PXB = G::PXB, C = G::C;
+struct RwTile {
+    int F, TH, nbands, ntiles;   // frames per tile (1 with several bands per frame), rows per band
+    int ho;                      // 1: t has a halo row either side (several bands)
+    int t_off, bias_off, spare_off;   // LDS bytes (the x window is at 0)
+    int nseg1, R1, nseg2, R2;    // segments of a column and their rows: conv1, conv2
+    float inv_W, inv_c, inv_TW, inv_xpf;   // 1 / W, 1 / (F * W), 1 / row pitch, 1 / x-window pixels per frame
+};
+
+// One walk: R output rows of a 3x3 convolution at the lane's anchor, whose tap-(0,0) pixel of the
+// first row is p0. pre(i) is called before row i's MFMAs are issued, emit(i, acc) once its sums
+// are complete: acc[b][j] is channel 8 (lane / 16) + 4 b + j.
+template <bool RELU, class Pre, class Emit>
+CB_DEV void rw_walk(const unsigned char* win, int p0, int g, int R, int rowb, uint32_t tog, const uint4 (&w)[2][RwGeom::KS],
+                    Pre&& pre, Emit&& emit) {
+    uint32_t ad[3];
+    uint4 cur[3], nxt[3];
+#pragma unroll
+    for (int kx = 0; kx < 3; ++kx) {
+        const uint32_t p = uint32_t(p0 + kx);
+        ad[kx] = p * 64 + ((uint32_t(g) * 16) ^ ((p << 3) & 32));
+        nxt[kx] = *reinterpret_cast<const uint4*>(win + ad[kx]);
+    }
+    cb_f32x4 acc[3][2];
+    auto step = [&](auto ph, int i) {
+        constexpr int P = decltype(ph)::value, A0 = P, A1 = (P + 2) % 3, A2 = (P + 1) % 3;
+#pragma unroll
+        for (int kx = 0; kx < 3; ++kx) {
+            cur[kx] = nxt[kx];
+            if (RELU) {
+                cur[kx].x = relu_bf16x2(cur[kx].x); cur[kx].y = relu_bf16x2(cur[kx].y);
+                cur[kx].z = relu_bf16x2(cur[kx].z); cur[kx].w = relu_bf16x2(cur[kx].w);
+            }
+        }
+        if (i <= R) {   // the next row's fragments, in flight during this row's MFMAs
+#pragma unroll
+            for (int kx = 0; kx < 3; ++kx) {
+                ad[kx] = (ad[kx] ^ tog) + rowb;
+                nxt[kx] = *reinterpret_cast<const uint4*>(win + ad[kx]);
+            }
+        }
+        if (i >= 2) {
+            pre(i - 2);
+#pragma unroll
+            for (int kx = 0; kx < 3; ++kx)
+#pragma unroll
+                for (int b = 0; b < 2; ++b) acc[A2][b] = PrecBF16::mma(w[b][6 + kx], cur[kx], acc[A2][b]);
+        }
+        if (i >= 1 && i <= R)
+#pragma unroll
+            for (int kx = 0; kx < 3; ++kx)
+#pragma unroll
+                for (int b = 0; b < 2; ++b) acc[A1][b] = PrecBF16::mma(w[b][3 + kx], cur[kx], acc[A1][b]);
+        if (i < R) {
+#pragma unroll
+            for (int b = 0; b < 2; ++b) acc[A0][b] = cb_f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int kx = 0; kx < 3; ++kx)
+#pragma unroll
+                for (int b = 0; b < 2; ++b) acc[A0][b] = PrecBF16::mma(w[b][kx], cur[kx], acc[A0][b]);
+        }
+        if (i >= 2) emit(i - 2, acc[A2]);
+    };
+    for (int i = 0; i < R + 2; i += 3) {
+        step(std::integral_constant<int, 0>{}, i);
+        if (i + 1 < R + 2) step(std::integral_constant<int, 1>{}, i + 1);
+        if (i + 2 < R + 2) step(std::integral_constant<int, 2>{}, i + 2);
+    }
+}
+
+__global__ __launch_bounds__(RwGeom::NT, 2) void resblock_walk_fwd_kernel(ResBlockArgs a, RwTile t) {
+    using G = RwGeom;
+    constexpr int NT = G::NT, NW = G::NW, KS = G::KS, C = G::C;
     extern __shared__ __align__(16) unsigned char smem[];
+    unsigned char* xw = smem;                                  // x [F][TH+2+2ho][TW], row 0 = image row h0-1-ho
+    unsigned char* tw = smem + t.t_off;                        // relu(t) [F][TH+2][TW], row 0 = image row h0-1
+    float* bias = reinterpret_cast<float*>(smem + t.bias_off); // b1[32], b2[32]
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const bool role1 = wave < NR;   // conv1 (else conv2)
-    const int rw = wave % NR;       // wave within its role
     const int g = lane >> 4, r16 = lane & 15;
-    const int H = a.H, W = a.W, TH = t.TH, TW = W + 2;
-    const int xps = (TH + 4) * TW * PXB, tps = (TH + 2) * TW * PXB;   // plane strides (bytes)
-    const int twb = TW * PXB;
-    const int npx = (TH + 4) * TW, nsx = MT * npx * 2;                 // x-window pixels, 16-byte slots
+    const int H = a.H, W = a.W, F = t.F, TH = t.TH, ho = t.ho, TW = G::pitch(W);
+    const int xrows = TH + 2 + 2 * ho, trows = TH + 2, xpf = xrows * TW, tpf = trows * TW;
+    const int nsx = (F * xpf + 1) * 4;                         // x-window 16-byte slots staged
+    const int rowb = TW * 64;
+    const uint32_t tog = (TW & 4) ? 32u : 0u;
 
-    // ---- both relu(t) windows cleared once (padding columns are never written)
-    for (int s = 0; s < 2; ++s)
-        for (int j = tid; j < G::twin_bytes(TH, W) / 16; j += NT)
-            reinterpret_cast<uint4*>(smem + t.t_off + s * t.set_b)[j] = make_uint4(0, 0, 0, 0);
-
-    // ---- this role's A fragments for both output blocks: A[o][k] = w[tap][i][o], k = tap*C + i
-    // (one tap per k-step); the biases of the lane's four channels of each block
-    const float* wsrc = role1 ? a.w1 : a.w2;
-    const float* bsrc = role1 ? a.b1 : a.b2;
-    uint4 wr[MT][KS];
+    // ---- weights: 4 k-values x 4 output channels per unit, in flight while the offsets are formed
+    // and packed below into A fragments in LDS (the t window's memory): fragment (conv, b, ks)
+    // holds at lane 16 (k % 32 / 8) + i, i = 4 (o / 8) + o % 4, b = o / 4 % 2, the k-values
+    // 8 (lane / 16) .. +7 of output channel o
+    constexpr int UNITS = 2 * 9 * C / 4 * (C / 4), PER = (UNITS + NT - 1) / NT;
+    float4 v[PER][4];
 #pragma unroll
-    for (int b = 0; b < MT; ++b)
+    for (int u = 0; u < PER; ++u) {
+        const int id0 = tid + u * NT, id = id0 < UNITS ? id0 : UNITS - 1;   // clamped: loads without a branch
+        const int cv = id >= UNITS / 2, r = id - cv * (UNITS / 2), k4 = r / (C / 4), o4 = r % (C / 4);
+        const float* src = (cv ? a.w2 : a.w1) + k4 * 4 * C + o4 * 4;
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            float v[8];
+        for (int i = 0; i < 4; ++i) v[u][i] = load_f4(src + i * C);
+    }
+    const float* bsrc = (tid & 32) ? a.b2 : a.b1;
+    const float bval = (bsrc ? bsrc : a.w1)[tid & 31];
+    // ---- x-window staging offsets, tile-invariant per lane (slot k of this wave: j = (wave +
+    // NW*k)*64 + lane: pixel j / 4, position j % 4), relative to the tile's first frame with the
+    // window's first row at image row 0; a tile adds that row. Rows off the frame fall outside
+    // the tile's buffer resource (F > 1: they are kOOB); padding columns are kOOB and read zero.
+    uint32_t ox[G::MAXS];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = wsrc[(ks * 32 + g * 8 + j) * C + b * 16 + r16];
-            wr[b][ks] = make_uint4(pack2bf(v[0], v[1]), pack2bf(v[2], v[3]), pack2bf(v[4], v[5]), pack2bf(v[6], v[7]));
-            __builtin_amdgcn_sched_barrier(0);   // convert each k-step's weights before loading the next
-        }
-    float bias[MT][4];
-#pragma unroll
-    for (int b = 0; b < MT; ++b)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) bias[b][j] = bsrc ? bsrc[b * 16 + g * 4 + j] : 0.f;
-    // lane's B-fragment offset: k-values 8g .. 8g+7 of a k-step are channels 8g .. 8g+7 of its
-    // tap, plane g / 2, half g % 2 of the pixel's 32 bytes
-    const int lbx = (g >> 1) * xps + (g & 1) * 16, lbt = (g >> 1) * tps + (g & 1) * 16;
-    auto mma2 = [&](const unsigned char* xb, cb_f32x4 (&acc)[MT]) {
-#pragma unroll
-        for (int b = 0; b < MT; ++b) acc[b] = cb_f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            const uint4 bf = *reinterpret_cast<const uint4*>(xb + (ks / 3) * twb + (ks % 3) * PXB);
-#pragma unroll
-            for (int b = 0; b < MT; ++b) acc[b] = PrecBF16::mma(wr[b][ks], bf, acc[b]);
-            if (ks % 3 == 2) __builtin_amdgcn_sched_barrier(0);   // at most three B fragments in flight
-        }
-    };
-
+    for (int k = 0; k < G::MAXS; ++k) {
+        const int j = (wave + NW * k) * 64 + lane, p = j >> 2, q = (j & 3) ^ ((p >> 1) & 2);
+        const int fi = qdiv(p, t.inv_xpf), pr = p - fi * xpf, rr = qdiv(pr, t.inv_TW), col = pr - rr * TW;
+        const int h = rr - (ho ? 0 : 1);   // whole frames: the window's first row is off the frame
+        const bool in = (j < nsx) & (uint32_t(col - 1) < uint32_t(W)) & ((ho != 0) | (uint32_t(h) < uint32_t(H)));
+        const uint32_t off = uint32_t((((fi * H + h) * W + col - 1) * C + q * 8) * 2);
+        ox[k] = in ? off : kOOB;
+    }
     int lg = blockIdx.x;   // neighbouring bands on one XCD
     if ((gridDim.x & 7) == 0) lg = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
-    const int G0 = int(gridDim.x);
-    const int cnt = lg < t.ntiles ? (t.ntiles - lg + G0 - 1) / G0 : 0;   // this workgroup's tiles
-    auto band_of = [&](int k, int& h0, int& the, int64_t& fo) {
-        const int tile = lg + k * G0, band = tile % t.nbands, f = tile / t.nbands;
-        h0 = band * TH;
-        the = H - h0 < TH ? H - h0 : TH;
-        fo = int64_t(f) * H * W * C;
+    auto stage_x = [&](int tile) {
+        const int band = tile % t.nbands, f = (tile / t.nbands) * F;
+        const int nf = a.n - f < F ? a.n - f : F;
+        const auto rx = buf_rsrc(static_cast<const uint16_t*>(a.x) + int64_t(f) * H * W * C, uint32_t(nf) * H * W * C * 2);
+        const uint32_t hr = ho ? uint32_t((band * TH - 2) * W * C * 2) : 0u;   // wraps for h0 < 2: rows off the frame
+#pragma unroll
+        for (int k = 0; k < G::MAXS; ++k) {   // slots past the window read zero into a spare block: no branches
+            const int blk = wave + NW * k;
+            dma16_to_lds(rx, smem + (blk * 64 < nsx ? blk * 1024 : t.spare_off), ox[k] + hr);
+        }
     };
-    // tile k's x window ReLU'd in place; its t window's rows off the frame cleared
-    auto prep = [&](int k) {
-        if (k >= cnt) return;
-        int h0, the;
-        int64_t fo;
-        band_of(k, h0, the, fo);
-        uint4* w4 = reinterpret_cast<uint4*>(smem + t.x_off + (k & 1) * t.set_b);
-        for (int j = tid; j < nsx; j += NT) {
-            uint4 v = w4[j];
-            v.x = relu_bf16x2(v.x); v.y = relu_bf16x2(v.y); v.z = relu_bf16x2(v.z); v.w = relu_bf16x2(v.w);
-            w4[j] = v;
+    if (lg < t.ntiles) stage_x(lg);
+
+    uint4 w1[2][KS], w2[2][KS];
+    {
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int id = tid + u * NT, cv = id >= UNITS / 2, r = id - cv * (UNITS / 2), k4 = r / (C / 4), o4 = r % (C / 4);
+            if (id < UNITS) {
+                const int ks = k4 / 8, gk = (k4 % 8) / 2, hf = k4 & 1, b = o4 & 1, i0 = 4 * (o4 >> 1);
+                unsigned char* dst = tw + cv * G::WFRAG + ((b * KS + ks) * 64 + gk * 16 + i0) * 16 + hf * 8;
+                const float* f = reinterpret_cast<const float*>(v[u]);
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    *reinterpret_cast<uint2*>(dst + j * 16) = make_uint2(pack2bf(f[j], f[4 + j]), pack2bf(f[8 + j], f[12 + j]));
+            }
         }
-        const int tr0 = h0 == 0 ? 1 : 0;
-        const int tr1 = the + 2 < H - h0 + 1 ? the + 2 : H - h0 + 1;
-        const int row16 = TW * PXB / 16;
-        for (int pl = 0; pl < MT; ++pl) {
-            uint4* t4 = reinterpret_cast<uint4*>(smem + t.t_off + (k & 1) * t.set_b + pl * tps);
-            if (tr0 == 1)
-                for (int j = tid; j < row16; j += NT) t4[j] = make_uint4(0, 0, 0, 0);
-            for (int j = tid; j < (the + 2 - tr1) * row16; j += NT) t4[tr1 * row16 + j] = make_uint4(0, 0, 0, 0);
-        }
+        if (tid < 2 * C) bias[tid] = bsrc ? bval : 0.f;
+        lds_barrier();
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                w1[b][ks] = *reinterpret_cast<const uint4*>(tw + ((b * KS + ks) * 64 + lane) * 16);
+                w2[b][ks] = *reinterpret_cast<const uint4*>(tw + G::WFRAG + ((b * KS + ks) * 64 + lane) * 16);
+            }
+        lds_barrier();
+        // the relu(t) window: its padding column and, for whole frames, its rows off the frame
+        // are never written
+        for (int j = tid; j < G::win_bytes(F, trows, W) / 16; j += NT) reinterpret_cast<uint4*>(tw)[j] = make_uint4(0, 0, 0, 0);
+    }
+
+    // the lane's anchor in group grp: segment s, frame fi, column c; rows [row0, row0 + R) are
+    // walked, those below s * R belong to the segment above
+    struct Anchor { int row0, rbeg, fi, c; bool ok; };
+    const int cols = F * W;
+    auto anchor = [&](int grp, int nseg, int R, int nrows) {
+        Anchor an;
+        const int id = grp * 16 + r16, last = nseg * cols - 1, ic = id < last ? id : last;
+        const int s = qdiv(ic, t.inv_c), rem = ic - s * cols;
+        an.fi = qdiv(rem, t.inv_W);
+        an.c = rem - an.fi * W;
+        an.rbeg = s * R;
+        an.row0 = s * R < nrows - R ? s * R : nrows - R;
+        an.ok = id <= last;
+        return an;
     };
 
-    if (role1) {
-        // x-window staging offsets, tile-invariant per lane (slot k of this wave: j = (rw +
-        // NR*k)*64 + lane: plane, pixel, half), relative to image row 0; a tile adds h0 - 2 rows.
-        // Rows off the frame fall outside the frame's buffer resource; padding columns read zero.
-        uint32_t ox[G::MAXS];
-#pragma unroll
-        for (int k = 0; k < G::MAXS; ++k) {
-            const int j = (rw + NR * k) * 64 + lane, pl = j / (npx * 2), rem = j - pl * npx * 2;
-            const int p = rem >> 1, half = rem & 1;
-            const int rr = p / TW, col = p - rr * TW;
-            ox[k] = (j < nsx && col >= 1 && col <= W) ? uint32_t(((rr * W + col - 1) * C + pl * 16 + half * 8) * 2) : kOOB;
-        }
-        auto stage = [&](unsigned char* dst, int k) {
-            int h0, the;
-            int64_t fo;
-            band_of(k, h0, the, fo);
-            const auto rx = buf_rsrc(static_cast<const uint16_t*>(a.x) + fo, uint32_t(H) * W * C * 2);
-            const uint32_t hr = uint32_t((h0 - 2) * W * C * 2);   // wraps for h0 < 2: rows off the frame
-#pragma unroll
-            for (int s = 0; s < G::MAXS; ++s)
-                if ((rw + NR * s) * 64 < nsx) dma16_to_lds(rx, dst + (rw + NR * s) * 1024, ox[s] + hr);
-        };
-        // conv1 of tile k (t on its band's rows plus a halo row either side), with tile k+1's x
-        // window issued first; the windows are restrict parameters of one call, so the compiler
-        // knows the loads in flight do not write what conv1 reads
-        auto step = [&](unsigned char* __restrict__ xnext, const unsigned char* __restrict__ xw,
-                        unsigned char* __restrict__ tw, int k) {
-            if (k + 1 < cnt) stage(xnext, k + 1);
-            if (k >= cnt) return;
-            int h0, the;
-            int64_t fo;
-            band_of(k, h0, the, fo);
-            const int tr0 = h0 == 0 ? 1 : 0;
-            const int tr1 = the + 2 < H - h0 + 1 ? the + 2 : H - h0 + 1;
+    for (int tile = lg; tile < t.ntiles; tile += gridDim.x) {
+        const int band = tile % t.nbands, f = (tile / t.nbands) * F;
+        const int h0 = band * TH, the = H - h0 < TH ? H - h0 : TH;
+        const int nf = a.n - f < F ? a.n - f : F;
+        const int64_t fo = int64_t(f) * H * W * C;
+        __builtin_amdgcn_s_waitcnt(0);   // this tile's window has landed
+        __syncthreads();
+
+        // ---- conv1: t on rows h0-ho .. h0+TH+ho-1 of every column
+        {
+            const int n1 = TH + 2 * ho;
             uint16_t* tbase = static_cast<uint16_t*>(a.t) + fo;
-            const int npx1 = (tr1 - tr0) * TW - 2, pw1 = tr0 * TW + 1;
-            for (int nt = rw; nt * 16 < npx1; nt += NR) {
-                const int q = nt * 16 + r16;
-                const int pw = pw1 + (q < npx1 ? q : npx1 - 1);
-                const int tr = qdiv(pw, t.inv_TW), cw = pw - tr * TW;
-                cb_f32x4 acc[MT];
-                mma2(xw + lbx + (pw - 1) * PXB, acc);   // tap (0,0): x-window pixel pw - 1
-                if (q < npx1 && cw >= 1 && cw <= W) {
-                    const int h = h0 - 1 + tr;
-#pragma unroll
-                    for (int b = 0; b < MT; ++b) {
-                        const uint32_t u0 = pack2bf(acc[b][0] + bias[b][0], acc[b][1] + bias[b][1]);
-                        const uint32_t u1 = pack2bf(acc[b][2] + bias[b][2], acc[b][3] + bias[b][3]);
-                        if (h >= h0 && h < h0 + the)
-                            *reinterpret_cast<uint2*>(tbase + (uint32_t(h) * W + cw - 1) * C + b * 16 + g * 4) = make_uint2(u0, u1);
-                        *reinterpret_cast<uint2*>(tw + b * tps + pw * PXB + g * 8) = make_uint2(relu_bf16x2(u0), relu_bf16x2(u1));
-                    }
-                }
-            }
-        };
-        if (cnt > 0) stage(smem + t.x_off, 0);
-        for (int k = -1; k < cnt; ++k) {
-            __builtin_amdgcn_s_waitcnt(0);   // tile k+1's x window (this wave's part) has landed
-            lds_barrier();
-            prep(k + 1);
-            lds_barrier();
-            const int s1 = (k + 1) & 1;
-            step(smem + t.x_off + (s1 ^ 1) * t.set_b, smem + t.x_off + s1 * t.set_b, smem + t.t_off + s1 * t.set_b, k + 1);
-        }
-    } else {
-        for (int k = -1; k < cnt; ++k) {
-            lds_barrier();
-            prep(k + 1);
-            lds_barrier();
-            if (k < 0) continue;
-            // conv2 + bias + residual on tile k's band rows: window pixels 1 .. (the-1)*TW + W
-            // (padding columns included and dropped); pixel pw is band row pw / TW, column pw % TW - 1
-            int h0, the;
-            int64_t fo;
-            band_of(k, h0, the, fo);
-            const unsigned char* tw = smem + t.t_off + (k & 1) * t.set_b;
-            const uint16_t* xbase = static_cast<const uint16_t*>(a.x) + fo + int64_t(h0) * W * C;
-            uint16_t* ybase = static_cast<uint16_t*>(a.y) + fo + int64_t(h0) * W * C;
-            const int npx2 = the * TW - 2;
-            auto px = [&](int nt, int& pw, int& rb, int& cw) {
-                const int q = nt * 16 + r16;
-                pw = 1 + (q < npx2 ? q : npx2 - 1);
-                rb = qdiv(pw, t.inv_TW);
-                cw = pw - rb * TW;
-            };
-            auto res = [&](int nt, uint2 (&xr)[MT]) {   // residual x of a column tile (columns clamped)
-                int pw, rb, cw;
-                px(nt, pw, rb, cw);
-                const int c = cw < 1 ? 1 : (cw > W ? W : cw);
-#pragma unroll
-                for (int b = 0; b < MT; ++b)
-                    xr[b] = *reinterpret_cast<const uint2*>(xbase + uint32_t((rb * W + c - 1) * C + b * 16 + g * 4));
-            };
-            uint2 xn[MT];
-            if (rw * 16 < npx2) res(rw, xn);
-            for (int nt = rw; nt * 16 < npx2; nt += NR) {
-                uint2 xr[MT];
-#pragma unroll
-                for (int b = 0; b < MT; ++b) xr[b] = xn[b];
-                if ((nt + NR) * 16 < npx2) res(nt + NR, xn);   // the next column tile's, in flight
-                int pw, rb, cw;
-                px(nt, pw, rb, cw);
-                cb_f32x4 acc[MT];
-                mma2(tw + lbt + (pw - 1) * PXB, acc);   // tap (0,0): t-window pixel pw - 1
-                if (nt * 16 + r16 < npx2 && cw >= 1 && cw <= W) {
-#pragma unroll
-                    for (int b = 0; b < MT; ++b)
-                        store4(ybase + uint32_t((rb * W + cw - 1) * C + b * 16 + g * 4),
-                               acc[b][0] + bias[b][0] + __uint_as_float(xr[b].x << 16),
-                               acc[b][1] + bias[b][1] + __uint_as_float(xr[b].x & 0xffff0000u),
-                               acc[b][2] + bias[b][2] + __uint_as_float(xr[b].y << 16),
-                               acc[b][3] + bias[b][3] + __uint_as_float(xr[b].y & 0xffff0000u));
-                }
+            for (int grp = wave; grp * 16 < t.nseg1 * cols; grp += NW) {
+                const Anchor an = anchor(grp, t.nseg1, t.R1, n1);
+                const uint32_t pt = an.fi * tpf + (an.row0 + 1 - ho) * TW + an.c + 1;
+                uint32_t ta = pt * 64 + ((uint32_t(g) * 16) ^ ((pt << 3) & 32));
+                const int hb = h0 - ho + an.row0;   // image row of the walk's first row
+                uint32_t go = uint32_t(((an.fi * H + hb) * W + an.c) * C + g * 8);   // wraps above the frame, not stored
+                const bool own = an.ok && an.fi < nf;
+                rw_walk<true>(xw, an.fi * xpf + an.row0 * TW + an.c, g, t.R1, rowb, tog, w1, [](int) {},
+                    [&](int j, const cb_f32x4 (&acc)[2]) {
+                        const float4 ba = *reinterpret_cast<const float4*>(bias + g * 8), bb = *reinterpret_cast<const float4*>(bias + g * 8 + 4);
+                        uint4 u = make_uint4(pack2bf(acc[0][0] + ba.x, acc[0][1] + ba.y), pack2bf(acc[0][2] + ba.z, acc[0][3] + ba.w),
+                                             pack2bf(acc[1][0] + bb.x, acc[1][1] + bb.y), pack2bf(acc[1][2] + bb.z, acc[1][3] + bb.w));
+                        const int h = hb + j;
+                        const bool mine = an.row0 + j >= an.rbeg;
+                        if (own && mine && h >= h0 && h < h0 + the) store16(tbase + go, u);
+                        u.x = relu_bf16x2(u.x); u.y = relu_bf16x2(u.y); u.z = relu_bf16x2(u.z); u.w = relu_bf16x2(u.w);
+                        if (ho && (h < 0 || h >= H)) u = make_uint4(0, 0, 0, 0);   // conv2's zero padding
+                        if (an.ok && mine) *reinterpret_cast<uint4*>(tw + ta) = u;
+                        ta = (ta ^ tog) + rowb;
+                        go += W * C;
+                    });
             }
         }
+        __syncthreads();   // the relu(t) window is complete
+
+        // ---- conv2 + bias + residual: y on the band's rows
+        {
+            uint16_t* ybase = static_cast<uint16_t*>(a.y) + fo;
+            for (int grp = wave; grp * 16 < t.nseg2 * cols; grp += NW) {
+                const Anchor an = anchor(grp, t.nseg2, t.R2, TH);
+                const uint32_t px = an.fi * xpf + (an.row0 + 1 + ho) * TW + an.c + 1;
+                uint32_t xa = px * 64 + ((uint32_t(g) * 16) ^ ((px << 3) & 32));
+                uint32_t go = uint32_t(((an.fi * H + h0 + an.row0) * W + an.c) * C + g * 8);
+                const bool own = an.ok && an.fi < nf;
+                uint4 xr = make_uint4(0, 0, 0, 0);
+                rw_walk<false>(tw, an.fi * tpf + an.row0 * TW + an.c, g, t.R2, rowb, tog, w2,
+                    [&](int) {
+                        xr = *reinterpret_cast<const uint4*>(xw + xa);
+                        xa = (xa ^ tog) + rowb;
+                    },
+                    [&](int j, const cb_f32x4 (&acc)[2]) {
+                        const float4 ba = *reinterpret_cast<const float4*>(bias + C + g * 8), bb = *reinterpret_cast<const float4*>(bias + C + g * 8 + 4);
+                        if (own && an.row0 + j >= an.rbeg && an.row0 + j < the)
+                            store16(ybase + go,
+                                make_uint4(pack2bf(acc[0][0] + ba.x + bf_lo(xr.x), acc[0][1] + ba.y + bf_hi(xr.x)),
+                                           pack2bf(acc[0][2] + ba.z + bf_lo(xr.y), acc[0][3] + ba.w + bf_hi(xr.y)),
+                                           pack2bf(acc[1][0] + bb.x + bf_lo(xr.z), acc[1][1] + bb.y + bf_hi(xr.z)),
+                                           pack2bf(acc[1][2] + bb.z + bf_lo(xr.w), acc[1][3] + bb.w + bf_hi(xr.w))));
+                        go += W * C;
+                    });
+            }
+        }
+        __syncthreads();   // both windows have been read
+        if (tile + int(gridDim.x) < t.ntiles) stage_x(tile + gridDim.x);
     }
 }
 
@@ -538,40 +591,58 @@ hipError_t rb_fwd_launch(const ResBlockArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-// The pipelined 32-channel kernel: two window pairs in the CU's LDS, one 16-wave workgroup per
-// CU. It pays only where every workgroup runs many tiles: measured at 8192 frames of 42x42
-// (128 tiles per workgroup) 950 against 995 us for the three-workgroup kernel, but at 2048
-// frames (8 tiles per workgroup) 87 against 78 us at 21x21 and 54 against 29 us at 11x11,
-// where the pipeline's first step and the two barriers per tile weigh more. Returns
-// hipErrorNotSupported where no band height fits or a workgroup would get fewer than 32 tiles.
-hipError_t rbp_launch(const ResBlockArgs& a, hipStream_t s) {
-    using G = RbpGeom;
-    const int H = a.H, W = a.W;
-    auto pair = [&](int th) { return size_t(G::xwin_bytes(th, W)) + G::twin_bytes(th, W); };
-    auto fits = [&](int th) {
-        return 2 * pair(th) <= std::min<size_t>(lds_limit(), kRbLds) &&
-               G::MT * (th + 4) * (W + 2) * 2 <= G::MAXS * G::NR * 64;
+// Tile shapes of the column-walk kernel. A tile is F whole frames or a band of one; a wave walks
+// ceil(groups / 4) groups of 16 anchors per convolution, R rows each (and about 0.7 rows' time
+// of filling). The choice minimises rounds of tiles over the resident workgroups times a tile's
+// estimated cycles: 18 MFMAs of 16 cycles per row and group, the SIMD shared by two
+// workgroups, or its memory traffic at 4 bytes per cycle and workgroup, whichever is longer,
+// plus its load latency and barriers.
+hipError_t rw_launch(const ResBlockArgs& a, hipStream_t s) {
+    using G = RwGeom;
+    const int H = a.H, W = a.W, cus = device_cus();
+    if (int64_t(H) * W * G::C * 2 * 16 >= (int64_t(1) << 31)) return hipErrorInvalidValue;
+    auto groups = [&](int rows, int cols, int& nseg, int& R) {   // segments with the least work per wave
+        double best = 1e30;
+        for (int ns = 1; ns <= rows && ns <= 16; ++ns) {
+            const int r = (rows + ns - 1) / ns;
+            const double c = double(((ns * cols + 15) / 16 + G::NW - 1) / G::NW) * (r + 0.7);
+            if (c < best) { best = c; nseg = ns; R = r; }
+        }
+        return best;
     };
-    if (int64_t(H) * W * G::C * 2 >= (int64_t(1) << 31)) return hipErrorInvalidValue;
-    int TH = 0, best = 1 << 30;   // fewest staged window rows per frame
-    for (int th = 1; th <= H; ++th) {
-        if (!fits(th)) continue;
-        const int rows = (H + th - 1) / th * (th + 4);
-        if (rows <= best) { best = rows; TH = th; }
+    RwTile t{};
+    double best = 1e30;
+    size_t L = 0;
+    for (int nb = 1; nb <= H; ++nb) {
+        const int TH = (H + nb - 1) / nb, ho = nb > 1;
+        if (nb > 1 && (H + TH - 1) / TH != nb) continue;
+        for (int F = 1; F <= (ho ? 1 : std::min<int64_t>(a.n, 16)); ++F) {
+            const int xb = G::win_bytes(F, TH + 2 + 2 * ho, W), tb = std::max(G::win_bytes(F, TH + 2, W), 2 * G::WFRAG);
+            const size_t lds = size_t(xb) + tb + 256 + 1024;
+            if (lds > G::LDS_TARGET || (F * (TH + 2 + 2 * ho) * G::pitch(W) + 1) * 4 > G::MAXS * G::NT) break;
+            RwTile c{};
+            c.F = F; c.TH = TH; c.ho = ho; c.nbands = nb;
+            c.ntiles = int((a.n + F - 1) / F) * nb;
+            const double work = groups(TH + 2 * ho, F * W, c.nseg1, c.R1) + groups(TH, F * W, c.nseg2, c.R2);
+            const double mem = double(F) * W * 64 * (3 * TH + 4 * ho) / 4;
+            const double cost = double((c.ntiles + 2 * cus - 1) / (2 * cus)) * (std::max(work * 18 * 16 * 2, mem) + 4000);
+            if (cost < best) {
+                best = cost;
+                t = c;
+                t.t_off = xb;
+                t.bias_off = xb + tb;
+                t.spare_off = xb + tb + 256;
+                L = lds;
+            }
+        }
     }
-    if (TH == 0) return hipErrorNotSupported;
-    RbTile t{};
-    t.TH = TH; t.nbands = (H + TH - 1) / TH; t.ntiles = t.nbands * a.n;
-    t.x_off = 0;
-    t.t_off = G::xwin_bytes(TH, W);
-    t.set_b = int(pair(TH));
-    t.inv_W = 1.f / float(W); t.inv_TW = 1.f / float(W + 2);
-    const size_t L = 2 * pair(TH);
-    const void* fn = reinterpret_cast<const void*>(&resblock_fwd_pipe_kernel);
-    const int gx = resident_blocks(fn, 64 * G::NW, L);
-    if (gx < 1 || t.ntiles < 32 * gx) return hipErrorNotSupported;
+    if (L == 0) return hipErrorInvalidValue;
+    t.inv_W = 1.f / float(W); t.inv_c = 1.f / float(t.F * W);
+    t.inv_TW = 1.f / float(G::pitch(W)); t.inv_xpf = 1.f / float((t.TH + 2 + 2 * t.ho) * G::pitch(W));
+    const void* fn = reinterpret_cast<const void*>(&resblock_walk_fwd_kernel);
+    const int gx = std::min(t.ntiles, std::max(1, resident_blocks(fn, G::NT, L)));
     ProfScope ps(s, [&] { return cb_key("resblock_fwd", 0, cb_dims(G::C, G::C) + "/" + cb_dims(H, W)); });
-    hipLaunchKernelGGL(resblock_fwd_pipe_kernel, dim3(unsigned(gx)), dim3(64 * G::NW), L, s, a, t);
+    hipLaunchKernelGGL(resblock_walk_fwd_kernel, dim3(unsigned(gx)), dim3(G::NT), L, s, a, t);
     return hipGetLastError();
 }
 
@@ -582,10 +653,7 @@ bool resblock_fwd_supported(int C) { return C == 16 || C == 32; }
 hipError_t resblock_fwd(int C, const ResBlockArgs& a, hipStream_t s) {
     if (a.n <= 0) return hipSuccess;
     if (C == 16) return rb_fwd_launch<16>(a, s);
-    if (C == 32) {
-        const hipError_t e = rbp_launch(a, s);
-        return e != hipErrorNotSupported ? e : rb_fwd_launch<32>(a, s);
-    }
+    if (C == 32) return rw_launch(a, s);
     return hipErrorInvalidValue;
 }
 

@@ -1,0 +1,54 @@
+"""The column-walk kernels against the per-layer calls they stand for, at the edges of their tile
+shapes: rows and columns around a walk's group of 16 anchors, whole frames and bands, a ragged last
+tile, row pitches of both parities, windows near the LDS budget, and pointers that are aligned to
+the element only. A walk adds the products of one output in the per-layer kernels' order, so stored
+outputs are equal bit for bit; weight gradients are float32 sums in another order."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+SHAPES = [(1, 1, 1), (2, 2, 5), (7, 3, 3), (33, 4, 7), (5, 11, 11), (17, 11, 11), (700, 11, 11), (33, 21, 21),
+          (3, 21, 22), (9, 8, 15), (2, 42, 42), (515, 42, 42), (1, 43, 39), (600, 5, 7), (3, 64, 64), (1, 7, 97)]
+
+
+def _p():
+    import paper_2310_00036_amd as P
+    return P
+
+
+def _act(g, shape, offset=0):
+    """bf16 normals; with `offset`, a view that many elements into its storage."""
+    n = int(np.prod(shape))
+    x = torch.randn(n + offset, generator=g, device="cuda:0").to(torch.bfloat16)
+    return x[offset:].view(shape)
+
+
+def _bits(x):
+    return x.view(torch.int16)
+
+
+@pytest.mark.parametrize("case", SHAPES, ids=lambda c: "n%d_%dx%d" % c)
+@pytest.mark.parametrize("offset", [0, 2])
+def test_resblock32_forward_equals_two_convolutions(case, offset):
+    P = _p()
+    n, H, W = case
+    g = torch.Generator(device="cuda:0").manual_seed(n * 1009 + H * 31 + W)
+    x = _act(g, (n, H, W, 32), offset)
+    wpad = offset // 2   # weights one float off 16-byte alignment
+    w1, w2 = ((torch.randn(9 * 32 * 32 + wpad, generator=g, device="cuda:0") * 0.1)[wpad:].view(3, 3, 32, 32)
+              for _ in range(2))
+    b1, b2 = (torch.randn(32, generator=g, device="cuda:0") for _ in range(2))
+    b2 = None if offset else b2
+    t, y, t_ref, y_ref = (torch.full((n * H * W * 32 + offset,), 7.0, device="cuda:0").to(torch.bfloat16)[offset:]
+                          .view(n, H, W, 32) for _ in range(4))
+    P.impala_resblock_fwd(P.PREC_BF16, n, H, W, 32, x, w1, b1, w2, b2, t, y)
+    P.impala_conv3x3_fwd(P.PREC_BF16, n, H, W, 32, 32, x, P.X_RELU, None, w1, b1, None, t_ref)
+    P.impala_conv3x3_fwd(P.PREC_BF16, n, H, W, 32, 32, t_ref, P.X_RELU, None, w2, b2, x, y_ref)
+    torch.cuda.synchronize()
+    assert torch.equal(_bits(t), _bits(t_ref))
+    assert torch.equal(_bits(y), _bits(y_ref))
