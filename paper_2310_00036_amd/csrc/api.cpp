@@ -793,8 +793,7 @@ impala_status_t impala_resblock_bwd(impala_prec_t prec, int64_t n, int32_t H, in
     a.partial = static_cast<float*>(ws); a.n = int(n); a.H = H; a.W = W;
     PendingReduce out[2];
     hipError_t he = resblock_bwd(C, a, stream, out);
-    if (he == hipSuccess) he = flush_pending_reduce(out[0], stream);
-    if (he == hipSuccess) he = flush_pending_reduce(out[1], stream);
+    if (he == hipSuccess) he = flush_pending_reduces(out[0], out[1], stream);
     return hip_status(he, "impala_resblock_bwd");
 }
 

@@ -6,6 +6,8 @@
 #include <stdint.h>
 
 #define CB_DEV __device__ __forceinline__
+// On lambdas too large for the inliner's own choice: a call would put their captures in memory.
+#define CB_INLINE_LAMBDA __attribute__((always_inline))
 
 #include <string>
 
@@ -132,6 +134,26 @@ typedef short cb_s16x2 __attribute__((ext_vector_type(2)));
 CB_DEV uint32_t relu_bf16x2(uint32_t u) {
     return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(cb_s16x2, u),
                                                                   cb_s16x2{0, 0}));
+}
+
+// 16 bytes of a buffer resource: loads past its end read zero, stores past its end are dropped.
+typedef uint32_t cb_u32x4 __attribute__((ext_vector_type(4)));
+CB_DEV uint4 buf_load16(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+    const cb_u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
+    return make_uint4(v[0], v[1], v[2], v[3]);
+}
+CB_DEV void buf_store16(__amdgpu_buffer_rsrc_t r, uint32_t off, uint4 v) {
+    __builtin_amdgcn_raw_buffer_store_b128(cb_u32x4{v.x, v.y, v.z, v.w}, r, off, 0, 0);
+}
+
+// v where the bf16 value in the same half of k is > 0, else +0 (k NaN: +0), two halves at once in
+// four packed 16-bit instructions: the patterns above zero are 1 .. 0x7f80, so with `one` =
+// 0x00010001 and `top` = 0x7f807f80, min(sat(top - (k - 1)), 1) is 1 for them and 0 otherwise.
+CB_DEV uint32_t pos_mask16x2(uint32_t k, uint32_t v, uint32_t one, uint32_t top) {
+    uint32_t r;
+    asm("v_pk_sub_u16 %0, %1, %2\n\tv_pk_sub_u16 %0, %3, %0 clamp\n\tv_pk_min_u16 %0, %0, %2\n\tv_pk_mul_lo_u16 %0, %4, %0"
+        : "=&v"(r) : "v"(k), "v"(one), "v"(top), "v"(v));
+    return r;
 }
 
 // One DMA lane: 4 or 16 bytes at byte offset off of the resource -> LDS at lds + lane * size

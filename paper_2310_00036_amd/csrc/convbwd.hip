@@ -1113,8 +1113,7 @@ size_t conv3x3_bwd_partial_floats(int cin, int cout) {
 hipError_t conv3x3_bwd(int cin, int cout, int mode, const ConvBwdArgs& a, hipStream_t s, PendingReduce* deferred) {
     if (deferred) deferred->nparts = 0;
     if (a.n <= 0) {
-        const hipError_t e = flush_pending_reduce(a.pend, s);
-        return e != hipSuccess ? e : flush_pending_reduce(a.pend2, s);
+        return flush_pending_reduces(a.pend, a.pend2, s);
     }
     const int add = a.add != nullptr, pdy = a.arg != nullptr;
 #define CB_B(CI, CO, MD, AD, PD) \

@@ -83,7 +83,7 @@ struct PendingReduce {
     float scale;
 };
 // Launches the standalone fixed-order reduce of a pending partial sum (no-op if none).
-hipError_t flush_pending_reduce(const PendingReduce& r, hipStream_t s);
+hipError_t flush_pending_reduces(const PendingReduce& a, const PendingReduce& b, hipStream_t s);
 
 // ---- backward of a whole residual block, t = conv_a(relu(x)) + b_a, y = x + conv_b(relu(t)) + b_b
 // (bf16): dx = conv_a^T(conv_b^T(dy) * [t > 0]) * [x > 0] + dy and both weight gradients
@@ -137,7 +137,7 @@ struct CbTile {
 bool conv3x3_bwd_supported(int cin, int cout, int mode, int add, int pooled);
 size_t conv3x3_bwd_partial_floats(int cin, int cout);
 // deferred: when non-NULL the launch's own partial sum is not reduced; it is described there
-// for a later launch (conv3x3_bwd / pool_wgrad_u8 via .pend, or flush_pending_reduce).
+// for a later launch (conv3x3_bwd / pool_wgrad_u8 via .pend, or flush_pending_reduces).
 hipError_t conv3x3_bwd(int cin, int cout, int mode, const ConvBwdArgs& a, hipStream_t s,
                        PendingReduce* deferred = nullptr);
 // Fixed-order sum of nparts bf16 weight-gradient partials laid out [mt*(NB+1) + nb]

@@ -271,8 +271,7 @@ hipError_t run_backward(const NetPlan& p, const float* params, const uint8_t* ob
         return e;
     };
     auto flush = [&]() -> hipError_t {
-        hipError_t e = flush_pending_reduce(pend[0], s);
-        if (e == hipSuccess) e = flush_pending_reduce(pend[1], s);
+        const hipError_t e = flush_pending_reduces(pend[0], pend[1], s);
         pend[0].nparts = 0;
         pend[1].nparts = 0;
         return e;

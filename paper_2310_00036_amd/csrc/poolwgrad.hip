@@ -346,8 +346,7 @@ size_t pool_wgrad_u8_partial_floats(int cout) {
 
 hipError_t pool_wgrad_u8(int cout, const PoolWgArgs& a, hipStream_t s) {
     if (a.n <= 0) {
-        const hipError_t e = flush_pending_reduce(a.pend, s);
-        return e != hipSuccess ? e : flush_pending_reduce(a.pend2, s);
+        return flush_pending_reduces(a.pend, a.pend2, s);
     }
     if (cout == 16) return pw_launch<16>(a, s);
     if (cout == 32) return pw_launch<32>(a, s);

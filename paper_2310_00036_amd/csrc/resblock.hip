@@ -27,9 +27,9 @@
 // fragments for it in registers, loaded once per workgroup, so LDS holds only the windows.
 #include "common.h"
 #include "kernels.h"
+#include "walk.h"
 
 #include <algorithm>
-#include <type_traits>
 
 namespace cb {
 
@@ -282,11 +282,8 @@ __global__ __launch_bounds__(64 * NW, RbGeom<C>::WPS) void resblock_fwd_kernel(R
 // output blocks (144 registers): two 4-wave workgroups per CU, each with its own windows.
 // Sums keep the tap order of one output pixel's chain, so results are those of the per-layer
 // convolutions bit for bit.
-//   - Window pixels hold their 32 channels in 64 bytes, the four 16-byte slots of pixel p
-//     permuted by XOR with 2 * bit 2 of p, which makes every 16-byte fragment read of 16
-//     consecutive pixels free of bank conflicts; the row pitch TW is a multiple of 4 pixels, so
-//     a walk steps by one constant and flips that bit by another. One padding column serves
-//     both sides (the right neighbour of a row's last pixel is the next row's padding).
+//   - One padding column serves both sides (the right neighbour of a row's last pixel is the next
+//     row's padding), and the windows' layout (walk.h) is free of bank conflicts.
 //   - The x window stays as loaded (the fragments are ReLU'd in registers), so the residual comes
 //     from LDS too, and nothing is read twice from memory but a band's halo rows.
 //   - Output rows of the A operand are permuted so that lane group g receives channels 8g .. 8g+7:
@@ -302,80 +299,17 @@ struct RwGeom {
     static constexpr int MAXS = 11;                  // x-window staging slots per lane
     static constexpr int WFRAG = 2 * KS * 1024;      // one convolution's A fragments (bytes)
     static constexpr size_t LDS_TARGET = 80 * 1024;  // two workgroups per CU
-    __host__ __device__ static int pitch(int W) { return (W + 4) / 4 * 4; }
-    // a window of F frames of `rows` rows, one pixel past the end (the last row's right neighbour)
-    __host__ __device__ static int win_bytes(int F, int rows, int W) { return (F * rows * pitch(W) + 1 + 15) / 16 * 1024; }
 };
 
 struct RwTile {
     int F, TH, nbands, ntiles;   // frames per tile (1 with several bands per frame), rows per band
     int ho;                      // 1: t has a halo row either side (several bands)
     int t_off, bias_off, spare_off;   // LDS bytes (the x window is at 0)
-    int nseg1, R1, nseg2, R2;    // segments of a column and their rows: conv1, conv2
+    int R, nseg1, nseg2;         // rows per walk (the kernel's R), segments of a column: conv1, conv2
     float inv_W, inv_c, inv_TW, inv_xpf;   // 1 / W, 1 / (F * W), 1 / row pitch, 1 / x-window pixels per frame
 };
 
-// One walk: R output rows of a 3x3 convolution at the lane's anchor, whose tap-(0,0) pixel of the
-// first row is p0. pre(i) is called before row i's MFMAs are issued, emit(i, acc) once its sums
-// are complete: acc[b][j] is channel 8 (lane / 16) + 4 b + j.
-template <bool RELU, class Pre, class Emit>
-CB_DEV void rw_walk(const unsigned char* win, int p0, int g, int R, int rowb, uint32_t tog, const uint4 (&w)[2][RwGeom::KS],
-                    Pre&& pre, Emit&& emit) {
-    uint32_t ad[3];
-    uint4 cur[3], nxt[3];
-#pragma unroll
-    for (int kx = 0; kx < 3; ++kx) {
-        const uint32_t p = uint32_t(p0 + kx);
-        ad[kx] = p * 64 + ((uint32_t(g) * 16) ^ ((p << 3) & 32));
-        nxt[kx] = *reinterpret_cast<const uint4*>(win + ad[kx]);
-    }
-    cb_f32x4 acc[3][2];
-    auto step = [&](auto ph, int i) {
-        constexpr int P = decltype(ph)::value, A0 = P, A1 = (P + 2) % 3, A2 = (P + 1) % 3;
-#pragma unroll
-        for (int kx = 0; kx < 3; ++kx) {
-            cur[kx] = nxt[kx];
-            if (RELU) {
-                cur[kx].x = relu_bf16x2(cur[kx].x); cur[kx].y = relu_bf16x2(cur[kx].y);
-                cur[kx].z = relu_bf16x2(cur[kx].z); cur[kx].w = relu_bf16x2(cur[kx].w);
-            }
-        }
-        if (i <= R) {   // the next row's fragments, in flight during this row's MFMAs
-#pragma unroll
-            for (int kx = 0; kx < 3; ++kx) {
-                ad[kx] = (ad[kx] ^ tog) + rowb;
-                nxt[kx] = *reinterpret_cast<const uint4*>(win + ad[kx]);
-            }
-        }
-        if (i >= 2) {
-            pre(i - 2);
-#pragma unroll
-            for (int kx = 0; kx < 3; ++kx)
-#pragma unroll
-                for (int b = 0; b < 2; ++b) acc[A2][b] = PrecBF16::mma(w[b][6 + kx], cur[kx], acc[A2][b]);
-        }
-        if (i >= 1 && i <= R)
-#pragma unroll
-            for (int kx = 0; kx < 3; ++kx)
-#pragma unroll
-                for (int b = 0; b < 2; ++b) acc[A1][b] = PrecBF16::mma(w[b][3 + kx], cur[kx], acc[A1][b]);
-        if (i < R) {
-#pragma unroll
-            for (int b = 0; b < 2; ++b) acc[A0][b] = cb_f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int kx = 0; kx < 3; ++kx)
-#pragma unroll
-                for (int b = 0; b < 2; ++b) acc[A0][b] = PrecBF16::mma(w[b][kx], cur[kx], acc[A0][b]);
-        }
-        if (i >= 2) emit(i - 2, acc[A2]);
-    };
-    for (int i = 0; i < R + 2; i += 3) {
-        step(std::integral_constant<int, 0>{}, i);
-        if (i + 1 < R + 2) step(std::integral_constant<int, 1>{}, i + 1);
-        if (i + 2 < R + 2) step(std::integral_constant<int, 2>{}, i + 2);
-    }
-}
-
+template <int R>
 __global__ __launch_bounds__(RwGeom::NT, 2) void resblock_walk_fwd_kernel(ResBlockArgs a, RwTile t) {
     using G = RwGeom;
     constexpr int NT = G::NT, NW = G::NW, KS = G::KS, C = G::C;
@@ -387,11 +321,10 @@ __global__ __launch_bounds__(RwGeom::NT, 2) void resblock_walk_fwd_kernel(ResBlo
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = lane >> 4, r16 = lane & 15;
-    const int H = a.H, W = a.W, F = t.F, TH = t.TH, ho = t.ho, TW = G::pitch(W);
+    const int H = a.H, W = a.W, F = t.F, TH = t.TH, ho = t.ho, TW = walk_pitch(W);
     const int xrows = TH + 2 + 2 * ho, trows = TH + 2, xpf = xrows * TW, tpf = trows * TW;
     const int nsx = (F * xpf + 1) * 4;                         // x-window 16-byte slots staged
     const int rowb = TW * 64;
-    const uint32_t tog = (TW & 4) ? 32u : 0u;
 
     // ---- weights: 4 k-values x 4 output channels per unit, in flight while the offsets are formed
     // and packed below into A fragments in LDS (the t window's memory): fragment (conv, b, ks)
@@ -416,8 +349,9 @@ __global__ __launch_bounds__(RwGeom::NT, 2) void resblock_walk_fwd_kernel(ResBlo
     uint32_t ox[G::MAXS];
 #pragma unroll
     for (int k = 0; k < G::MAXS; ++k) {
-        const int j = (wave + NW * k) * 64 + lane, p = j >> 2, q = (j & 3) ^ ((p >> 1) & 2);
+        const int j = (wave + NW * k) * 64 + lane, p = j >> 2;
         const int fi = qdiv(p, t.inv_xpf), pr = p - fi * xpf, rr = qdiv(pr, t.inv_TW), col = pr - rr * TW;
+        const int q = (j & 3) ^ ((col >> 1) & 2);
         const int h = rr - (ho ? 0 : 1);   // whole frames: the window's first row is off the frame
         const bool in = (j < nsx) & (uint32_t(col - 1) < uint32_t(W)) & ((ho != 0) | (uint32_t(h) < uint32_t(H)));
         const uint32_t off = uint32_t((((fi * H + h) * W + col - 1) * C + q * 8) * 2);
@@ -464,23 +398,12 @@ __global__ __launch_bounds__(RwGeom::NT, 2) void resblock_walk_fwd_kernel(ResBlo
         lds_barrier();
         // the relu(t) window: its padding column and, for whole frames, its rows off the frame
         // are never written
-        for (int j = tid; j < G::win_bytes(F, trows, W) / 16; j += NT) reinterpret_cast<uint4*>(tw)[j] = make_uint4(0, 0, 0, 0);
+        for (int j = tid; j < walk_win_bytes(F, trows, W) / 16; j += NT) reinterpret_cast<uint4*>(tw)[j] = make_uint4(0, 0, 0, 0);
     }
 
-    // the lane's anchor in group grp: segment s, frame fi, column c; rows [row0, row0 + R) are
-    // walked, those below s * R belong to the segment above
-    struct Anchor { int row0, rbeg, fi, c; bool ok; };
     const int cols = F * W;
-    auto anchor = [&](int grp, int nseg, int R, int nrows) {
-        Anchor an;
-        const int id = grp * 16 + r16, last = nseg * cols - 1, ic = id < last ? id : last;
-        const int s = qdiv(ic, t.inv_c), rem = ic - s * cols;
-        an.fi = qdiv(rem, t.inv_W);
-        an.c = rem - an.fi * W;
-        an.rbeg = s * R;
-        an.row0 = s * R < nrows - R ? s * R : nrows - R;
-        an.ok = id <= last;
-        return an;
+    auto anchor = [&](int grp, int nseg, int nrows) {
+        return walk_anchor(grp * 16 + r16, cols, W, nseg, R, nrows, t.inv_c, t.inv_W);
     };
 
     for (int tile = lg; tile < t.ntiles; tile += gridDim.x) {
@@ -496,13 +419,12 @@ __global__ __launch_bounds__(RwGeom::NT, 2) void resblock_walk_fwd_kernel(ResBlo
             const int n1 = TH + 2 * ho;
             uint16_t* tbase = static_cast<uint16_t*>(a.t) + fo;
             for (int grp = wave; grp * 16 < t.nseg1 * cols; grp += NW) {
-                const Anchor an = anchor(grp, t.nseg1, t.R1, n1);
-                const uint32_t pt = an.fi * tpf + (an.row0 + 1 - ho) * TW + an.c + 1;
-                uint32_t ta = pt * 64 + ((uint32_t(g) * 16) ^ ((pt << 3) & 32));
+                const WalkAnchor an = anchor(grp, t.nseg1, n1);
+                uint32_t ta = uint32_t(an.fi * tpf + (an.row0 + 1 - ho) * TW + an.c + 1) * 64 + walk_ch(an.c + 1, g * 16);
                 const int hb = h0 - ho + an.row0;   // image row of the walk's first row
                 uint32_t go = uint32_t(((an.fi * H + hb) * W + an.c) * C + g * 8);   // wraps above the frame, not stored
                 const bool own = an.ok && an.fi < nf;
-                rw_walk<true>(xw, an.fi * xpf + an.row0 * TW + an.c, g, t.R1, rowb, tog, w1, [](int) {},
+                walk_conv32<R, true>(xw, an.fi * xpf + an.row0 * TW + an.c, an.c, g, rowb, w1, [] {},
                     [&](int j, const cb_f32x4 (&acc)[2]) {
                         const float4 ba = *reinterpret_cast<const float4*>(bias + g * 8), bb = *reinterpret_cast<const float4*>(bias + g * 8 + 4);
                         uint4 u = make_uint4(pack2bf(acc[0][0] + ba.x, acc[0][1] + ba.y), pack2bf(acc[0][2] + ba.z, acc[0][3] + ba.w),
@@ -513,7 +435,7 @@ __global__ __launch_bounds__(RwGeom::NT, 2) void resblock_walk_fwd_kernel(ResBlo
                         u.x = relu_bf16x2(u.x); u.y = relu_bf16x2(u.y); u.z = relu_bf16x2(u.z); u.w = relu_bf16x2(u.w);
                         if (ho && (h < 0 || h >= H)) u = make_uint4(0, 0, 0, 0);   // conv2's zero padding
                         if (an.ok && mine) *reinterpret_cast<uint4*>(tw + ta) = u;
-                        ta = (ta ^ tog) + rowb;
+                        ta += rowb;
                         go += W * C;
                     });
             }
@@ -524,16 +446,15 @@ __global__ __launch_bounds__(RwGeom::NT, 2) void resblock_walk_fwd_kernel(ResBlo
         {
             uint16_t* ybase = static_cast<uint16_t*>(a.y) + fo;
             for (int grp = wave; grp * 16 < t.nseg2 * cols; grp += NW) {
-                const Anchor an = anchor(grp, t.nseg2, t.R2, TH);
-                const uint32_t px = an.fi * xpf + (an.row0 + 1 + ho) * TW + an.c + 1;
-                uint32_t xa = px * 64 + ((uint32_t(g) * 16) ^ ((px << 3) & 32));
+                const WalkAnchor an = anchor(grp, t.nseg2, TH);
+                uint32_t xa = uint32_t(an.fi * xpf + (an.row0 + 1 + ho) * TW + an.c + 1) * 64 + walk_ch(an.c + 1, g * 16);
                 uint32_t go = uint32_t(((an.fi * H + h0 + an.row0) * W + an.c) * C + g * 8);
                 const bool own = an.ok && an.fi < nf;
                 uint4 xr = make_uint4(0, 0, 0, 0);
-                rw_walk<false>(tw, an.fi * tpf + an.row0 * TW + an.c, g, t.R2, rowb, tog, w2,
-                    [&](int) {
+                walk_conv32<R, false>(tw, an.fi * tpf + an.row0 * TW + an.c, an.c, g, rowb, w2,
+                    [&] {
                         xr = *reinterpret_cast<const uint4*>(xw + xa);
-                        xa = (xa ^ tog) + rowb;
+                        xa += rowb;
                     },
                     [&](int j, const cb_f32x4 (&acc)[2]) {
                         const float4 ba = *reinterpret_cast<const float4*>(bias + C + g * 8), bb = *reinterpret_cast<const float4*>(bias + C + g * 8 + 4);
@@ -601,48 +522,49 @@ hipError_t rw_launch(const ResBlockArgs& a, hipStream_t s) {
     using G = RwGeom;
     const int H = a.H, W = a.W, cus = device_cus();
     if (int64_t(H) * W * G::C * 2 * 16 >= (int64_t(1) << 31)) return hipErrorInvalidValue;
-    auto groups = [&](int rows, int cols, int& nseg, int& R) {   // segments with the least work per wave
+    static thread_local WalkPlans<RwTile> plans;
+    const auto* plan = plans.find(a.n, H, W, cus);
+    if (!plan) {
+        RwTile t{};
         double best = 1e30;
-        for (int ns = 1; ns <= rows && ns <= 16; ++ns) {
-            const int r = (rows + ns - 1) / ns;
-            const double c = double(((ns * cols + 15) / 16 + G::NW - 1) / G::NW) * (r + 0.7);
-            if (c < best) { best = c; nseg = ns; R = r; }
-        }
-        return best;
-    };
-    RwTile t{};
-    double best = 1e30;
-    size_t L = 0;
-    for (int nb = 1; nb <= H; ++nb) {
-        const int TH = (H + nb - 1) / nb, ho = nb > 1;
-        if (nb > 1 && (H + TH - 1) / TH != nb) continue;
-        for (int F = 1; F <= (ho ? 1 : std::min<int64_t>(a.n, 16)); ++F) {
-            const int xb = G::win_bytes(F, TH + 2 + 2 * ho, W), tb = std::max(G::win_bytes(F, TH + 2, W), 2 * G::WFRAG);
-            const size_t lds = size_t(xb) + tb + 256 + 1024;
-            if (lds > G::LDS_TARGET || (F * (TH + 2 + 2 * ho) * G::pitch(W) + 1) * 4 > G::MAXS * G::NT) break;
-            RwTile c{};
-            c.F = F; c.TH = TH; c.ho = ho; c.nbands = nb;
-            c.ntiles = int((a.n + F - 1) / F) * nb;
-            const double work = groups(TH + 2 * ho, F * W, c.nseg1, c.R1) + groups(TH, F * W, c.nseg2, c.R2);
-            const double mem = double(F) * W * 64 * (3 * TH + 4 * ho) / 4;
-            const double cost = double((c.ntiles + 2 * cus - 1) / (2 * cus)) * (std::max(work * 18 * 16 * 2, mem) + 4000);
-            if (cost < best) {
-                best = cost;
-                t = c;
-                t.t_off = xb;
-                t.bias_off = xb + tb;
-                t.spare_off = xb + tb + 256;
-                L = lds;
+        size_t L = 0;
+        for (int nb = 1; nb <= H; ++nb) {
+            const int TH = (H + nb - 1) / nb, ho = nb > 1;
+            if (nb > 1 && (H + TH - 1) / TH != nb) continue;
+            for (int F = 1; F <= (ho ? 1 : std::min<int64_t>(a.n, 16)); ++F) {
+                const int xb = walk_win_bytes(F, TH + 2 + 2 * ho, W), tb = std::max(walk_win_bytes(F, TH + 2, W), 2 * G::WFRAG);
+                const size_t lds = size_t(xb) + tb + 256 + 1024;
+                if (lds > G::LDS_TARGET || xb > G::MAXS * G::NW * 1024) break;
+                RwTile c{};
+                c.F = F; c.TH = TH; c.ho = ho; c.nbands = nb;
+                c.ntiles = int((a.n + F - 1) / F) * nb;
+                const double mem = double(F) * W * 64 * (3 * TH + 4 * ho) / 4;
+                for (c.R = 1; c.R <= std::min(TH, kWalkMaxR); ++c.R) {
+                    const double work = walk_rows(TH + 2 * ho, F * W, 16, G::NW, c.R, c.nseg1) + walk_rows(TH, F * W, 16, G::NW, c.R, c.nseg2);
+                    const double cost = double((c.ntiles + 2 * cus - 1) / (2 * cus)) * (std::max(work * 18 * 16 * 2, mem) + 4000);
+                    if (cost < best) {
+                        best = cost;
+                        t = c;
+                        t.t_off = xb;
+                        t.bias_off = xb + tb;
+                        t.spare_off = xb + tb + 256;
+                        L = lds;
+                    }
+                }
             }
         }
+        if (L == 0) return hipErrorInvalidValue;
+        t.inv_W = 1.f / float(W); t.inv_c = 1.f / float(t.F * W);
+        t.inv_TW = 1.f / float(walk_pitch(W)); t.inv_xpf = 1.f / float((t.TH + 2 + 2 * t.ho) * walk_pitch(W));
+        plan = plans.put({a.n, H, W, cus, t, L});
     }
-    if (L == 0) return hipErrorInvalidValue;
-    t.inv_W = 1.f / float(W); t.inv_c = 1.f / float(t.F * W);
-    t.inv_TW = 1.f / float(G::pitch(W)); t.inv_xpf = 1.f / float((t.TH + 2 + 2 * t.ho) * G::pitch(W));
-    const void* fn = reinterpret_cast<const void*>(&resblock_walk_fwd_kernel);
-    const int gx = std::min(t.ntiles, std::max(1, resident_blocks(fn, G::NT, L)));
-    ProfScope ps(s, [&] { return cb_key("resblock_fwd", 0, cb_dims(G::C, G::C) + "/" + cb_dims(H, W)); });
-    hipLaunchKernelGGL(resblock_walk_fwd_kernel, dim3(unsigned(gx)), dim3(G::NT), L, s, a, t);
+    walk_dispatch(plan->t.R, [&](auto r) {
+        constexpr int R = decltype(r)::value;
+        const void* fn = reinterpret_cast<const void*>(&resblock_walk_fwd_kernel<R>);
+        const int gx = std::min(plan->t.ntiles, std::max(1, resident_blocks(fn, G::NT, plan->lds)));
+        ProfScope ps(s, [&] { return cb_key("resblock_fwd", 0, cb_dims(G::C, G::C) + "/" + cb_dims(H, W)); });
+        hipLaunchKernelGGL(resblock_walk_fwd_kernel<R>, dim3(unsigned(gx)), dim3(G::NT), plan->lds, s, a, plan->t);
+    });
     return hipGetLastError();
 }
 

@@ -23,6 +23,7 @@
 // later launch (deterministic, no atomics).
 #include "common.h"
 #include "kernels.h"
+#include "walk.h"
 
 #include <algorithm>
 #include <type_traits>
@@ -344,354 +345,297 @@ __global__ __launch_bounds__(64 * NW, RbbGeom<C>::WPS) void resblock_bwd_kernel(
     }
 }
 
-// The 32-channel block backward with specialised waves. Every wave forming dt and dx for one
-// 16-channel block reads each B fragment for that block alone and holds both convs'
-// weight-gradient accumulators beside the input-gradient weights. Here waves 0-3 form dt and
-// dx for both channel blocks (each B fragment feeding two MFMAs; 144 registers of weights)
-// and waves 4-7 both weight gradients (conv_b's while dt is formed, conv_a's once it is
-// complete), each for a quarter of the column blocks.
-template <int C, int NW>
-__global__ __launch_bounds__(64 * NW, RbbGeom<C>::WPS) void resblock_bwd_spec_kernel(ResBwdArgs a, RbbTile t) {
-    using G = RbbGeom<C>;
-    constexpr int NT = 64 * NW;
-    constexpr int DSL = G::DSL, DYP = G::DYP, XPB = G::XPB, XSL = G::XSL;
-    constexpr int MT = G::MT, KSD = G::KSD, NB = G::NB, NBB = G::NBB;
-    // weight gradients: waves 0 .. NW/2-1 form conv_b's, the others conv_a's, each wave TPW
-    // column blocks, so each dy / dt fragment is read by half the waves
-    constexpr int NWG = NW / 2;
-    constexpr int TPW = (NBB + NWG - 1) / NWG;   // weight-gradient column blocks per wave
-    constexpr int CB16 = C / 16;
-    static_assert(C == 32 && NW == 8 && NWG == 4, "32 channels: four input-gradient and four weight-gradient waves");
-    constexpr int DB = MT;   // dx / dt channel blocks per input-gradient wave (all of them)
+// The 32-channel block backward by column walks (walk.h), in one 8-wave workgroup per CU with
+// two wave roles. Waves 0-3 form dt, then dx, for both channel blocks (both convolutions' weights:
+// 144 registers; each input fragment feeds 18 MFMAs); waves 4-7 form conv_b's weight gradient
+// while dt is formed and conv_a's beside dx, each wave one 16x16 channel block of all nine taps (18
+// tap tiles and the bias columns: 80 registers; each x fragment feeds three rows of dy). A tile (F whole frames, or a band of one) has two phases:
+//   a: dt = conv_b^T(dy) * [t > 0] into the dt window; dWb from dy and t; x and dy's own pixels
+//      once more (for the skip term; an L2 hit) are being staged;
+//   b: dx = conv_a^T(dt) * [x > 0] + dy; dWa from dt and x; the next tile's dy and t are staged.
+// No phase reads what is being staged in it, so loads overlap all of the work with one set of
+// windows in LDS.
+// Measured against a form that read every fragment once per tap and block (its own two roles
+// bound by LDS and by the vector instructions beside the MFMAs): 2048 frames of 21x21 138 -> 101 us,
+// of 11x11 56 -> 45 us, 8192 of 42x42 1590 -> 1490 us, 640 of 11x11 with its reduce 36 -> 25 us.
+// What bounds it: a SIMD's MFMAs (about 270 of 16 cycles per phase at 21x21) and the vector
+// instructions of its two waves, which overlap 1.6 to 1; then staging and barriers.
+struct RbwGeom {
+    static constexpr int C = 32, NW = 8, NT = 512, NS = 4;   // NS: waves per role
+    static constexpr int NBB = 19, PSTRIDE = 2 * NBB * 256;  // partial: [co block][tap x ci block, bias][co][ci]
+    static constexpr int MAXD = 6, MAXX = 6, MAXK = 5;       // staging slots per lane: dy; t / x; skip term
+    static constexpr int WFRAG = 2 * 9 * 1024;               // one convolution's A fragments (bytes)
+};
+struct RbwTile {
+    int F, TH, nbands, ntiles;
+    int ho;                      // 1: dt has a halo row either side (several bands)
+    int t_off, x_off, dt_off, sk_off, dt_bytes;   // LDS bytes (the dy window is at 0)
+    int R, nsegt, nsegx, nsegw;  // rows per walk (the kernel's R), segments of a column: dt, dx, weight gradients
+    int pset;                    // floats per partial set (one per convolution)
+    float inv_W, inv_c, inv_TW, inv_dpf, inv_xpf;    // 1 / W, F * W, row pitch, window pixels per frame (dy; t, x, dt)
+};
 
+// One window of a tile, HBM -> LDS: block wave + NW*k of 64 16-byte slots from the lane's offset
+// off[k], shifted by `row` rows.
+template <int N>
+CB_DEV void rbw_stage(const ResBwdArgs& a, const RbwTile& t, const void* src, unsigned char* win, int ns,
+                      const uint32_t (&off)[N], int wave, int tile, int row) {
+    constexpr int C = RbwGeom::C, NW = RbwGeom::NW;
+    const int band = tile % t.nbands, f = (tile / t.nbands) * t.F;
+    const int nf = a.n - f < t.F ? a.n - f : t.F, fel = a.H * a.W * C;
+    const auto r = buf_rsrc(static_cast<const uint16_t*>(src) + int64_t(f) * fel, uint32_t(nf) * fel * 2);
+    const uint32_t hr = uint32_t((band * t.TH - row) * a.W * C * 2);   // wraps above the frame
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        const int blk = wave + NW * k;
+        if (blk * 64 < ns) dma16_to_lds(r, win + blk * 1024, off[k] + hr);
+    }
+}
+
+// Waits for this wave's loads, then relu of the blocks it staged of a window, in place: before
+// the barrier that shows them to the other waves, so it takes no barrier of its own. Both convs
+// read relu'd inputs, and relu(v) > 0 exactly where v > 0, so the masks read them too.
+template <int N>
+CB_DEV void rbw_landed(unsigned char* win, int ns, int wave, int lane) {
+    __builtin_amdgcn_s_waitcnt(0);
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        const int blk = wave + RbwGeom::NW * k;
+        if (blk * 64 < ns) {
+            uint4* p = reinterpret_cast<uint4*>(win + blk * 1024) + lane;
+            *p = relu8(*p);
+        }
+    }
+}
+
+template <int R>
+__global__ __launch_bounds__(RbwGeom::NT, 2) void resblock_bwd_walk_kernel(ResBwdArgs a, RbwTile t) {
+    using G = RbwGeom;
+    constexpr int NT = G::NT, NW = G::NW, NS = G::NS, C = G::C;
     extern __shared__ __align__(16) unsigned char smem[];
-    unsigned char* zero = smem;                   // 64 zero bytes
-    unsigned char* dyw = smem + t.dy_off;         // dy [TH+4][W+2], row 0 = image row h0-2
-    unsigned char* tw = smem + t.t_off + XPB;     // relu(t) [TH+2][W+2], row 0 = h0-1, guard pixels
-    unsigned char* xw = smem + t.x_off + XPB;     // relu(x) [TH+2][W+2], likewise
-    unsigned char* dtw = smem + t.dt_off;         // dt [TH+2][W+2], row 0 = h0-1
+    unsigned char* dyw = smem;               // dy [F][TH+2+2ho][TW], row 0 = image row h0-1-ho
+    unsigned char* tw = smem + t.t_off;      // relu(t) [F][TH+2][TW], row 0 = image row h0-1
+    unsigned char* xw = smem + t.x_off;      // relu(x), likewise
+    unsigned char* dtw = smem + t.dt_off;    // dt, likewise
+    unsigned char* skw = smem + t.sk_off;    // dy's own pixels [F][TH][W]
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int g = lane >> 4, r16 = lane & 15, jj = r16 >> 2, m = r16 & 3;
-    const int H = a.H, W = a.W, TH = t.TH;
-    const int TW = W + 2;
+    const bool dgrad = wave < NS;            // input-gradient role
+    const int rw = wave & (NS - 1);          // wave within its role
+    const int H = a.H, W = a.W, F = t.F, TH = t.TH, ho = t.ho, TW = walk_pitch(W);
+    const int dpf = (TH + 2 + 2 * ho) * TW, xpf = (TH + 2) * TW;
+    const int nsd = (F * dpf + 1) * 4, nsx = (F * xpf + 1) * 4, nsk = F * TH * W * 4;   // 16-byte slots staged
+    const int rowb = TW * 64, cols = F * W;
 
-    // earlier launches' weight-gradient partials, summed first (LDS is free until staging)
-    if (a.pend.nparts > 0) pending_reduce<NT>(a.pend, smem);
-    if (a.pend2.nparts > 0) pending_reduce<NT>(a.pend2, smem);
-    if (tid < 16) reinterpret_cast<uint32_t*>(zero)[tid] = 0u;
-    // the dt window: its padding columns and zero slots are never written
-    for (int j = tid; j < t.dt_bytes / 16; j += NT) reinterpret_cast<uint4*>(dtw)[j] = make_uint4(0, 0, 0, 0);
-    // the t and x windows' guard pixels (read only against zero dy / dt, never staged)
-    if (tid < XPB / 4) {
-        reinterpret_cast<uint32_t*>(tw - XPB)[tid] = 0u;
-        reinterpret_cast<uint32_t*>(tw + t.tx_guard)[tid] = 0u;
-        reinterpret_cast<uint32_t*>(xw - XPB)[tid] = 0u;
-        reinterpret_cast<uint32_t*>(xw + t.tx_guard)[tid] = 0u;
-    }
-
-    // ---- input-gradient A fragments of both convs for this wave's channel block:
-    // A[o][k] = w[8 - tap][o][co] with k = tap * C + co (zero past the 9 taps)
-    const int ci0 = g * 4;   // the lane's first channel of each block (block b adds 16 b)
-    auto load_w = [&](uint4 (&wfa)[DB][KSD], uint4 (&wfb)[DB][KSD]) {
-#pragma unroll
-        for (int b = 0; b < DB; ++b)
-#pragma unroll
-            for (int ks = 0; ks < KSD; ++ks) {
-                const int o = b * 16 + r16;
-                float va[8], vb[8];
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const int k = ks * 32 + g * 8 + j, tap = k / C, co = k % C;
-                    va[j] = tap < 9 ? a.wa[((8 - tap) * C + o) * C + co] : 0.f;
-                    vb[j] = tap < 9 ? a.wb[((8 - tap) * C + o) * C + co] : 0.f;
-                }
-                wfa[b][ks] = make_uint4(pack2bf(va[0], va[1]), pack2bf(va[2], va[3]), pack2bf(va[4], va[5]), pack2bf(va[6], va[7]));
-                wfb[b][ks] = make_uint4(pack2bf(vb[0], vb[1]), pack2bf(vb[2], vb[3]), pack2bf(vb[4], vb[5]), pack2bf(vb[6], vb[7]));
-            }
+    // ---- staging offsets, tile-invariant per lane (slot k of this wave: j = (wave + NW*k)*64 +
+    // lane: pixel j / 4, position j % 4), relative to the tile's first frame with the window's
+    // first row at image row 0 (whole frames: at row -1); a tile adds that row. Rows off the frame fall
+    // outside the buffer resource (whole frames: they are kOOB), padding columns are kOOB.
+    uint32_t od[G::MAXD], ox[G::MAXX], ok[G::MAXK];
+    auto win_off = [&](int j, int ns, int pf, float inv_pf) CB_INLINE_LAMBDA {
+        const int p = j >> 2, fi = qdiv(p, inv_pf), pr = p - fi * pf, rr = qdiv(pr, t.inv_TW), col = pr - rr * TW;
+        const int q = (j & 3) ^ ((col >> 1) & 2);
+        const int h = rr - (ho ? 0 : 1);
+        const bool in = (j < ns) & (uint32_t(col - 1) < uint32_t(W)) & ((ho != 0) | (uint32_t(h) < uint32_t(H)));
+        const uint32_t off = uint32_t((((fi * H + h) * W + col - 1) * C + q * 8) * 2);
+        return in ? off : kOOB;
     };
-    // B-fragment byte offsets from the lane's tap-(0,0) pixel of a dy-like window; with 16
-    // channels a k-step spans two taps (a per-lane table), from 32 on only the slot is the lane's.
-    // Past the ninth tap the weights are zero, so those lanes re-read tap 8 (a value that
-    // already enters the sum through tap 8 itself)
-    int dboff[C < 32 ? KSD : 1];
-    if constexpr (C < 32) {
-#pragma unroll
-        for (int ks = 0; ks < KSD; ++ks) {
-            const int k0 = ks * 32 + g * 8, tap = k0 / C, slot = (k0 % C) / 8;
-            const int tp = tap < 9 ? tap : 8;
-            dboff[ks] = ((tp / 3) * TW + tp % 3) * DYP + slot * 16;
-        }
-    }
-    const int twdy = TW * DYP;
-    auto dgrad_off = [&](int ks) -> int {
-        if constexpr (C < 32) return dboff[ks];
-        else return (ks / (C / 32) / 3) * twdy + (ks / (C / 32) % 3) * DYP + ((ks % (C / 32)) * 4 + g) * 16;
-    };
-    // weight-gradient column blocks nb = wg + NWG * i (16 input channels of one tap, or the
-    // bias block), each for all C/16 output-channel blocks, of both convs (waves 4..7)
-    const int wg = wave % NWG;
-    int wboff[TPW];
-#pragma unroll
-    for (int i = 0; i < TPW; ++i) {
-        const int nb = wg + NWG * i;
-        const int tap = nb / CB16, cb = nb % CB16;
-        wboff[i] = nb < NB ? ((tap / 3) * TW + tap % 3) * XPB + (cb * 16 + 4 * m) * 2 : 0;
-    }
-    const uint4 ones = make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u);
-
-    // ---- staging offsets, tile-invariant per lane (slot k of this wave: j = (wave + NW*k)*64
-    // + lane), relative to the window's first row at image row 0; a tile adds that row's
-    // image row. Rows off the frame fall outside the frame's buffer resource and read zero,
-    // as do padding slots and columns (kOOB).
-    const int nsd = (TH + 4) * TW * DSL, nsx = (TH + 2) * TW * XSL;
-    auto win_off = [&](int j, int slots, int rows) -> uint32_t {
-        const int p = j / slots, c = j - p * slots;
-        const int rr = p / TW, col = p - rr * TW;
-        if (j >= rows * TW * slots || c >= C / 8 || col < 1 || col > W) return kOOB;
-        return uint32_t(((rr * W + col - 1) * C + c * 8) * 2);
-    };
-    uint32_t od[G::MAXD], ox[G::MAXX];
-#pragma unroll
-    for (int k = 0; k < G::MAXD; ++k) od[k] = win_off((wave + NW * k) * 64 + lane, DSL, TH + 4);
-#pragma unroll
-    for (int k = 0; k < G::MAXX; ++k) ox[k] = win_off((wave + NW * k) * 64 + lane, XSL, TH + 2);
-
-    // ---- one weight gradient over the band's own rows: dy-like window dwin (own row 0 at
-    // window row drow0) against the relu'd window bwin (row 0 = image row h0-1): pixel idx of
-    // the own rows pairs with bwin pixel idx - 1 + tap offset. Lane (g, 4jj+m) takes pixels
-    // o = 16*half + 4g + jj (channels 4m.. of a 16-channel block).
-    auto wgrad = [&](const unsigned char* dwin, int drow0, const unsigned char* bwin, const unsigned char* bguard,
-                     int L, cb_f32x4 (&wacc)[TPW][MT]) {
-        // specialised per wave, so that each column block's kind (loaded or bias) is known at
-        // compile time and the k-step loop carries no branches
-        auto run = [&](auto wv) {
-            constexpr int WG = decltype(wv)::value;
-            const int nfull = L >> 5;
-            const int o0 = 4 * g + jj;
-            const unsigned char* ap = dwin + (drow0 * TW + o0) * DYP + 8 * m;
-            const unsigned char* bp = bwin + (o0 - 1) * XPB;
-            auto kstep = [&](const unsigned char* a0, const unsigned char* a1, const unsigned char* b0,
-                             const unsigned char* b1) {
-                uint4 af[MT];
-#pragma unroll
-                for (int mo = 0; mo < MT; ++mo) {
-                    const uint2 lo = lds_read_tr16(a0 + mo * 32);   // a0, a1: zero past L
-                    const uint2 hi = lds_read_tr16(a1 + mo * 32);
-                    af[mo] = make_uint4(lo.x, lo.y, hi.x, hi.y);
-                }
-#pragma unroll
-                for (int i = 0; i < TPW; ++i) {
-                    const int nb = WG + NWG * i;
-                    if (nb < NB) {
-                        const uint2 lo = lds_read_tr16(b0 + wboff[i]);
-                        const uint2 hi = lds_read_tr16(b1 + wboff[i]);
-                        const uint4 bf = make_uint4(lo.x, lo.y, hi.x, hi.y);
-#pragma unroll
-                        for (int mo = 0; mo < MT; ++mo) wacc[i][mo] = PrecBF16::mma(af[mo], bf, wacc[i][mo]);
-                    } else if (nb == NB) {   // the bias block: a column of ones
-#pragma unroll
-                        for (int mo = 0; mo < MT; ++mo) wacc[i][mo] = PrecBF16::mma(af[mo], ones, wacc[i][mo]);
-                    }
-                }
-            };
-            int ks = 0;
-            for (; ks + 2 <= nfull; ks += 2) {   // two k-steps per trip: half the pointer updates
-                kstep(ap, ap + 16 * DYP, bp, bp + 16 * XPB);
-                kstep(ap + 32 * DYP, ap + 48 * DYP, bp + 32 * XPB, bp + 48 * XPB);
-                ap += 64 * DYP;
-                bp += 64 * XPB;
-            }
-            if (ks < nfull) {
-                kstep(ap, ap + 16 * DYP, bp, bp + 16 * XPB);
-                ap += 32 * DYP;
-                bp += 32 * XPB;
-            }
-            if (L & 31) {   // the last, partial k-step
-                const int o = nfull * 32 + o0;
-                const bool ok0 = o < L, ok1 = o + 16 < L;
-                kstep(ok0 ? ap : zero, ok1 ? ap + 16 * DYP : zero, ok0 ? bp : bguard, ok1 ? bp + 16 * XPB : bguard);
-            }
-        };
-        static_assert(NWG == 4, "one specialisation per wave of a group");
-        switch (wg) {
-            case 0: run(std::integral_constant<int, 0>{}); break;
-            case 1: run(std::integral_constant<int, 1>{}); break;
-            case 2: run(std::integral_constant<int, 2>{}); break;
-            default: run(std::integral_constant<int, 3>{}); break;
-        }
-    };
+    const int rd = ho ? 2 : 0, rx = ho ? 1 : 0;   // a window's first row above the band (whole frames: in the offsets)
 
     int lg = blockIdx.x;   // neighbouring bands (which share halo rows) on one XCD
     if ((gridDim.x & 7) == 0) lg = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    const int G0 = int(gridDim.x);
 
-    auto prologue = [&](int tile) {
-        const int band = tile % t.nbands, f = tile / t.nbands;
-        const int h0 = band * TH;
-        const int64_t fo = int64_t(f) * H * W * C;   // the frame's first element
-        __syncthreads();   // the previous tile's LDS reads are done
-
-        // ---- stage dy (rows h0-2 ..), t and x (rows h0-1 ..)
-        {
-            const uint32_t fb = uint32_t(H) * W * C * 2;
-            const auto rd = buf_rsrc(static_cast<const uint16_t*>(a.dy) + fo, fb);
-            const auto rt = buf_rsrc(static_cast<const uint16_t*>(a.t) + fo, fb);
-            const auto rx = buf_rsrc(static_cast<const uint16_t*>(a.x) + fo, fb);
-            const uint32_t hd = uint32_t((h0 - 2) * W * C * 2);   // wraps above the frame: reads zero
-            const uint32_t hx = uint32_t((h0 - 1) * W * C * 2);
+    // ---- weights, loaded first and packed below: 4 k-values (output channels of the forward) of one
+    // input channel o per unit; A[o][tap * 32 + co] = w[8 - tap][o][co]
+    constexpr int UNITS = 2 * 9 * C * (C / 4), PER = UNITS / NT;
+    static_assert(UNITS % NT == 0, "whole units per thread");
+    float4 v[PER];
 #pragma unroll
-            for (int k = 0; k < G::MAXD; ++k)
-                if ((wave + NW * k) * 64 < nsd) dma16_to_lds(rd, dyw + (wave + NW * k) * 1024, od[k] + hd);
-#pragma unroll
-            for (int k = 0; k < G::MAXX; ++k)
-                if ((wave + NW * k) * 64 < nsx) {
-                    dma16_to_lds(rt, tw + (wave + NW * k) * 1024, ox[k] + hx);
-                    dma16_to_lds(rx, xw + (wave + NW * k) * 1024, ox[k] + hx);
-                }
-        }
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
-        {
-            // both convs read relu'd inputs; relu(v) > 0 exactly where v > 0, so the masks
-            // read the same windows
-            uint4* t4 = reinterpret_cast<uint4*>(tw);
-            uint4* x4 = reinterpret_cast<uint4*>(xw);
-            for (int j = tid; j < nsx; j += NT) {
-                uint4 u = t4[j], v = x4[j];
-                u.x = relu_bf16x2(u.x); u.y = relu_bf16x2(u.y); u.z = relu_bf16x2(u.z); u.w = relu_bf16x2(u.w);
-                v.x = relu_bf16x2(v.x); v.y = relu_bf16x2(v.y); v.z = relu_bf16x2(v.z); v.w = relu_bf16x2(v.w);
-                t4[j] = u;
-                x4[j] = v;
-            }
-        }
-        __syncthreads();
-
-    };
-
-    auto band_of = [&](int tile, int& h0, int& the, int64_t& fo) {
-        const int band = tile % t.nbands, f = tile / t.nbands;
-        h0 = band * TH;
-        the = H - h0 < TH ? H - h0 : TH;
-        fo = int64_t(f) * H * W * C;
-    };
-
-    // Two loops over the same tiles, one per role, so that each role keeps only its own
-    // registers live; every wave runs the prologue's barriers and the one between the halves
-    // of a tile (after dt / after conv_b's weight gradient, which need no dt).
-    if (wave < NWG) {
-        uint4 wfa[DB][KSD], wfb[DB][KSD];
-        load_w(wfa, wfb);
-        for (int tile = lg; tile < t.ntiles; tile += gridDim.x) {
-            prologue(tile);
-            int h0, the;
-            int64_t fo;
-            band_of(tile, h0, the, fo);
-            // ---- conv_b's input gradient dt on window rows r = 0 .. the+1 (image rows h0-1+r;
-            // zero off the frame), 16-pixel column tiles, into the dt window
-            {
-                const int npx = (the + 2) * W;
-                for (int nt = wave; nt * 16 < npx; nt += NWG) {
-                    const int q = nt * 16 + r16;
-                    const int qc = q < npx ? q : npx - 1;   // past npx: computed, not stored
-                    const int row = qdiv(qc, t.inv_W), col = qc - row * W;
-                    const unsigned char* xb = dyw + (row * TW + col) * DYP;
-                    cb_f32x4 acc[DB];
-    #pragma unroll
-                    for (int b = 0; b < DB; ++b) acc[b] = cb_f32x4{0.f, 0.f, 0.f, 0.f};
-    #pragma unroll
-                    for (int ks = 0; ks < KSD; ++ks) {
-                        const uint4 bf = *reinterpret_cast<const uint4*>(xb + dgrad_off(ks));
-    #pragma unroll
-                        for (int b = 0; b < DB; ++b) acc[b] = PrecBF16::mma(wfb[b][ks], bf, acc[b]);
-                    }
-                    if (q < npx) {
-                        const int h = h0 - 1 + row;
-    #pragma unroll
-                        for (int b = 0; b < DB; ++b) {
-                            uint2 o = make_uint2(0u, 0u);
-                            if (h >= 0 && h < H) {
-                                float mk[4];
-                                load4(reinterpret_cast<const uint16_t*>(tw + (row * TW + col + 1) * XPB + (ci0 + 16 * b) * 2), mk);
-                                o = make_uint2(pack2bf(mk[0] > 0.f ? acc[b][0] : 0.f, mk[1] > 0.f ? acc[b][1] : 0.f),
-                                               pack2bf(mk[2] > 0.f ? acc[b][2] : 0.f, mk[3] > 0.f ? acc[b][3] : 0.f));
-                            }
-                            *reinterpret_cast<uint2*>(dtw + (row * TW + col + 1) * DYP + (ci0 + 16 * b) * 2) = o;
-                        }
-                    }
-                }
-            }
-            __syncthreads();   // the dt window is complete
-            // ---- dx = conv_a^T(dt) * [x > 0] + dy on the band's rows
-            {
-                const int npx = the * W;
-                uint16_t* dxt = static_cast<uint16_t*>(a.dx) + fo + int64_t(h0) * W * C;
-                for (int nt = wave; nt * 16 < npx; nt += NWG) {
-                    const int q = nt * 16 + r16;
-                    const int qc = q < npx ? q : npx - 1;
-                    const int row = qdiv(qc, t.inv_W), col = qc - row * W;
-                    const unsigned char* xb = dtw + (row * TW + col) * DYP;
-                    cb_f32x4 acc[DB];
-    #pragma unroll
-                    for (int b = 0; b < DB; ++b) acc[b] = cb_f32x4{0.f, 0.f, 0.f, 0.f};
-    #pragma unroll
-                    for (int ks = 0; ks < KSD; ++ks) {
-                        const uint4 bf = *reinterpret_cast<const uint4*>(xb + dgrad_off(ks));
-    #pragma unroll
-                        for (int b = 0; b < DB; ++b) acc[b] = PrecBF16::mma(wfa[b][ks], bf, acc[b]);
-                    }
-                    if (q < npx) {
-    #pragma unroll
-                        for (int b = 0; b < DB; ++b) {
-                            const int cb = ci0 + 16 * b;
-                            float mk[4], sk[4];
-                            load4(reinterpret_cast<const uint16_t*>(xw + ((row + 1) * TW + col + 1) * XPB + cb * 2), mk);
-                            load4(reinterpret_cast<const uint16_t*>(dyw + ((row + 2) * TW + col + 1) * DYP + cb * 2), sk);
-                            float v[4];
-    #pragma unroll
-                            for (int j = 0; j < 4; ++j) v[j] = (mk[j] > 0.f ? acc[b][j] : 0.f) + sk[j];
-                            store4(dxt + uint32_t(q * C + cb), v[0], v[1], v[2], v[3]);
-                        }
-                    }
-                }
-            }
-        }
-    } else {
-        cb_f32x4 wb_acc[TPW][MT], wa_acc[TPW][MT];
-#pragma unroll
-        for (int i = 0; i < TPW; ++i)
-#pragma unroll
-            for (int mo = 0; mo < MT; ++mo) wb_acc[i][mo] = wa_acc[i][mo] = cb_f32x4{0.f, 0.f, 0.f, 0.f};
-        for (int tile = lg; tile < t.ntiles; tile += gridDim.x) {
-            prologue(tile);
-            int h0, the;
-            int64_t fo;
-            band_of(tile, h0, the, fo);
-            (void)h0;
-            (void)fo;
-            // conv_b's: dy (own rows from dy-window row 2) against relu(t); then, once dt is
-            // complete, conv_a's: dt (own rows from dt-window row 1) against relu(x)
-            wgrad(dyw, 2, tw, tw - XPB, the * TW, wb_acc);
-            __syncthreads();   // the dt window is complete
-            wgrad(dtw, 1, xw, xw - XPB, the * TW, wa_acc);
-        }
-        // ---- this workgroup's partials: conv_b's set, then conv_a's, each [mo*NBB + nb][co 16][ci 16]
-        float* pb = a.partial + int64_t(blockIdx.x) * G::PSTRIDE;
-        float* pa = pb + t.pset;
-#pragma unroll
-        for (int i = 0; i < TPW; ++i) {
-            const int nb = wg + NWG * i;
-            if (nb < NBB) {
-#pragma unroll
-                for (int mo = 0; mo < MT; ++mo)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        pb[(mo * NBB + nb) * 256 + (4 * g + e) * 16 + r16] = wb_acc[i][mo][e];
-                        pa[(mo * NBB + nb) * 256 + (4 * g + e) * 16 + r16] = wa_acc[i][mo][e];
-                    }
-            }
-        }
+    for (int u = 0; u < PER; ++u) {
+        const int id = tid + u * NT, cv = id >= UNITS / 2, r = id - cv * (UNITS / 2);   // r = ((tap * 32) + o) * 8 + co / 4
+        v[u] = load_f4((cv ? a.wb : a.wa) + r * 4);
     }
+#pragma unroll
+    for (int k = 0; k < G::MAXD; ++k) od[k] = win_off((wave + NW * k) * 64 + lane, nsd, dpf, t.inv_dpf);
+#pragma unroll
+    for (int k = 0; k < G::MAXX; ++k) ox[k] = win_off((wave + NW * k) * 64 + lane, nsx, xpf, t.inv_xpf);
+#pragma unroll
+    for (int k = 0; k < G::MAXK; ++k) {   // slot j: pixel j / 4 of the own pixels, permuted by its column
+        const int j = (wave + NW * k) * 64 + lane, p = j >> 2;
+        const int col = p - qdiv(p, t.inv_W) * W + 1, q = (j & 3) ^ ((col >> 1) & 2);
+        ok[k] = j < nsk ? uint32_t(p * 64 + q * 16) : kOOB;
+    }
+    rbw_stage(a, t, a.dy, dyw, nsd, od, wave, lg, rd);
+    rbw_stage(a, t, a.t, tw, nsx, ox, wave, lg, rx);
+    // earlier launches' weight-gradient partials
+    if (a.pend.nparts > 0) pending_reduce<NT>(a.pend, dtw);
+    if (a.pend2.nparts > 0) pending_reduce<NT>(a.pend2, dtw);
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int id = tid + u * NT, cv = id >= UNITS / 2, r = id - cv * (UNITS / 2);
+        const int ks = 8 - r / (C * 8), o = r / 8 % C, c4 = r % 8;   // k-step (rotated tap), row, 4-channel group
+        *reinterpret_cast<uint2*>(dtw + cv * G::WFRAG + ((((o >> 2) & 1) * 9 + ks) * 64 + (c4 >> 1) * 16 + 4 * (o >> 3) + (o & 3)) * 16 +
+                                  (c4 & 1) * 8) = make_uint2(pack2bf(v[u].x, v[u].y), pack2bf(v[u].z, v[u].w));
+    }
+    lds_barrier();
+    // the dt window: its padding and, for whole frames, its rows off the frame are never written
+    auto clear_dt = [&] {
+        for (int j = tid; j < t.dt_bytes / 16; j += NT) reinterpret_cast<uint4*>(dtw)[j] = make_uint4(0, 0, 0, 0);
+    };
+
+    if (dgrad) {
+        uint4 wa[2][9], wb[2][9];
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int ks = 0; ks < 9; ++ks) {
+                wa[b][ks] = *reinterpret_cast<const uint4*>(dtw + ((b * 9 + ks) * 64 + lane) * 16);
+                wb[b][ks] = *reinterpret_cast<const uint4*>(dtw + G::WFRAG + ((b * 9 + ks) * 64 + lane) * 16);
+            }
+        lds_barrier();
+        clear_dt();
+        for (int tile = lg; tile < t.ntiles; tile += G0) {
+            int ln = lane;
+            asm volatile("" : "+v"(ln));   // anchors and row masks are formed per tile: kept over tiles they spill
+            const int g = ln >> 4, r16 = ln & 15;
+            const int band = tile % t.nbands, f = (tile / t.nbands) * F;
+            const int h0 = band * TH, the = H - h0 < TH ? H - h0 : TH;
+            const int nf = a.n - f < F ? a.n - f : F;
+            const int64_t fo = int64_t(f) * H * W * C;
+            rbw_landed<G::MAXX>(tw, nsx, wave, lane);
+            lds_barrier();   // dy and t have landed; x and dt of the previous tile have been read
+            // (the windows being staged and those read are restrict parameters of one call, so the
+            // compiler knows that the loads in flight do not write what is read)
+            auto phase_a = [&](unsigned char* __restrict__ xdst, unsigned char* __restrict__ kdst, unsigned char* __restrict__ dtdst,
+                               const unsigned char* __restrict__ dsrc, const unsigned char* __restrict__ tsrc) CB_INLINE_LAMBDA {
+                rbw_stage(a, t, a.x, xdst, nsx, ox, wave, tile, rx);
+                rbw_stage(a, t, a.dy, kdst, nsk, ok, wave, tile, 0);
+                const int n1 = TH + 2 * ho;
+                for (int grp = rw; grp * 16 < t.nsegt * cols; grp += NS) {
+                    const WalkAnchor an = walk_anchor(grp * 16 + r16, cols, W, t.nsegt, R, n1, t.inv_c, t.inv_W);
+                    uint32_t ta = uint32_t(an.fi * xpf + (an.row0 + 1 - ho) * TW + an.c + 1) * 64 + walk_ch(an.c + 1, g * 16);
+                    const int hb = h0 - ho + an.row0;   // image row of the walk's first row
+                    const uint32_t one = 0x00010001u, top = 0x7f807f80u;
+                    uint4 mk = make_uint4(0, 0, 0, 0);
+                    walk_conv32<R, false>(dsrc, an.fi * dpf + an.row0 * TW + an.c, an.c, g, rowb, wb,
+                        [&] { mk = *reinterpret_cast<const uint4*>(tsrc + ta); },
+                        [&](int j, const cb_f32x4 (&acc)[2]) {
+                            const int h = hb + j;
+                            const bool in = uint32_t(h) < uint32_t(H);   // rows off the frame stay zero
+                            uint4 u = make_uint4(pos_mask16x2(mk.x, pack2bf(acc[0][0], acc[0][1]), one, top), pos_mask16x2(mk.y, pack2bf(acc[0][2], acc[0][3]), one, top),
+                                                 pos_mask16x2(mk.z, pack2bf(acc[1][0], acc[1][1]), one, top), pos_mask16x2(mk.w, pack2bf(acc[1][2], acc[1][3]), one, top));
+                            if (!in) u = make_uint4(0, 0, 0, 0);
+                            if (an.ok && an.row0 + j >= an.rbeg) *reinterpret_cast<uint4*>(dtdst + ta) = u;
+                            ta += rowb;
+                        });
+                }
+            };
+            phase_a(xw, skw, dtw, dyw, tw);
+            rbw_landed<G::MAXX>(xw, nsx, wave, lane);
+            lds_barrier();   // the dt window is complete, x has landed
+            auto phase_b = [&](unsigned char* __restrict__ ddst, unsigned char* __restrict__ tdst, const unsigned char* __restrict__ dtsrc,
+                               const unsigned char* __restrict__ xsrc, const unsigned char* __restrict__ ksrc) CB_INLINE_LAMBDA {
+                if (tile + G0 < t.ntiles) {
+                    rbw_stage(a, t, a.dy, ddst, nsd, od, wave, tile + G0, rd);
+                    rbw_stage(a, t, a.t, tdst, nsx, ox, wave, tile + G0, rx);
+                }
+                uint16_t* dxb = static_cast<uint16_t*>(a.dx) + fo;
+                for (int grp = rw; grp * 16 < t.nsegx * cols; grp += NS) {
+                    const WalkAnchor an = walk_anchor(grp * 16 + r16, cols, W, t.nsegx, R, TH, t.inv_c, t.inv_W);
+                    uint32_t xa = uint32_t(an.fi * xpf + (an.row0 + 1) * TW + an.c + 1) * 64 + walk_ch(an.c + 1, g * 16);
+                    uint32_t ka = uint32_t((an.fi * TH + an.row0) * W + an.c) * 64 + walk_ch(an.c + 1, g * 16);
+                    uint32_t go = uint32_t(((an.fi * H + h0 + an.row0) * W + an.c) * C + g * 8);
+                    const bool own = an.ok && an.fi < nf;
+                    uint4 mk = make_uint4(0, 0, 0, 0), sk = make_uint4(0, 0, 0, 0);
+                    walk_conv32<R, false>(dtsrc, an.fi * xpf + an.row0 * TW + an.c, an.c, g, rowb, wa,
+                        [&] {
+                            mk = *reinterpret_cast<const uint4*>(xsrc + xa);
+                            sk = *reinterpret_cast<const uint4*>(ksrc + ka);
+                            xa += rowb;
+                            ka += W * 64;
+                        },
+                        [&](int j, const cb_f32x4 (&acc)[2]) {
+                            if (own && an.row0 + j >= an.rbeg && an.row0 + j < the)
+                                store16(dxb + go,
+                                    make_uint4(pack2bf((bf_lo(mk.x) > 0.f ? acc[0][0] : 0.f) + bf_lo(sk.x), (bf_hi(mk.x) > 0.f ? acc[0][1] : 0.f) + bf_hi(sk.x)),
+                                               pack2bf((bf_lo(mk.y) > 0.f ? acc[0][2] : 0.f) + bf_lo(sk.y), (bf_hi(mk.y) > 0.f ? acc[0][3] : 0.f) + bf_hi(sk.y)),
+                                               pack2bf((bf_lo(mk.z) > 0.f ? acc[1][0] : 0.f) + bf_lo(sk.z), (bf_hi(mk.z) > 0.f ? acc[1][1] : 0.f) + bf_hi(sk.z)),
+                                               pack2bf((bf_lo(mk.w) > 0.f ? acc[1][2] : 0.f) + bf_lo(sk.w), (bf_hi(mk.w) > 0.f ? acc[1][3] : 0.f) + bf_hi(sk.w))));
+                            go += W * C;
+                        });
+                }
+            };
+            phase_b(dyw, tw, dtw, xw, skw);
+        }
+        return;
+    }
+
+    // ---- weight-gradient role: channel blocks (co, ci) of this wave
+    lds_barrier();
+    clear_dt();
+    const int cob = rw & 1, cib = rw >> 1;
+    cb_f32x4 accA[9], accB[9], biasA, biasB;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) accA[k] = accB[k] = cb_f32x4{0.f, 0.f, 0.f, 0.f};
+    biasA = biasB = cb_f32x4{0.f, 0.f, 0.f, 0.f};
+    // dwin's own row 0 is window row drow; xwin's row 0 is one image row above it
+    auto wgrad = [&](const unsigned char* xwin, const unsigned char* dwin, int dstride, int drow, cb_f32x4 (&acc)[9], cb_f32x4& accb) CB_INLINE_LAMBDA {
+        for (int grp = 0; grp * 64 < t.nsegw * cols; ++grp) {
+            int ln = lane;
+            asm volatile("" : "+v"(ln));   // (as above)
+            const int g = ln >> 4, jj = (ln >> 2) & 3, m = ln & 3;
+            const uint32_t cx = uint32_t(cib * 32 + m * 8), cd = uint32_t(cob * 32 + m * 8);
+            int px[4], pd[4], c[4], skip[4];
+#pragma unroll
+            for (int h = 0; h < 4; ++h) {
+                const WalkAnchor an = walk_anchor(grp * 64 + h * 16 + 4 * g + jj, cols, W, t.nsegw, R, TH, t.inv_c, t.inv_W);
+                px[h] = an.fi * xpf + an.row0 * TW + an.c;
+                pd[h] = an.fi * dstride + (an.row0 + drow) * TW + an.c + 1;
+                c[h] = an.c;
+                skip[h] = an.ok ? an.rbeg - an.row0 : R;
+            }
+            walk_wgrad<R>(xwin, dwin, px, pd, c, skip, cx, cd, rowb, acc, accb);
+        }
+    };
+    auto phase_a = [&](unsigned char* __restrict__ xdst, unsigned char* __restrict__ kdst, const unsigned char* __restrict__ tsrc,
+                       const unsigned char* __restrict__ dsrc, int tile) CB_INLINE_LAMBDA {
+        rbw_stage(a, t, a.x, xdst, nsx, ox, wave, tile, rx);
+        rbw_stage(a, t, a.dy, kdst, nsk, ok, wave, tile, 0);
+        wgrad(tsrc, dsrc, dpf, 1 + ho, accB, biasB);
+    };
+    auto phase_b = [&](unsigned char* __restrict__ ddst, unsigned char* __restrict__ tdst, const unsigned char* __restrict__ xsrc,
+                       const unsigned char* __restrict__ dtsrc, int next) CB_INLINE_LAMBDA {
+        if (next < t.ntiles) {
+            rbw_stage(a, t, a.dy, ddst, nsd, od, wave, next, rd);
+            rbw_stage(a, t, a.t, tdst, nsx, ox, wave, next, rx);
+        }
+        wgrad(xsrc, dtsrc, xpf, 1, accA, biasA);
+    };
+    for (int tile = lg; tile < t.ntiles; tile += G0) {
+        rbw_landed<G::MAXX>(tw, nsx, wave, lane);
+        lds_barrier();
+        phase_a(xw, skw, tw, dyw, tile);
+        rbw_landed<G::MAXX>(xw, nsx, wave, lane);
+        lds_barrier();
+        phase_b(dyw, tw, xw, dtw, tile + G0);
+    }
+
+    // ---- this workgroup's partials: conv_b's set, then conv_a's
+    float* part = a.partial + int64_t(blockIdx.x) * G::PSTRIDE + cob * G::NBB * 256;
+    const int g = lane >> 4, r16 = lane & 15;
+    auto put = [&](float* dst, const cb_f32x4& acc) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) dst[(4 * g + e) * 16 + r16] = acc[e];
+    };
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+        put(part + (2 * k + cib) * 256, accB[k]);
+        put(part + t.pset + (2 * k + cib) * 256, accA[k]);
+    }
+    if (cib == 0) put(part + 18 * 256, biasB);
+    else put(part + t.pset + 18 * 256, biasA);
 }
 
 namespace {
@@ -703,6 +647,66 @@ template <int C>
 int rbb_parts_cap() {
     const size_t cap = kRbbPartBytes / (2 * size_t(RbbGeom<C>::PSTRIDE) * sizeof(float));
     return int(cap < 256 ? 256 : (cap > 1024 ? 1024 : cap));
+}
+
+// Tile shapes of the column-walk kernel: minimise rounds of tiles over the CUs times a tile's
+// estimated cycles, each phase the longer of its MFMAs (16 cycles, the SIMD shared by an
+// input-gradient and a weight-gradient wave) and of the loads it covers (8 bytes per cycle and
+// CU, plus their latency).
+hipError_t rbw_launch(const ResBwdArgs& a, hipStream_t s, PendingReduce out[2]) {
+    using G = RbwGeom;
+    const int H = a.H, W = a.W, cus = std::min(device_cus(), 256);
+    if (int64_t(H) * W * G::C * 2 * 16 >= (int64_t(1) << 31)) return hipErrorInvalidValue;
+    static thread_local WalkPlans<RbwTile> plans;
+    const auto* plan = plans.find(a.n, H, W, cus);
+    if (!plan) {
+        const size_t limit = std::min<size_t>(lds_limit(), 160 * 1024);
+        RbwTile t{};
+        double best = 1e30;
+        size_t L = 0;
+        for (int nb = 1; nb <= H; ++nb) {
+            const int TH = (H + nb - 1) / nb, ho = nb > 1;
+            if (nb > 1 && (H + TH - 1) / TH != nb) continue;
+            for (int F = 1; F <= (ho ? 1 : std::min<int64_t>(a.n, 16)); ++F) {
+                const int db = walk_win_bytes(F, TH + 2 + 2 * ho, W), xb = walk_win_bytes(F, TH + 2, W);
+                const int kb = (F * TH * W + 15) / 16 * 1024;
+                const int tail = std::max(xb + kb, 2 * G::WFRAG);   // dt, skip term; the weights at first
+                const size_t lds = size_t(db) + 2 * xb + tail;
+                if (lds > limit || kb > G::MAXK * G::NW * 1024 || db > G::MAXD * G::NW * 1024 || xb > G::MAXX * G::NW * 1024) break;
+                RbwTile c{};
+                c.F = F; c.TH = TH; c.ho = ho; c.nbands = nb;
+                c.ntiles = int((a.n + F - 1) / F) * nb;
+                const double mx = double(F) * W * 64 * (TH + 2 * ho) / 8 + 1500, md = double(F) * W * 64 * (2 * TH + 6 * ho) / 8 + 1500;
+                for (c.R = 1; c.R <= std::min(TH, kWalkMaxR); ++c.R) {
+                    const double wt = 18 * walk_rows(TH + 2 * ho, F * W, 16, G::NS, c.R, c.nsegt);
+                    const double wx = 18 * walk_rows(TH, F * W, 16, G::NS, c.R, c.nsegx);
+                    const double ww = 20 * walk_rows(TH, F * W, 64, 1, c.R, c.nsegw);
+                    const double cost = double((c.ntiles + cus - 1) / cus) * (std::max(20 * (wt + ww), mx) + std::max(20 * (wx + ww), md) + 800);
+                    if (cost < best) {
+                        best = cost;
+                        t = c;
+                        t.t_off = db; t.x_off = db + xb; t.dt_off = db + 2 * xb; t.sk_off = t.dt_off + xb;
+                        t.dt_bytes = xb;
+                        L = lds;
+                    }
+                }
+            }
+        }
+        if (L == 0) return hipErrorInvalidValue;
+        t.inv_W = 1.f / float(W); t.inv_c = 1.f / float(t.F * W); t.inv_TW = 1.f / float(walk_pitch(W));
+        t.inv_dpf = 1.f / float((t.TH + 2 + 2 * t.ho) * walk_pitch(W));
+        t.inv_xpf = 1.f / float((t.TH + 2) * walk_pitch(W));
+        t.pset = std::min(cus, t.ntiles) * G::PSTRIDE;
+        plan = plans.put({a.n, H, W, cus, t, L});
+    }
+    const int parts = plan->t.pset / G::PSTRIDE;
+    walk_dispatch(plan->t.R, [&](auto r) {
+        ProfScope ps(s, [&] { return cb_key("resblock_bwd", 0, cb_dims(G::C, G::C) + "/" + cb_dims(H, W)); });
+        hipLaunchKernelGGL(resblock_bwd_walk_kernel<decltype(r)::value>, dim3(unsigned(parts)), dim3(G::NT), plan->lds, s, a, plan->t);
+    });
+    out[0] = PendingReduce{a.partial, a.dwb, a.dbb, parts, G::PSTRIDE, G::C, G::C, 0, 1.f};
+    out[1] = PendingReduce{a.partial + plan->t.pset, a.dwa, a.dba, parts, G::PSTRIDE, G::C, G::C, 0, 1.f};
+    return hipGetLastError();
 }
 
 template <int C>
@@ -739,19 +743,14 @@ hipError_t rbb_launch(const ResBwdArgs& a, hipStream_t s, PendingReduce out[2]) 
     t.dt_bytes = dtb;
     t.inv_W = 1.f / float(W);
     const size_t L = std::max(lds(TH), size_t(kRbbWaves * 4) * 17 * 16);   // (pending reduce)
-    const void* fn;
-    if constexpr (C == 32) fn = reinterpret_cast<const void*>(&resblock_bwd_spec_kernel<C, kRbbWaves>);
-    else fn = reinterpret_cast<const void*>(&resblock_bwd_kernel<C, kRbbWaves>);
+    const void* fn = reinterpret_cast<const void*>(&resblock_bwd_kernel<C, kRbbWaves>);
     int parts = std::min(resident_blocks(fn, 64 * kRbbWaves, L), rbb_parts_cap<C>());
     if (parts > t.ntiles) parts = t.ntiles;
     t.pset = parts * G::PSTRIDE;
     const std::string shape = cb_dims(C, C) + "/" + cb_dims(H, W);
     {
         ProfScope ps(s, [&] { return cb_key("resblock_bwd", 0, shape); });
-        if constexpr (C == 32)
-            hipLaunchKernelGGL((resblock_bwd_spec_kernel<C, kRbbWaves>), dim3(unsigned(parts)), dim3(64 * kRbbWaves), L, s, a, t);
-        else
-            hipLaunchKernelGGL((resblock_bwd_kernel<C, kRbbWaves>), dim3(unsigned(parts)), dim3(64 * kRbbWaves), L, s, a, t);
+        hipLaunchKernelGGL((resblock_bwd_kernel<C, kRbbWaves>), dim3(unsigned(parts)), dim3(64 * kRbbWaves), L, s, a, t);
     }
     out[0] = PendingReduce{a.partial, a.dwb, a.dbb, parts, G::PSTRIDE, C, C, 0, 1.f};
     out[1] = PendingReduce{a.partial + t.pset, a.dwa, a.dba, parts, G::PSTRIDE, C, C, 0, 1.f};
@@ -762,9 +761,9 @@ hipError_t rbb_launch(const ResBwdArgs& a, hipStream_t s, PendingReduce out[2]) 
 
 bool resblock_bwd_supported(int C) { return C == 16 || C == 32; }
 
-// With 32 channels the block backward (its specialised-wave form) beats the two conv backward
-// launches at every shape the networks use (2048 frames: 11x11 55 against 75 us, 21x21 136
-// against 148 us; 8192 frames at 42x42: 1.66 against 1.97 ms).
+// The block backward beats the two conv backward launches at every shape the networks use (32
+// channels, 2048 frames: 11x11 45 against 75 us, 21x21 101 against 148 us; 8192 frames at 42x42:
+// 1.49 against 1.97 ms).
 bool resblock_bwd_preferred(int C, int H, int W) { return (C == 16 || C == 32) && H > 0 && W > 0; }
 
 size_t resblock_bwd_partial_floats(int C) {
@@ -777,11 +776,10 @@ hipError_t resblock_bwd(int C, const ResBwdArgs& a, hipStream_t s, PendingReduce
     out[0].nparts = 0;
     out[1].nparts = 0;
     if (a.n <= 0) {
-        const hipError_t e = flush_pending_reduce(a.pend, s);
-        return e != hipSuccess ? e : flush_pending_reduce(a.pend2, s);
+        return flush_pending_reduces(a.pend, a.pend2, s);
     }
     if (C == 16) return rbb_launch<16>(a, s, out);
-    if (C == 32) return rbb_launch<32>(a, s, out);
+    if (C == 32) return rbw_launch(a, s, out);
     return hipErrorInvalidValue;
 }
 

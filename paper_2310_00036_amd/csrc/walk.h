@@ -1,0 +1,200 @@
+// Column walks: 3x3 convolutions of 32 channels, and their weight gradients, over LDS windows, with
+// every fragment read feeding all the rows it touches.
+//
+// A window holds F frames of `rows` image rows at a row pitch of W + 1 pixels and one pixel past
+// the end. Column 0 is zero padding, the right neighbour of a row's last pixel the next row's
+// column 0. A pixel's 32 channels take 64 bytes, its four 16-byte slots permuted by XOR with 2 *
+// bit 2 of its column: 16-byte reads of 16 consecutive pixels, and 8-byte transpose reads of 8,
+// then fall on distinct banks, and a step of one row is one constant.
+//
+// The pixels of a fragment are anchors: a column of the tile, or one of nseg segments of it, R
+// rows each. All lanes walk down their anchors together.
+#pragma once
+
+#include <type_traits>
+
+#include "common.h"
+
+namespace cb {
+
+__host__ __device__ inline int walk_pitch(int W) { return W + 1; }
+__host__ __device__ inline int walk_win_bytes(int F, int rows, int W) { return (F * rows * walk_pitch(W) + 1 + 15) / 16 * 1024; }
+
+// Byte offset, in a pixel's 64 bytes at window column col, of the 16-byte slot or 8-byte chunk that
+// starts at channel byte ch.
+CB_DEV uint32_t walk_ch(uint32_t col, uint32_t ch) { return ch ^ ((col << 3) & 32); }
+
+// Anchor `id` of nseg * cols (cols = F * W): frame fi, column c, rows [row0, row0 + R) of nrows. The
+// last segment starts early enough to end at nrows; its rows below rbeg belong to the one above.
+struct WalkAnchor { int row0, rbeg, fi, c; bool ok; };
+CB_DEV WalkAnchor walk_anchor(int id, int cols, int W, int nseg, int R, int nrows, float inv_c, float inv_W) {
+    WalkAnchor an;
+    const int last = nseg * cols - 1, ic = id < last ? id : last;
+    const int s = qdiv(ic, inv_c), rem = ic - s * cols;
+    an.fi = qdiv(rem, inv_W);
+    an.c = rem - an.fi * W;
+    an.rbeg = s * R;
+    an.row0 = s * R < nrows - R ? s * R : nrows - R;
+    an.ok = id <= last;
+    return an;
+}
+
+// Host: rows a wave walks (its filling counted as 0.7 rows per walk) where `waves` waves take groups of
+// gw anchors, segments of R <= rows rows; nseg: segments per column.
+inline double walk_rows(int rows, int cols, int gw, int waves, int R, int& nseg) {
+    nseg = (rows + R - 1) / R;
+    return double(((nseg * cols + gw - 1) / gw + waves - 1) / waves) * (R + 0.7);
+}
+constexpr int kWalkMaxR = 7;   // kernels exist for 1 .. kWalkMaxR rows per walk
+// Calls f(std::integral_constant<int, R>) for a run-time R.
+template <class F>
+inline void walk_dispatch(int R, F&& f) {
+    switch (R) {
+        case 1: f(std::integral_constant<int, 1>{}); break;
+        case 2: f(std::integral_constant<int, 2>{}); break;
+        case 3: f(std::integral_constant<int, 3>{}); break;
+        case 4: f(std::integral_constant<int, 4>{}); break;
+        case 5: f(std::integral_constant<int, 5>{}); break;
+        case 6: f(std::integral_constant<int, 6>{}); break;
+        default: f(std::integral_constant<int, 7>{}); break;
+    }
+}
+// The last tile shapes chosen, per thread (the choice takes some microseconds): a few entries by
+// problem size, overwritten in turn.
+template <class Tile>
+struct WalkPlans {
+    struct Entry { int64_t n; int H, W, cus; Tile t; size_t lds; };
+    Entry e[8];
+    int used = 0, next = 0;
+    const Entry* find(int64_t n, int H, int W, int cus) const {
+        for (int i = 0; i < used; ++i)
+            if (e[i].n == n && e[i].H == H && e[i].W == W && e[i].cus == cus) return &e[i];
+        return nullptr;
+    }
+    const Entry* put(const Entry& v) {
+        Entry* p = &e[next];
+        *p = v;
+        next = (next + 1) % 8;
+        used = used < 8 ? used + 1 : 8;
+        return p;
+    }
+};
+
+CB_DEV uint4 relu8(uint4 v) {
+    return make_uint4(relu_bf16x2(v.x), relu_bf16x2(v.y), relu_bf16x2(v.z), relu_bf16x2(v.w));
+}
+
+// One walk of a 3x3 convolution, 32 -> 32 channels: R output rows at the lane's anchor, whose
+// tap-(0,0) pixel of the first row is p0, at window column c. w[b][tap] are the A fragments of
+// output block b, whose row 4 i + j is channel 8 i + 4 b + j, so that acc[b][j] is channel
+// 8 (lane / 16) + 4 b + j. pre() is called before the last MFMAs of each output row, emit(j, acc)
+// after them. A wave's vector instructions and MFMAs take turns (4 and 16 cycles each, measured
+// to add up within a wave), so nothing is copied: R is a constant and the rows are unrolled, the
+// sums of an output row staying in one of three accumulators, input rows alternating between
+// two sets of fragment registers.
+template <int R, bool RELU, class Pre, class Emit>
+CB_DEV void walk_conv32(const unsigned char* win, int p0, int c, int g, int rowb, const uint4 (&w)[2][9], Pre&& pre, Emit&& emit) {
+    uint32_t ad[3];
+    uint4 x[2][3];
+    cb_f32x4 acc[3][2];
+    auto load = [&](uint4 (&dst)[3]) CB_INLINE_LAMBDA {
+#pragma unroll
+        for (int kx = 0; kx < 3; ++kx) dst[kx] = *reinterpret_cast<const uint4*>(win + ad[kx]);
+    };
+#pragma unroll
+    for (int kx = 0; kx < 3; ++kx) ad[kx] = uint32_t(p0 + kx) * 64 + walk_ch(uint32_t(c + kx), uint32_t(g) * 16);
+    load(x[0]);
+#pragma unroll
+    for (int i = 0; i < R + 2; ++i) {   // input row i: tap rows 2, 1, 0 of output rows i - 2, i - 1, i
+        uint4 (&cur)[3] = x[i & 1];
+        if (i < R + 1) {                // the next row's fragments, in flight during this row's MFMAs
+#pragma unroll
+            for (int kx = 0; kx < 3; ++kx) ad[kx] += rowb;
+            load(x[(i + 1) & 1]);
+        }
+        if (RELU)
+#pragma unroll
+            for (int kx = 0; kx < 3; ++kx) cur[kx] = relu8(cur[kx]);
+        if (i >= 2) pre();
+#pragma unroll
+        for (int ky = 2; ky >= 0; --ky)
+            if (i >= ky && i - ky < R)
+#pragma unroll
+                for (int kx = 0; kx < 3; ++kx)
+#pragma unroll
+                    for (int b = 0; b < 2; ++b)
+                        acc[(i - ky) % 3][b] = PrecBF16::mma(w[b][3 * ky + kx], cur[kx],
+                                                             ky + kx == 0 ? cb_f32x4{0.f, 0.f, 0.f, 0.f} : acc[(i - ky) % 3][b]);
+        if (i >= 2) emit(i - 2, acc[(i - 2) % 3]);
+        __builtin_amdgcn_sched_barrier(0);   // one row's reads in flight: registers are short
+    }
+}
+
+// One walk of a 3x3 weight gradient for one block of 16 input and one of 16 output channels, 64
+// anchors as two fragments of 32 (two at once: a step then has MFMAs enough to cover its reads):
+// acc[tap][...] += sum over the anchors and R rows of dy[row] (rows of D: output channels) times
+// x[row + ky - 1, col + kx - 1] (columns: input channels); accb += sum of dy.
+// Lane (g, 4 jj + m) addresses channels 4m .. of anchors 16 h + 4 g + jj, h = 0 .. 3: px[h] is the
+// tap-(0,0) pixel of its first row in xwin (window column c[h]), pd[h] that row's pixel in dwin;
+// rows below skip[h] add nothing (they read pixel 0 of dwin, which is zero). chx,
+// chd: byte of the lane's chunk in a pixel. Each x fragment feeds the three dy rows it meets.
+template <int R>
+CB_DEV void walk_wgrad(const unsigned char* xwin, const unsigned char* dwin, const int (&px)[4], const int (&pd)[4], const int (&c)[4],
+                       const int (&skip)[4], uint32_t chx, uint32_t chd, int rowb, cb_f32x4 (&acc)[9], cb_f32x4& accb) {
+    uint32_t ax[4][3], ad[4];
+    uint4 x[2][3], d[3][2];
+    const uint4 ones = make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u);
+    auto load_d = [&](uint4& dst, int q, int i) CB_INLINE_LAMBDA {
+        const uint2 lo = lds_read_tr16(dwin + (i >= skip[2 * q] ? ad[2 * q] : 0u));
+        const uint2 hi = lds_read_tr16(dwin + (i >= skip[2 * q + 1] ? ad[2 * q + 1] : 0u));
+        dst = make_uint4(lo.x, lo.y, hi.x, hi.y);
+    };
+    auto load_x = [&](int q) CB_INLINE_LAMBDA {
+#pragma unroll
+        for (int kx = 0; kx < 3; ++kx) {
+            const uint2 lo = lds_read_tr16(xwin + ax[2 * q][kx]), hi = lds_read_tr16(xwin + ax[2 * q + 1][kx]);
+            x[q][kx] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+        }
+    };
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+        ad[h] = uint32_t(pd[h]) * 64 + walk_ch(uint32_t(c[h] + 1), chd);
+#pragma unroll
+        for (int kx = 0; kx < 3; ++kx) ax[h][kx] = uint32_t(px[h] + kx) * 64 + walk_ch(uint32_t(c[h] + kx), chx);
+    }
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        load_x(q);
+        load_d(d[0][q], q, 0);
+    }
+    // x row i: tap rows 2, 1, 0 against dy rows i - 2, i - 1, i, row j in d[j % 3]. Each
+    // fragment's next rows are read into the registers its MFMAs have just taken, while the
+    // other fragment's MFMAs run.
+#pragma unroll
+    for (int i = 0; i < R + 2; ++i)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+#pragma unroll
+            for (int ky = 2; ky >= 0; --ky)
+                if (i >= ky && i - ky < R)
+#pragma unroll
+                    for (int kx = 0; kx < 3; ++kx) acc[3 * ky + kx] = PrecBF16::mma(d[(i - ky) % 3][q], x[q][kx], acc[3 * ky + kx]);
+            if (i < R) accb = PrecBF16::mma(d[i % 3][q], ones, accb);
+            __builtin_amdgcn_sched_barrier(0);
+            if (i < R + 1) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int kx = 0; kx < 3; ++kx) ax[2 * q + h][kx] += rowb;
+                load_x(q);
+            }
+            if (i + 1 < R) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) ad[2 * q + h] += rowb;
+                load_d(d[(i + 1) % 3][q], q, i + 1);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+}
+
+}  // namespace cb

@@ -746,15 +746,21 @@ hipError_t conv3x3_wgrad(int prec, int cin, int cout, int mode, const WgradArgs&
                         : wg_dispatch<PrecF32>(cin, cout, mode, a, s);
 }
 
-__global__ __launch_bounds__(1024) void pending_reduce_kernel(PendingReduce r) {
+// One launch for up to two pending reduces (a residual block's backward leaves one per conv):
+// blockIdx.y picks. Each launch of its own is about 4.7 us for some 20 MB of partials.
+__global__ __launch_bounds__(1024) void pending_reduce_kernel(PendingReduce r0, PendingReduce r1) {
     __shared__ __align__(16) unsigned char sh[64 * 17 * 16];
-    pending_reduce<1024>(r, sh);
+    if (blockIdx.y == 0) pending_reduce<1024>(r0, sh);
+    else pending_reduce<1024>(r1, sh);
 }
 
-hipError_t flush_pending_reduce(const PendingReduce& r, hipStream_t s) {
-    if (r.nparts <= 0) return hipSuccess;
-    ProfScope ps(s, [&] { return "wgrad_reduce_pending/" + cb_dims(r.cin, r.cout); });
-    hipLaunchKernelGGL(pending_reduce_kernel, dim3(unsigned(r.pstride / 64)), dim3(1024), 0, s, r);
+hipError_t flush_pending_reduces(const PendingReduce& a, const PendingReduce& b, hipStream_t s) {
+    const PendingReduce& r0 = a.nparts > 0 ? a : b;
+    if (r0.nparts <= 0) return hipSuccess;
+    const int two = a.nparts > 0 && b.nparts > 0;
+    ProfScope ps(s, [&] { return "wgrad_reduce_pending/" + cb_dims(r0.cin, r0.cout); });
+    const int nb = std::max(r0.pstride, two ? b.pstride : 0) / 64;
+    hipLaunchKernelGGL(pending_reduce_kernel, dim3(unsigned(nb), unsigned(1 + two)), dim3(1024), 0, s, r0, b);
     return hipGetLastError();
 }
 
