@@ -485,11 +485,13 @@ hipError_t cast_bf16(const float* x, uint16_t* y, int64_t n, hipStream_t s) {
 }
 
 // Whether the DMA path takes this GEMM: bf16 operands with 16-byte aligned rows, multiples of
-// 8 where a tile row is cut along the contiguous dimension, tiles worth filling, operands
-// addressable with 32-bit offsets.
+// 8 where a tile row is cut along the contiguous dimension, operands addressable with 32-bit
+// offsets, and tiles worth filling: at least 64 columns, or a k long enough that what counts is
+// how many workgroups share it (the dense layer on 8 frames, k = 3872: 13 us in 15 splits against
+// 46 us in the register-staged kernel's 8, whose k-blocks wait for their loads in turn).
 static bool gemm_dma_ok(const GemmArgs& a) {
     auto al = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
-    if (a.a_f32 || a.b_f32 || a.M < 64 || a.N < 64 || a.K % 8) return false;
+    if (a.a_f32 || a.b_f32 || a.M < 64 || (a.N < 64 && a.K < 1024) || a.K % 8) return false;
     if (!al(a.a) || !al(a.b) || a.lda % 8 || a.ldb % 8) return false;
     if (!a.a_kcontig && a.M % 8) return false;
     if (!a.b_kcontig && a.N % 8) return false;

@@ -79,3 +79,27 @@ def test_resblock32_backward_equals_two_conv_backwards(case, offset):
         # the sum of their magnitudes, which for these normals is about sqrt(terms) times the sum
         scale = float(n * H * W) ** 0.5 * 0.5 + 1.0
         assert torch.allclose(got, want, rtol=1e-5, atol=2.0 ** -20 * scale * max(float(n * H * W) ** 0.5, 1.0))
+
+
+@pytest.mark.parametrize("n", [1, 7, 8, 63, 64, 65])
+def test_dense_layer_on_few_frames(n):
+    """The dense GEMM at and around the frame count where its tiles are mostly empty: the
+    forward's logits and values against those of the same frames in a batch of 128."""
+    from synth import NetShape, draw_params
+    P = _p()
+    net = NetShape(num_actions=6)
+    params = torch.from_numpy(draw_params(net, 11)).cuda()
+    g = torch.Generator(device="cuda:0").manual_seed(n)
+    obs = torch.randint(0, 256, (n, 84, 84, 4), dtype=torch.uint8, generator=g, device="cuda:0")
+    big = torch.cat([obs, obs[:1].expand(128 - n, -1, -1, -1)]).contiguous()   # the same frames among 128
+    out = []
+    for k, o in ((n, obs), (128, big)):
+        ws = torch.empty(P.impala_workspace_bytes(net, k, P.PREC_BF16, 0), dtype=torch.uint8, device="cuda:0")
+        z, v = torch.empty((k, 6), device="cuda:0"), torch.empty(k, device="cuda:0")
+        P.impala_cnn_fwd(net, P.PREC_BF16, params, o, None, k, ws, 0, z, v)
+        out.append(torch.cat([z[:n], v[:n, None]], 1).double())
+    torch.cuda.synchronize()
+    # h is bf16: its rounding may turn where the k-splits' float32 sums differ, by one part in 2^8 of
+    # single hidden units
+    err = (out[0] - out[1]).norm() / out[1].norm()
+    assert err <= 2.0 ** -8, err
