@@ -127,7 +127,8 @@ __global__ __launch_bounds__(64 * NW, (CbGeom<CI, CO>::WPS)) void conv_bwd_kerne
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             const int k = ks * 32 + g * 8 + j, tap = k / CO, co = k % CO;
-            v[j] = tap < 9 ? a.w[((8 - tap) * CI + o) * CO + co] : 0.f;
+            const float w = a.w[((tap < 9 ? 8 - tap : 0) * CI + o) * CO + co];   // clamped, then selected: no branch
+                    v[j] = tap < 9 ? w : 0.f;
         }
         wf[ks] = make_uint4(pack2bf(v[0], v[1]), pack2bf(v[2], v[3]), pack2bf(v[4], v[5]), pack2bf(v[6], v[7]));
     }
@@ -173,31 +174,35 @@ __global__ __launch_bounds__(64 * NW, (CbGeom<CI, CO>::WPS)) void conv_bwd_kerne
     uint32_t od[G::MAXD], ox[G::MAXX];
     auto win_off = [&](int j, int slots, int nreal, int cbytes) -> uint32_t {
         const int p = j / slots, c = j - p * slots;
-        const int rowi = p / TW, col = p - rowi * TW;
-        const int f = rowi / TR, rr = rowi - f * TR;
-        if (j >= FR * TR * TW * slots || c >= nreal || col < 1 || col > W) return kOOB;
-        if (FR > 1 && (rr < 1 || rr > TH)) return kOOB;
-        return uint32_t(((f * H + rr - 1) * W + col - 1) * cbytes + c * 16);
+        const int rowi = qdiv(p, t.inv_TW), col = p - rowi * TW;
+        const int f = qdiv(rowi, t.inv_TR), rr = rowi - f * TR;
+        const bool in = (j < FR * TR * TW * slots) & (c < nreal) & (uint32_t(col - 1) < uint32_t(W)) &
+                        ((FR == 1) | (uint32_t(rr - 1) < uint32_t(TH)));
+        const uint32_t o = uint32_t(((f * H + rr - 1) * W + col - 1) * cbytes + c * 16);
+        return in ? o : kOOB;
     };
 #pragma unroll
     for (int k = 0; k < G::MAXD; ++k) od[k] = PDY ? kOOB : win_off((wave + NW * k) * 64 + lane, DSL, CO / 8, CO * 2);
     // pooled gradient / argmax rows (PDY): LDS row rr holds pooled row ib0 - 1 + rr with a zero
     // column either side; offsets relative to pooled row -1, a tile adds ib0 rows
     const int PW2 = t.OW + 2;
+    const float inv_PW2 = 1.f / float(PW2);
     const int nsp = t.PR * PW2 * (CO / 8), nsg = t.PR * PW2 * (CO / 16);
     uint32_t opd[PDY ? G::MAXP : 1], oag[PDY ? G::MAXG : 1];
     if constexpr (PDY) {
 #pragma unroll
         for (int k = 0; k < G::MAXP; ++k) {
             const int j = (wave + NW * k) * 64 + lane, px = j / (CO / 8), c = j - px * (CO / 8);
-            const int rr = px / PW2, col = px - rr * PW2;
-            opd[k] = (j < nsp && col >= 1 && col <= t.OW) ? uint32_t((((rr - 1) * t.OW + col - 1) * CO + c * 8) * 2) : kOOB;
+            const int rr = qdiv(px, inv_PW2), col = px - rr * PW2;
+            const uint32_t o = uint32_t((((rr - 1) * t.OW + col - 1) * CO + c * 8) * 2);
+            opd[k] = (j < nsp) & (uint32_t(col - 1) < uint32_t(t.OW)) ? o : kOOB;
         }
 #pragma unroll
         for (int k = 0; k < G::MAXG; ++k) {
             const int j = (wave + NW * k) * 64 + lane, px = j / (CO / 16), c = j - px * (CO / 16);
-            const int rr = px / PW2, col = px - rr * PW2;
-            oag[k] = (j < nsg && col >= 1 && col <= t.OW) ? uint32_t(((rr - 1) * t.OW + col - 1) * CO + c * 16) : kOOB;
+            const int rr = qdiv(px, inv_PW2), col = px - rr * PW2;
+            const uint32_t o = uint32_t(((rr - 1) * t.OW + col - 1) * CO + c * 16);
+            oag[k] = (j < nsg) & (uint32_t(col - 1) < uint32_t(t.OW)) ? o : kOOB;
         }
     }
 #pragma unroll
@@ -563,7 +568,8 @@ __global__ __launch_bounds__(64 * NW, (CbGeom<CI, CO>::WPS)) void conv_bwd_spec_
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
                     const int k = ks * 32 + g * 8 + j, tap = k / CO, co = k % CO;
-                    v[j] = tap < 9 ? a.w[((8 - tap) * CI + o) * CO + co] : 0.f;
+                    const float w = a.w[((tap < 9 ? 8 - tap : 0) * CI + o) * CO + co];   // clamped, then selected: no branch
+                    v[j] = tap < 9 ? w : 0.f;
                 }
                 wf[b][ks] = make_uint4(pack2bf(v[0], v[1]), pack2bf(v[2], v[3]), pack2bf(v[4], v[5]), pack2bf(v[6], v[7]));
             }
@@ -605,31 +611,35 @@ __global__ __launch_bounds__(64 * NW, (CbGeom<CI, CO>::WPS)) void conv_bwd_spec_
     uint32_t od[G::MAXD], ox[G::MAXX];
     auto win_off = [&](int j, int slots, int nreal, int cbytes) -> uint32_t {
         const int p = j / slots, c = j - p * slots;
-        const int rowi = p / TW, col = p - rowi * TW;
-        const int f = rowi / TR, rr = rowi - f * TR;
-        if (j >= FR * TR * TW * slots || c >= nreal || col < 1 || col > W) return kOOB;
-        if (FR > 1 && (rr < 1 || rr > TH)) return kOOB;
-        return uint32_t(((f * H + rr - 1) * W + col - 1) * cbytes + c * 16);
+        const int rowi = qdiv(p, t.inv_TW), col = p - rowi * TW;
+        const int f = qdiv(rowi, t.inv_TR), rr = rowi - f * TR;
+        const bool in = (j < FR * TR * TW * slots) & (c < nreal) & (uint32_t(col - 1) < uint32_t(W)) &
+                        ((FR == 1) | (uint32_t(rr - 1) < uint32_t(TH)));
+        const uint32_t o = uint32_t(((f * H + rr - 1) * W + col - 1) * cbytes + c * 16);
+        return in ? o : kOOB;
     };
 #pragma unroll
     for (int k = 0; k < G::MAXD; ++k) od[k] = PDY ? kOOB : win_off((wave + NW * k) * 64 + lane, DSL, CO / 8, CO * 2);
     // pooled gradient / argmax rows (PDY): LDS row rr holds pooled row ib0 - 1 + rr with a zero
     // column either side; offsets relative to pooled row -1, a tile adds ib0 rows
     const int PW2 = t.OW + 2;
+    const float inv_PW2 = 1.f / float(PW2);
     const int nsp = t.PR * PW2 * (CO / 8), nsg = t.PR * PW2 * (CO / 16);
     uint32_t opd[PDY ? G::MAXP : 1], oag[PDY ? G::MAXG : 1];
     if constexpr (PDY) {
 #pragma unroll
         for (int k = 0; k < G::MAXP; ++k) {
             const int j = (wave + NW * k) * 64 + lane, px = j / (CO / 8), c = j - px * (CO / 8);
-            const int rr = px / PW2, col = px - rr * PW2;
-            opd[k] = (j < nsp && col >= 1 && col <= t.OW) ? uint32_t((((rr - 1) * t.OW + col - 1) * CO + c * 8) * 2) : kOOB;
+            const int rr = qdiv(px, inv_PW2), col = px - rr * PW2;
+            const uint32_t o = uint32_t((((rr - 1) * t.OW + col - 1) * CO + c * 8) * 2);
+            opd[k] = (j < nsp) & (uint32_t(col - 1) < uint32_t(t.OW)) ? o : kOOB;
         }
 #pragma unroll
         for (int k = 0; k < G::MAXG; ++k) {
             const int j = (wave + NW * k) * 64 + lane, px = j / (CO / 16), c = j - px * (CO / 16);
-            const int rr = px / PW2, col = px - rr * PW2;
-            oag[k] = (j < nsg && col >= 1 && col <= t.OW) ? uint32_t(((rr - 1) * t.OW + col - 1) * CO + c * 16) : kOOB;
+            const int rr = qdiv(px, inv_PW2), col = px - rr * PW2;
+            const uint32_t o = uint32_t(((rr - 1) * t.OW + col - 1) * CO + c * 16);
+            oag[k] = (j < nsg) & (uint32_t(col - 1) < uint32_t(t.OW)) ? o : kOOB;
         }
     }
 #pragma unroll

@@ -60,6 +60,55 @@ __global__ __launch_bounds__(64 * NW, (CpGeom<CIN, COUT, MODE>::WPS)) void conv_
     const int H = a.H, W = a.W, TW = W + 2, TRM = t.THmax + 2;
     const int mt = wave % MT, co0 = mt * 16 + g * 4;
 
+    // ---- input staging offsets, tile-invariant per lane (slot k of this wave:
+    // j = (wave + NW*k)*64 + lane), relative to window row 1 at image row 0; a tile adds hc0
+    // rows. Rows off the frame fall outside the frame's buffer resource and read zero.
+    const int ns = U8 ? TRM * TW : TRM * TW * G::SPP;
+    const float inv_TW = 1.f / float(TW);
+    uint32_t ox[G::MAXS];
+#pragma unroll
+    for (int k = 0; k < G::MAXS; ++k) {
+        const int j = (wave + NW * k) * 64 + lane;
+        if constexpr (U8) {
+            const int rr = qdiv(j, inv_TW), col = j - rr * TW;
+            const uint32_t o = uint32_t(((rr - 1) * W + col - 1) * 4);
+            ox[k] = (j < ns) & (uint32_t(col - 1) < uint32_t(W)) ? o : kOOB;
+        } else {
+            const int p = j / G::SPP, c = j - p * G::SPP, rr = qdiv(p, inv_TW), col = p - rr * TW;
+            const uint32_t o = uint32_t((((rr - 1) * W + col - 1) * CIN + c * 8) * 2);
+            ox[k] = (j < ns) & (c < CIN / 8) & (uint32_t(col - 1) < uint32_t(W)) ? o : kOOB;
+        }
+    }
+
+    int lg = blockIdx.x;   // neighbouring bands on one XCD
+    if ((gridDim.x & 7) == 0) lg = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+
+    // input window of a tile, image rows hc0-1 .. hc0+THmax (uint8 frames: the raw bytes). The
+    // next tile's window is issued as soon as the conv has read this one, so its latency
+    // overlaps the max-pool.
+    unsigned char* const sdst = U8 ? raw : win;
+    auto stage = [&](unsigned char* dst, int tile) {
+        const int band = tile % t.nbands, f = tile / t.nbands;
+        const int hc0 = max(2 * band * t.PTH - t.ph, 0);
+        if constexpr (U8) {
+            const int64_t row = a.row_idx ? a.row_idx[f] : f;
+            const uint32_t fb = uint32_t(H) * W * 4;
+            const auto rx = buf_rsrc(static_cast<const uint8_t*>(a.x) + row * fb, fb);
+            const uint32_t hr = uint32_t(hc0 * W * 4);
+#pragma unroll
+            for (int k = 0; k < G::MAXS; ++k)
+                if ((wave + NW * k) * 64 < ns) dma4_to_lds(rx, dst + (wave + NW * k) * 256, ox[k] + hr);
+        } else {
+            const uint32_t fb = uint32_t(H) * W * CIN * 2;
+            const auto rx = buf_rsrc(static_cast<const uint16_t*>(a.x) + int64_t(f) * H * W * CIN, fb);
+            const uint32_t hr = uint32_t(hc0 * W * CIN * 2);
+#pragma unroll
+            for (int k = 0; k < G::MAXS; ++k)
+                if ((wave + NW * k) * 64 < ns) dma16_to_lds(rx, dst + (wave + NW * k) * 1024, ox[k] + hr);
+        }
+    };
+    if (lg < t.ntiles) stage(sdst, lg);
+
     // ---- weight fragments of this wave's output block: A[o][k] = w[k*COUT + o] (HWIO, k =
     // tap*CIN + i), zero past the 9 taps; biases of the lane's four output channels
     uint4 wr[KSTEPS];
@@ -68,8 +117,9 @@ __global__ __launch_bounds__(64 * NW, (CpGeom<CIN, COUT, MODE>::WPS)) void conv_
         float v[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            const int k = ks * 32 + g * 8 + j;
-            v[j] = k < G::K ? a.w[k * COUT + mt * 16 + r16] : 0.f;
+            const int k = ks * 32 + g * 8 + j;   // clamped load, then selected: no branch
+            const float w = a.w[(k < G::K ? k : G::K - 1) * COUT + mt * 16 + r16];
+            v[j] = k < G::K ? w : 0.f;
         }
         wr[ks] = make_uint4(pack2bf(v[0], v[1]), pack2bf(v[2], v[3]), pack2bf(v[4], v[5]), pack2bf(v[6], v[7]));
     }
@@ -123,53 +173,7 @@ __global__ __launch_bounds__(64 * NW, (CpGeom<CIN, COUT, MODE>::WPS)) void conv_
     }
     for (int j = tid; j < t.THmax * TW * KPB / 16; j += NT) reinterpret_cast<uint4*>(keys)[j] = make_uint4(0, 0, 0, 0);
 
-    // ---- input staging offsets, tile-invariant per lane (slot k of this wave:
-    // j = (wave + NW*k)*64 + lane), relative to window row 1 at image row 0; a tile adds hc0
-    // rows. Rows off the frame fall outside the frame's buffer resource and read zero.
-    const int ns = U8 ? TRM * TW : TRM * TW * G::SPP;
-    uint32_t ox[G::MAXS];
-#pragma unroll
-    for (int k = 0; k < G::MAXS; ++k) {
-        const int j = (wave + NW * k) * 64 + lane;
-        if constexpr (U8) {
-            const int rr = j / TW, col = j - rr * TW;
-            ox[k] = (j < ns && col >= 1 && col <= W) ? uint32_t(((rr - 1) * W + col - 1) * 4) : kOOB;
-        } else {
-            const int p = j / G::SPP, c = j - p * G::SPP, rr = p / TW, col = p - rr * TW;
-            ox[k] = (j < ns && c < CIN / 8 && col >= 1 && col <= W)
-                        ? uint32_t((((rr - 1) * W + col - 1) * CIN + c * 8) * 2) : kOOB;
-        }
-    }
     __syncthreads();
-
-    int lg = blockIdx.x;   // neighbouring bands on one XCD
-    if ((gridDim.x & 7) == 0) lg = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
-
-    // input window of a tile, image rows hc0-1 .. hc0+THmax (uint8 frames: the raw bytes). The
-    // next tile's window is issued as soon as the conv has read this one, so its latency
-    // overlaps the max-pool.
-    unsigned char* const sdst = U8 ? raw : win;
-    auto stage = [&](unsigned char* dst, int tile) {
-        const int band = tile % t.nbands, f = tile / t.nbands;
-        const int hc0 = max(2 * band * t.PTH - t.ph, 0);
-        if constexpr (U8) {
-            const int64_t row = a.row_idx ? a.row_idx[f] : f;
-            const uint32_t fb = uint32_t(H) * W * 4;
-            const auto rx = buf_rsrc(static_cast<const uint8_t*>(a.x) + row * fb, fb);
-            const uint32_t hr = uint32_t(hc0 * W * 4);
-#pragma unroll
-            for (int k = 0; k < G::MAXS; ++k)
-                if ((wave + NW * k) * 64 < ns) dma4_to_lds(rx, dst + (wave + NW * k) * 256, ox[k] + hr);
-        } else {
-            const uint32_t fb = uint32_t(H) * W * CIN * 2;
-            const auto rx = buf_rsrc(static_cast<const uint16_t*>(a.x) + int64_t(f) * H * W * CIN, fb);
-            const uint32_t hr = uint32_t(hc0 * W * CIN * 2);
-#pragma unroll
-            for (int k = 0; k < G::MAXS; ++k)
-                if ((wave + NW * k) * 64 < ns) dma16_to_lds(rx, dst + (wave + NW * k) * 1024, ox[k] + hr);
-        }
-    };
-    if (lg < t.ntiles) stage(sdst, lg);
 
     for (int tile = lg; tile < t.ntiles; tile += gridDim.x) {
         const int band = tile % t.nbands, f = tile / t.nbands;

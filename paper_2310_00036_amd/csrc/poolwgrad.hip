@@ -78,23 +78,27 @@ __global__ __launch_bounds__(64 * NW, 4) void pool_wgrad_u8_kernel(PoolWgArgs a,
     // relative to window row 0 at image row 0 / pooled row 0; a tile adds its first row. Rows
     // off the frame fall outside the buffer resource (negative, or past its end) and read zero.
     const int nsr = TR * TW, nsp = (TB + 1) * PW2 * CG, nsg = (TB + 1) * PW2 * (CO / 16);
+    const float inv_TW = 1.f / float(TW), inv_PW2 = 1.f / float(PW2);
     uint32_t orw[G::MAXR], opd[G::MAXP], oag[G::MAXG];
 #pragma unroll
     for (int k = 0; k < G::MAXR; ++k) {
-        const int j = (wave + NW * k) * 64 + lane, rr = j / TW, col = j - rr * TW;
-        orw[k] = (j < nsr && col >= 1 && col <= W) ? uint32_t((rr * W + col - 1) * 4) : kOOB;
+        const int j = (wave + NW * k) * 64 + lane, rr = qdiv(j, inv_TW), col = j - rr * TW;
+        const uint32_t o = uint32_t((rr * W + col - 1) * 4);
+        orw[k] = (j < nsr) & (uint32_t(col - 1) < uint32_t(W)) ? o : kOOB;
     }
 #pragma unroll
     for (int k = 0; k < G::MAXP; ++k) {
         const int j = (wave + NW * k) * 64 + lane, px = j / CG, c = j - px * CG;
-        const int rr = px / PW2, col = px - rr * PW2;
-        opd[k] = (j < nsp && col >= 1 && col <= OW) ? uint32_t(((rr * OW + col - 1) * CO + c * 8) * 2) : kOOB;
+        const int rr = qdiv(px, inv_PW2), col = px - rr * PW2;
+        const uint32_t o = uint32_t(((rr * OW + col - 1) * CO + c * 8) * 2);
+        opd[k] = (j < nsp) & (uint32_t(col - 1) < uint32_t(OW)) ? o : kOOB;
     }
 #pragma unroll
     for (int k = 0; k < G::MAXG; ++k) {
         const int j = (wave + NW * k) * 64 + lane, px = j / (CO / 16), c = j - px * (CO / 16);
-        const int rr = px / PW2, col = px - rr * PW2;
-        oag[k] = (j < nsg && col >= 1 && col <= OW) ? uint32_t((rr * OW + col - 1) * CO + c * 16) : kOOB;
+        const int rr = qdiv(px, inv_PW2), col = px - rr * PW2;
+        const uint32_t o = uint32_t((rr * OW + col - 1) * CO + c * 16);
+        oag[k] = (j < nsg) & (uint32_t(col - 1) < uint32_t(OW)) ? o : kOOB;
     }
 
     // ---- weight-gradient fragments: B column block nb covers taps 4nb..4nb+3 (lane group m

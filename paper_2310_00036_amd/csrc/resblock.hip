@@ -13,7 +13,7 @@
 //     padding columns, exactly what conv2 would have read from HBM;
 //   - conv2 reads that window and writes y with the bias and the residual add fused; the
 //     residual x comes from global memory into registers, fetched with the tile's staging.
-// LDS layout: each window is stored as C/16 planes of 16 channels, 32 bytes per pixel, pixels
+// LDS layout (16 channels): each window is one plane, 32 bytes per pixel, pixels
 // row-major with one zero padding column on each side. gfx950's LDS has 64 four-byte banks and
 // serves a 16-byte read of a wave in four passes of 16 lanes (the lanes of each half-wave whose
 // bits 2..4 have one parity); a pass is conflict-free when its 16 reads land on distinct 16-byte
@@ -21,8 +21,8 @@
 // 64 banks for any run of 16 consecutive window pixels, so a column tile is 16 consecutive window
 // pixels, padding columns included (their outputs are dropped) and never a wrapped run of
 // frame pixels, whose two-pixel jump at a row end would fold two reads onto one bank group.
-// Per MFMA: 16 output pixels per column tile, one 16-byte B fragment per lane and k-step; with
-// 16 channels the k-steps past the 9 taps read a zeroed 16-byte word.
+// Per MFMA: 16 output pixels per column tile, one 16-byte B fragment per lane and k-step; the
+// k-steps past the 9 taps read a zeroed 16-byte word. (32 channels: resblock_walk_fwd_kernel.)
 // Each wave owns one 16-channel block of the outputs and holds both convolutions' A
 // fragments for it in registers, loaded once per workgroup, so LDS holds only the windows.
 #include "common.h"
@@ -39,20 +39,13 @@ struct RbGeom {
     static constexpr int KSTEPS = (K + 31) / 32;
     static constexpr int MT = C / 16;                      // 16-channel planes (and output blocks)
     static constexpr int PXB = 32;                         // bytes per pixel and plane
-    // Workgroup shape: 16 channels hold both weight sets in 8-wave workgroups at 4 waves per
-    // SIMD (128 registers); 32 channels need about 170 registers, so 4-wave workgroups at 3
-    // waves per SIMD (three workgroups per CU) instead of spilling.
-    static constexpr int NW = C >= 32 ? 4 : 8;
-    static constexpr int WPS = C >= 32 ? 3 : 4;            // waves per SIMD (register budget)
+    static_assert(C == 16, "32 channels have a kernel of their own");
+    // Both weight sets in 8-wave workgroups at 4 waves per SIMD (128 registers).
+    static constexpr int NW = 8;
+    static constexpr int WPS = 4;                          // waves per SIMD (register budget)
     static constexpr int WGS = WPS * 4 / NW;               // workgroups per CU
-    static constexpr int MAXS = C >= 32 ? 8 : 5;           // x-window staging slots per lane
-    // conv2 column tiles per wave and tile whose residual is fetched at the tile's start; with 16
-    // channels that covers all of them, with 32 (whose registers hold both weight sets) the
-    // first two, and the rest are read per column tile
-    static constexpr int MAXT = C >= 32 ? 2 : 5;
-    static constexpr bool ALLPRE = C < 32;
-    // x-window staging offsets kept in registers (with 32 channels, recomputed per tile)
-    static constexpr bool OXREG = C < 32;
+    static constexpr int MAXS = 5;                         // x-window staging slots per lane
+    static constexpr int MAXT = 5;   // conv2 column tiles per wave, whose residuals are fetched at the tile's start
     __host__ __device__ static int blocks(int slots) { return (slots + 63) / 64; }
     // x window: MT planes of (TH+4) x (W+2) pixels, in whole 1 KB staging blocks
     __host__ __device__ static int xwin_bytes(int TH, int W) { return blocks(MT * (TH + 4) * (W + 2) * 2) * 1024; }
@@ -86,21 +79,27 @@ __global__ __launch_bounds__(64 * NW, RbGeom<C>::WPS) void resblock_fwd_kernel(R
 
     // ---- A fragments of both convolutions for rows mt*16 .. +15: A[o][k] = w[tap][i][o]
     // with k = tap*C + i (zero past the 9 taps); biases of the lane's four output channels
+    // (the loads of one convolution all in flight, from clamped rows: a launch on few frames
+    // spends most of its time up to here)
     uint4 wr1[KSTEPS], wr2[KSTEPS];
-#pragma unroll
-    for (int ks = 0; ks < KSTEPS; ++ks) {
+    auto load_w = [&](const float* w, uint4 (&wr)[KSTEPS]) CB_INLINE_LAMBDA {
         const int o = mt * 16 + r16;
-        float v1[8], v2[8];
+        float v[KSTEPS][8];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int k = ks * 32 + g * 8 + j;
-            v1[j] = k < G::K ? a.w1[k * C + o] : 0.f;
-            v2[j] = k < G::K ? a.w2[k * C + o] : 0.f;
+        for (int ks = 0; ks < KSTEPS; ++ks)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const int k = ks * 32 + g * 8 + j;
+                v[ks][j] = w[(k < G::K ? k : G::K - 1) * C + o];
+            }
+#pragma unroll
+        for (int ks = 0; ks < KSTEPS; ++ks) {
+            wr[ks] = make_uint4(pack2bf(v[ks][0], v[ks][1]), pack2bf(v[ks][2], v[ks][3]), pack2bf(v[ks][4], v[ks][5]), pack2bf(v[ks][6], v[ks][7]));
+            if (ks * 32 + 31 >= G::K && ks * 32 + g * 8 >= G::K) wr[ks] = make_uint4(0, 0, 0, 0);
         }
-        wr1[ks] = make_uint4(pack2bf(v1[0], v1[1]), pack2bf(v1[2], v1[3]), pack2bf(v1[4], v1[5]), pack2bf(v1[6], v1[7]));
-        wr2[ks] = make_uint4(pack2bf(v2[0], v2[1]), pack2bf(v2[2], v2[3]), pack2bf(v2[4], v2[5]), pack2bf(v2[6], v2[7]));
-        __builtin_amdgcn_sched_barrier(0);   // convert each k-step's weights before loading the next
-    }
+    };
+    load_w(a.w1, wr1);
+    load_w(a.w2, wr2);
     float b1[4], b2[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -111,28 +110,19 @@ __global__ __launch_bounds__(64 * NW, RbGeom<C>::WPS) void resblock_fwd_kernel(R
     // channels (8g % C) .. +7 of one tap: plane (8g % C) / 16, half (g & 1) of the pixel's 32
     // bytes. With 16 channels a k-step spans two taps (table per k-step; lanes g >= 2 of the
     // last k-step are past the 9 taps and read the zero word); with 32, one tap per k-step.
-    int boff[C < 32 ? KSTEPS : 1];
-    if constexpr (C < 32) {
+    int boff[KSTEPS];
 #pragma unroll
-        for (int ks = 0; ks < KSTEPS; ++ks) {
-            const int tap = ks * 2 + (g >> 1);
-            boff[ks] = ((tap / 3) * TW + tap % 3) * PXB + (g & 1) * 16;
-        }
+    for (int ks = 0; ks < KSTEPS; ++ks) {
+        const int tap = ks * 2 + (g >> 1);
+        boff[ks] = ((tap / 3) * TW + tap % 3) * PXB + (g & 1) * 16;
     }
-    const bool zsel = C < 32 && g >= 2;
-    const int lbx = C < 32 ? 0 : (g >> 1) * xps + (g & 1) * 16;   // lane's plane and half
-    const int lbt = C < 32 ? 0 : (g >> 1) * tps + (g & 1) * 16;
-    const int twb = TW * PXB;
+    const bool zsel = g >= 2;
     auto mma = [&](const unsigned char* xb, const unsigned char* zp, const uint4* wr) {
         cb_f32x4 acc = cb_f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int ks = 0; ks < KSTEPS; ++ks) {
-            const unsigned char* p;
-            if constexpr (C < 32) p = ks == KSTEPS - 1 && zsel ? zp : xb + boff[ks];
-            else p = xb + (ks / 3) * twb + (ks % 3) * PXB;
+            const unsigned char* p = ks == KSTEPS - 1 && zsel ? zp : xb + boff[ks];
             acc = PrecBF16::mma(wr[ks], *reinterpret_cast<const uint4*>(p), acc);
-            // with both weight sets held, keep at most three B fragments in flight
-            if (C >= 32 && ks % 3 == 2) __builtin_amdgcn_sched_barrier(0);
         }
         return acc;
     };
@@ -145,16 +135,13 @@ __global__ __launch_bounds__(64 * NW, RbGeom<C>::WPS) void resblock_fwd_kernel(R
     // tile adds h0 - 2 rows. Rows off the frame fall outside the frame's buffer resource
     // (negative, or past its end); padding columns read zero (kOOB).
     const int npx = (TH + 4) * TW, nsx = MT * npx * 2;
-    auto x_off = [&](int k) {
-        const int j = (wave + NW * k) * 64 + lane, pl = j / (npx * 2), rem = j - pl * npx * 2;
-        const int p = rem >> 1, half = rem & 1;
-        const int rr = p / TW, col = p - rr * TW;
-        return (j < nsx && col >= 1 && col <= W) ? uint32_t(((rr * W + col - 1) * C + pl * 16 + half * 8) * 2) : kOOB;
-    };
-    uint32_t ox[G::OXREG ? G::MAXS : 1];
-    if constexpr (G::OXREG) {
+    uint32_t ox[G::MAXS];
 #pragma unroll
-        for (int k = 0; k < G::MAXS; ++k) ox[k] = x_off(k);
+    for (int k = 0; k < G::MAXS; ++k) {
+        const int j = (wave + NW * k) * 64 + lane, p = j >> 1, half = j & 1;
+        const int rr = qdiv(p, t.inv_TW), col = p - rr * TW;
+        const uint32_t off = uint32_t(((rr * W + col - 1) * C + half * 8) * 2);
+        ox[k] = (j < nsx) & (uint32_t(col - 1) < uint32_t(W)) ? off : kOOB;
     }
     __syncthreads();
 
@@ -169,7 +156,7 @@ __global__ __launch_bounds__(64 * NW, RbGeom<C>::WPS) void resblock_fwd_kernel(R
         const uint32_t hr = uint32_t((band * TH - 2) * W * C * 2);   // wraps for h0 < 2: rows off the frame
 #pragma unroll
         for (int k = 0; k < G::MAXS; ++k)
-            if ((wave + NW * k) * 64 < nsx) dma16_to_lds(rx, dst + (wave + NW * k) * 1024, (G::OXREG ? ox[k] : x_off(k)) + hr);
+            if ((wave + NW * k) * 64 < nsx) dma16_to_lds(rx, dst + (wave + NW * k) * 1024, ox[k] + hr);
     };
     if (lg < t.ntiles) stage_x(xw, lg);
 
@@ -231,7 +218,7 @@ __global__ __launch_bounds__(64 * NW, RbGeom<C>::WPS) void resblock_fwd_kernel(R
             const int q = nt * 16 + r16;
             const int pw = pw1 + (q < npx1 ? q : npx1 - 1);
             const int tr = qdiv(pw, t.inv_TW), cw = pw - tr * TW;
-            const cb_f32x4 acc = mma(xw + lbx + (pw - 1) * PXB, tw + MT * tps, wr1);   // tap (0,0): x-window pixel pw - 1
+            const cb_f32x4 acc = mma(xw + (pw - 1) * PXB, tw + MT * tps, wr1);   // tap (0,0): x-window pixel pw - 1
             if (q < npx1 && cw >= 1 && cw <= W) {
                 const int h = h0 - 1 + tr;
                 const uint32_t u0 = pack2bf(acc[0] + b1[0], acc[1] + b1[1]);
@@ -250,12 +237,11 @@ __global__ __launch_bounds__(64 * NW, RbGeom<C>::WPS) void resblock_fwd_kernel(R
         auto stage_conv2 = [&](unsigned char* __restrict__ xdst, const unsigned char* __restrict__ tsrc) {
             if (tile + int(gridDim.x) < t.ntiles) stage_x(xdst, tile + gridDim.x);
             uint16_t* ybase = static_cast<uint16_t*>(a.y) + fo + int64_t(h0) * W * C;
-            auto conv2_tile = [&](int nt, const uint2* pre) {
+            auto conv2_tile = [&](int nt, const uint2& xr) {
                 const int q = nt * 16 + r16;
                 int rb, cw;
                 const int pw = y_px(q, rb, cw);
-                const uint2 xr = pre ? *pre : *reinterpret_cast<const uint2*>(xbase + res_off(rb, cw));
-                const cb_f32x4 acc = mma(tsrc + lbt + (pw - 1) * PXB, tsrc + MT * tps, wr2);   // tap (0,0): t-window pixel pw - 1
+                const cb_f32x4 acc = mma(tsrc + (pw - 1) * PXB, tsrc + MT * tps, wr2);   // tap (0,0): t-window pixel pw - 1
                 if (q < npx2 && cw >= 1 && cw <= W)
                     store4(ybase + uint32_t((rb * W + cw - 1) * C + co0), acc[0] + b2[0] + __uint_as_float(xr.x << 16),
                            acc[1] + b2[1] + __uint_as_float(xr.x & 0xffff0000u),
@@ -264,9 +250,7 @@ __global__ __launch_bounds__(64 * NW, RbGeom<C>::WPS) void resblock_fwd_kernel(R
             };
 #pragma unroll
             for (int k = 0; k < G::MAXT; ++k)
-                if ((wave / MT + k * (NW / MT)) * 16 < npx2) conv2_tile(wave / MT + k * (NW / MT), &xres[k]);
-            if constexpr (!G::ALLPRE)
-                for (int nt = wave / MT + G::MAXT * (NW / MT); nt * 16 < npx2; nt += NW / MT) conv2_tile(nt, nullptr);
+                if ((wave / MT + k * (NW / MT)) * 16 < npx2) conv2_tile(wave / MT + k * (NW / MT), xres[k]);
         };
         stage_conv2(xw, tw);
     }
@@ -290,8 +274,8 @@ __global__ __launch_bounds__(64 * NW, RbGeom<C>::WPS) void resblock_fwd_kernel(R
 //     one 16-byte store per pixel, 1 KB contiguous per wave.
 //   - The weights are read once per workgroup, coalesced, and shared through LDS.
 // Measured against the tile-by-tile form (and, at 42x42, a two-role pipelined form of it):
-// 2048 frames of 21x21 75.0 -> 49.5 us (2.3 -> 3.5 TB/s of its three tensors), 8192 of 42x42 921 ->
-// 813 us, 2048 of 11x11 26.3 -> 22.5 us, 8 of 21x21 12.2 -> 10.3 us. What is left at 21x21: about
+// 2048 frames of 21x21 75 -> 51 us (2.3 -> 3.4 TB/s of its three tensors), 8192 of 42x42 930 -> 825
+// us, 2048 of 11x11 27.3 -> 20.4 us, 8 of 21x21 12.4 -> 9.9 us. What is left at 21x21: about
 // 2.6 us before the first row, then 70% of the matrix cores' time (vector ALU work of the
 // epilogues beside them) and the loads of a tile that the other workgroup does not cover.
 struct RwGeom {
@@ -304,7 +288,7 @@ struct RwGeom {
 struct RwTile {
     int F, TH, nbands, ntiles;   // frames per tile (1 with several bands per frame), rows per band
     int ho;                      // 1: t has a halo row either side (several bands)
-    int t_off, bias_off, spare_off;   // LDS bytes (the x window is at 0)
+    int t_off;                   // LDS bytes of the t window (the x window is at 0)
     int R, nseg1, nseg2;         // rows per walk (the kernel's R), segments of a column: conv1, conv2
     float inv_W, inv_c, inv_TW, inv_xpf;   // 1 / W, 1 / (F * W), 1 / row pitch, 1 / x-window pixels per frame
 };
@@ -316,7 +300,6 @@ __global__ __launch_bounds__(RwGeom::NT, 2) void resblock_walk_fwd_kernel(ResBlo
     extern __shared__ __align__(16) unsigned char smem[];
     unsigned char* xw = smem;                                  // x [F][TH+2+2ho][TW], row 0 = image row h0-1-ho
     unsigned char* tw = smem + t.t_off;                        // relu(t) [F][TH+2][TW], row 0 = image row h0-1
-    float* bias = reinterpret_cast<float*>(smem + t.bias_off); // b1[32], b2[32]
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -340,8 +323,13 @@ __global__ __launch_bounds__(RwGeom::NT, 2) void resblock_walk_fwd_kernel(ResBlo
 #pragma unroll
         for (int i = 0; i < 4; ++i) v[u][i] = load_f4(src + i * C);
     }
-    const float* bsrc = (tid & 32) ? a.b2 : a.b1;
-    const float bval = (bsrc ? bsrc : a.w1)[tid & 31];
+    // biases of the lane's channels 8g .. 8g+7 (loaded from a valid address where there are none)
+    float4 bias1[2], bias2[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        bias1[k] = load_f4((a.b1 ? a.b1 : a.w1) + g * 8 + 4 * k);
+        bias2[k] = load_f4((a.b2 ? a.b2 : a.w1) + g * 8 + 4 * k);
+    }
     // ---- x-window staging offsets, tile-invariant per lane (slot k of this wave: j = (wave +
     // NW*k)*64 + lane: pixel j / 4, position j % 4), relative to the tile's first frame with the
     // window's first row at image row 0; a tile adds that row. Rows off the frame fall outside
@@ -365,10 +353,8 @@ __global__ __launch_bounds__(RwGeom::NT, 2) void resblock_walk_fwd_kernel(ResBlo
         const auto rx = buf_rsrc(static_cast<const uint16_t*>(a.x) + int64_t(f) * H * W * C, uint32_t(nf) * H * W * C * 2);
         const uint32_t hr = ho ? uint32_t((band * TH - 2) * W * C * 2) : 0u;   // wraps for h0 < 2: rows off the frame
 #pragma unroll
-        for (int k = 0; k < G::MAXS; ++k) {   // slots past the window read zero into a spare block: no branches
-            const int blk = wave + NW * k;
-            dma16_to_lds(rx, smem + (blk * 64 < nsx ? blk * 1024 : t.spare_off), ox[k] + hr);
-        }
+        for (int k = 0; k < G::MAXS; ++k)
+            if ((wave + NW * k) * 64 < nsx) dma16_to_lds(rx, xw + (wave + NW * k) * 1024, ox[k] + hr);
     };
     if (lg < t.ntiles) stage_x(lg);
 
@@ -386,7 +372,11 @@ __global__ __launch_bounds__(RwGeom::NT, 2) void resblock_walk_fwd_kernel(ResBlo
                     *reinterpret_cast<uint2*>(dst + j * 16) = make_uint2(pack2bf(f[j], f[4 + j]), pack2bf(f[8 + j], f[12 + j]));
             }
         }
-        if (tid < 2 * C) bias[tid] = bsrc ? bval : 0.f;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            if (!a.b1) bias1[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (!a.b2) bias2[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+        }
         lds_barrier();
 #pragma unroll
         for (int b = 0; b < 2; ++b)
@@ -426,7 +416,7 @@ __global__ __launch_bounds__(RwGeom::NT, 2) void resblock_walk_fwd_kernel(ResBlo
                 const bool own = an.ok && an.fi < nf;
                 walk_conv32<R, true>(xw, an.fi * xpf + an.row0 * TW + an.c, an.c, g, rowb, w1, [] {},
                     [&](int j, const cb_f32x4 (&acc)[2]) {
-                        const float4 ba = *reinterpret_cast<const float4*>(bias + g * 8), bb = *reinterpret_cast<const float4*>(bias + g * 8 + 4);
+                        const float4 ba = bias1[0], bb = bias1[1];
                         uint4 u = make_uint4(pack2bf(acc[0][0] + ba.x, acc[0][1] + ba.y), pack2bf(acc[0][2] + ba.z, acc[0][3] + ba.w),
                                              pack2bf(acc[1][0] + bb.x, acc[1][1] + bb.y), pack2bf(acc[1][2] + bb.z, acc[1][3] + bb.w));
                         const int h = hb + j;
@@ -457,7 +447,7 @@ __global__ __launch_bounds__(RwGeom::NT, 2) void resblock_walk_fwd_kernel(ResBlo
                         xa += rowb;
                     },
                     [&](int j, const cb_f32x4 (&acc)[2]) {
-                        const float4 ba = *reinterpret_cast<const float4*>(bias + C + g * 8), bb = *reinterpret_cast<const float4*>(bias + C + g * 8 + 4);
+                        const float4 ba = bias2[0], bb = bias2[1];
                         if (own && an.row0 + j >= an.rbeg && an.row0 + j < the)
                             store16(ybase + go,
                                 make_uint4(pack2bf(acc[0][0] + ba.x + bf_lo(xr.x), acc[0][1] + ba.y + bf_hi(xr.x)),
@@ -486,8 +476,7 @@ hipError_t rb_fwd_launch(const ResBlockArgs& a, hipStream_t s) {
     auto lds = [&](int th) { return size_t(G::xwin_bytes(th, W)) + G::twin_bytes(th, W); };
     auto fits = [&](int th) {
         const int tiles = (th * (W + 2) - 2 + 15) / 16, per = kRbWaves / G::MT;
-        return G::blocks(G::MT * (th + 4) * (W + 2) * 2) <= G::MAXS * kRbWaves &&
-               (!G::ALLPRE || (tiles + per - 1) / per <= G::MAXT);
+        return G::blocks(G::MT * (th + 4) * (W + 2) * 2) <= G::MAXS * kRbWaves && (tiles + per - 1) / per <= G::MAXT;
     };
     int thmax = H;
     while (thmax > 1 && (lds(thmax) > kRbLdsTarget || !fits(thmax))) --thmax;
@@ -533,7 +522,7 @@ hipError_t rw_launch(const ResBlockArgs& a, hipStream_t s) {
             if (nb > 1 && (H + TH - 1) / TH != nb) continue;
             for (int F = 1; F <= (ho ? 1 : std::min<int64_t>(a.n, 16)); ++F) {
                 const int xb = walk_win_bytes(F, TH + 2 + 2 * ho, W), tb = std::max(walk_win_bytes(F, TH + 2, W), 2 * G::WFRAG);
-                const size_t lds = size_t(xb) + tb + 256 + 1024;
+                const size_t lds = size_t(xb) + tb;
                 if (lds > G::LDS_TARGET || xb > G::MAXS * G::NW * 1024) break;
                 RwTile c{};
                 c.F = F; c.TH = TH; c.ho = ho; c.nbands = nb;
@@ -546,8 +535,6 @@ hipError_t rw_launch(const ResBlockArgs& a, hipStream_t s) {
                         best = cost;
                         t = c;
                         t.t_off = xb;
-                        t.bias_off = xb + tb;
-                        t.spare_off = xb + tb + 256;
                         L = lds;
                     }
                 }
