@@ -28,6 +28,7 @@
 // k-steps, loaded once per workgroup.
 #include "common.h"
 #include "kernels.h"
+#include "walk.h"
 
 #include <algorithm>
 #include <type_traits>
@@ -502,8 +503,8 @@ __global__ __launch_bounds__(64 * NW, (CbGeom<CI, CO>::WPS)) void conv_bwd_kerne
     }
 }
 
-// The same backward with specialised waves, for 64 channels (one workgroup per CU) and the
-// 16 -> 32 stage entry (two per CU). There every wave forming both gradients reads each
+// The same backward with specialised waves, for 64 channels (one workgroup per CU; relu'd inputs
+// only where conv_bwd64_walk_kernel below finds no tile) and the 16 -> 32 stage entry (two per CU). There every wave forming both gradients reads each
 // input-gradient B fragment for one dx channel block (1 KB of LDS per MFMA, more than the LDS
 // delivers at the matrix cores' rate) and holds the weight-gradient accumulators beside the
 // input-gradient weights. Here the first half of the waves forms the input gradient, two dx
@@ -1006,6 +1007,218 @@ __global__ __launch_bounds__(64 * NW, (CbGeom<CI, CO>::WPS)) void conv_bwd_spec_
     }
 }
 
+// The backward of a 64 -> 64 convolution with a relu'd input by column walks (walk.h), one 8-wave
+// workgroup per CU with two wave roles running beside each other on a tile: waves 0-3 form dx,
+// each for 32 channels (144 registers of weights) and every other group of anchors; waves 4-7 the
+// weight gradients, each a 32 x 32 channel block of all nine taps (152 registers), and stage the
+// next tile's windows into the other buffers. Each dy fragment read feeds the three dx rows it
+// touches (6 MFMAs instead of 2), each x fragment the three dy rows it meets. Measured against the
+// form that reads each fragment once per tap (conv_bwd_spec_kernel): 8192 frames of 21x21 with the
+// residual 830 -> 577 us (640 -> 925 TFLOP/s), of 11x11 254 -> 183 us, 640 of 21x21 98.7 -> 68.4 us, 5
+// of 21x21 25 -> 20 us. What bounds it: the MFMAs of a SIMD's two waves (230 us at the matrix cores' rate at
+// 21x21) and the vector instructions between them.
+struct Cw64Geom {
+    static constexpr int C = 64, NW = 8, NT = 512, NS = 4;   // NS: waves per role
+    static constexpr int NBB = 37, PSTRIDE = 4 * NBB * 256;  // partial: [co block][tap x ci block, bias][co][ci]
+    static constexpr int MAXS = 10;                          // staging slots per lane and window
+};
+struct Cw64Tile {
+    int F, TH, nbands, ntiles;
+    int ho;                    // several bands per frame
+    int win;                   // window bytes; LDS: dy, x of buffer 0, then of buffer 1
+    int R, nsegd, nsegw;       // rows per walk (the kernel's R), segments of a column: dx, weight gradients
+    int parts;                 // workgroups
+    float inv_W, inv_c, inv_TW, inv_pf;   // 1 / W, F * W, row pitch, window pixels per frame
+};
+
+template <int R, int ADD>
+__global__ __launch_bounds__(Cw64Geom::NT, 2) void conv_bwd64_walk_kernel(ConvBwdArgs a, Cw64Tile t) {
+    using G = Cw64Geom;
+    constexpr int NT = G::NT, NS = G::NS, C = G::C;
+    extern __shared__ __align__(16) unsigned char smem[];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const bool dgrad = wave < NS;
+    const int rw = wave & (NS - 1);
+    const int H = a.H, W = a.W, F = t.F, TH = t.TH, TW = walk_pitch(W);
+    const int pf = (TH + 2) * TW, nsl = (F * pf + 1) * 8, rowb = TW * 128, cols = F * W;
+
+    if (a.pend.nparts > 0) pending_reduce<NT>(a.pend, smem);
+    if (a.pend2.nparts > 0) pending_reduce<NT>(a.pend2, smem);
+    // ---- weights: A[o][tap * 64 + co] = w[8 - tap][o][co], packed into A fragments in LDS (73 KB):
+    // fragment (o / 32, b, k-step), whose row 4 i + j is channel 32 (o / 32) + 8 i + 4 b + j
+    {
+        constexpr int UNITS = 9 * C * (C / 4), PER = UNITS / NT, BATCH = 9;
+        static_assert(PER == 2 * BATCH && PER * NT == UNITS, "two whole batches per thread");
+#pragma unroll
+        for (int bt = 0; bt < 2; ++bt) {
+            float4 v[BATCH];
+#pragma unroll
+            for (int u = 0; u < BATCH; ++u) v[u] = load_f4(a.w + (tid + (bt * BATCH + u) * NT) * 4);
+#pragma unroll
+            for (int u = 0; u < BATCH; ++u) {
+                const int r = tid + (bt * BATCH + u) * NT;   // ((tap * 64) + o) * 16 + co / 4
+                const int tap = 8 - r / (C * 16), o = r / 16 % C, c4 = r % 16;
+                const int fr = ((o >> 5) * 2 + ((o >> 2) & 1)) * 18 + tap * 2 + (c4 >> 3);
+                *reinterpret_cast<uint2*>(smem + (fr * 64 + ((c4 >> 1) & 3) * 16 + 4 * ((o >> 3) & 3) + (o & 3)) * 16 + (c4 & 1) * 8) =
+                    make_uint2(pack2bf(v[u].x, v[u].y), pack2bf(v[u].z, v[u].w));
+            }
+        }
+    }
+    __syncthreads();
+
+    int lg = blockIdx.x;   // neighbouring bands (which share halo rows) on one XCD
+    if ((gridDim.x & 7) == 0) lg = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    const int G0 = int(gridDim.x);
+
+    if (dgrad) {
+        const int oh = rw & 1;
+        uint4 w[2][18];
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int ks = 0; ks < 18; ++ks) w[b][ks] = *reinterpret_cast<const uint4*>(smem + (((oh * 2 + b) * 18 + ks) * 64 + lane) * 16);
+        lds_barrier();   // the windows may land there
+        for (int tile = lg, k = 0; tile < t.ntiles; tile += G0, k ^= 1) {
+            int ln = lane;
+            asm volatile("" : "+v"(ln));   // anchors and row masks are formed per tile: kept over tiles they spill
+            const int g = ln >> 4, r16 = ln & 15;
+            const int band = tile % t.nbands, f = (tile / t.nbands) * F;
+            const int h0 = band * TH, the = H - h0 < TH ? H - h0 : TH;
+            const int nf = a.n - f < F ? a.n - f : F;
+            const int64_t fo = int64_t(f) * H * W * C;
+            const unsigned char* dyw = smem + k * 2 * t.win;
+            const unsigned char* xw = dyw + t.win;
+            const uint32_t bytes = uint32_t(nf) * H * W * C * 2;
+            const auto radd = buf_rsrc(ADD ? static_cast<const uint16_t*>(a.add) + fo : nullptr, ADD ? bytes : 0);
+            const auto rdx = buf_rsrc(static_cast<uint16_t*>(a.dx) + fo, bytes);
+            lds_barrier();   // this tile's windows have landed
+            for (int grp = rw >> 1; grp * 16 < t.nsegd * cols; grp += 2) {
+                const WalkAnchor an = walk_anchor(grp * 16 + r16, cols, W, t.nsegd, R, TH, t.inv_c, t.inv_W);
+                uint32_t xa = uint32_t(an.fi * pf + (an.row0 + 1) * TW + an.c + 1) * 128 + walk64_ch(an.c + 1, oh * 64 + g * 16);
+                const uint32_t go = uint32_t((((an.fi * H + h0 + an.row0) * W + an.c) * C + oh * 32 + g * 8) * 2);
+                const int jbeg = an.ok ? an.rbeg - an.row0 : R, jend = the - an.row0;   // rows this lane stores
+                const uint32_t one = 0x00010001u, top = 0x7f807f80u;
+                uint4 mk = make_uint4(0, 0, 0, 0), sk[3];
+                walk_conv64<R>(dyw, an.fi * pf + an.row0 * TW + an.c, an.c, g, rowb, w,
+                    [&](int i) {
+                        if (ADD && i < R) sk[i % 3] = buf_load16(radd, go + uint32_t(i * W * C * 2));   // two rows ahead
+                        if (i >= 2) {
+                            mk = *reinterpret_cast<const uint4*>(xw + xa);
+                            xa += rowb;
+                        }
+                    },
+                    [&](int j, const cb_f32x4 (&acc)[2]) {
+                        uint4 u;
+                        if constexpr (ADD) {
+                            const uint4 s = sk[j % 3];
+                            u = make_uint4(pack2bf((bf_lo(mk.x) > 0.f ? acc[0][0] : 0.f) + bf_lo(s.x), (bf_hi(mk.x) > 0.f ? acc[0][1] : 0.f) + bf_hi(s.x)),
+                                           pack2bf((bf_lo(mk.y) > 0.f ? acc[0][2] : 0.f) + bf_lo(s.y), (bf_hi(mk.y) > 0.f ? acc[0][3] : 0.f) + bf_hi(s.y)),
+                                           pack2bf((bf_lo(mk.z) > 0.f ? acc[1][0] : 0.f) + bf_lo(s.z), (bf_hi(mk.z) > 0.f ? acc[1][1] : 0.f) + bf_hi(s.z)),
+                                           pack2bf((bf_lo(mk.w) > 0.f ? acc[1][2] : 0.f) + bf_lo(s.w), (bf_hi(mk.w) > 0.f ? acc[1][3] : 0.f) + bf_hi(s.w)));
+                        } else {
+                            u = make_uint4(pos_mask16x2(mk.x, pack2bf(acc[0][0], acc[0][1]), one, top), pos_mask16x2(mk.y, pack2bf(acc[0][2], acc[0][3]), one, top),
+                                           pos_mask16x2(mk.z, pack2bf(acc[1][0], acc[1][1]), one, top), pos_mask16x2(mk.w, pack2bf(acc[1][2], acc[1][3]), one, top));
+                        }
+                        const bool mine = (j >= jbeg) & (j < jend);   // others' offsets fall off the buffer
+                        buf_store16(rdx, mine ? go + uint32_t(j * W * C * 2) : kOOB, u);
+                    });
+            }
+        }
+        return;
+    }
+
+    // ---- weight-gradient role. Staging offsets, the same for dy and x: slot j = (rw + NS*k)*64 +
+    // lane: pixel j / 8, position j % 8, relative to the tile's first frame with the window's first
+    // row at image row -1; rows off the frame fall outside the buffer resource (whole frames: kOOB)
+    uint32_t ox[G::MAXS];
+#pragma unroll
+    for (int k = 0; k < G::MAXS; ++k) {
+        const int j = (rw + NS * k) * 64 + lane, p = j >> 3;
+        const int fi = qdiv(p, t.inv_pf), pr = p - fi * pf, rr = qdiv(pr, t.inv_TW), col = pr - rr * TW, h = rr - 1;
+        const int q = (j & 7) ^ (col & 6);
+        const bool in = (j < nsl) & (uint32_t(col - 1) < uint32_t(W)) & ((t.ho != 0) | (uint32_t(h) < uint32_t(H)));
+        const uint32_t off = uint32_t((((fi * H + h) * W + col - 1) * C + q * 8) * 2);
+        ox[k] = in ? off : kOOB;
+    }
+    const int cip = rw & 1, cop = rw >> 1;
+    cb_f32x4 acc[9][2][2], accb[2];
+#pragma unroll
+    for (int k = 0; k < 9; ++k)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[k][q >> 1][q & 1] = cb_f32x4{0.f, 0.f, 0.f, 0.f};
+    accb[0] = accb[1] = cb_f32x4{0.f, 0.f, 0.f, 0.f};
+    auto stage = [&](unsigned char* ddst, unsigned char* xdst, int tile) CB_INLINE_LAMBDA {
+        const int band = tile % t.nbands, f = (tile / t.nbands) * F;
+        const int nf = a.n - f < F ? a.n - f : F, fel = H * W * C;
+        const uint32_t bytes = uint32_t(nf) * fel * 2, hr = uint32_t(band * TH * W * C * 2);
+        const auto rd = buf_rsrc(static_cast<const uint16_t*>(a.dy) + int64_t(f) * fel, bytes);
+        const auto rx = buf_rsrc(static_cast<const uint16_t*>(a.x) + int64_t(f) * fel, bytes);
+#pragma unroll
+        for (int k = 0; k < G::MAXS; ++k)
+            if ((rw + NS * k) * 64 < nsl) {
+                dma16_to_lds(rd, ddst + (rw + NS * k) * 1024, ox[k] + hr);
+                dma16_to_lds(rx, xdst + (rw + NS * k) * 1024, ox[k] + hr);
+            }
+    };
+    // the windows being staged and those read are restrict parameters of one call, so the compiler
+    // knows that the loads in flight do not write what is read
+    auto work = [&](unsigned char* __restrict__ ddst, unsigned char* __restrict__ xdst, const unsigned char* __restrict__ dsrc,
+                    const unsigned char* __restrict__ xsrc, int next) CB_INLINE_LAMBDA {
+        if (next < t.ntiles) stage(ddst, xdst, next);
+        for (int grp = 0; grp * 32 < t.nsegw * cols; ++grp) {
+            int ln = lane;
+            asm volatile("" : "+v"(ln));   // (as above)
+            const int g = ln >> 4, jj = (ln >> 2) & 3, m = ln & 3;
+            int px[2], pd[2], c[2], skip[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const WalkAnchor an = walk_anchor(grp * 32 + h * 16 + 4 * g + jj, cols, W, t.nsegw, R, TH, t.inv_c, t.inv_W);
+                px[h] = an.fi * pf + an.row0 * TW + an.c;
+                pd[h] = an.fi * pf + (an.row0 + 1) * TW + an.c + 1;
+                c[h] = an.c;
+                skip[h] = an.ok ? an.rbeg - an.row0 : R;
+            }
+            walk_wgrad64<R>(xsrc, dsrc, px, pd, c, skip, uint32_t(cip * 64 + m * 8), uint32_t(cop * 64 + m * 8), rowb, acc, accb);
+        }
+    };
+    lds_barrier();   // the weights have been read
+    if (lg < t.ntiles) stage(smem, smem + t.win, lg);
+    for (int tile = lg, k = 0; tile < t.ntiles; tile += G0, k ^= 1) {
+        unsigned char* cur = smem + k * 2 * t.win;
+        unsigned char* nxt = smem + (k ^ 1) * 2 * t.win;
+        // this wave's loads have landed; relu of its own x blocks before the others see them
+        // (relu(x) > 0 exactly where x > 0, so dx's mask reads them too)
+        __builtin_amdgcn_s_waitcnt(0);
+#pragma unroll
+        for (int q = 0; q < G::MAXS; ++q)
+            if ((rw + NS * q) * 64 < nsl) {
+                uint4* p = reinterpret_cast<uint4*>(cur + t.win + (rw + NS * q) * 1024) + lane;
+                *p = relu8(*p);
+            }
+        lds_barrier();   // this tile's windows have landed; the other buffers have been read
+        work(nxt, nxt + t.win, cur, cur + t.win, tile + G0);
+    }
+
+    // ---- this workgroup's partial
+    const int g = lane >> 4, r16 = lane & 15;
+    float* part = a.partial + int64_t(blockIdx.x) * G::PSTRIDE;
+#pragma unroll
+    for (int co = 0; co < 2; ++co) {
+        float* dst = part + (cop * 2 + co) * G::NBB * 256;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int at = (4 * g + e) * 16 + r16;
+#pragma unroll
+            for (int k = 0; k < 9; ++k)
+#pragma unroll
+                for (int ci = 0; ci < 2; ++ci) dst[(k * 4 + cip * 2 + ci) * 256 + at] = acc[k][ci][co][e];
+            if (cip == 0) dst[36 * 256 + at] = accb[co][e];
+        }
+    }
+}
+
 namespace {
 
 constexpr int kCbWaves = 8;
@@ -1018,10 +1231,69 @@ int cb_parts_cap() {
     return int(cap < 256 ? 256 : (cap > 1024 ? 1024 : cap));
 }
 
+// Tile shapes of the 64-channel column-walk kernel: rounds of tiles over the CUs times a tile's
+// estimated cycles (both roles' MFMAs on their shared SIMD, or its loads at 8 bytes per cycle and
+// CU). Returns hipErrorNotSupported where no tile fits two window pairs (widths above about 100).
+template <int ADD>
+hipError_t cw64_launch(const ConvBwdArgs& a, hipStream_t s, int& parts) {
+    using G = Cw64Geom;
+    const int H = a.H, W = a.W, cus = std::min(device_cus(), 256);
+    if (int64_t(H) * W * G::C * 2 * 16 >= (int64_t(1) << 31)) return hipErrorNotSupported;
+    static thread_local WalkPlans<Cw64Tile> plans;
+    const auto* plan = plans.find(a.n, H, W, cus);
+    if (!plan) {
+        const size_t limit = std::min<size_t>(lds_limit(), 160 * 1024);
+        Cw64Tile t{};
+        double best = 1e30;
+        for (int nb = 1; nb <= H; ++nb) {
+            const int TH = (H + nb - 1) / nb, ho = nb > 1;
+            if (nb > 1 && (H + TH - 1) / TH != nb) continue;
+            for (int F = 1; F <= (ho ? 1 : std::min<int64_t>(a.n, 16)); ++F) {
+                Cw64Tile c{};
+                c.win = walk64_win_bytes(F, TH + 2, W);
+                if (4 * size_t(c.win) > limit || c.win > G::MAXS * G::NS * 1024) break;
+                c.F = F; c.TH = TH; c.ho = ho; c.nbands = nb;
+                c.ntiles = int((a.n + F - 1) / F) * nb;
+                const double mem = double(F) * W * 128 * (3 * TH + 4) / 8;
+                for (c.R = 1; c.R <= std::min(TH, kWalkMaxR); ++c.R) {
+                    const double work = 36 * walk_rows(TH, F * W, 16, 2, c.R, c.nsegd) + 38 * walk_rows(TH, F * W, 32, 1, c.R, c.nsegw);
+                    const double cost = double((c.ntiles + cus - 1) / cus) * (std::max(18 * work, mem) + 1500);
+                    if (cost < best) { best = cost; t = c; }
+                }
+            }
+        }
+        if (t.win == 0) return hipErrorNotSupported;
+        t.parts = std::min(cus, t.ntiles);
+        t.inv_W = 1.f / float(W); t.inv_c = 1.f / float(t.F * W); t.inv_TW = 1.f / float(walk_pitch(W));
+        t.inv_pf = 1.f / float((t.TH + 2) * walk_pitch(W));
+        plan = plans.put({a.n, H, W, cus, t, std::max<size_t>(4 * size_t(t.win), 72 * 1024)});
+    }
+    parts = plan->t.parts;
+    walk_dispatch(plan->t.R, [&](auto r) {
+        ProfScope ps(s, [&] { return cb_key("conv_bwd", 0, cb_dims(64, 64) + "/" + cb_dims(H, W) + cb_flags(IN_RELU, false, ADD)); });
+        hipLaunchKernelGGL((conv_bwd64_walk_kernel<decltype(r)::value, ADD>), dim3(unsigned(parts)), dim3(G::NT), plan->lds, s, a, plan->t);
+    });
+    return hipGetLastError();
+}
+
 template <int CI, int CO, int MODE, int ADD, int PDY>
 hipError_t cb_launch(const ConvBwdArgs& a, hipStream_t s, PendingReduce* deferred) {
     using G = CbG<CI, CO, PDY>;
     const int H = a.H, W = a.W;
+    if constexpr (CI == 64 && CO == 64 && MODE == IN_RELU) {
+        static_assert(Cw64Geom::PSTRIDE == G::PSTRIDE, "one partial layout");
+        int parts = 0;
+        const hipError_t e = cw64_launch<ADD>(a, s, parts);
+        if (e != hipErrorNotSupported) {
+            if (e != hipSuccess) return e;
+            if (deferred) {
+                *deferred = PendingReduce{a.partial, a.dw, a.db, parts, G::PSTRIDE, CI, CO, 0, 1.f};
+                return hipSuccess;
+            }
+            ProfScope ps(s, [&] { return cb_key("conv_bwd_reduce", 0, cb_dims(CI, CO) + "/" + cb_dims(H, W) + cb_flags(MODE, false, ADD)); });
+            return wgrad_reduce_tr(CI, CO, a.partial, parts, a.dw, a.db, 1.f, s);
+        }
+    }
     // max-pool geometry of a pooled input gradient (PDY): XLA SAME padding split
     const int OH = (H + 1) / 2, OW = (W + 1) / 2;
     const int PH = (OH - 1) * 2 + 3 - H, PWd = (OW - 1) * 2 + 3 - W;

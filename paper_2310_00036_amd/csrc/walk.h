@@ -197,4 +197,112 @@ CB_DEV void walk_wgrad(const unsigned char* xwin, const unsigned char* dwin, con
         }
 }
 
+// ---- 64 channels: 128 bytes per pixel, the eight 16-byte slots permuted by XOR with bits 1, 2 of the
+// column (free of bank conflicts for the same reads). A fragment's registers take the next row's
+// fragment as soon as its MFMAs are issued, so one set of them is enough.
+__host__ __device__ inline int walk64_win_bytes(int F, int rows, int W) { return ((F * rows * walk_pitch(W) + 1) * 128 + 1023) / 1024 * 1024; }
+CB_DEV uint32_t walk64_ch(uint32_t col, uint32_t ch) { return ch ^ ((col << 4) & 96); }
+
+// walk_conv32 for 64 input channels and 32 of the output channels: w[b][2 tap + half].
+template <int R, class Pre, class Emit>
+CB_DEV void walk_conv64(const unsigned char* win, int p0, int c, int g, int rowb, const uint4 (&w)[2][18], Pre&& pre, Emit&& emit) {
+    uint32_t ad[3][2];
+    uint4 x[3][2];
+    cb_f32x4 acc[3][2];
+#pragma unroll
+    for (int kx = 0; kx < 3; ++kx)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            ad[kx][h] = uint32_t(p0 + kx) * 128 + walk64_ch(uint32_t(c + kx), uint32_t(h) * 64 + uint32_t(g) * 16);
+            x[kx][h] = *reinterpret_cast<const uint4*>(win + ad[kx][h]);
+        }
+#pragma unroll
+    for (int i = 0; i < R + 2; ++i) {
+        pre(i);
+#pragma unroll
+        for (int kx = 0; kx < 3; ++kx)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+#pragma unroll
+                for (int ky = 2; ky >= 0; --ky)
+                    if (i >= ky && i - ky < R)
+#pragma unroll
+                        for (int b = 0; b < 2; ++b)
+                            acc[(i - ky) % 3][b] = PrecBF16::mma(w[b][(3 * ky + kx) * 2 + h], x[kx][h],
+                                                                 ky + kx + h == 0 ? cb_f32x4{0.f, 0.f, 0.f, 0.f} : acc[(i - ky) % 3][b]);
+                if (i < R + 1) {
+                    ad[kx][h] += rowb;
+                    x[kx][h] = *reinterpret_cast<const uint4*>(win + ad[kx][h]);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        if (i >= 2) emit(i - 2, acc[(i - 2) % 3]);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// walk_wgrad for 32 of the input channels (blocks cb, cb + 1, cb even) and 32 of the output channels,
+// over one fragment of 32 anchors: acc[tap][ci block][co block], accb[co block].
+template <int R>
+CB_DEV void walk_wgrad64(const unsigned char* xwin, const unsigned char* dwin, const int (&px)[2], const int (&pd)[2], const int (&c)[2],
+                         const int (&skip)[2], uint32_t chx, uint32_t chd, int rowb, cb_f32x4 (&acc)[9][2][2], cb_f32x4 (&accb)[2]) {
+    uint32_t ax[2][3], ad[2];
+    uint4 x[3][2], d[4][2];
+    const uint4 ones = make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u);
+    auto load_d = [&](uint4 (&dst)[2], int i) CB_INLINE_LAMBDA {
+        const uint32_t a0 = i >= skip[0] ? ad[0] : 0u, a1 = i >= skip[1] ? ad[1] : 0u;
+#pragma unroll
+        for (int co = 0; co < 2; ++co) {   // the next channel block's chunk: address bit 5
+            const uint2 lo = lds_read_tr16(dwin + (a0 ^ uint32_t(co * 32))), hi = lds_read_tr16(dwin + (a1 ^ uint32_t(co * 32)));
+            dst[co] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+        }
+    };
+    auto load_x = [&](int kx, int ci) CB_INLINE_LAMBDA {
+        const uint2 lo = lds_read_tr16(xwin + (ax[0][kx] ^ uint32_t(ci * 32))), hi = lds_read_tr16(xwin + (ax[1][kx] ^ uint32_t(ci * 32)));
+        x[kx][ci] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+    };
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        ad[h] = uint32_t(pd[h]) * 128 + walk64_ch(uint32_t(c[h] + 1), chd);
+#pragma unroll
+        for (int kx = 0; kx < 3; ++kx) ax[h][kx] = uint32_t(px[h] + kx) * 128 + walk64_ch(uint32_t(c[h] + kx), chx);
+    }
+    load_d(d[0], 0);
+#pragma unroll
+    for (int kx = 0; kx < 3; ++kx)
+#pragma unroll
+        for (int ci = 0; ci < 2; ++ci) load_x(kx, ci);
+#pragma unroll
+    for (int i = 0; i < R + 2; ++i) {
+        if (i + 1 < R) {
+            ad[0] += rowb;
+            ad[1] += rowb;
+            load_d(d[(i + 1) % 4], i + 1);
+        }
+#pragma unroll
+        for (int kx = 0; kx < 3; ++kx) {
+#pragma unroll
+            for (int ci = 0; ci < 2; ++ci)
+#pragma unroll
+                for (int ky = 2; ky >= 0; --ky)
+                    if (i >= ky && i - ky < R)
+#pragma unroll
+                        for (int co = 0; co < 2; ++co)
+                            acc[3 * ky + kx][ci][co] = PrecBF16::mma(d[(i - ky) % 4][co], x[kx][ci], acc[3 * ky + kx][ci][co]);
+            __builtin_amdgcn_sched_barrier(0);
+            if (i < R + 1) {
+                ax[0][kx] += rowb;
+                ax[1][kx] += rowb;
+                load_x(kx, 0);
+                load_x(kx, 1);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (i < R)
+#pragma unroll
+            for (int co = 0; co < 2; ++co) accb[co] = PrecBF16::mma(d[i % 4][co], ones, accb[co]);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
 }  // namespace cb

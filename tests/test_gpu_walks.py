@@ -103,3 +103,28 @@ def test_dense_layer_on_few_frames(n):
     # single hidden units
     err = (out[0] - out[1]).norm() / out[1].norm()
     assert err <= 2.0 ** -8, err
+
+
+@pytest.mark.parametrize("case", SHAPES, ids=lambda c: "n%d_%dx%d" % c)
+@pytest.mark.parametrize("add", [False, True])
+def test_conv64_backward_equals_input_and_weight_gradient(case, add):
+    P = _p()
+    n, H, W = case
+    off = 2 if add else 0
+    g = torch.Generator(device="cuda:0").manual_seed(n * 1019 + H * 41 + W)
+    dy, x, skip = (_act(g, (n, H, W, 64), off) for _ in range(3))
+    skip = skip if add else None
+    w = (torch.randn(9 * 64 * 64 + off // 2, generator=g, device="cuda:0") * 0.1)[off // 2:].view(3, 3, 64, 64)
+    dx, dx_ref = (torch.full((n * H * W * 64 + off,), 7.0, device="cuda:0").to(torch.bfloat16)[off:]
+                  .view(n, H, W, 64) for _ in range(2))
+    gw = [torch.full(s, 9.0, device="cuda:0") for s in ((3, 3, 64, 64), (64,)) * 2]
+    ws = torch.empty(max(P.impala_conv3x3_bwd_workspace_bytes(0, 64, 64),
+                         P.impala_conv3x3_wgrad_workspace_bytes(0, H, W, 64, 64)), dtype=torch.uint8, device="cuda:0")
+    P.impala_conv3x3_bwd(P.PREC_BF16, n, H, W, 64, 64, dy, x, P.X_RELU, w, skip, dx, gw[0], gw[1], ws)
+    P.impala_conv3x3_dgrad(P.PREC_BF16, n, H, W, 64, 64, dy, w, x, skip, dx_ref)
+    P.impala_conv3x3_wgrad(P.PREC_BF16, n, H, W, 64, 64, x, P.X_RELU, None, dy, gw[2], gw[3], ws)
+    torch.cuda.synchronize()
+    assert torch.equal(_bits(dx), _bits(dx_ref))
+    for got, want in zip(gw[:2], gw[2:]):   # (the bound of the residual block's test)
+        scale = float(n * H * W) ** 0.5 * 0.5 + 1.0
+        assert torch.allclose(got, want, rtol=1e-5, atol=2.0 ** -20 * scale * max(float(n * H * W) ** 0.5, 1.0))
