@@ -624,10 +624,8 @@ impala_status_t impala_actor_step(const impala_net_t* net, impala_prec_t prec, c
         return fail(IMPALA_EWORKSPACE, "impala_actor_step: workspace %zu < %zu bytes (add n*A*4 when logits is NULL)",
                     ws_bytes, p.total + extra);
     float* z = logits ? logits : reinterpret_cast<float*>(static_cast<char*>(ws) + p.total);
-    hipError_t he = run_forward(p, params, obs, nullptr, n, static_cast<char*>(ws), z, value, stream);
-    if (he != hipSuccess) return hip_status(he, "impala_actor_step: forward");
-    return hip_status(gumbel_max(n, net->num_actions, z, gumbel, actions, logp, stream),
-                      "impala_actor_step: sample");
+    return hip_status(run_forward(p, params, obs, nullptr, n, static_cast<char*>(ws), z, value, stream, false,
+                                  RowSample{gumbel, actions, logp}), "impala_actor_step");
 }
 
 // ------------------------------------------------------------------ layer-level entry points

@@ -12,6 +12,7 @@
 //             as stored); a second kernel adds the partials in a fixed order.
 #include "common.h"
 #include "kernels.h"
+#include "lsm.h"
 
 #include <algorithm>
 
@@ -443,6 +444,10 @@ std::string heads_shape(const HeadsArgs& a) {
 // fragment read land on distinct bank groups); each wave takes 16 rows i of h, whose
 // B fragments (8 consecutive hidden units of one row) are plain 16-byte loads from h.
 
+// With SAMPLE each wave also samples its 16 rows: their logits go through LDS beside the noise (loaded
+// first), and 16 lanes take a row each with the arithmetic of gumbel_max_kernel. A launch of its
+// own for that took 5.0 us at 8 rows and 5.8 at 128, nearly all of it starting up.
+template <bool SAMPLE>
 __global__ __launch_bounds__(64 * kHmWaves) void heads_fwd_mfma_kernel(HeadsArgs a, float* __restrict__ logits,
                                                                       float* __restrict__ value) {
     extern __shared__ __align__(16) uint16_t wsh[];   // [kHmOut][J + 8]
@@ -453,6 +458,16 @@ __global__ __launch_bounds__(64 * kHmWaves) void heads_fwd_mfma_kernel(HeadsArgs
     const bool live = i0 < a.n;
     const int64_t ir = live ? std::min<int64_t>(i0 + r16, a.n - 1) : 0;   // rows past n: computed, not stored
     const uint16_t* hrow = static_cast<const uint16_t*>(a.h) + ir * J + g * 8;
+    float* zs = reinterpret_cast<float*>(wsh + kHmOut * P) + wave * 2 * 16 * kHmOut;   // the wave's logits, noise: [16][A]
+    float* gs = zs + 16 * kHmOut;
+    float gn[SAMPLE ? kHmOut / 4 : 1];
+    if constexpr (SAMPLE) {
+#pragma unroll
+        for (int u = 0; u < kHmOut / 4; ++u) {
+            const int64_t at = (live ? i0 : 0) * A + lane + 64 * u;
+            gn[u] = a.gumbel[at < a.n * A ? at : a.n * A - 1];
+        }
+    }
     // B fragments of up to eight k-steps in flight at once; the first eight are issued before
     // the weights are staged, so their latencies overlap
     constexpr int KC = 8;
@@ -472,6 +487,10 @@ __global__ __launch_bounds__(64 * kHmWaves) void heads_fwd_mfma_kernel(HeadsArgs
 #pragma unroll
         for (int o = 0; o < kHmOut; ++o) wsh[o * P + j] = f2bf(v[o]);
     }
+    if constexpr (SAMPLE)
+#pragma unroll
+        for (int u = 0; u < kHmOut / 4; ++u)
+            if (lane + 64 * u < 16 * A) gs[lane + 64 * u] = gn[u];
     __syncthreads();
     if (!live) return;
     cb_f32x4 acc[2] = {cb_f32x4{0.f, 0.f, 0.f, 0.f}, cb_f32x4{0.f, 0.f, 0.f, 0.f}};
@@ -498,9 +517,19 @@ __global__ __launch_bounds__(64 * kHmWaves) void heads_fwd_mfma_kernel(HeadsArgs
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int o = ob * 16 + 4 * g + e;
-            if (o < A) logits[i * A + o] = acc[ob][e] + (a.bl ? a.bl[o] : 0.f);
-            else if (o == A) value[i] = acc[ob][e] + (a.bv ? a.bv[0] : 0.f);
+            if (o < A) {
+                const float z = acc[ob][e] + (a.bl ? a.bl[o] : 0.f);
+                logits[i * A + o] = z;
+                if constexpr (SAMPLE) zs[r16 * A + o] = z;
+            } else if (o == A) {
+                value[i] = acc[ob][e] + (a.bv ? a.bv[0] : 0.f);
+            }
         }
+    if constexpr (SAMPLE) {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // within the wave: no barrier
+        __builtin_amdgcn_wave_barrier();
+        if (g == 0) row_gumbel_max(zs + r16 * A, gs + r16 * A, A, a.act[i], a.logp[i]);
+    }
 }
 
 }  // namespace
@@ -523,8 +552,12 @@ hipError_t heads_fwd(int prec, const HeadsArgs& a, float* logits, float* value, 
         (reinterpret_cast<uintptr_t>(a.h) & 15) == 0) {
         const int64_t waves = (a.n + 15) / 16;
         const size_t lds = size_t(kHmOut) * (a.J + 8) * sizeof(uint16_t);
-        hipLaunchKernelGGL(heads_fwd_mfma_kernel, dim3(unsigned((waves + kHmWaves - 1) / kHmWaves)),
-                           dim3(64 * kHmWaves), lds, s, a, logits, value);
+        const dim3 mgrid(unsigned((waves + kHmWaves - 1) / kHmWaves));
+        if (a.gumbel)
+            hipLaunchKernelGGL(heads_fwd_mfma_kernel<true>, mgrid, dim3(64 * kHmWaves), lds + kHmWaves * 2 * 16 * kHmOut * sizeof(float),
+                               s, a, logits, value);
+        else
+            hipLaunchKernelGGL(heads_fwd_mfma_kernel<false>, mgrid, dim3(64 * kHmWaves), lds, s, a, logits, value);
         return hipGetLastError();
     }
     const int MA = heads_ma(a.A);
@@ -543,7 +576,9 @@ hipError_t heads_fwd(int prec, const HeadsArgs& a, float* logits, float* value, 
     }
 #undef CB_HF_ALL
 #undef CB_HF
-    return hipGetLastError();
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || !a.gumbel) return e;
+    return gumbel_max(a.n, a.A, logits, a.gumbel, a.act, a.logp, s);
 }
 
 hipError_t heads_bwd(int prec, const HeadsArgs& a, const float* dlogits, const float* dvalue, void* dh,

@@ -209,8 +209,11 @@ struct HeadsArgs {
     const float* wv;    // [J] value weights
     const float* bv;    // [1]
     int64_t n; int J, A;
+    // optional Gumbel-max sample of each row beside the forward: noise [n][A], actions and
+    // log-probabilities [n] (NULL: none)
+    const float* gumbel; int32_t* act; float* logp;
 };
-// logits [n][A] and value [n], float32.
+// logits [n][A] and value [n], float32; the rows' samples where a.gumbel is given.
 hipError_t heads_fwd(int prec, const HeadsArgs& a, float* logits, float* value, hipStream_t s);
 // dh [n][J] (storage type) = (dz W^T) * (h > 0) with dz = [dlogits | dvalue]; the head weight
 // and bias gradients and the dense bias gradient (column sums of dh as stored) are

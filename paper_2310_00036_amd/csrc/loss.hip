@@ -9,6 +9,7 @@
 // float64 and every reduction order is fixed, so results are bit-reproducible.
 #include "common.h"
 #include "kernels.h"
+#include "lsm.h"
 
 #include <algorithm>
 
@@ -16,27 +17,6 @@ namespace cb {
 
 constexpr int kStatThreads = 1024;
 
-// Log-softmax of one row, kept as (zmax, lse): log pi_j = (z_j - zmax) - lse, recomputed from
-// the logits where needed (no per-row array, so nothing spills to scratch). Also the entropy.
-struct RowLsm {
-    float zmax, lse, H;
-    CB_DEV float l(float zj) const { return (zj - zmax) - lse; }
-};
-
-CB_DEV RowLsm row_log_softmax(const float* z, int A) {
-    RowLsm r;
-    r.zmax = z[0];
-    for (int j = 1; j < A; ++j) r.zmax = fmaxf(r.zmax, z[j]);
-    float se = 0.f;
-    for (int j = 0; j < A; ++j) se += expf(z[j] - r.zmax);
-    r.lse = logf(se);
-    r.H = 0.f;
-    for (int j = 0; j < A; ++j) {
-        const float l = r.l(z[j]);
-        r.H -= expf(l) * l;
-    }
-    return r;
-}
 
 struct PpoRow {
     RowLsm s;
@@ -872,17 +852,7 @@ __global__ void gumbel_max_kernel(int64_t m, int A, const float* __restrict__ z,
                                   float* __restrict__ logp) {
     const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
     if (i >= m) return;
-    const float* zr = z + i * A;
-    const float* gr = g + i * A;
-    int best = 0;
-    float bv = zr[0] + gr[0];
-    for (int j = 1; j < A; ++j) {
-        const float v = zr[j] + gr[j];
-        if (v > bv) { bv = v; best = j; }
-    }
-    const RowLsm rs = row_log_softmax(zr, A);
-    act[i] = best;
-    logp[i] = rs.l(zr[best]);
+    row_gumbel_max(z + i * A, g + i * A, A, act[i], logp[i]);
 }
 
 hipError_t gumbel_max(int64_t m, int A, const float* z, const float* g, int32_t* act, float* logp,

@@ -142,7 +142,7 @@ NetPlan make_plan(const impala_net_t& net, int prec, int64_t cap, int training) 
 
 hipError_t run_forward(const NetPlan& p, const float* params, const uint8_t* obs,
                        const int32_t* row_idx, int64_t n, char* ws, float* logits, float* value,
-                       hipStream_t s, bool dense_bf16_ready) {
+                       hipStream_t s, bool dense_bf16_ready, const RowSample& sample) {
     if (n <= 0) return hipSuccess;
     const ParamOffsets& po = p.po;
     for (int st = 0; st < 3; ++st) {
@@ -207,7 +207,7 @@ hipError_t run_forward(const NetPlan& p, const float* params, const uint8_t* obs
     CB_TRY(gemm(p.prec, d, s));
     // heads: logits[i][a] = bl[a] + sum_j h[i][j] Wl[j][a]; value[i] = bv + sum_j h[i][j] Wv[j]
     HeadsArgs hd{ws + p.h, params + po.logits_w, params + po.logits_b, params + po.value_w,
-                 params + po.value_b, n, p.hidden, p.A};
+                 params + po.value_b, n, p.hidden, p.A, sample.gumbel, sample.act, sample.logp};
     CB_TRY(heads_fwd(p.prec, hd, logits, value, s));
     return hipSuccess;
 }
@@ -225,7 +225,7 @@ hipError_t run_backward(const NetPlan& p, const float* params, const uint8_t* ob
     // heads: dh = (dz Wh^T) * (h > 0), the head weight / bias gradients and the dense bias
     // gradient (column sums of dh) from one pass over h
     HeadsArgs hd{ws + p.h, params + po.logits_w, params + po.logits_b, params + po.value_w,
-                 params + po.value_b, n, p.hidden, A};
+                 params + po.value_b, n, p.hidden, A, nullptr, nullptr, nullptr};
     CB_TRY(heads_bwd(p.prec, hd, dlogits, dvalue, G[0], grads + po.logits_w, grads + po.logits_b,
                      grads + po.value_w, grads + po.value_b, grads + po.dense_b, scratch,
                      p.scratch_bytes / sizeof(float), s));
