@@ -510,7 +510,7 @@ hipError_t rb_fwd_launch(const ResBlockArgs& a, hipStream_t s) {
 hipError_t rw_launch(const ResBlockArgs& a, hipStream_t s) {
     using G = RwGeom;
     const int H = a.H, W = a.W, cus = device_cus();
-    if (int64_t(H) * W * G::C * 2 * 16 >= (int64_t(1) << 31)) return hipErrorInvalidValue;
+    if (int64_t(H) * W * G::C * 2 >= (int64_t(1) << 31)) return hipErrorInvalidValue;
     static thread_local WalkPlans<RwTile> plans;
     const auto* plan = plans.find(a.n, H, W, cus);
     if (!plan) {
