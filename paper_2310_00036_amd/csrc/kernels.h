@@ -98,14 +98,7 @@ struct ResBwdArgs {
     int n, H, W;
     PendingReduce pend, pend2;   // earlier launches' partials, summed by this kernel first
 };
-struct RbbTile {
-    int TH, nbands, ntiles;
-    int dy_off, t_off, x_off, dt_off;   // LDS byte offsets; 64 zero bytes at offset 0
-    int tx_guard;                       // t / x windows: byte offset of the rear guard pixel
-    int dt_bytes;                       // dt window bytes
-    int pset;                           // floats per partial set (one per conv)
-    float inv_W;
-};
+
 bool resblock_bwd_supported(int C);
 bool resblock_bwd_preferred(int C, int H, int W);   // over two fused conv backward launches
 size_t resblock_bwd_partial_floats(int C);

@@ -9,18 +9,13 @@
 //   dx  = conv_a^T(dt) * [x > 0] + dy      dWa = sum_p relu(x)[p + d(tap)] dt[p],  dba = sum_p dt[p]
 //
 // As two fused conv backward launches this moves seven activation tensors through HBM (dy and
-// t in, dt out; dt, x and dy in, dx out). Here a tile, a band of TH rows of one frame, stages
-// dy on rows h0-2 .. h0+TH+1 and t and x on rows h0-1 .. h0+TH, forms dt on rows h0-1 .. h0+TH
-// (the band and one halo row either side, which the neighbouring bands form too) in an LDS
-// window, rounded to bf16 as the two-launch path stores it, and moves four tensors: dy, t and
-// x in, dx out. The skip term of dx comes from the staged dy window.
+// t in, dt out; dt, x and dy in, dx out). Here dt is formed in an LDS window, rounded to bf16 as the
+// two-launch path stores it (a band of a frame forms one halo row either side, which the
+// neighbouring bands form too), and four tensors move: dy, t and x in, dx out.
 //
-// Each half follows the single conv backward kernel: the input-gradient weights (taps rotated
-// by 180 degrees, channels swapped) live in registers, each wave owning one 16-channel block;
-// the weight gradients run over the band's own rows with the linear window walk (padding
-// columns included, where dy and dt are zero) and accumulate in registers over all tiles of a
-// workgroup; each workgroup writes one float32 partial per conv, summed in a fixed order by a
-// later launch (deterministic, no atomics).
+// The input-gradient weights (taps rotated by 180 degrees, channels swapped) live in registers; the
+// weight gradients accumulate in registers over all tiles of a workgroup; each workgroup writes one
+// float32 partial per conv, summed in a fixed order by a later launch (deterministic, no atomics).
 #include "common.h"
 #include "kernels.h"
 #include "walk.h"
@@ -30,326 +25,12 @@
 
 namespace cb {
 
-template <int C>
-struct RbbGeom {
-    // dy / dt windows: 16-byte slots per pixel. A 16-lane B-fragment read on consecutive
-    // pixels lands on distinct bank groups when the pitch is 2 (mod 4) slots: 16 channels fill
-    // 2; 32 channels take two extra slots (never read) for 6
-    static constexpr int DSL = C >= 32 ? C / 8 + 2 : C / 8;
-    static constexpr int DYP = DSL * 16;
-    static constexpr int XPB = C * 2 + (C >= 32 ? 32 : 0);    // t / x windows: bytes per pixel
-    static constexpr int XSL = XPB / 16;
-    static constexpr int MT = C / 16;
-    static constexpr int KSD = (9 * C + 31) / 32;          // input-gradient k-steps
-    static constexpr int NB = 9 * C / 16, NBB = NB + 1;    // weight-gradient column blocks (+ bias)
-    static constexpr int PSTRIDE = MT * NBB * 256;         // floats per workgroup partial, one conv
-    static constexpr int MAXD = C >= 32 ? 6 : 4, MAXX = C >= 32 ? 6 : 4;   // staging slots per lane (8 waves)
-    // 16 channels: two workgroups per CU (4 waves per SIMD, 128 registers); 32 channels hold
-    // both convs' input-gradient weights (72 registers) and wider accumulators: one
-    // workgroup per CU with 256 registers and all of the LDS
-    static constexpr int WPS = C >= 32 ? 2 : 4;
-    static constexpr size_t LDS_TARGET = C >= 32 ? 160 * 1024 : 80 * 1024;
-    __host__ __device__ static int blocks(int slots) { return (slots + 63) / 64; }
-};
-
-template <int C, int NW>
-__global__ __launch_bounds__(64 * NW, RbbGeom<C>::WPS) void resblock_bwd_kernel(ResBwdArgs a, RbbTile t) {
-    using G = RbbGeom<C>;
-    constexpr int NT = 64 * NW;
-    constexpr int DSL = G::DSL, DYP = G::DYP, XPB = G::XPB, XSL = G::XSL;
-    constexpr int MT = G::MT, KSD = G::KSD, NB = G::NB, NBB = G::NBB;
-    // weight gradients: waves 0 .. NW/2-1 form conv_b's, the others conv_a's, each wave TPW
-    // column blocks, so each dy / dt fragment is read by half the waves
-    constexpr int NWG = NW / 2;
-    constexpr int TPW = (NBB + NWG - 1) / NWG;   // weight-gradient column blocks per wave
-    constexpr int CB16 = C / 16;
-    static_assert(NW % MT == 0, "waves split evenly over the channel blocks");
-
-    extern __shared__ __align__(16) unsigned char smem[];
-    unsigned char* zero = smem;                   // 64 zero bytes
-    unsigned char* dyw = smem + t.dy_off;         // dy [TH+4][W+2], row 0 = image row h0-2
-    unsigned char* tw = smem + t.t_off + XPB;     // relu(t) [TH+2][W+2], row 0 = h0-1, guard pixels
-    unsigned char* xw = smem + t.x_off + XPB;     // relu(x) [TH+2][W+2], likewise
-    unsigned char* dtw = smem + t.dt_off;         // dt [TH+2][W+2], row 0 = h0-1
-
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int g = lane >> 4, r16 = lane & 15, jj = r16 >> 2, m = r16 & 3;
-    const int H = a.H, W = a.W, TH = t.TH;
-    const int TW = W + 2;
-
-    // earlier launches' weight-gradient partials, summed first (LDS is free until staging)
-    if (a.pend.nparts > 0) pending_reduce<NT>(a.pend, smem);
-    if (a.pend2.nparts > 0) pending_reduce<NT>(a.pend2, smem);
-    if (tid < 16) reinterpret_cast<uint32_t*>(zero)[tid] = 0u;
-    // the dt window: its padding columns and zero slots are never written
-    for (int j = tid; j < t.dt_bytes / 16; j += NT) reinterpret_cast<uint4*>(dtw)[j] = make_uint4(0, 0, 0, 0);
-    // the t and x windows' guard pixels (read only against zero dy / dt, never staged)
-    if (tid < XPB / 4) {
-        reinterpret_cast<uint32_t*>(tw - XPB)[tid] = 0u;
-        reinterpret_cast<uint32_t*>(tw + t.tx_guard)[tid] = 0u;
-        reinterpret_cast<uint32_t*>(xw - XPB)[tid] = 0u;
-        reinterpret_cast<uint32_t*>(xw + t.tx_guard)[tid] = 0u;
-    }
-
-    // ---- input-gradient A fragments of both convs for this wave's channel block:
-    // A[o][k] = w[8 - tap][o][co] with k = tap * C + co (zero past the 9 taps)
-    const int dmt = wave % MT;
-    const int ci0 = dmt * 16 + g * 4;   // the lane's first output channel
-    uint4 wfa[KSD], wfb[KSD];
-#pragma unroll
-    for (int ks = 0; ks < KSD; ++ks) {
-        const int o = dmt * 16 + r16;
-        float va[8], vb[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int k = ks * 32 + g * 8 + j, tap = k / C, co = k % C;
-            va[j] = tap < 9 ? a.wa[((8 - tap) * C + o) * C + co] : 0.f;
-            vb[j] = tap < 9 ? a.wb[((8 - tap) * C + o) * C + co] : 0.f;
-        }
-        wfa[ks] = make_uint4(pack2bf(va[0], va[1]), pack2bf(va[2], va[3]), pack2bf(va[4], va[5]), pack2bf(va[6], va[7]));
-        wfb[ks] = make_uint4(pack2bf(vb[0], vb[1]), pack2bf(vb[2], vb[3]), pack2bf(vb[4], vb[5]), pack2bf(vb[6], vb[7]));
-    }
-    // B-fragment byte offsets from the lane's tap-(0,0) pixel of a dy-like window; with 16
-    // channels a k-step spans two taps (a per-lane table), from 32 on only the slot is the lane's.
-    // Past the ninth tap the weights are zero, so those lanes re-read tap 8 (a value that
-    // already enters the sum through tap 8 itself)
-    int dboff[C < 32 ? KSD : 1];
-    if constexpr (C < 32) {
-#pragma unroll
-        for (int ks = 0; ks < KSD; ++ks) {
-            const int k0 = ks * 32 + g * 8, tap = k0 / C, slot = (k0 % C) / 8;
-            const int tp = tap < 9 ? tap : 8;
-            dboff[ks] = ((tp / 3) * TW + tp % 3) * DYP + slot * 16;
-        }
-    }
-    const int twdy = TW * DYP;
-    auto dgrad_off = [&](int ks) -> int {
-        if constexpr (C < 32) return dboff[ks];
-        else return (ks / (C / 32) / 3) * twdy + (ks / (C / 32) % 3) * DYP + ((ks % (C / 32)) * 4 + g) * 16;
-    };
-    // weight-gradient column blocks nb = wg + NWG * i (16 input channels of one tap, or the
-    // bias block), each for all C/16 output-channel blocks, of conv_b (grp 0) or conv_a (grp 1)
-    const int wg = wave % NWG, grp = wave / NWG;
-    int wboff[TPW];
-#pragma unroll
-    for (int i = 0; i < TPW; ++i) {
-        const int nb = wg + NWG * i;
-        const int tap = nb / CB16, cb = nb % CB16;
-        wboff[i] = nb < NB ? ((tap / 3) * TW + tap % 3) * XPB + (cb * 16 + 4 * m) * 2 : 0;
-    }
-    cb_f32x4 wacc[TPW][MT];
-#pragma unroll
-    for (int i = 0; i < TPW; ++i)
-#pragma unroll
-        for (int mo = 0; mo < MT; ++mo) wacc[i][mo] = cb_f32x4{0.f, 0.f, 0.f, 0.f};
-    const uint4 ones = make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u);
-
-    // ---- staging offsets, tile-invariant per lane (slot k of this wave: j = (wave + NW*k)*64
-    // + lane), relative to the window's first row at image row 0; a tile adds that row's
-    // image row. Rows off the frame fall outside the frame's buffer resource and read zero,
-    // as do padding slots and columns (kOOB).
-    const int nsd = (TH + 4) * TW * DSL, nsx = (TH + 2) * TW * XSL;
-    auto win_off = [&](int j, int slots, int rows) -> uint32_t {
-        const int p = j / slots, c = j - p * slots;
-        const int rr = p / TW, col = p - rr * TW;
-        if (j >= rows * TW * slots || c >= C / 8 || col < 1 || col > W) return kOOB;
-        return uint32_t(((rr * W + col - 1) * C + c * 8) * 2);
-    };
-    uint32_t od[G::MAXD], ox[G::MAXX];
-#pragma unroll
-    for (int k = 0; k < G::MAXD; ++k) od[k] = win_off((wave + NW * k) * 64 + lane, DSL, TH + 4);
-#pragma unroll
-    for (int k = 0; k < G::MAXX; ++k) ox[k] = win_off((wave + NW * k) * 64 + lane, XSL, TH + 2);
-
-    // ---- one weight gradient over the band's own rows: dy-like window dwin (own row 0 at
-    // window row drow0) against the relu'd window bwin (row 0 = image row h0-1): pixel idx of
-    // the own rows pairs with bwin pixel idx - 1 + tap offset. Lane (g, 4jj+m) takes pixels
-    // o = 16*half + 4g + jj (channels 4m.. of a 16-channel block).
-    auto wgrad = [&](const unsigned char* dwin, int drow0, const unsigned char* bwin, const unsigned char* bguard,
-                     int L) {
-        // specialised per wave, so that each column block's kind (loaded or bias) is known at
-        // compile time and the k-step loop carries no branches
-        auto run = [&](auto wv) {
-            constexpr int WG = decltype(wv)::value;
-            const int nfull = L >> 5;
-            const int o0 = 4 * g + jj;
-            const unsigned char* ap = dwin + (drow0 * TW + o0) * DYP + 8 * m;
-            const unsigned char* bp = bwin + (o0 - 1) * XPB;
-            auto kstep = [&](const unsigned char* a0, const unsigned char* a1, const unsigned char* b0,
-                             const unsigned char* b1) {
-                uint4 af[MT];
-#pragma unroll
-                for (int mo = 0; mo < MT; ++mo) {
-                    const uint2 lo = lds_read_tr16(a0 + mo * 32);   // a0, a1: zero past L
-                    const uint2 hi = lds_read_tr16(a1 + mo * 32);
-                    af[mo] = make_uint4(lo.x, lo.y, hi.x, hi.y);
-                }
-#pragma unroll
-                for (int i = 0; i < TPW; ++i) {
-                    const int nb = WG + NWG * i;
-                    if (nb < NB) {
-                        const uint2 lo = lds_read_tr16(b0 + wboff[i]);
-                        const uint2 hi = lds_read_tr16(b1 + wboff[i]);
-                        const uint4 bf = make_uint4(lo.x, lo.y, hi.x, hi.y);
-#pragma unroll
-                        for (int mo = 0; mo < MT; ++mo) wacc[i][mo] = PrecBF16::mma(af[mo], bf, wacc[i][mo]);
-                    } else if (nb == NB) {   // the bias block: a column of ones
-#pragma unroll
-                        for (int mo = 0; mo < MT; ++mo) wacc[i][mo] = PrecBF16::mma(af[mo], ones, wacc[i][mo]);
-                    }
-                }
-            };
-            int ks = 0;
-            for (; ks + 2 <= nfull; ks += 2) {   // two k-steps per trip: half the pointer updates
-                kstep(ap, ap + 16 * DYP, bp, bp + 16 * XPB);
-                kstep(ap + 32 * DYP, ap + 48 * DYP, bp + 32 * XPB, bp + 48 * XPB);
-                ap += 64 * DYP;
-                bp += 64 * XPB;
-            }
-            if (ks < nfull) {
-                kstep(ap, ap + 16 * DYP, bp, bp + 16 * XPB);
-                ap += 32 * DYP;
-                bp += 32 * XPB;
-            }
-            if (L & 31) {   // the last, partial k-step
-                const int o = nfull * 32 + o0;
-                const bool ok0 = o < L, ok1 = o + 16 < L;
-                kstep(ok0 ? ap : zero, ok1 ? ap + 16 * DYP : zero, ok0 ? bp : bguard, ok1 ? bp + 16 * XPB : bguard);
-            }
-        };
-        static_assert(NWG == 4, "one specialisation per wave of a group");
-        switch (wg) {
-            case 0: run(std::integral_constant<int, 0>{}); break;
-            case 1: run(std::integral_constant<int, 1>{}); break;
-            case 2: run(std::integral_constant<int, 2>{}); break;
-            default: run(std::integral_constant<int, 3>{}); break;
-        }
-    };
-
-    int lg = blockIdx.x;   // neighbouring bands (which share halo rows) on one XCD
-    if ((gridDim.x & 7) == 0) lg = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
-
-    for (int tile = lg; tile < t.ntiles; tile += gridDim.x) {
-        const int band = tile % t.nbands, f = tile / t.nbands;
-        const int h0 = band * TH;
-        const int the = H - h0 < TH ? H - h0 : TH;
-        const int64_t fo = int64_t(f) * H * W * C;   // the frame's first element
-        __syncthreads();   // the previous tile's LDS reads are done
-
-        // ---- stage dy (rows h0-2 ..), t and x (rows h0-1 ..)
-        {
-            const uint32_t fb = uint32_t(H) * W * C * 2;
-            const auto rd = buf_rsrc(static_cast<const uint16_t*>(a.dy) + fo, fb);
-            const auto rt = buf_rsrc(static_cast<const uint16_t*>(a.t) + fo, fb);
-            const auto rx = buf_rsrc(static_cast<const uint16_t*>(a.x) + fo, fb);
-            const uint32_t hd = uint32_t((h0 - 2) * W * C * 2);   // wraps above the frame: reads zero
-            const uint32_t hx = uint32_t((h0 - 1) * W * C * 2);
-#pragma unroll
-            for (int k = 0; k < G::MAXD; ++k)
-                if ((wave + NW * k) * 64 < nsd) dma16_to_lds(rd, dyw + (wave + NW * k) * 1024, od[k] + hd);
-#pragma unroll
-            for (int k = 0; k < G::MAXX; ++k)
-                if ((wave + NW * k) * 64 < nsx) {
-                    dma16_to_lds(rt, tw + (wave + NW * k) * 1024, ox[k] + hx);
-                    dma16_to_lds(rx, xw + (wave + NW * k) * 1024, ox[k] + hx);
-                }
-        }
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
-        {
-            // both convs read relu'd inputs; relu(v) > 0 exactly where v > 0, so the masks
-            // read the same windows
-            uint4* t4 = reinterpret_cast<uint4*>(tw);
-            uint4* x4 = reinterpret_cast<uint4*>(xw);
-            for (int j = tid; j < nsx; j += NT) {
-                uint4 u = t4[j], v = x4[j];
-                u.x = relu_bf16x2(u.x); u.y = relu_bf16x2(u.y); u.z = relu_bf16x2(u.z); u.w = relu_bf16x2(u.w);
-                v.x = relu_bf16x2(v.x); v.y = relu_bf16x2(v.y); v.z = relu_bf16x2(v.z); v.w = relu_bf16x2(v.w);
-                t4[j] = u;
-                x4[j] = v;
-            }
-        }
-        __syncthreads();
-
-        // ---- conv_b's input gradient dt on window rows r = 0 .. the+1 (image rows h0-1+r;
-        // zero off the frame), 16-pixel column tiles, into the dt window
-        {
-            const int npx = (the + 2) * W;
-            for (int nt = wave / MT; nt * 16 < npx; nt += NW / MT) {
-                const int q = nt * 16 + r16;
-                const int qc = q < npx ? q : npx - 1;   // past npx: computed, not stored
-                const int row = qdiv(qc, t.inv_W), col = qc - row * W;
-                const unsigned char* xb = dyw + (row * TW + col) * DYP;
-                cb_f32x4 acc = cb_f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int ks = 0; ks < KSD; ++ks)
-                    acc = PrecBF16::mma(wfb[ks], *reinterpret_cast<const uint4*>(xb + dgrad_off(ks)), acc);
-                if (q < npx) {
-                    const int h = h0 - 1 + row;
-                    uint2 o = make_uint2(0u, 0u);
-                    if (h >= 0 && h < H) {
-                        float mk[4];
-                        load4(reinterpret_cast<const uint16_t*>(tw + (row * TW + col + 1) * XPB + ci0 * 2), mk);
-                        o = make_uint2(pack2bf(mk[0] > 0.f ? acc[0] : 0.f, mk[1] > 0.f ? acc[1] : 0.f),
-                                       pack2bf(mk[2] > 0.f ? acc[2] : 0.f, mk[3] > 0.f ? acc[3] : 0.f));
-                    }
-                    *reinterpret_cast<uint2*>(dtw + (row * TW + col + 1) * DYP + ci0 * 2) = o;
-                }
-            }
-        }
-        __syncthreads();   // the dt window is complete
-
-        // ---- dx = conv_a^T(dt) * [x > 0] + dy on the band's rows
-        {
-            const int npx = the * W;
-            uint16_t* dxt = static_cast<uint16_t*>(a.dx) + fo + int64_t(h0) * W * C;
-            for (int nt = wave / MT; nt * 16 < npx; nt += NW / MT) {
-                const int q = nt * 16 + r16;
-                const int qc = q < npx ? q : npx - 1;
-                const int row = qdiv(qc, t.inv_W), col = qc - row * W;
-                const unsigned char* xb = dtw + (row * TW + col) * DYP;
-                cb_f32x4 acc = cb_f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int ks = 0; ks < KSD; ++ks)
-                    acc = PrecBF16::mma(wfa[ks], *reinterpret_cast<const uint4*>(xb + dgrad_off(ks)), acc);
-                if (q < npx) {
-                    float mk[4], sk[4];
-                    load4(reinterpret_cast<const uint16_t*>(xw + ((row + 1) * TW + col + 1) * XPB + ci0 * 2), mk);
-                    load4(reinterpret_cast<const uint16_t*>(dyw + ((row + 2) * TW + col + 1) * DYP + ci0 * 2), sk);
-                    float v[4];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) v[j] = (mk[j] > 0.f ? acc[j] : 0.f) + sk[j];
-                    store4(dxt + uint32_t(q * C + ci0), v[0], v[1], v[2], v[3]);
-                }
-            }
-        }
-        // ---- the weight gradients: conv_b's, dy (own rows from dy-window row 2) against
-        // relu(t), by the first half of the waves; conv_a's, dt (own rows from dt-window row
-        // 1) against relu(x), by the second
-        if (grp == 0) wgrad(dyw, 2, tw, tw - XPB, the * TW);
-        else wgrad(dtw, 1, xw, xw - XPB, the * TW);
-    }
-
-    // ---- this workgroup's partials: conv_b's set, then conv_a's, each [mo*NBB + nb][co 16][ci 16]
-    float* part = a.partial + (grp == 0 ? 0 : t.pset) + int64_t(blockIdx.x) * G::PSTRIDE;
-#pragma unroll
-    for (int i = 0; i < TPW; ++i) {
-        const int nb = wg + NWG * i;
-        if (nb < NBB) {
-#pragma unroll
-            for (int mo = 0; mo < MT; ++mo)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) part[(mo * NBB + nb) * 256 + (4 * g + e) * 16 + r16] = wacc[i][mo][e];
-        }
-    }
-}
-
 // The 32-channel block backward by column walks (walk.h), in one 8-wave workgroup per CU with
 // two wave roles. Waves 0-3 form dt, then dx, for both channel blocks (both convolutions' weights:
 // 144 registers; each input fragment feeds 18 MFMAs); waves 4-7 form conv_b's weight gradient
 // while dt is formed and conv_a's beside dx, each wave one 16x16 channel block of all nine taps (18
-// tap tiles and the bias columns: 80 registers; each x fragment feeds three rows of dy). A tile (F whole frames, or a band of one) has two phases:
+// tap tiles and the bias columns: 80 registers; each x fragment feeds three rows of dy). A tile (F
+// whole frames, or a band of one) has two phases:
 //   a: dt = conv_b^T(dy) * [t > 0] into the dt window; dWb from dy and t; x and dy's own pixels
 //      once more (for the skip term; an L2 hit) are being staged;
 //   b: dx = conv_a^T(dt) * [x > 0] + dy; dWa from dt and x; the next tile's dy and t are staged.
@@ -377,10 +58,10 @@ struct RbwTile {
 
 // One window of a tile, HBM -> LDS: block wave + NW*k of 64 16-byte slots from the lane's offset
 // off[k], shifted by `row` rows.
-template <int N>
+template <int C, int N>
 CB_DEV void rbw_stage(const ResBwdArgs& a, const RbwTile& t, const void* src, unsigned char* win, int ns,
                       const uint32_t (&off)[N], int wave, int tile, int row) {
-    constexpr int C = RbwGeom::C, NW = RbwGeom::NW;
+    constexpr int NW = RbwGeom::NW;
     const int band = tile % t.nbands, f = (tile / t.nbands) * t.F;
     const int nf = a.n - f < t.F ? a.n - f : t.F, fel = a.H * a.W * C;
     const auto r = buf_rsrc(static_cast<const uint16_t*>(src) + int64_t(f) * fel, uint32_t(nf) * fel * 2);
@@ -467,8 +148,8 @@ __global__ __launch_bounds__(RbwGeom::NT, 2) void resblock_bwd_walk_kernel(ResBw
         const int col = p - qdiv(p, t.inv_W) * W + 1, q = (j & 3) ^ ((col >> 1) & 2);
         ok[k] = j < nsk ? uint32_t(p * 64 + q * 16) : kOOB;
     }
-    rbw_stage(a, t, a.dy, dyw, nsd, od, wave, lg, rd);
-    rbw_stage(a, t, a.t, tw, nsx, ox, wave, lg, rx);
+    rbw_stage<C>(a, t, a.dy, dyw, nsd, od, wave, lg, rd);
+    rbw_stage<C>(a, t, a.t, tw, nsx, ox, wave, lg, rx);
     // earlier launches' weight-gradient partials
     if (a.pend.nparts > 0) pending_reduce<NT>(a.pend, dtw);
     if (a.pend2.nparts > 0) pending_reduce<NT>(a.pend2, dtw);
@@ -510,8 +191,8 @@ __global__ __launch_bounds__(RbwGeom::NT, 2) void resblock_bwd_walk_kernel(ResBw
             // compiler knows that the loads in flight do not write what is read)
             auto phase_a = [&](unsigned char* __restrict__ xdst, unsigned char* __restrict__ kdst, unsigned char* __restrict__ dtdst,
                                const unsigned char* __restrict__ dsrc, const unsigned char* __restrict__ tsrc) CB_INLINE_LAMBDA {
-                rbw_stage(a, t, a.x, xdst, nsx, ox, wave, tile, rx);
-                rbw_stage(a, t, a.dy, kdst, nsk, ok, wave, tile, 0);
+                rbw_stage<C>(a, t, a.x, xdst, nsx, ox, wave, tile, rx);
+                rbw_stage<C>(a, t, a.dy, kdst, nsk, ok, wave, tile, 0);
                 const int n1 = TH + 2 * ho;
                 for (int grp = rw; grp * 16 < t.nsegt * cols; grp += NS) {
                     const WalkAnchor an = walk_anchor(grp * 16 + r16, cols, W, t.nsegt, R, n1, t.inv_c, t.inv_W);
@@ -538,8 +219,8 @@ __global__ __launch_bounds__(RbwGeom::NT, 2) void resblock_bwd_walk_kernel(ResBw
             auto phase_b = [&](unsigned char* __restrict__ ddst, unsigned char* __restrict__ tdst, const unsigned char* __restrict__ dtsrc,
                                const unsigned char* __restrict__ xsrc, const unsigned char* __restrict__ ksrc) CB_INLINE_LAMBDA {
                 if (tile + G0 < t.ntiles) {
-                    rbw_stage(a, t, a.dy, ddst, nsd, od, wave, tile + G0, rd);
-                    rbw_stage(a, t, a.t, tdst, nsx, ox, wave, tile + G0, rx);
+                    rbw_stage<C>(a, t, a.dy, ddst, nsd, od, wave, tile + G0, rd);
+                    rbw_stage<C>(a, t, a.t, tdst, nsx, ox, wave, tile + G0, rx);
                 }
                 uint16_t* dxb = static_cast<uint16_t*>(a.dx) + fo;
                 for (int grp = rw; grp * 16 < t.nsegx * cols; grp += NS) {
@@ -601,15 +282,15 @@ __global__ __launch_bounds__(RbwGeom::NT, 2) void resblock_bwd_walk_kernel(ResBw
     };
     auto phase_a = [&](unsigned char* __restrict__ xdst, unsigned char* __restrict__ kdst, const unsigned char* __restrict__ tsrc,
                        const unsigned char* __restrict__ dsrc, int tile) CB_INLINE_LAMBDA {
-        rbw_stage(a, t, a.x, xdst, nsx, ox, wave, tile, rx);
-        rbw_stage(a, t, a.dy, kdst, nsk, ok, wave, tile, 0);
+        rbw_stage<C>(a, t, a.x, xdst, nsx, ox, wave, tile, rx);
+        rbw_stage<C>(a, t, a.dy, kdst, nsk, ok, wave, tile, 0);
         wgrad(tsrc, dsrc, dpf, 1 + ho, accB, biasB);
     };
     auto phase_b = [&](unsigned char* __restrict__ ddst, unsigned char* __restrict__ tdst, const unsigned char* __restrict__ xsrc,
                        const unsigned char* __restrict__ dtsrc, int next) CB_INLINE_LAMBDA {
         if (next < t.ntiles) {
-            rbw_stage(a, t, a.dy, ddst, nsd, od, wave, next, rd);
-            rbw_stage(a, t, a.t, tdst, nsx, ox, wave, next, rx);
+            rbw_stage<C>(a, t, a.dy, ddst, nsd, od, wave, next, rd);
+            rbw_stage<C>(a, t, a.t, tdst, nsx, ox, wave, next, rx);
         }
         wgrad(xsrc, dtsrc, xpf, 1, accA, biasA);
     };
@@ -638,15 +319,256 @@ __global__ __launch_bounds__(RbwGeom::NT, 2) void resblock_bwd_walk_kernel(ResBw
     else put(part + t.pset + 18 * 256, biasA);
 }
 
+// The 16-channel block backward in the same form. One fragment of weight-gradient anchors fills a wave
+// (all nine taps of the one channel block: 40 registers a convolution), so the four waves share the
+// anchors and their sums are added at the end.
+// Measured against a form of two workgroups per CU that staged a tile, waited, and read every
+// fragment once per tap: 2048 frames of 42x42 152.5 -> 144.7 us, 640 of 42x42 60 -> 55.5 us, of 21x21
+// 31.5 -> 26 us, of 11x11 22.7 -> 17.8 us. Two workgroups of this form per CU (80 KB windows, 128
+// registers, which spill) were slower: 180 us on 2048 frames of 42x42. What bounds it: 462 MB at the
+// rate of a large copy are 97 us; the rest is a phase's loads that outlast its work, and barriers.
+struct Rbw16Geom {
+    static constexpr int C = 16, NW = 8, NT = 512, NS = 4;   // NS: waves per role
+    static constexpr int NBB = 10, PSTRIDE = NBB * 256;      // partial: [tap, bias][co][ci]
+    static constexpr int MAXD = 6, MAXX = 6, MAXK = 5;       // staging slots per lane: dy; t / x; skip term
+};
+
+template <int R>
+__global__ __launch_bounds__(Rbw16Geom::NT, 2) void resblock_bwd16_walk_kernel(ResBwdArgs a, RbwTile t) {
+    using G = Rbw16Geom;
+    constexpr int NT = G::NT, NW = G::NW, NS = G::NS, C = G::C;
+    extern __shared__ __align__(16) unsigned char smem[];
+    unsigned char* dyw = smem;               // dy [F][TH+2+2ho][TW], row 0 = image row h0-1-ho
+    unsigned char* tw = smem + t.t_off;      // relu(t) [F][TH+2][TW], row 0 = image row h0-1
+    unsigned char* xw = smem + t.x_off;      // relu(x), likewise
+    unsigned char* dtw = smem + t.dt_off;    // dt, likewise
+    unsigned char* skw = smem + t.sk_off;    // dy's own pixels [F][TH][W]
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const bool dgrad = wave < NS;            // input-gradient role
+    const int rw = wave & (NS - 1);          // wave within its role
+    const int H = a.H, W = a.W, F = t.F, TH = t.TH, ho = t.ho, TW = walk_pitch(W);
+    const int dpf = (TH + 2 + 2 * ho) * TW, xpf = (TH + 2) * TW;
+    const int nsd = (F * dpf + 1) * 2, nsx = (F * xpf + 1) * 2, nsk = F * TH * W * 2;   // 16-byte slots staged
+    const int rowb = TW * 32, cols = F * W;
+
+    // ---- staging offsets, tile-invariant per lane (slot k of this wave: j = (wave + NW*k)*64 +
+    // lane: pixel j / 2, half j % 2), relative to the tile's first frame with the window's
+    // first row at image row 0 (whole frames: at row -1); a tile adds that row. Rows off the frame fall
+    // outside the buffer resource (whole frames: they are kOOB), padding columns are kOOB.
+    uint32_t od[G::MAXD], ox[G::MAXX], ok[G::MAXK];
+    auto win_off = [&](int j, int ns, int pf, float inv_pf) CB_INLINE_LAMBDA {
+        const int p = j >> 1, fi = qdiv(p, inv_pf), pr = p - fi * pf, rr = qdiv(pr, t.inv_TW), col = pr - rr * TW;
+        const int h = rr - (ho ? 0 : 1);
+        const bool in = (j < ns) & (uint32_t(col - 1) < uint32_t(W)) & ((ho != 0) | (uint32_t(h) < uint32_t(H)));
+        const uint32_t off = uint32_t((((fi * H + h) * W + col - 1) * C + (j & 1) * 8) * 2);
+        return in ? off : kOOB;
+    };
+    const int rd = ho ? 2 : 0, rx = ho ? 1 : 0;   // a window's first row above the band (whole frames: in the offsets)
+
+    int lg = blockIdx.x;   // neighbouring bands (which share halo rows) on one XCD
+    if ((gridDim.x & 7) == 0) lg = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    const int G0 = int(gridDim.x);
+
+#pragma unroll
+    for (int k = 0; k < G::MAXD; ++k) od[k] = win_off((wave + NW * k) * 64 + lane, nsd, dpf, t.inv_dpf);
+#pragma unroll
+    for (int k = 0; k < G::MAXX; ++k) ox[k] = win_off((wave + NW * k) * 64 + lane, nsx, xpf, t.inv_xpf);
+#pragma unroll
+    for (int k = 0; k < G::MAXK; ++k) {   // the own pixels in memory order
+        const int j = (wave + NW * k) * 64 + lane;
+        ok[k] = j < nsk ? uint32_t(j * 16) : kOOB;
+    }
+    rbw_stage<C>(a, t, a.dy, dyw, nsd, od, wave, lg, rd);
+    rbw_stage<C>(a, t, a.t, tw, nsx, ox, wave, lg, rx);
+    // earlier launches' weight-gradient partials
+    if (a.pend.nparts > 0) pending_reduce<NT>(a.pend, dtw);
+    if (a.pend2.nparts > 0) pending_reduce<NT>(a.pend2, dtw);
+    lds_barrier();
+    // the dt window: its padding and, for whole frames, its rows off the frame are never written
+    auto clear_dt = [&] {
+        for (int j = tid; j < t.dt_bytes / 16; j += NT) reinterpret_cast<uint4*>(dtw)[j] = make_uint4(0, 0, 0, 0);
+    };
+
+    if (dgrad) {
+        // A[o][tap * 16 + co] = w[8 - tap][o][co], zero past the 9 taps (loads clamped)
+        uint4 wa[5], wb[5];
+        auto load_w = [&](const float* w, uint4 (&wf)[5]) CB_INLINE_LAMBDA {
+            const int g = lane >> 4, o = lane & 15;
+            float4 v[5][2];
+#pragma unroll
+            for (int ks = 0; ks < 5; ++ks)
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const int tap = 2 * ks + (g >> 1);
+                    v[ks][q] = load_f4(w + ((tap < 9 ? 8 - tap : 0) * C + o) * C + (g & 1) * 8 + 4 * q);
+                }
+#pragma unroll
+            for (int ks = 0; ks < 5; ++ks) {
+                wf[ks] = make_uint4(pack2bf(v[ks][0].x, v[ks][0].y), pack2bf(v[ks][0].z, v[ks][0].w), pack2bf(v[ks][1].x, v[ks][1].y),
+                                    pack2bf(v[ks][1].z, v[ks][1].w));
+                if (ks == 4 && g >= 2) wf[ks] = make_uint4(0, 0, 0, 0);
+            }
+        };
+        load_w(a.wa, wa);
+        load_w(a.wb, wb);
+        lds_barrier();
+        clear_dt();
+        for (int tile = lg; tile < t.ntiles; tile += G0) {
+            int ln = lane;
+            asm volatile("" : "+v"(ln));   // anchors and row masks are formed per tile: kept over tiles they spill
+            const int g = ln >> 4, r16 = ln & 15;
+            const int band = tile % t.nbands, f = (tile / t.nbands) * F;
+            const int h0 = band * TH, the = H - h0 < TH ? H - h0 : TH;
+            const int nf = a.n - f < F ? a.n - f : F;
+            const int64_t fo = int64_t(f) * H * W * C;
+            rbw_landed<G::MAXX>(tw, nsx, wave, lane);
+            lds_barrier();   // dy and t have landed; x and dt of the previous tile have been read
+            // (the windows being staged and those read are restrict parameters of one call, so the
+            // compiler knows that the loads in flight do not write what is read)
+            auto phase_a = [&](unsigned char* __restrict__ xdst, unsigned char* __restrict__ kdst, unsigned char* __restrict__ dtdst,
+                               const unsigned char* __restrict__ dsrc, const unsigned char* __restrict__ tsrc) CB_INLINE_LAMBDA {
+                rbw_stage<C>(a, t, a.x, xdst, nsx, ox, wave, tile, rx);
+                rbw_stage<C>(a, t, a.dy, kdst, nsk, ok, wave, tile, 0);
+                const int n1 = TH + 2 * ho;
+                for (int grp = rw; grp * 16 < t.nsegt * cols; grp += NS) {
+                    const WalkAnchor an = walk_anchor(grp * 16 + r16, cols, W, t.nsegt, R, n1, t.inv_c, t.inv_W);
+                    uint32_t ta = uint32_t(an.fi * xpf + (an.row0 + 1 - ho) * TW + an.c + 1) * 32 + g * 8;
+                    const int hb = h0 - ho + an.row0;   // image row of the walk's first row
+                    const uint32_t one = 0x00010001u, top = 0x7f807f80u;
+                    uint2 mk = make_uint2(0, 0);
+                    walk_conv16<R>(dsrc, an.fi * dpf + an.row0 * TW + an.c, g, rowb, wb,
+                        [&] { mk = *reinterpret_cast<const uint2*>(tsrc + ta); },
+                        [&](int j, const cb_f32x4& acc) {
+                            const int h = hb + j;
+                            const bool in = uint32_t(h) < uint32_t(H);   // rows off the frame stay zero
+                            uint2 u = make_uint2(pos_mask16x2(mk.x, pack2bf(acc[0], acc[1]), one, top), pos_mask16x2(mk.y, pack2bf(acc[2], acc[3]), one, top));
+                            if (!in) u = make_uint2(0, 0);
+                            if (an.ok && an.row0 + j >= an.rbeg) *reinterpret_cast<uint2*>(dtdst + ta) = u;
+                            ta += rowb;
+                        });
+                }
+            };
+            phase_a(xw, skw, dtw, dyw, tw);
+            rbw_landed<G::MAXX>(xw, nsx, wave, lane);
+            lds_barrier();   // the dt window is complete, x has landed
+            auto phase_b = [&](unsigned char* __restrict__ ddst, unsigned char* __restrict__ tdst, const unsigned char* __restrict__ dtsrc,
+                               const unsigned char* __restrict__ xsrc, const unsigned char* __restrict__ ksrc) CB_INLINE_LAMBDA {
+                if (tile + G0 < t.ntiles) {
+                    rbw_stage<C>(a, t, a.dy, ddst, nsd, od, wave, tile + G0, rd);
+                    rbw_stage<C>(a, t, a.t, tdst, nsx, ox, wave, tile + G0, rx);
+                }
+                uint16_t* dxb = static_cast<uint16_t*>(a.dx) + fo;
+                for (int grp = rw; grp * 16 < t.nsegx * cols; grp += NS) {
+                    const WalkAnchor an = walk_anchor(grp * 16 + r16, cols, W, t.nsegx, R, TH, t.inv_c, t.inv_W);
+                    uint32_t xa = uint32_t(an.fi * xpf + (an.row0 + 1) * TW + an.c + 1) * 32 + g * 8;
+                    uint32_t ka = uint32_t((an.fi * TH + an.row0) * W + an.c) * 32 + g * 8;
+                    uint32_t go = uint32_t(((an.fi * H + h0 + an.row0) * W + an.c) * C + g * 4);
+                    const bool own = an.ok && an.fi < nf;
+                    uint2 mk = make_uint2(0, 0), sk = make_uint2(0, 0);
+                    walk_conv16<R>(dtsrc, an.fi * xpf + an.row0 * TW + an.c, g, rowb, wa,
+                        [&] {
+                            mk = *reinterpret_cast<const uint2*>(xsrc + xa);
+                            sk = *reinterpret_cast<const uint2*>(ksrc + ka);
+                            xa += rowb;
+                            ka += W * 32;
+                        },
+                        [&](int j, const cb_f32x4& acc) {
+                            if (own && an.row0 + j >= an.rbeg && an.row0 + j < the)
+                                store4(dxb + go, (bf_lo(mk.x) > 0.f ? acc[0] : 0.f) + bf_lo(sk.x), (bf_hi(mk.x) > 0.f ? acc[1] : 0.f) + bf_hi(sk.x),
+                                       (bf_lo(mk.y) > 0.f ? acc[2] : 0.f) + bf_lo(sk.y), (bf_hi(mk.y) > 0.f ? acc[3] : 0.f) + bf_hi(sk.y));
+                            go += W * C;
+                        });
+                }
+            };
+            phase_b(dyw, tw, dtw, xw, skw);
+        }
+        lds_barrier();   // (the weight-gradient role's two barriers)
+        lds_barrier();
+        return;
+    }
+
+    // ---- weight-gradient role: channel blocks (co, ci) of this wave
+    lds_barrier();
+    clear_dt();
+    cb_f32x4 accA[9], accB[9], biasA, biasB;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) accA[k] = accB[k] = cb_f32x4{0.f, 0.f, 0.f, 0.f};
+    biasA = biasB = cb_f32x4{0.f, 0.f, 0.f, 0.f};
+    // dwin's own row 0 is window row drow; xwin's row 0 is one image row above it
+    auto wgrad = [&](const unsigned char* xwin, const unsigned char* dwin, int dstride, int drow, cb_f32x4 (&acc)[9], cb_f32x4& accb) CB_INLINE_LAMBDA {
+        for (int grp = rw; grp * 32 < t.nsegw * cols; grp += NS) {
+            int ln = lane;
+            asm volatile("" : "+v"(ln));   // (as above)
+            const int g = ln >> 4, jj = (ln >> 2) & 3, m = ln & 3;
+            int px[2], pd[2], skip[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const WalkAnchor an = walk_anchor(grp * 32 + h * 16 + 4 * g + jj, cols, W, t.nsegw, R, TH, t.inv_c, t.inv_W);
+                px[h] = an.fi * xpf + an.row0 * TW + an.c;
+                pd[h] = an.fi * dstride + (an.row0 + drow) * TW + an.c + 1;
+                skip[h] = an.ok ? an.rbeg - an.row0 : R;
+            }
+            walk_wgrad16<R>(xwin, dwin, px, pd, skip, uint32_t(m * 8), rowb, acc, accb);
+        }
+    };
+    auto phase_a = [&](unsigned char* __restrict__ xdst, unsigned char* __restrict__ kdst, const unsigned char* __restrict__ tsrc,
+                       const unsigned char* __restrict__ dsrc, int tile) CB_INLINE_LAMBDA {
+        rbw_stage<C>(a, t, a.x, xdst, nsx, ox, wave, tile, rx);
+        rbw_stage<C>(a, t, a.dy, kdst, nsk, ok, wave, tile, 0);
+        wgrad(tsrc, dsrc, dpf, 1 + ho, accB, biasB);
+    };
+    auto phase_b = [&](unsigned char* __restrict__ ddst, unsigned char* __restrict__ tdst, const unsigned char* __restrict__ xsrc,
+                       const unsigned char* __restrict__ dtsrc, int next) CB_INLINE_LAMBDA {
+        if (next < t.ntiles) {
+            rbw_stage<C>(a, t, a.dy, ddst, nsd, od, wave, next, rd);
+            rbw_stage<C>(a, t, a.t, tdst, nsx, ox, wave, next, rx);
+        }
+        wgrad(xsrc, dtsrc, xpf, 1, accA, biasA);
+    };
+    for (int tile = lg; tile < t.ntiles; tile += G0) {
+        rbw_landed<G::MAXX>(tw, nsx, wave, lane);
+        lds_barrier();
+        phase_a(xw, skw, tw, dyw, tile);
+        rbw_landed<G::MAXX>(xw, nsx, wave, lane);
+        lds_barrier();
+        phase_b(dyw, tw, xw, dtw, tile + G0);
+    }
+
+    // ---- the four waves' sums, wave 0 first, through LDS (the dgrad waves are done with it at the
+    // barrier), as this workgroup's partials: conv_b's set, then conv_a's
+    lds_barrier();
+    float* red = reinterpret_cast<float*>(smem);
+    const int g = lane >> 4, r16 = lane & 15;
+    auto put = [&](int at, const cb_f32x4& acc) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) red[(rw * 20 + at) * 256 + (4 * g + e) * 16 + r16] = acc[e];
+    };
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+        put(k, accB[k]);
+        put(10 + k, accA[k]);
+    }
+    put(9, biasB);
+    put(19, biasA);
+    lds_barrier();
+    float* part = a.partial + int64_t(blockIdx.x) * G::PSTRIDE;
+    for (int e = tid - NS * 64; e < 20 * 256; e += NS * 64) {
+        const float v = ((red[e] + red[20 * 256 + e]) + red[40 * 256 + e]) + red[60 * 256 + e];
+        part[e < 10 * 256 ? e : e - 10 * 256 + t.pset] = v;
+    }
+}
+
 namespace {
 
-constexpr int kRbbWaves = 8;
-constexpr size_t kRbbPartBytes = 24u << 20;   // both partial sets
+// Scratch: both partial sets. The kernels use one partial per CU at most (256).
+constexpr size_t kRbwPartBytes = 24u << 20;
 
-template <int C>
-int rbb_parts_cap() {
-    const size_t cap = kRbbPartBytes / (2 * size_t(RbbGeom<C>::PSTRIDE) * sizeof(float));
-    return int(cap < 256 ? 256 : (cap > 1024 ? 1024 : cap));
+template <class G>
+constexpr size_t rbw_partial_floats() {
+    const size_t cap = kRbwPartBytes / (2 * size_t(G::PSTRIDE) * sizeof(float));
+    return 2 * (cap < 256 ? 256 : (cap > 1024 ? 1024 : cap)) * size_t(G::PSTRIDE);
 }
 
 // Tile shapes of the column-walk kernel: minimise rounds of tiles over the CUs times a tile's
@@ -656,7 +578,7 @@ int rbb_parts_cap() {
 hipError_t rbw_launch(const ResBwdArgs& a, hipStream_t s, PendingReduce out[2]) {
     using G = RbwGeom;
     const int H = a.H, W = a.W, cus = std::min(device_cus(), 256);
-    if (int64_t(H) * W * G::C * 2 * 16 >= (int64_t(1) << 31)) return hipErrorInvalidValue;
+    if (int64_t(H) * W * G::C * 2 >= (int64_t(1) << 31)) return hipErrorInvalidValue;
     static thread_local WalkPlans<RbwTile> plans;
     const auto* plan = plans.find(a.n, H, W, cus);
     if (!plan) {
@@ -709,51 +631,61 @@ hipError_t rbw_launch(const ResBwdArgs& a, hipStream_t s, PendingReduce out[2]) 
     return hipGetLastError();
 }
 
-template <int C>
-hipError_t rbb_launch(const ResBwdArgs& a, hipStream_t s, PendingReduce out[2]) {
-    using G = RbbGeom<C>;
-    const int H = a.H, W = a.W, TW = W + 2;
-    auto regions = [&](int th, int& dyb, int& txb, int& dtb) {
-        dyb = G::blocks((th + 4) * TW * G::DSL) * 1024;
-        txb = G::blocks((th + 2) * TW * G::XSL) * 1024 + 2 * G::XPB;   // + a guard pixel either side
-        dtb = ((th + 2) * TW * G::DYP + 15) / 16 * 16;
-    };
-    auto lds = [&](int th) {
-        int dyb, txb, dtb;
-        regions(th, dyb, txb, dtb);
-        return size_t(64 + dyb + 2 * txb + dtb);
-    };
-    auto fits = [&](int th) {
-        const int per = kRbbWaves * 64;
-        return ((th + 4) * TW * G::DSL + per - 1) / per <= G::MAXD && ((th + 2) * TW * G::XSL + per - 1) / per <= G::MAXX;
-    };
-    const size_t limit = std::min<size_t>(lds_limit(), 160 * 1024);
-    int thmax = H;
-    while (thmax > 1 && (lds(thmax) > G::LDS_TARGET || !fits(thmax))) --thmax;
-    if (lds(thmax) > limit || !fits(thmax)) return hipErrorInvalidValue;
-    if (int64_t(H) * W * C * 2 >= (int64_t(1) << 31)) return hipErrorInvalidValue;
-    const int nb0 = (H + thmax - 1) / thmax;
-    const int TH = (H + nb0 - 1) / nb0;   // balanced bands
-    RbbTile t{};
-    t.TH = TH; t.nbands = (H + TH - 1) / TH; t.ntiles = t.nbands * a.n;
-    int dyb, txb, dtb;
-    regions(TH, dyb, txb, dtb);
-    t.dy_off = 64; t.t_off = t.dy_off + dyb; t.x_off = t.t_off + txb; t.dt_off = t.x_off + txb;
-    t.tx_guard = txb - 2 * G::XPB;
-    t.dt_bytes = dtb;
-    t.inv_W = 1.f / float(W);
-    const size_t L = std::max(lds(TH), size_t(kRbbWaves * 4) * 17 * 16);   // (pending reduce)
-    const void* fn = reinterpret_cast<const void*>(&resblock_bwd_kernel<C, kRbbWaves>);
-    int parts = std::min(resident_blocks(fn, 64 * kRbbWaves, L), rbb_parts_cap<C>());
-    if (parts > t.ntiles) parts = t.ntiles;
-    t.pset = parts * G::PSTRIDE;
-    const std::string shape = cb_dims(C, C) + "/" + cb_dims(H, W);
-    {
-        ProfScope ps(s, [&] { return cb_key("resblock_bwd", 0, shape); });
-        hipLaunchKernelGGL((resblock_bwd_kernel<C, kRbbWaves>), dim3(unsigned(parts)), dim3(64 * kRbbWaves), L, s, a, t);
+hipError_t rbw16_launch(const ResBwdArgs& a, hipStream_t s, PendingReduce out[2]) {
+    using G = Rbw16Geom;
+    const int H = a.H, W = a.W, cus = std::min(device_cus(), 256);
+    if (int64_t(H) * W * G::C * 2 >= (int64_t(1) << 31)) return hipErrorInvalidValue;
+    static thread_local WalkPlans<RbwTile> plans;
+    const auto* plan = plans.find(a.n, H, W, cus);
+    if (!plan) {
+        const size_t limit = std::min<size_t>(lds_limit(), 160 * 1024);
+        RbwTile t{};
+        double best = 1e30;
+        size_t L = 0;
+        for (int nb = 1; nb <= H; ++nb) {
+            const int TH = (H + nb - 1) / nb, ho = nb > 1;
+            if (nb > 1 && (H + TH - 1) / TH != nb) continue;
+            for (int F = 1; F <= (ho ? 1 : std::min<int64_t>(a.n, 16)); ++F) {
+                const int db = walk16_win_bytes(F, TH + 2 + 2 * ho, W), xb = walk16_win_bytes(F, TH + 2, W);
+                const int kb = (F * TH * W * 32 + 1023) / 1024 * 1024;
+                const int tail = xb + kb;   // dt, skip term
+                const size_t lds = size_t(db) + 2 * xb + tail;
+                if (lds > limit || kb > G::MAXK * G::NW * 1024 || db > G::MAXD * G::NW * 1024 || xb > G::MAXX * G::NW * 1024) break;
+                RbwTile c{};
+                c.F = F; c.TH = TH; c.ho = ho; c.nbands = nb;
+                c.ntiles = int((a.n + F - 1) / F) * nb;
+                const double mx = double(F) * W * 32 * (TH + 2 * ho) / 8 + 1500, md = double(F) * W * 32 * (2 * TH + 6 * ho) / 8 + 1500;
+                for (c.R = 1; c.R <= std::min(TH, kWalk16MaxR); ++c.R) {
+                    const double wt = 10 * walk_rows(TH + 2 * ho, F * W, 16, G::NS, c.R, c.nsegt);
+                    const double wx = 10 * walk_rows(TH, F * W, 16, G::NS, c.R, c.nsegx);
+                    const double ww = 16 * walk_rows(TH, F * W, 32, G::NS, c.R, c.nsegw);
+                    const double cost = double((c.ntiles + cus - 1) / cus) * (std::max(20 * (wt + ww), mx) + std::max(20 * (wx + ww), md) + 800);
+                    if (cost < best) {
+                        best = cost;
+                        t = c;
+                        t.t_off = db; t.x_off = db + xb; t.dt_off = db + 2 * xb; t.sk_off = t.dt_off + xb;
+                        t.dt_bytes = xb;
+                        L = std::max(lds, size_t(4) * 20 * 1024);   // (the waves' sums)
+                    }
+                }
+            }
+        }
+        if (L == 0) return hipErrorInvalidValue;
+        t.inv_W = 1.f / float(W); t.inv_c = 1.f / float(t.F * W); t.inv_TW = 1.f / float(walk_pitch(W));
+        t.inv_dpf = 1.f / float((t.TH + 2 + 2 * t.ho) * walk_pitch(W));
+        t.inv_xpf = 1.f / float((t.TH + 2) * walk_pitch(W));
+        t.pset = std::min(cus, t.ntiles) * G::PSTRIDE;
+        plan = plans.put({a.n, H, W, cus, t, L});
     }
-    out[0] = PendingReduce{a.partial, a.dwb, a.dbb, parts, G::PSTRIDE, C, C, 0, 1.f};
-    out[1] = PendingReduce{a.partial + t.pset, a.dwa, a.dba, parts, G::PSTRIDE, C, C, 0, 1.f};
+    const int parts = plan->t.pset / G::PSTRIDE;
+    auto launch = [&](auto r) {
+        ProfScope ps(s, [&] { return cb_key("resblock_bwd", 0, cb_dims(G::C, G::C) + "/" + cb_dims(H, W)); });
+        hipLaunchKernelGGL(resblock_bwd16_walk_kernel<decltype(r)::value>, dim3(unsigned(parts)), dim3(G::NT), plan->lds, s, a, plan->t);
+    };
+    if (plan->t.R == 8) launch(std::integral_constant<int, 8>{});
+    else walk_dispatch(plan->t.R, launch);
+    out[0] = PendingReduce{a.partial, a.dwb, a.dbb, parts, G::PSTRIDE, G::C, G::C, 0, 1.f};
+    out[1] = PendingReduce{a.partial + plan->t.pset, a.dwa, a.dba, parts, G::PSTRIDE, G::C, G::C, 0, 1.f};
     return hipGetLastError();
 }
 
@@ -767,8 +699,8 @@ bool resblock_bwd_supported(int C) { return C == 16 || C == 32; }
 bool resblock_bwd_preferred(int C, int H, int W) { return (C == 16 || C == 32) && H > 0 && W > 0; }
 
 size_t resblock_bwd_partial_floats(int C) {
-    if (C == 16) return 2 * size_t(rbb_parts_cap<16>()) * RbbGeom<16>::PSTRIDE;
-    if (C == 32) return 2 * size_t(rbb_parts_cap<32>()) * RbbGeom<32>::PSTRIDE;
+    if (C == 16) return rbw_partial_floats<Rbw16Geom>();
+    if (C == 32) return rbw_partial_floats<RbwGeom>();
     return 0;
 }
 
@@ -778,7 +710,7 @@ hipError_t resblock_bwd(int C, const ResBwdArgs& a, hipStream_t s, PendingReduce
     if (a.n <= 0) {
         return flush_pending_reduces(a.pend, a.pend2, s);
     }
-    if (C == 16) return rbb_launch<16>(a, s, out);
+    if (C == 16) return rbw16_launch(a, s, out);
     if (C == 32) return rbw_launch(a, s, out);
     return hipErrorInvalidValue;
 }

@@ -1,4 +1,4 @@
-// Column walks: 3x3 convolutions of 32 channels, and their weight gradients, over LDS windows, with
+// Column walks: 3x3 convolutions of 16, 32 and 64 channels, and their weight gradients, over LDS windows, with
 // every fragment read feeding all the rows it touches.
 //
 // A window holds F frames of `rows` image rows at a row pitch of W + 1 pixels and one pixel past
@@ -45,7 +45,8 @@ inline double walk_rows(int rows, int cols, int gw, int waves, int R, int& nseg)
     nseg = (rows + R - 1) / R;
     return double(((nseg * cols + gw - 1) / gw + waves - 1) / waves) * (R + 0.7);
 }
-constexpr int kWalkMaxR = 7;   // kernels exist for 1 .. kWalkMaxR rows per walk
+constexpr int kWalkMaxR = 7;     // kernels exist for 1 .. kWalkMaxR rows per walk
+constexpr int kWalk16MaxR = 8;   // (16 channels)
 // Calls f(std::integral_constant<int, R>) for a run-time R.
 template <class F>
 inline void walk_dispatch(int R, F&& f) {
@@ -56,7 +57,8 @@ inline void walk_dispatch(int R, F&& f) {
         case 4: f(std::integral_constant<int, 4>{}); break;
         case 5: f(std::integral_constant<int, 5>{}); break;
         case 6: f(std::integral_constant<int, 6>{}); break;
-        default: f(std::integral_constant<int, 7>{}); break;
+        case 7: f(std::integral_constant<int, 7>{}); break;
+        default: break;
     }
 }
 // The last tile shapes chosen, per thread (the choice takes some microseconds): a few entries by
@@ -195,6 +197,95 @@ CB_DEV void walk_wgrad(const unsigned char* xwin, const unsigned char* dwin, con
             }
             __builtin_amdgcn_sched_barrier(0);
         }
+}
+
+// ---- 16 channels: 32 bytes per pixel, as they are (16-byte reads of 16 consecutive pixels and
+// transpose reads of 8 are free of bank conflicts). A k-step of 32 is two taps, in the order of the
+// per-layer kernels: (0,1) (2,3) (4,5) (6,7) (8), the last against zero weights in its second half.
+__host__ __device__ inline int walk16_win_bytes(int F, int rows, int W) { return ((F * rows * walk_pitch(W) + 1) * 32 + 1023) / 1024 * 1024; }
+
+// walk_conv32 for 16 -> 16 channels: w[k-step], output row 4 i + j is channel 4 i + j. Input row i
+// serves output rows i (taps 0,1; with row i + 1: 2,3), i - 1 (4,5) and i - 2 (6,7; 8).
+template <int R, class Pre, class Emit>
+CB_DEV void walk_conv16(const unsigned char* win, int p0, int g, int rowb, const uint4 (&w)[5], Pre&& pre, Emit&& emit) {
+    const uint32_t base = uint32_t(p0) * 32 + uint32_t(g & 1) * 16;
+    const bool up = g >= 2;
+    uint32_t a01 = base + (up ? 32u : 0u), a12 = base + (up ? 64u : 32u), am = up ? base + rowb : base + 64u, a2 = base + 64u;
+    uint4 x[2][4];
+    cb_f32x4 acc[3];
+    auto load = [&](uint4 (&dst)[4], int i) CB_INLINE_LAMBDA {
+        dst[0] = *reinterpret_cast<const uint4*>(win + a01);
+        if (i < R) dst[1] = *reinterpret_cast<const uint4*>(win + am);
+        if (i >= 1 && i <= R) dst[2] = *reinterpret_cast<const uint4*>(win + a12);
+        if (i >= 2) dst[3] = *reinterpret_cast<const uint4*>(win + a2);
+    };
+    load(x[0], 0);
+#pragma unroll
+    for (int i = 0; i < R + 2; ++i) {
+        const uint4 (&cur)[4] = x[i & 1];
+        if (i < R + 1) {
+            a01 += rowb; a12 += rowb; am += rowb; a2 += rowb;
+            load(x[(i + 1) & 1], i + 1);
+        }
+        if (i >= 2) {
+            pre();
+            acc[(i - 2) % 3] = PrecBF16::mma(w[3], cur[0], acc[(i - 2) % 3]);
+        }
+        if (i < R) acc[i % 3] = PrecBF16::mma(w[0], cur[0], cb_f32x4{0.f, 0.f, 0.f, 0.f});
+        if (i >= 1 && i <= R) acc[(i - 1) % 3] = PrecBF16::mma(w[2], cur[2], acc[(i - 1) % 3]);
+        if (i >= 2) acc[(i - 2) % 3] = PrecBF16::mma(w[4], cur[3], acc[(i - 2) % 3]);
+        if (i < R) acc[i % 3] = PrecBF16::mma(w[1], cur[1], acc[i % 3]);
+        if (i >= 2) emit(i - 2, acc[(i - 2) % 3]);
+        __builtin_amdgcn_sched_barrier(0);   // one row's reads in flight
+    }
+}
+
+// walk_wgrad for 16 x 16 channels over one fragment of 32 anchors (ch: byte of the lane's chunk).
+template <int R>
+CB_DEV void walk_wgrad16(const unsigned char* xwin, const unsigned char* dwin, const int (&px)[2], const int (&pd)[2], const int (&skip)[2],
+                         uint32_t ch, int rowb, cb_f32x4 (&acc)[9], cb_f32x4& accb) {
+    uint32_t ax[2], ad[2];
+    uint4 x[2][3], d[4];
+    const uint4 ones = make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u);
+    auto load_d = [&](uint4& dst, int i) CB_INLINE_LAMBDA {
+        const uint2 lo = lds_read_tr16(dwin + (i >= skip[0] ? ad[0] : 0u)), hi = lds_read_tr16(dwin + (i >= skip[1] ? ad[1] : 0u));
+        dst = make_uint4(lo.x, lo.y, hi.x, hi.y);
+    };
+    auto load_x = [&](uint4 (&dst)[3]) CB_INLINE_LAMBDA {
+#pragma unroll
+        for (int kx = 0; kx < 3; ++kx) {
+            const uint2 lo = lds_read_tr16(xwin + ax[0] + kx * 32), hi = lds_read_tr16(xwin + ax[1] + kx * 32);
+            dst[kx] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+        }
+    };
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        ad[h] = uint32_t(pd[h]) * 32 + ch;
+        ax[h] = uint32_t(px[h]) * 32 + ch;
+    }
+    load_d(d[0], 0);
+    load_x(x[0]);
+#pragma unroll
+    for (int i = 0; i < R + 2; ++i) {
+        const uint4 (&cur)[3] = x[i & 1];
+        if (i + 1 < R) {
+            ad[0] += rowb;
+            ad[1] += rowb;
+            load_d(d[(i + 1) % 4], i + 1);
+        }
+        if (i < R + 1) {
+            ax[0] += rowb;
+            ax[1] += rowb;
+            load_x(x[(i + 1) & 1]);
+        }
+#pragma unroll
+        for (int ky = 2; ky >= 0; --ky)
+            if (i >= ky && i - ky < R)
+#pragma unroll
+                for (int kx = 0; kx < 3; ++kx) acc[3 * ky + kx] = PrecBF16::mma(d[(i - ky) % 4], cur[kx], acc[3 * ky + kx]);
+        if (i < R) accb = PrecBF16::mma(d[i % 4], ones, accb);
+        __builtin_amdgcn_sched_barrier(0);
+    }
 }
 
 // ---- 64 channels: 128 bytes per pixel, the eight 16-byte slots permuted by XOR with bits 1, 2 of the

@@ -56,22 +56,23 @@ def test_resblock32_forward_equals_two_convolutions(case, offset):
 
 @pytest.mark.parametrize("case", SHAPES, ids=lambda c: "n%d_%dx%d" % c)
 @pytest.mark.parametrize("offset", [0, 2])
-def test_resblock32_backward_equals_two_conv_backwards(case, offset):
+@pytest.mark.parametrize("C", [16, 32])
+def test_resblock_backward_equals_two_conv_backwards(case, offset, C):
     P = _p()
     n, H, W = case
     g = torch.Generator(device="cuda:0").manual_seed(n * 1013 + H * 37 + W)
-    dy, t, x = (_act(g, (n, H, W, 32), offset) for _ in range(3))
+    dy, t, x = (_act(g, (n, H, W, C), offset) for _ in range(3))
     wpad = offset // 2
-    wa, wb = ((torch.randn(9 * 32 * 32 + wpad, generator=g, device="cuda:0") * 0.1)[wpad:].view(3, 3, 32, 32)
+    wa, wb = ((torch.randn(9 * C * C + wpad, generator=g, device="cuda:0") * 0.1)[wpad:].view(3, 3, C, C)
               for _ in range(2))
-    dx, dt, dx_ref = (torch.full((n * H * W * 32 + offset,), 7.0, device="cuda:0").to(torch.bfloat16)[offset:]
-                      .view(n, H, W, 32) for _ in range(3))
-    gw = [torch.full(s, 9.0, device="cuda:0") for s in ((3, 3, 32, 32), (32,)) * 4]
-    ws = torch.empty(max(P.impala_resblock_bwd_workspace_bytes(0, 32), P.impala_conv3x3_bwd_workspace_bytes(0, 32, 32)),
+    dx, dt, dx_ref = (torch.full((n * H * W * C + offset,), 7.0, device="cuda:0").to(torch.bfloat16)[offset:]
+                      .view(n, H, W, C) for _ in range(3))
+    gw = [torch.full(s, 9.0, device="cuda:0") for s in ((3, 3, C, C), (C,)) * 4]
+    ws = torch.empty(max(P.impala_resblock_bwd_workspace_bytes(0, C), P.impala_conv3x3_bwd_workspace_bytes(0, C, C)),
                      dtype=torch.uint8, device="cuda:0")
-    P.impala_resblock_bwd(P.PREC_BF16, n, H, W, 32, dy, t, x, wa, wb, dx, *gw[:4], ws)
-    P.impala_conv3x3_bwd(P.PREC_BF16, n, H, W, 32, 32, dy, t, P.X_RELU, wb, None, dt, gw[6], gw[7], ws)
-    P.impala_conv3x3_bwd(P.PREC_BF16, n, H, W, 32, 32, dt, x, P.X_RELU, wa, dy, dx_ref, gw[4], gw[5], ws)
+    P.impala_resblock_bwd(P.PREC_BF16, n, H, W, C, dy, t, x, wa, wb, dx, *gw[:4], ws)
+    P.impala_conv3x3_bwd(P.PREC_BF16, n, H, W, C, C, dy, t, P.X_RELU, wb, None, dt, gw[6], gw[7], ws)
+    P.impala_conv3x3_bwd(P.PREC_BF16, n, H, W, C, C, dt, x, P.X_RELU, wa, dy, dx_ref, gw[4], gw[5], ws)
     torch.cuda.synchronize()
     assert torch.equal(_bits(dx), _bits(dx_ref))
     for got, want in zip(gw[:4], gw[4:]):
