@@ -129,3 +129,34 @@ def test_conv64_backward_equals_input_and_weight_gradient(case, add):
     for got, want in zip(gw[:2], gw[2:]):   # (the bound of the residual block's test)
         scale = float(n * H * W) ** 0.5 * 0.5 + 1.0
         assert torch.allclose(got, want, rtol=1e-5, atol=2.0 ** -20 * scale * max(float(n * H * W) ** 0.5, 1.0))
+
+
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 200])
+@pytest.mark.parametrize("A", [1, 2, 15, 16, 18, 31, 32])   # the head kernel's two 16-row blocks; past them its fallback
+@pytest.mark.parametrize("keep_logits", [False, True])
+def test_actor_step_samples_as_the_sampling_call_does(n, A, keep_logits):
+    """The sample formed by the head kernel is the one impala_gumbel_sample forms from its logits, also
+    with ties (noise of few distinct values: the lowest index wins) and with excluded actions."""
+    from types import SimpleNamespace
+    P = _p()
+    net = SimpleNamespace(in_h=20, in_w=18, in_c=4, ch=(16, 32, 32), hidden=256, num_actions=A)
+    g = torch.Generator(device="cuda:0").manual_seed(n * 101 + A)
+    params = torch.randn(P.impala_param_count(net), generator=g, device="cuda:0") * 0.1
+    obs = torch.randint(0, 256, (n, 20, 18, 4), generator=g, device="cuda:0", dtype=torch.int32).to(torch.uint8)
+    gum = torch.randint(0, 3, (n, A), generator=g, device="cuda:0").float() * 50.0
+    gum[:, A // 2] = -float("inf") if A > 1 else 0.0
+    ws = torch.empty(P.impala_workspace_bytes(net, n, P.PREC_BF16, 0) + n * A * 4 + 256, dtype=torch.uint8, device="cuda:0")
+    out = []
+    for logits in (torch.empty((n, A), device="cuda:0"), torch.empty((n, A), device="cuda:0") if keep_logits else None):
+        act = torch.full((n,), -7, dtype=torch.int32, device="cuda:0")
+        logp, value = (torch.full((n,), 9.0, device="cuda:0") for _ in range(2))
+        P.impala_actor_step(net, P.PREC_BF16, params, obs, n, gum, ws, act, logp, value, logits)
+        out.append((act, logp, value, logits))
+    act, logp, value, logits = out[0]
+    act_ref, logp_ref = torch.empty_like(act), torch.empty_like(logp)
+    P.impala_gumbel_sample(n, A, logits, gum, act_ref, logp_ref)
+    torch.cuda.synchronize()
+    for a, lp, v, _ in out:
+        assert torch.equal(a, act_ref)
+        assert torch.equal(lp.view(torch.int32), logp_ref.view(torch.int32))
+        assert torch.equal(v.view(torch.int32), value.view(torch.int32))
