@@ -1017,20 +1017,6 @@ __global__ __launch_bounds__(64 * NW, (CbGeom<CI, CO>::WPS)) void conv_bwd_spec_
 // residual 830 -> 577 us (640 -> 925 TFLOP/s), of 11x11 254 -> 183 us, 640 of 21x21 98.7 -> 68.4 us, 5
 // of 21x21 25 -> 20 us. What bounds it: the MFMAs of a SIMD's two waves (230 us at the matrix cores' rate at
 // 21x21) and the vector instructions between them.
-struct Cw64Geom {
-    static constexpr int C = 64, NW = 8, NT = 512, NS = 4;   // NS: waves per role
-    static constexpr int NBB = 37, PSTRIDE = 4 * NBB * 256;  // partial: [co block][tap x ci block, bias][co][ci]
-    static constexpr int MAXS = 10;                          // staging slots per lane and window
-};
-struct Cw64Tile {
-    int F, TH, nbands, ntiles;
-    int ho;                    // several bands per frame
-    int win;                   // window bytes; LDS: dy, x of buffer 0, then of buffer 1
-    int R, nsegd, nsegw;       // rows per walk (the kernel's R), segments of a column: dx, weight gradients
-    int parts;                 // workgroups
-    float inv_W, inv_c, inv_TW, inv_pf;   // 1 / W, F * W, row pitch, window pixels per frame
-};
-
 template <int R, int ADD>
 __global__ __launch_bounds__(Cw64Geom::NT, 2) void conv_bwd64_walk_kernel(ConvBwdArgs a, Cw64Tile t) {
     using G = Cw64Geom;
@@ -1244,32 +1230,12 @@ hipError_t cw64_launch(const ConvBwdArgs& a, hipStream_t s, int& parts) {
     if (!plan) {
         const size_t limit = std::min<size_t>(lds_limit(), 160 * 1024);
         Cw64Tile t{};
-        double best = 1e30;
-        for (int nb = 1; nb <= H; ++nb) {
-            const int TH = (H + nb - 1) / nb, ho = nb > 1;
-            if (nb > 1 && (H + TH - 1) / TH != nb) continue;
-            for (int F = 1; F <= (ho ? 1 : std::min<int64_t>(a.n, 16)); ++F) {
-                Cw64Tile c{};
-                c.win = walk64_win_bytes(F, TH + 2, W);
-                if (4 * size_t(c.win) > limit || c.win > G::MAXS * G::NS * 1024) break;
-                c.F = F; c.TH = TH; c.ho = ho; c.nbands = nb;
-                c.ntiles = int((a.n + F - 1) / F) * nb;
-                const double mem = double(F) * W * 128 * (3 * TH + 4) / 8;
-                for (c.R = 1; c.R <= std::min(TH, kWalkMaxR); ++c.R) {
-                    const double work = 36 * walk_rows(TH, F * W, 16, 2, c.R, c.nsegd) + 38 * walk_rows(TH, F * W, 32, 1, c.R, c.nsegw);
-                    const double cost = double((c.ntiles + cus - 1) / cus) * (std::max(18 * work, mem) + 1500);
-                    if (cost < best) { best = cost; t = c; }
-                }
-            }
-        }
-        if (t.win == 0) return hipErrorNotSupported;
-        t.parts = std::min(cus, t.ntiles);
-        t.inv_W = 1.f / float(W); t.inv_c = 1.f / float(t.F * W); t.inv_TW = 1.f / float(walk_pitch(W));
-        t.inv_pf = 1.f / float((t.TH + 2) * walk_pitch(W));
-        plan = plans.put({a.n, H, W, cus, t, std::max<size_t>(4 * size_t(t.win), 72 * 1024)});
+        size_t L = 0;
+        if (!walk_choose([&](auto&& f) { cw64_shapes(a.n, H, W, cus, limit, f); }, t, L)) return hipErrorNotSupported;
+        plan = plans.put({a.n, H, W, cus, t, L});
     }
     parts = plan->t.parts;
-    walk_dispatch(plan->t.R, [&](auto r) {
+    walk_dispatch<G::MAXR>(plan->t.R, [&](auto r) {
         ProfScope ps(s, [&] { return cb_key("conv_bwd", 0, cb_dims(64, 64) + "/" + cb_dims(H, W) + cb_flags(IN_RELU, false, ADD)); });
         hipLaunchKernelGGL((conv_bwd64_walk_kernel<decltype(r)::value, ADD>), dim3(unsigned(parts)), dim3(G::NT), plan->lds, s, a, plan->t);
     });

@@ -278,21 +278,6 @@ __global__ __launch_bounds__(64 * NW, RbGeom<C>::WPS) void resblock_fwd_kernel(R
 // us, 2048 of 11x11 27.3 -> 20.4 us, 8 of 21x21 12.4 -> 9.9 us. What is left at 21x21: about
 // 2.6 us before the first row, then 70% of the matrix cores' time (vector ALU work of the
 // epilogues beside them) and the loads of a tile that the other workgroup does not cover.
-struct RwGeom {
-    static constexpr int C = 32, NW = 4, NT = 256, KS = 9;
-    static constexpr int MAXS = 11;                  // x-window staging slots per lane
-    static constexpr int WFRAG = 2 * KS * 1024;      // one convolution's A fragments (bytes)
-    static constexpr size_t LDS_TARGET = 80 * 1024;  // two workgroups per CU
-};
-
-struct RwTile {
-    int F, TH, nbands, ntiles;   // frames per tile (1 with several bands per frame), rows per band
-    int ho;                      // 1: t has a halo row either side (several bands)
-    int t_off;                   // LDS bytes of the t window (the x window is at 0)
-    int R, nseg1, nseg2;         // rows per walk (the kernel's R), segments of a column: conv1, conv2
-    float inv_W, inv_c, inv_TW, inv_xpf;   // 1 / W, 1 / (F * W), 1 / row pitch, 1 / x-window pixels per frame
-};
-
 template <int R>
 __global__ __launch_bounds__(RwGeom::NT, 2) void resblock_walk_fwd_kernel(ResBlockArgs a, RwTile t) {
     using G = RwGeom;
@@ -388,7 +373,7 @@ __global__ __launch_bounds__(RwGeom::NT, 2) void resblock_walk_fwd_kernel(ResBlo
         lds_barrier();
         // the relu(t) window: its padding column and, for whole frames, its rows off the frame
         // are never written
-        for (int j = tid; j < walk_win_bytes(F, trows, W) / 16; j += NT) reinterpret_cast<uint4*>(tw)[j] = make_uint4(0, 0, 0, 0);
+        for (int j = tid; j < walk_win_bytes(64, F, trows, W) / 16; j += NT) reinterpret_cast<uint4*>(tw)[j] = make_uint4(0, 0, 0, 0);
     }
 
     const int cols = F * W;
@@ -501,12 +486,6 @@ hipError_t rb_fwd_launch(const ResBlockArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-// Tile shapes of the column-walk kernel. A tile is F whole frames or a band of one; a wave walks
-// ceil(groups / 4) groups of 16 anchors per convolution, R rows each (and about 0.7 rows' time
-// of filling). The choice minimises rounds of tiles over the resident workgroups times a tile's
-// estimated cycles: 18 MFMAs of 16 cycles per row and group, the SIMD shared by two
-// workgroups, or its memory traffic at 4 bytes per cycle and workgroup, whichever is longer,
-// plus its load latency and barriers.
 hipError_t rw_launch(const ResBlockArgs& a, hipStream_t s) {
     using G = RwGeom;
     const int H = a.H, W = a.W, cus = device_cus();
@@ -515,37 +494,11 @@ hipError_t rw_launch(const ResBlockArgs& a, hipStream_t s) {
     const auto* plan = plans.find(a.n, H, W, cus);
     if (!plan) {
         RwTile t{};
-        double best = 1e30;
         size_t L = 0;
-        for (int nb = 1; nb <= H; ++nb) {
-            const int TH = (H + nb - 1) / nb, ho = nb > 1;
-            if (nb > 1 && (H + TH - 1) / TH != nb) continue;
-            for (int F = 1; F <= (ho ? 1 : std::min<int64_t>(a.n, 16)); ++F) {
-                const int xb = walk_win_bytes(F, TH + 2 + 2 * ho, W), tb = std::max(walk_win_bytes(F, TH + 2, W), 2 * G::WFRAG);
-                const size_t lds = size_t(xb) + tb;
-                if (lds > G::LDS_TARGET || xb > G::MAXS * G::NW * 1024) break;
-                RwTile c{};
-                c.F = F; c.TH = TH; c.ho = ho; c.nbands = nb;
-                c.ntiles = int((a.n + F - 1) / F) * nb;
-                const double mem = double(F) * W * 64 * (3 * TH + 4 * ho) / 4;
-                for (c.R = 1; c.R <= std::min(TH, kWalkMaxR); ++c.R) {
-                    const double work = walk_rows(TH + 2 * ho, F * W, 16, G::NW, c.R, c.nseg1) + walk_rows(TH, F * W, 16, G::NW, c.R, c.nseg2);
-                    const double cost = double((c.ntiles + 2 * cus - 1) / (2 * cus)) * (std::max(work * 18 * 16 * 2, mem) + 4000);
-                    if (cost < best) {
-                        best = cost;
-                        t = c;
-                        t.t_off = xb;
-                        L = lds;
-                    }
-                }
-            }
-        }
-        if (L == 0) return hipErrorInvalidValue;
-        t.inv_W = 1.f / float(W); t.inv_c = 1.f / float(t.F * W);
-        t.inv_TW = 1.f / float(walk_pitch(W)); t.inv_xpf = 1.f / float((t.TH + 2 + 2 * t.ho) * walk_pitch(W));
+        if (!walk_choose([&](auto&& f) { rw_shapes(a.n, H, W, cus, f); }, t, L)) return hipErrorInvalidValue;
         plan = plans.put({a.n, H, W, cus, t, L});
     }
-    walk_dispatch(plan->t.R, [&](auto r) {
+    walk_dispatch<G::MAXR>(plan->t.R, [&](auto r) {
         constexpr int R = decltype(r)::value;
         const void* fn = reinterpret_cast<const void*>(&resblock_walk_fwd_kernel<R>);
         const int gx = std::min(plan->t.ntiles, std::max(1, resident_blocks(fn, G::NT, plan->lds)));

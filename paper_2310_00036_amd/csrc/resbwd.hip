@@ -41,21 +41,6 @@ namespace cb {
 // of 11x11 56 -> 45 us, 8192 of 42x42 1590 -> 1490 us, 640 of 11x11 with its reduce 36 -> 25 us.
 // What bounds it: a SIMD's MFMAs (about 270 of 16 cycles per phase at 21x21) and the vector
 // instructions of its two waves, which overlap 1.6 to 1; then staging and barriers.
-struct RbwGeom {
-    static constexpr int C = 32, NW = 8, NT = 512, NS = 4;   // NS: waves per role
-    static constexpr int NBB = 19, PSTRIDE = 2 * NBB * 256;  // partial: [co block][tap x ci block, bias][co][ci]
-    static constexpr int MAXD = 6, MAXX = 6, MAXK = 5;       // staging slots per lane: dy; t / x; skip term
-    static constexpr int WFRAG = 2 * 9 * 1024;               // one convolution's A fragments (bytes)
-};
-struct RbwTile {
-    int F, TH, nbands, ntiles;
-    int ho;                      // 1: dt has a halo row either side (several bands)
-    int t_off, x_off, dt_off, sk_off, dt_bytes;   // LDS bytes (the dy window is at 0)
-    int R, nsegt, nsegx, nsegw;  // rows per walk (the kernel's R), segments of a column: dt, dx, weight gradients
-    int pset;                    // floats per partial set (one per convolution)
-    float inv_W, inv_c, inv_TW, inv_dpf, inv_xpf;    // 1 / W, F * W, row pitch, window pixels per frame (dy; t, x, dt)
-};
-
 // One window of a tile, HBM -> LDS: block wave + NW*k of 64 16-byte slots from the lane's offset
 // off[k], shifted by `row` rows.
 template <int C, int N>
@@ -327,12 +312,6 @@ __global__ __launch_bounds__(RbwGeom::NT, 2) void resblock_bwd_walk_kernel(ResBw
 // 31.5 -> 26 us, of 11x11 22.7 -> 17.8 us. Two workgroups of this form per CU (80 KB windows, 128
 // registers, which spill) were slower: 180 us on 2048 frames of 42x42. What bounds it: 462 MB at the
 // rate of a large copy are 97 us; the rest is a phase's loads that outlast its work, and barriers.
-struct Rbw16Geom {
-    static constexpr int C = 16, NW = 8, NT = 512, NS = 4;   // NS: waves per role
-    static constexpr int NBB = 10, PSTRIDE = NBB * 256;      // partial: [tap, bias][co][ci]
-    static constexpr int MAXD = 6, MAXX = 6, MAXK = 5;       // staging slots per lane: dy; t / x; skip term
-};
-
 template <int R>
 __global__ __launch_bounds__(Rbw16Geom::NT, 2) void resblock_bwd16_walk_kernel(ResBwdArgs a, RbwTile t) {
     using G = Rbw16Geom;
@@ -571,12 +550,9 @@ constexpr size_t rbw_partial_floats() {
     return 2 * (cap < 256 ? 256 : (cap > 1024 ? 1024 : cap)) * size_t(G::PSTRIDE);
 }
 
-// Tile shapes of the column-walk kernel: minimise rounds of tiles over the CUs times a tile's
-// estimated cycles, each phase the longer of its MFMAs (16 cycles, the SIMD shared by an
-// input-gradient and a weight-gradient wave) and of the loads it covers (8 bytes per cycle and
-// CU, plus their latency).
-hipError_t rbw_launch(const ResBwdArgs& a, hipStream_t s, PendingReduce out[2]) {
-    using G = RbwGeom;
+// Launches kernel(std::integral_constant<int, R>) on the tile shape that walkplan.h chooses.
+template <class G, class Launch>
+hipError_t rbw_launch(const ResBwdArgs& a, hipStream_t s, PendingReduce out[2], Launch&& launch) {
     const int H = a.H, W = a.W, cus = std::min(device_cus(), 256);
     if (int64_t(H) * W * G::C * 2 >= (int64_t(1) << 31)) return hipErrorInvalidValue;
     static thread_local WalkPlans<RbwTile> plans;
@@ -584,106 +560,15 @@ hipError_t rbw_launch(const ResBwdArgs& a, hipStream_t s, PendingReduce out[2]) 
     if (!plan) {
         const size_t limit = std::min<size_t>(lds_limit(), 160 * 1024);
         RbwTile t{};
-        double best = 1e30;
         size_t L = 0;
-        for (int nb = 1; nb <= H; ++nb) {
-            const int TH = (H + nb - 1) / nb, ho = nb > 1;
-            if (nb > 1 && (H + TH - 1) / TH != nb) continue;
-            for (int F = 1; F <= (ho ? 1 : std::min<int64_t>(a.n, 16)); ++F) {
-                const int db = walk_win_bytes(F, TH + 2 + 2 * ho, W), xb = walk_win_bytes(F, TH + 2, W);
-                const int kb = (F * TH * W + 15) / 16 * 1024;
-                const int tail = std::max(xb + kb, 2 * G::WFRAG);   // dt, skip term; the weights at first
-                const size_t lds = size_t(db) + 2 * xb + tail;
-                if (lds > limit || kb > G::MAXK * G::NW * 1024 || db > G::MAXD * G::NW * 1024 || xb > G::MAXX * G::NW * 1024) break;
-                RbwTile c{};
-                c.F = F; c.TH = TH; c.ho = ho; c.nbands = nb;
-                c.ntiles = int((a.n + F - 1) / F) * nb;
-                const double mx = double(F) * W * 64 * (TH + 2 * ho) / 8 + 1500, md = double(F) * W * 64 * (2 * TH + 6 * ho) / 8 + 1500;
-                for (c.R = 1; c.R <= std::min(TH, kWalkMaxR); ++c.R) {
-                    const double wt = 18 * walk_rows(TH + 2 * ho, F * W, 16, G::NS, c.R, c.nsegt);
-                    const double wx = 18 * walk_rows(TH, F * W, 16, G::NS, c.R, c.nsegx);
-                    const double ww = 20 * walk_rows(TH, F * W, 64, 1, c.R, c.nsegw);
-                    const double cost = double((c.ntiles + cus - 1) / cus) * (std::max(20 * (wt + ww), mx) + std::max(20 * (wx + ww), md) + 800);
-                    if (cost < best) {
-                        best = cost;
-                        t = c;
-                        t.t_off = db; t.x_off = db + xb; t.dt_off = db + 2 * xb; t.sk_off = t.dt_off + xb;
-                        t.dt_bytes = xb;
-                        L = lds;
-                    }
-                }
-            }
-        }
-        if (L == 0) return hipErrorInvalidValue;
-        t.inv_W = 1.f / float(W); t.inv_c = 1.f / float(t.F * W); t.inv_TW = 1.f / float(walk_pitch(W));
-        t.inv_dpf = 1.f / float((t.TH + 2 + 2 * t.ho) * walk_pitch(W));
-        t.inv_xpf = 1.f / float((t.TH + 2) * walk_pitch(W));
-        t.pset = std::min(cus, t.ntiles) * G::PSTRIDE;
+        if (!walk_choose([&](auto&& f) { rbw_shapes<G>(a.n, H, W, cus, limit, f); }, t, L)) return hipErrorInvalidValue;
         plan = plans.put({a.n, H, W, cus, t, L});
     }
     const int parts = plan->t.pset / G::PSTRIDE;
-    walk_dispatch(plan->t.R, [&](auto r) {
+    walk_dispatch<G::MAXR>(plan->t.R, [&](auto r) {
         ProfScope ps(s, [&] { return cb_key("resblock_bwd", 0, cb_dims(G::C, G::C) + "/" + cb_dims(H, W)); });
-        hipLaunchKernelGGL(resblock_bwd_walk_kernel<decltype(r)::value>, dim3(unsigned(parts)), dim3(G::NT), plan->lds, s, a, plan->t);
+        launch(r, dim3(unsigned(parts)), dim3(G::NT), plan->lds, plan->t);
     });
-    out[0] = PendingReduce{a.partial, a.dwb, a.dbb, parts, G::PSTRIDE, G::C, G::C, 0, 1.f};
-    out[1] = PendingReduce{a.partial + plan->t.pset, a.dwa, a.dba, parts, G::PSTRIDE, G::C, G::C, 0, 1.f};
-    return hipGetLastError();
-}
-
-hipError_t rbw16_launch(const ResBwdArgs& a, hipStream_t s, PendingReduce out[2]) {
-    using G = Rbw16Geom;
-    const int H = a.H, W = a.W, cus = std::min(device_cus(), 256);
-    if (int64_t(H) * W * G::C * 2 >= (int64_t(1) << 31)) return hipErrorInvalidValue;
-    static thread_local WalkPlans<RbwTile> plans;
-    const auto* plan = plans.find(a.n, H, W, cus);
-    if (!plan) {
-        const size_t limit = std::min<size_t>(lds_limit(), 160 * 1024);
-        RbwTile t{};
-        double best = 1e30;
-        size_t L = 0;
-        for (int nb = 1; nb <= H; ++nb) {
-            const int TH = (H + nb - 1) / nb, ho = nb > 1;
-            if (nb > 1 && (H + TH - 1) / TH != nb) continue;
-            for (int F = 1; F <= (ho ? 1 : std::min<int64_t>(a.n, 16)); ++F) {
-                const int db = walk16_win_bytes(F, TH + 2 + 2 * ho, W), xb = walk16_win_bytes(F, TH + 2, W);
-                const int kb = (F * TH * W * 32 + 1023) / 1024 * 1024;
-                const int tail = xb + kb;   // dt, skip term
-                const size_t lds = size_t(db) + 2 * xb + tail;
-                if (lds > limit || kb > G::MAXK * G::NW * 1024 || db > G::MAXD * G::NW * 1024 || xb > G::MAXX * G::NW * 1024) break;
-                RbwTile c{};
-                c.F = F; c.TH = TH; c.ho = ho; c.nbands = nb;
-                c.ntiles = int((a.n + F - 1) / F) * nb;
-                const double mx = double(F) * W * 32 * (TH + 2 * ho) / 8 + 1500, md = double(F) * W * 32 * (2 * TH + 6 * ho) / 8 + 1500;
-                for (c.R = 1; c.R <= std::min(TH, kWalk16MaxR); ++c.R) {
-                    const double wt = 10 * walk_rows(TH + 2 * ho, F * W, 16, G::NS, c.R, c.nsegt);
-                    const double wx = 10 * walk_rows(TH, F * W, 16, G::NS, c.R, c.nsegx);
-                    const double ww = 16 * walk_rows(TH, F * W, 32, G::NS, c.R, c.nsegw);
-                    const double cost = double((c.ntiles + cus - 1) / cus) * (std::max(20 * (wt + ww), mx) + std::max(20 * (wx + ww), md) + 800);
-                    if (cost < best) {
-                        best = cost;
-                        t = c;
-                        t.t_off = db; t.x_off = db + xb; t.dt_off = db + 2 * xb; t.sk_off = t.dt_off + xb;
-                        t.dt_bytes = xb;
-                        L = std::max(lds, size_t(4) * 20 * 1024);   // (the waves' sums)
-                    }
-                }
-            }
-        }
-        if (L == 0) return hipErrorInvalidValue;
-        t.inv_W = 1.f / float(W); t.inv_c = 1.f / float(t.F * W); t.inv_TW = 1.f / float(walk_pitch(W));
-        t.inv_dpf = 1.f / float((t.TH + 2 + 2 * t.ho) * walk_pitch(W));
-        t.inv_xpf = 1.f / float((t.TH + 2) * walk_pitch(W));
-        t.pset = std::min(cus, t.ntiles) * G::PSTRIDE;
-        plan = plans.put({a.n, H, W, cus, t, L});
-    }
-    const int parts = plan->t.pset / G::PSTRIDE;
-    auto launch = [&](auto r) {
-        ProfScope ps(s, [&] { return cb_key("resblock_bwd", 0, cb_dims(G::C, G::C) + "/" + cb_dims(H, W)); });
-        hipLaunchKernelGGL(resblock_bwd16_walk_kernel<decltype(r)::value>, dim3(unsigned(parts)), dim3(G::NT), plan->lds, s, a, plan->t);
-    };
-    if (plan->t.R == 8) launch(std::integral_constant<int, 8>{});
-    else walk_dispatch(plan->t.R, launch);
     out[0] = PendingReduce{a.partial, a.dwb, a.dbb, parts, G::PSTRIDE, G::C, G::C, 0, 1.f};
     out[1] = PendingReduce{a.partial + plan->t.pset, a.dwa, a.dba, parts, G::PSTRIDE, G::C, G::C, 0, 1.f};
     return hipGetLastError();
@@ -710,8 +595,14 @@ hipError_t resblock_bwd(int C, const ResBwdArgs& a, hipStream_t s, PendingReduce
     if (a.n <= 0) {
         return flush_pending_reduces(a.pend, a.pend2, s);
     }
-    if (C == 16) return rbw16_launch(a, s, out);
-    if (C == 32) return rbw_launch(a, s, out);
+    if (C == 16)
+        return rbw_launch<Rbw16Geom>(a, s, out, [&](auto r, dim3 grid, dim3 block, size_t lds, const RbwTile& t) {
+            hipLaunchKernelGGL(resblock_bwd16_walk_kernel<decltype(r)::value>, grid, block, lds, s, a, t);
+        });
+    if (C == 32)
+        return rbw_launch<RbwGeom>(a, s, out, [&](auto r, dim3 grid, dim3 block, size_t lds, const RbwTile& t) {
+            hipLaunchKernelGGL(resblock_bwd_walk_kernel<decltype(r)::value>, grid, block, lds, s, a, t);
+        });
     return hipErrorInvalidValue;
 }
 

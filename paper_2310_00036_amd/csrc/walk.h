@@ -1,11 +1,11 @@
 // Column walks: 3x3 convolutions of 16, 32 and 64 channels, and their weight gradients, over LDS windows, with
 // every fragment read feeding all the rows it touches.
 //
-// A window holds F frames of `rows` image rows at a row pitch of W + 1 pixels and one pixel past
-// the end. Column 0 is zero padding, the right neighbour of a row's last pixel the next row's
-// column 0. A pixel's 32 channels take 64 bytes, its four 16-byte slots permuted by XOR with 2 *
-// bit 2 of its column: 16-byte reads of 16 consecutive pixels, and 8-byte transpose reads of 8,
-// then fall on distinct banks, and a step of one row is one constant.
+// The windows (walkplan.h) hold rows of W + 1 pixels: column 0 is zero padding, the right
+// neighbour of a row's last pixel the next row's column 0. A pixel's 32 channels take 64 bytes,
+// its four 16-byte slots permuted by XOR with 2 * bit 2 of its column: 16-byte reads of 16
+// consecutive pixels, and 8-byte transpose reads of 8, then fall on distinct banks, and a step of
+// one row is one constant.
 //
 // The pixels of a fragment are anchors: a column of the tile, or one of nseg segments of it, R
 // rows each. All lanes walk down their anchors together.
@@ -14,11 +14,9 @@
 #include <type_traits>
 
 #include "common.h"
+#include "walkplan.h"
 
 namespace cb {
-
-__host__ __device__ inline int walk_pitch(int W) { return W + 1; }
-__host__ __device__ inline int walk_win_bytes(int F, int rows, int W) { return (F * rows * walk_pitch(W) + 1 + 15) / 16 * 1024; }
 
 // Byte offset, in a pixel's 64 bytes at window column col, of the 16-byte slot or 8-byte chunk that
 // starts at channel byte ch.
@@ -39,16 +37,8 @@ CB_DEV WalkAnchor walk_anchor(int id, int cols, int W, int nseg, int R, int nrow
     return an;
 }
 
-// Host: rows a wave walks (its filling counted as 0.7 rows per walk) where `waves` waves take groups of
-// gw anchors, segments of R <= rows rows; nseg: segments per column.
-inline double walk_rows(int rows, int cols, int gw, int waves, int R, int& nseg) {
-    nseg = (rows + R - 1) / R;
-    return double(((nseg * cols + gw - 1) / gw + waves - 1) / waves) * (R + 0.7);
-}
-constexpr int kWalkMaxR = 7;     // kernels exist for 1 .. kWalkMaxR rows per walk
-constexpr int kWalk16MaxR = 8;   // (16 channels)
-// Calls f(std::integral_constant<int, R>) for a run-time R.
-template <class F>
+// Calls f(std::integral_constant<int, R>) for a run-time R of 1 .. MAXR.
+template <int MAXR, class F>
 inline void walk_dispatch(int R, F&& f) {
     switch (R) {
         case 1: f(std::integral_constant<int, 1>{}); break;
@@ -58,6 +48,9 @@ inline void walk_dispatch(int R, F&& f) {
         case 5: f(std::integral_constant<int, 5>{}); break;
         case 6: f(std::integral_constant<int, 6>{}); break;
         case 7: f(std::integral_constant<int, 7>{}); break;
+        case 8:
+            if constexpr (MAXR >= 8) f(std::integral_constant<int, 8>{});
+            break;
         default: break;
     }
 }
@@ -202,7 +195,6 @@ CB_DEV void walk_wgrad(const unsigned char* xwin, const unsigned char* dwin, con
 // ---- 16 channels: 32 bytes per pixel, as they are (16-byte reads of 16 consecutive pixels and
 // transpose reads of 8 are free of bank conflicts). A k-step of 32 is two taps, in the order of the
 // per-layer kernels: (0,1) (2,3) (4,5) (6,7) (8), the last against zero weights in its second half.
-__host__ __device__ inline int walk16_win_bytes(int F, int rows, int W) { return ((F * rows * walk_pitch(W) + 1) * 32 + 1023) / 1024 * 1024; }
 
 // walk_conv32 for 16 -> 16 channels: w[k-step], output row 4 i + j is channel 4 i + j. Input row i
 // serves output rows i (taps 0,1; with row i + 1: 2,3), i - 1 (4,5) and i - 2 (6,7; 8).
@@ -291,7 +283,6 @@ CB_DEV void walk_wgrad16(const unsigned char* xwin, const unsigned char* dwin, c
 // ---- 64 channels: 128 bytes per pixel, the eight 16-byte slots permuted by XOR with bits 1, 2 of the
 // column (free of bank conflicts for the same reads). A fragment's registers take the next row's
 // fragment as soon as its MFMAs are issued, so one set of them is enough.
-__host__ __device__ inline int walk64_win_bytes(int F, int rows, int W) { return ((F * rows * walk_pitch(W) + 1) * 128 + 1023) / 1024 * 1024; }
 CB_DEV uint32_t walk64_ch(uint32_t col, uint32_t ch) { return ch ^ ((col << 4) & 96); }
 
 // walk_conv32 for 64 input channels and 32 of the output channels: w[b][2 tap + half].

@@ -1,0 +1,200 @@
+// Host side of the column-walk kernels: the sizes of their LDS windows and the tile shape of a
+// launch (frames and rows per tile, rows per walk), from the problem size and the compute units.
+// Plain C++ without HIP, so that the rules can be compiled and checked on any machine.
+#pragma once
+
+#include <stddef.h>
+#include <stdint.h>
+
+#include <algorithm>
+
+#ifdef __HIPCC__
+#define CB_HD __host__ __device__
+#else
+#define CB_HD
+#endif
+
+namespace cb {
+
+// A window holds F frames of `rows` image rows at a row pitch of W + 1 pixels (column 0 is zero
+// padding and serves both sides) and one pixel past the end, in whole blocks of 1 KB, `px` bytes
+// per pixel.
+CB_HD inline int walk_pitch(int W) { return W + 1; }
+CB_HD inline int walk_win_bytes(int px, int F, int rows, int W) {
+    return ((F * rows * walk_pitch(W) + 1) * px + 1023) / 1024 * 1024;
+}
+
+// Rows a wave walks (its filling counted as 0.7 rows per walk) where `waves` waves take groups of
+// gw anchors, segments of R <= rows rows; nseg: segments per column.
+inline double walk_rows(int rows, int cols, int gw, int waves, int R, int& nseg) {
+    nseg = (rows + R - 1) / R;
+    return double(((nseg * cols + gw - 1) / gw + waves - 1) / waves) * (R + 0.7);
+}
+
+// The tile heights worth trying: every TH that splits H into nb = 1 .. H balanced bands, f(nb, TH).
+template <class Fn>
+inline void walk_bands(int H, Fn&& f) {
+    for (int nb = 1; nb <= H; ++nb) {
+        const int TH = (H + nb - 1) / nb;
+        if (nb == 1 || (H + TH - 1) / TH == nb) f(nb, TH);
+    }
+}
+constexpr int kWalkMaxF = 16;    // frames per tile
+inline int walk_frames(int64_t n, int nb) { return nb > 1 ? 1 : int(std::min<int64_t>(n, kWalkMaxF)); }
+inline int walk_tiles(int64_t n, int F, int nb) { return int((n + F - 1) / F) * nb; }
+
+// ---------------------------------------------------------------- 32-channel block forward
+struct RwGeom {
+    static constexpr int C = 32, NW = 4, NT = 256, KS = 9, MAXR = 7;   // kernels exist for 1 .. MAXR rows per walk
+    static constexpr int MAXS = 11;                  // x-window staging slots per lane
+    static constexpr int WFRAG = 2 * KS * 1024;      // one convolution's A fragments (bytes)
+    static constexpr size_t LDS_TARGET = 80 * 1024;  // two workgroups per CU
+};
+
+struct RwTile {
+    int F, TH, nbands, ntiles;   // frames per tile (1 with several bands per frame), rows per band
+    int ho;                      // 1: t has a halo row either side (several bands)
+    int t_off;                   // LDS bytes of the t window (the x window is at 0)
+    int R, nseg1, nseg2;         // rows per walk (the kernel's R), segments of a column: conv1, conv2
+    float inv_W, inv_c, inv_TW, inv_xpf;   // 1 / W, 1 / (F * W), 1 / row pitch, 1 / x-window pixels per frame
+};
+
+// Every tile shape that fits, f(tile, lds, cost). A tile is F whole frames or a band of one; a wave
+// walks ceil(groups / NW) groups of 16 anchors per convolution, R rows each. The cost, in
+// microseconds, is rounds of tiles over the resident workgroups (two per CU; a last round with one
+// tile per CU at most counts 0.6) times what a tile was measured to take: its rows walked and its
+// memory traffic add up, 0.24 us a row, 0.055 a KB and 0.4 for the rest (least squares over every
+// shape of 130 problem sizes, 1 .. 8192 frames of 8x12 .. 150x90; the shape chosen takes 1.2% longer
+// than the best one on average). With the longer of the two terms instead, all row counts tied
+// wherever the traffic was longer, and walks of a single row were taken, which reuse nothing:
+// 2048 frames of 21x21 46.8 us against 38.3 with R = 7, 8192 of 21x21 191 against 151, 2048 of 42x42
+// 205 against 190, 2048 of 11x11 19.1 against 17.3.
+template <class Fn>
+inline void rw_shapes(int64_t n, int H, int W, int cus, Fn&& f) {
+    using G = RwGeom;
+    walk_bands(H, [&](int nb, int TH) {
+        const int ho = nb > 1;
+        for (int F = 1; F <= walk_frames(n, nb); ++F) {
+            const int xb = walk_win_bytes(64, F, TH + 2 + 2 * ho, W), tb = std::max(walk_win_bytes(64, F, TH + 2, W), 2 * G::WFRAG);
+            if (size_t(xb) + tb > G::LDS_TARGET || xb > G::MAXS * G::NW * 1024) break;
+            RwTile c{};
+            c.F = F; c.TH = TH; c.ho = ho; c.nbands = nb; c.ntiles = walk_tiles(n, F, nb); c.t_off = xb;
+            c.inv_W = 1.f / float(W); c.inv_c = 1.f / float(F * W);
+            c.inv_TW = 1.f / float(walk_pitch(W)); c.inv_xpf = 1.f / float((TH + 2 + 2 * ho) * walk_pitch(W));
+            const double kb = double(F) * W * 64 * (3 * TH + 4 * ho) / 1000;
+            const int full = c.ntiles / (2 * cus), rest = c.ntiles - full * 2 * cus;
+            const double rounds = full + (rest > cus ? 1.0 : rest > 0 ? 0.6 : 0.0);
+            for (c.R = 1; c.R <= std::min(TH, G::MAXR); ++c.R) {
+                const double rows = walk_rows(TH + 2 * ho, F * W, 16, G::NW, c.R, c.nseg1) + walk_rows(TH, F * W, 16, G::NW, c.R, c.nseg2);
+                f(c, size_t(xb) + tb, rounds * (0.244 * rows + 0.0546 * kb + 0.37));
+            }
+        }
+    });
+}
+
+// ---------------------------------------------------------------- block backward, 32 and 16 channels
+struct RbwGeom {
+    static constexpr int C = 32, NW = 8, NT = 512, NS = 4, PX = 64, MAXR = 7;   // NS: waves per role; PX: bytes per pixel
+    static constexpr int NBB = 19, PSTRIDE = 2 * NBB * 256;  // partial: [co block][tap x ci block, bias][co][ci]
+    static constexpr int MAXD = 6, MAXX = 6, MAXK = 5;       // staging slots per lane: dy; t / x; skip term
+    static constexpr int WFRAG = 2 * 9 * 1024;               // one convolution's A fragments (bytes)
+    static constexpr int MIN_TAIL = 2 * WFRAG;               // the dt window's memory holds the weights at first
+    static constexpr size_t MIN_LDS = 0;
+    static constexpr int MC = 18, MW = 20;                   // MFMAs per row and group: a convolution, a weight gradient
+    static constexpr int GW = 64, WW = 1;                    // anchors per weight-gradient group, waves sharing the groups
+};
+struct Rbw16Geom {
+    static constexpr int C = 16, NW = 8, NT = 512, NS = 4, PX = 32, MAXR = 8;
+    static constexpr int NBB = 10, PSTRIDE = NBB * 256;      // partial: [tap, bias][co][ci]
+    static constexpr int MAXD = 6, MAXX = 6, MAXK = 5;
+    static constexpr int MIN_TAIL = 0;
+    static constexpr size_t MIN_LDS = 4 * 20 * 1024;         // the four waves' sums, at the end
+    static constexpr int MC = 10, MW = 16;
+    static constexpr int GW = 32, WW = 4;
+};
+
+struct RbwTile {
+    int F, TH, nbands, ntiles;
+    int ho;                      // 1: dt has a halo row either side (several bands)
+    int t_off, x_off, dt_off, sk_off, dt_bytes;   // LDS bytes (the dy window is at 0)
+    int R, nsegt, nsegx, nsegw;  // rows per walk (the kernel's R), segments of a column: dt, dx, weight gradients
+    int pset;                    // floats per partial set (one per convolution)
+    float inv_W, inv_c, inv_TW, inv_dpf, inv_xpf;    // 1 / W, F * W, row pitch, window pixels per frame (dy; t, x, dt)
+};
+
+template <class G, class Fn>
+inline void rbw_shapes(int64_t n, int H, int W, int cus, size_t limit, Fn&& f) {
+    walk_bands(H, [&](int nb, int TH) {
+        const int ho = nb > 1;
+        for (int F = 1; F <= walk_frames(n, nb); ++F) {
+            const int db = walk_win_bytes(G::PX, F, TH + 2 + 2 * ho, W), xb = walk_win_bytes(G::PX, F, TH + 2, W);
+            const int kb = (F * TH * W * G::PX + 1023) / 1024 * 1024;
+            const size_t lds = size_t(db) + 2 * xb + std::max(xb + kb, G::MIN_TAIL);   // dy; t, x; dt, skip term
+            if (lds > limit || kb > G::MAXK * G::NW * 1024 || db > G::MAXD * G::NW * 1024 || xb > G::MAXX * G::NW * 1024) break;
+            RbwTile c{};
+            c.F = F; c.TH = TH; c.ho = ho; c.nbands = nb; c.ntiles = walk_tiles(n, F, nb);
+            c.t_off = db; c.x_off = db + xb; c.dt_off = db + 2 * xb; c.sk_off = c.dt_off + xb; c.dt_bytes = xb;
+            c.pset = std::min(cus, c.ntiles) * G::PSTRIDE;
+            c.inv_W = 1.f / float(W); c.inv_c = 1.f / float(F * W); c.inv_TW = 1.f / float(walk_pitch(W));
+            c.inv_dpf = 1.f / float((TH + 2 + 2 * ho) * walk_pitch(W)); c.inv_xpf = 1.f / float((TH + 2) * walk_pitch(W));
+            const double mx = double(F) * W * G::PX * (TH + 2 * ho) / 8 + 1500, md = double(F) * W * G::PX * (2 * TH + 6 * ho) / 8 + 1500;
+            for (c.R = 1; c.R <= std::min(TH, G::MAXR); ++c.R) {
+                const double wt = G::MC * walk_rows(TH + 2 * ho, F * W, 16, G::NS, c.R, c.nsegt);
+                const double wx = G::MC * walk_rows(TH, F * W, 16, G::NS, c.R, c.nsegx);
+                const double ww = G::MW * walk_rows(TH, F * W, G::GW, G::WW, c.R, c.nsegw);
+                f(c, std::max(lds, G::MIN_LDS),
+                  double((c.ntiles + cus - 1) / cus) * (std::max(20 * (wt + ww), mx) + std::max(20 * (wx + ww), md) + 800));
+            }
+        }
+    });
+}
+
+// ---------------------------------------------------------------- 64-channel conv backward
+struct Cw64Geom {
+    static constexpr int C = 64, NW = 8, NT = 512, NS = 4, MAXR = 7;   // NS: waves per role
+    static constexpr int NBB = 37, PSTRIDE = 4 * NBB * 256;  // partial: [co block][tap x ci block, bias][co][ci]
+    static constexpr int MAXS = 10;                          // staging slots per lane and window
+    static constexpr size_t WBYTES = 72 * 1024;              // the weights' A fragments, before the windows
+};
+struct Cw64Tile {
+    int F, TH, nbands, ntiles;
+    int ho;                    // several bands per frame
+    int win;                   // window bytes; LDS: dy, x of buffer 0, then of buffer 1
+    int R, nsegd, nsegw;       // rows per walk (the kernel's R), segments of a column: dx, weight gradients
+    int parts;                 // workgroups
+    float inv_W, inv_c, inv_TW, inv_pf;   // 1 / W, F * W, row pitch, window pixels per frame
+};
+
+template <class Fn>
+inline void cw64_shapes(int64_t n, int H, int W, int cus, size_t limit, Fn&& f) {
+    using G = Cw64Geom;
+    walk_bands(H, [&](int nb, int TH) {
+        const int ho = nb > 1;
+        for (int F = 1; F <= walk_frames(n, nb); ++F) {
+            Cw64Tile c{};
+            c.win = walk_win_bytes(128, F, TH + 2, W);
+            if (4 * size_t(c.win) > limit || c.win > G::MAXS * G::NS * 1024) break;
+            c.F = F; c.TH = TH; c.ho = ho; c.nbands = nb; c.ntiles = walk_tiles(n, F, nb);
+            c.parts = std::min(cus, c.ntiles);
+            c.inv_W = 1.f / float(W); c.inv_c = 1.f / float(F * W); c.inv_TW = 1.f / float(walk_pitch(W));
+            c.inv_pf = 1.f / float((TH + 2) * walk_pitch(W));
+            const double mem = double(F) * W * 128 * (3 * TH + 4) / 8;
+            for (c.R = 1; c.R <= std::min(TH, G::MAXR); ++c.R) {
+                const double work = 36 * walk_rows(TH, F * W, 16, 2, c.R, c.nsegd) + 38 * walk_rows(TH, F * W, 32, 1, c.R, c.nsegw);
+                f(c, std::max(4 * size_t(c.win), G::WBYTES), double((c.ntiles + cus - 1) / cus) * (std::max(18 * work, mem) + 1500));
+            }
+        }
+    });
+}
+
+// The cheapest of the shapes that `shapes` offers; false where none fits.
+template <class Tile, class Shapes>
+inline bool walk_choose(Shapes&& shapes, Tile& t, size_t& lds) {
+    double best = 1e30;
+    shapes([&](const Tile& c, size_t bytes, double cost) {
+        if (cost < best) { best = cost; t = c; lds = bytes; }
+    });
+    return best < 1e30;
+}
+
+}  // namespace cb

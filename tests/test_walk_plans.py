@@ -1,0 +1,61 @@
+"""The tile shapes of the column-walk kernels, as walkplan.h chooses them from a problem's size: that
+header is plain C++, compiled here with the host's compiler. Kinds: f32 the 32-channel block forward,
+b32 / b16 the block backward, c64 the 64-channel conv backward."""
+from __future__ import annotations
+
+import ctypes as C
+import os
+import random
+import shutil
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CUS = 256
+KINDS = {"f32": (7, 80), "b32": (7, 160), "b16": (8, 160), "c64": (7, 160)}   # most rows per walk, KB of LDS
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    cxx = os.environ.get("CXX") or shutil.which("g++") or shutil.which("clang++")
+    if cxx is None:
+        pytest.skip("no host C++ compiler")
+    so = str(tmp_path_factory.mktemp("walkplan") / "walkplan.so")
+    subprocess.run([cxx, "-O1", "-std=c++17", "-Wall", "-Werror", "-shared", "-fPIC", "-o", so,
+                    os.path.join(HERE, "walkplan_driver.cpp")], check=True)
+    fn = C.CDLL(so).walk_plan
+    fn.argtypes = [C.c_char_p, C.c_int64, C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int64)]
+
+    def choose(kind, n, H, W):
+        out = (C.c_int64 * 6)()
+        if not fn(kind.encode(), n, H, W, CUS, out):
+            return None
+        return dict(zip(("F", "TH", "bands", "tiles", "R", "lds"), out))
+
+    return choose
+
+
+@pytest.mark.parametrize("kind", KINDS)
+def test_a_shape_covers_the_frames_and_fits(plan, kind):
+    """Bands cover a frame, several of them hold one frame each, walks are no longer than a band, and
+    the windows fit; every width that a network's stage can have is taken."""
+    rng = random.Random(3)
+    max_rows, kb = KINDS[kind]
+    for _ in range(1500):
+        n, H, W = round(8192 ** rng.random()), rng.randint(1, 64), rng.randint(1, 64)
+        p = plan(kind, n, H, W)
+        assert p is not None, (n, H, W)
+        assert p["bands"] * p["TH"] >= H and (p["bands"] - 1) * p["TH"] < H, (n, H, W, p)
+        assert 1 <= p["F"] <= max(1, n) and (p["F"] == 1 or p["bands"] == 1), (n, H, W, p)
+        assert p["tiles"] == -(-n // p["F"]) * p["bands"], (n, H, W, p)
+        assert 1 <= p["R"] <= min(p["TH"], max_rows), (n, H, W, p)
+        assert 0 < p["lds"] <= kb * 1024, (n, H, W, p)
+
+
+@pytest.mark.parametrize("n,H,W,rows", [(2048, 21, 21, 5), (8192, 21, 21, 5), (640, 21, 21, 2), (2048, 11, 11, 2),
+                                        (8192, 42, 42, 2), (2048, 30, 45, 2), (128, 21, 21, 2)])
+def test_the_block_forward_walks_several_rows(plan, n, H, W, rows):
+    """A walk of one row reuses no input fragment: wherever the launch has rows to walk, R is above 1
+    (2048 frames of 21x21: 38 us at R = 7, 47 at R = 1)."""
+    assert plan("f32", n, H, W)["R"] >= rows
