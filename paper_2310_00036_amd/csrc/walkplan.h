@@ -165,6 +165,11 @@ struct Cw64Tile {
     float inv_W, inv_c, inv_TW, inv_pf;   // 1 / W, F * W, row pitch, window pixels per frame
 };
 
+// Every tile shape that fits, f(tile, lds, cost). The cost in microseconds, fitted like the forward's
+// over 90 problem sizes: each workgroup leaves 152 KB of partial sums to be added (0.29 us a MB), a
+// tile takes 0.55 us per row walked and 0.019 per KB of traffic. Without the partials' term, launches
+// of few frames were split into one- and two-row bands over all CUs: 40 frames of 11x11 28.9 us in 240
+// workgroups, 18.6 in 40; 8 of 24x24 27.9 against 19.2.
 template <class Fn>
 inline void cw64_shapes(int64_t n, int H, int W, int cus, size_t limit, Fn&& f) {
     using G = Cw64Geom;
@@ -178,10 +183,12 @@ inline void cw64_shapes(int64_t n, int H, int W, int cus, size_t limit, Fn&& f) 
             c.parts = std::min(cus, c.ntiles);
             c.inv_W = 1.f / float(W); c.inv_c = 1.f / float(F * W); c.inv_TW = 1.f / float(walk_pitch(W));
             c.inv_pf = 1.f / float((TH + 2) * walk_pitch(W));
-            const double mem = double(F) * W * 128 * (3 * TH + 4) / 8;
+            const double kb = double(F) * W * 128 * (4 * TH + 4 * ho) / 1000, partials = double(c.parts) * G::PSTRIDE * 4 / 1e6;
+            const double rounds = (c.ntiles + cus - 1) / cus;
             for (c.R = 1; c.R <= std::min(TH, G::MAXR); ++c.R) {
-                const double work = 36 * walk_rows(TH, F * W, 16, 2, c.R, c.nsegd) + 38 * walk_rows(TH, F * W, 32, 1, c.R, c.nsegw);
-                f(c, std::max(4 * size_t(c.win), G::WBYTES), double((c.ntiles + cus - 1) / cus) * (std::max(18 * work, mem) + 1500));
+                const double rows = walk_rows(TH, F * W, 16, 2, c.R, c.nsegd);
+                walk_rows(TH, F * W, 32, 1, c.R, c.nsegw);   // (in step with dx's: one wave, twice the anchors)
+                f(c, std::max(4 * size_t(c.win), G::WBYTES), 0.294 * partials + rounds * (0.550 * rows + 0.0185 * kb + 0.11));
             }
         }
     });

@@ -59,3 +59,11 @@ def test_the_block_forward_walks_several_rows(plan, n, H, W, rows):
     """A walk of one row reuses no input fragment: wherever the launch has rows to walk, R is above 1
     (2048 frames of 21x21: 38 us at R = 7, 47 at R = 1)."""
     assert plan("f32", n, H, W)["R"] >= rows
+
+
+@pytest.mark.parametrize("n,H,W,most", [(40, 11, 11, 80), (56, 10, 10, 112), (8, 24, 24, 64), (8, 21, 21, 64), (5, 11, 11, 32)])
+def test_few_frames_leave_few_partials(plan, n, H, W, most):
+    """Each workgroup of the 64-channel conv backward leaves 152 KB of partial sums: a launch on few
+    frames is not cut into single rows to reach every CU (40 frames of 11x11: 19 us in 40 workgroups, 29 in
+    240)."""
+    assert plan("c64", n, H, W)["tiles"] <= most
