@@ -81,12 +81,12 @@ inline void rw_shapes(int64_t n, int H, int W, int cus, Fn&& f) {
             c.F = F; c.TH = TH; c.ho = ho; c.nbands = nb; c.ntiles = walk_tiles(n, F, nb); c.t_off = xb;
             c.inv_W = 1.f / float(W); c.inv_c = 1.f / float(F * W);
             c.inv_TW = 1.f / float(walk_pitch(W)); c.inv_xpf = 1.f / float((TH + 2 + 2 * ho) * walk_pitch(W));
-            const double kb = double(F) * W * 64 * (3 * TH + 4 * ho) / 1000;
+            const double traffic = double(F) * W * 64 * (3 * TH + 4 * ho) / 1000;
             const int full = c.ntiles / (2 * cus), rest = c.ntiles - full * 2 * cus;
             const double rounds = full + (rest > cus ? 1.0 : rest > 0 ? 0.6 : 0.0);
             for (c.R = 1; c.R <= std::min(TH, G::MAXR); ++c.R) {
                 const double rows = walk_rows(TH + 2 * ho, F * W, 16, G::NW, c.R, c.nseg1) + walk_rows(TH, F * W, 16, G::NW, c.R, c.nseg2);
-                f(c, size_t(xb) + tb, rounds * (0.244 * rows + 0.0546 * kb + 0.37));
+                f(c, size_t(xb) + tb, rounds * (0.244 * rows + 0.0546 * traffic + 0.37));
             }
         }
     });
@@ -100,8 +100,10 @@ struct RbwGeom {
     static constexpr int WFRAG = 2 * 9 * 1024;               // one convolution's A fragments (bytes)
     static constexpr int MIN_TAIL = 2 * WFRAG;               // the dt window's memory holds the weights at first
     static constexpr size_t MIN_LDS = 0;
-    static constexpr int MC = 18, MW = 20;                   // MFMAs per row and group: a convolution, a weight gradient
     static constexpr int GW = 64, WW = 1;                    // anchors per weight-gradient group, waves sharing the groups
+    // microseconds: a launch; a MB of partial sums; a row walked by a convolution's and by a weight
+    // gradient's wave; a KB of a tile's traffic; a tile
+    static constexpr double US = 9.3, US_PARTIAL = 0.368, US_CONV = 0.060, US_WGRAD = 0.285, US_KB = 0.0183, US_TILE = 0.68;
 };
 struct Rbw16Geom {
     static constexpr int C = 16, NW = 8, NT = 512, NS = 4, PX = 32, MAXR = 8;
@@ -109,8 +111,8 @@ struct Rbw16Geom {
     static constexpr int MAXD = 6, MAXX = 6, MAXK = 5;
     static constexpr int MIN_TAIL = 0;
     static constexpr size_t MIN_LDS = 4 * 20 * 1024;         // the four waves' sums, at the end
-    static constexpr int MC = 10, MW = 16;
     static constexpr int GW = 32, WW = 4;
+    static constexpr double US = 9.4, US_PARTIAL = 0.653, US_CONV = 0.104, US_WGRAD = 0.0245, US_KB = 0.0199, US_TILE = 0.81;
 };
 
 struct RbwTile {
@@ -122,6 +124,12 @@ struct RbwTile {
     float inv_W, inv_c, inv_TW, inv_dpf, inv_xpf;    // 1 / W, F * W, row pitch, window pixels per frame (dy; t, x, dt)
 };
 
+// Every tile shape that fits, f(tile, lds, cost). The cost is the launch with its reduce in
+// microseconds, fitted like the forward's over 130 problem sizes for 32 channels and 260 for 16 (the
+// estimates of the shapes chosen are within 6% and 4%, the shapes chosen within 1% of the best on
+// average). Counting the longer of work and traffic in each phase, and no partial sums, cut launches of
+// few frames into one-row bands: 40 frames of 21x21 with 32 channels 23 against 18 us, 128 of 11x11 24
+// against 18; and took too tall bands for many: 2048 of 84x84 with 16 channels 658 against 617.
 template <class G, class Fn>
 inline void rbw_shapes(int64_t n, int H, int W, int cus, size_t limit, Fn&& f) {
     walk_bands(H, [&](int nb, int TH) {
@@ -137,13 +145,13 @@ inline void rbw_shapes(int64_t n, int H, int W, int cus, size_t limit, Fn&& f) {
             c.pset = std::min(cus, c.ntiles) * G::PSTRIDE;
             c.inv_W = 1.f / float(W); c.inv_c = 1.f / float(F * W); c.inv_TW = 1.f / float(walk_pitch(W));
             c.inv_dpf = 1.f / float((TH + 2 + 2 * ho) * walk_pitch(W)); c.inv_xpf = 1.f / float((TH + 2) * walk_pitch(W));
-            const double mx = double(F) * W * G::PX * (TH + 2 * ho) / 8 + 1500, md = double(F) * W * G::PX * (2 * TH + 6 * ho) / 8 + 1500;
+            const double traffic = double(F) * W * G::PX * (5 * TH + 8 * ho) / 1000, partials = 2.0 * c.pset * 4 / 1e6;
+            const double rounds = (c.ntiles + cus - 1) / cus;
             for (c.R = 1; c.R <= std::min(TH, G::MAXR); ++c.R) {
-                const double wt = G::MC * walk_rows(TH + 2 * ho, F * W, 16, G::NS, c.R, c.nsegt);
-                const double wx = G::MC * walk_rows(TH, F * W, 16, G::NS, c.R, c.nsegx);
-                const double ww = G::MW * walk_rows(TH, F * W, G::GW, G::WW, c.R, c.nsegw);
+                const double conv = walk_rows(TH + 2 * ho, F * W, 16, G::NS, c.R, c.nsegt) + walk_rows(TH, F * W, 16, G::NS, c.R, c.nsegx);
+                const double wgrad = 2 * walk_rows(TH, F * W, G::GW, G::WW, c.R, c.nsegw);
                 f(c, std::max(lds, G::MIN_LDS),
-                  double((c.ntiles + cus - 1) / cus) * (std::max(20 * (wt + ww), mx) + std::max(20 * (wx + ww), md) + 800));
+                  G::US + G::US_PARTIAL * partials + rounds * (G::US_CONV * conv + G::US_WGRAD * wgrad + G::US_KB * traffic + G::US_TILE));
             }
         }
     });
@@ -183,12 +191,12 @@ inline void cw64_shapes(int64_t n, int H, int W, int cus, size_t limit, Fn&& f) 
             c.parts = std::min(cus, c.ntiles);
             c.inv_W = 1.f / float(W); c.inv_c = 1.f / float(F * W); c.inv_TW = 1.f / float(walk_pitch(W));
             c.inv_pf = 1.f / float((TH + 2) * walk_pitch(W));
-            const double kb = double(F) * W * 128 * (4 * TH + 4 * ho) / 1000, partials = double(c.parts) * G::PSTRIDE * 4 / 1e6;
+            const double traffic = double(F) * W * 128 * (4 * TH + 4 * ho) / 1000, partials = double(c.parts) * G::PSTRIDE * 4 / 1e6;
             const double rounds = (c.ntiles + cus - 1) / cus;
             for (c.R = 1; c.R <= std::min(TH, G::MAXR); ++c.R) {
                 const double rows = walk_rows(TH, F * W, 16, 2, c.R, c.nsegd);
                 walk_rows(TH, F * W, 32, 1, c.R, c.nsegw);   // (in step with dx's: one wave, twice the anchors)
-                f(c, std::max(4 * size_t(c.win), G::WBYTES), 0.294 * partials + rounds * (0.550 * rows + 0.0185 * kb + 0.11));
+                f(c, std::max(4 * size_t(c.win), G::WBYTES), 0.294 * partials + rounds * (0.550 * rows + 0.0185 * traffic + 0.11));
             }
         }
     });

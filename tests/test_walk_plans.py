@@ -67,3 +67,10 @@ def test_few_frames_leave_few_partials(plan, n, H, W, most):
     frames is not cut into single rows to reach every CU (40 frames of 11x11: 19 us in 40 workgroups, 29 in
     240)."""
     assert plan("c64", n, H, W)["tiles"] <= most
+
+
+@pytest.mark.parametrize("kind,n,H,W,most", [("b32", 40, 21, 21, 120), ("b32", 128, 11, 11, 128), ("b32", 40, 8, 12, 40),
+                                             ("b16", 40, 11, 11, 80), ("b16", 40, 16, 16, 80)])
+def test_block_backwards_on_few_frames_are_not_cut_into_single_rows(plan, kind, n, H, W, most):
+    """128 frames of 11x11 with 32 channels: 18 us in 64 or 128 workgroups, 24 in 256."""
+    assert plan(kind, n, H, W)["tiles"] <= most
