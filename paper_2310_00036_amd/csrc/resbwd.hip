@@ -539,6 +539,266 @@ __global__ __launch_bounds__(Rbw16Geom::NT, 2) void resblock_bwd16_walk_kernel(R
     }
 }
 
+// The 16-channel block backward tile by tile, two workgroups per CU: a tile is a band of TH rows of one
+// frame, staged whole (dy on rows h0-2 .. h0+TH+1, t and x on rows h0-1 .. h0+TH), and all waves take
+// each phase's 16-pixel column tiles in turn. It reads every fragment once per tap, waits for its
+// loads and meets four barriers per tile, all of which the other workgroup overlaps, but its work
+// falls evenly on the waves whatever the width, where the walks pay for whole groups of 16 columns and
+// whole segments of rows. Walks against tiles, in turn on one card: 2048 frames of 42x42 144 against 155
+// us, 8192 of 21x21 134 against 152; but 8192 of 30x45 469 against 411, 32x32 347 against 320, 48x40 614
+// against 569, 2048 of 84x84 658 against 593. walkplan.h estimates both and takes the shorter.
+__global__ __launch_bounds__(RbtGeom::NT, 4) void resblock_bwd16_tile_kernel(ResBwdArgs a, RbtTile t) {
+    using G = RbtGeom;
+    constexpr int C = G::C, NW = G::NW, NT = G::NT, PX = G::PX, NB = G::NBB - 1;
+    constexpr int KSD = 5;                       // input-gradient k-steps of two taps
+    // weight gradients: waves 0 .. 3 form conv_b's, the others conv_a's, each wave TPW column
+    // blocks (a tap, or the bias), so each dy / dt fragment is read by half the waves
+    constexpr int NWG = NW / 2, TPW = (G::NBB + NWG - 1) / NWG;
+
+    extern __shared__ __align__(16) unsigned char smem[];
+    unsigned char* zero = smem;                   // 64 zero bytes
+    unsigned char* dyw = smem + t.dy_off;         // dy [TH+4][W+2], row 0 = image row h0-2
+    unsigned char* tw = smem + t.t_off + PX;      // relu(t) [TH+2][W+2], row 0 = h0-1, guard pixels
+    unsigned char* xw = smem + t.x_off + PX;      // relu(x) [TH+2][W+2], likewise
+    unsigned char* dtw = smem + t.dt_off;         // dt [TH+2][W+2], row 0 = h0-1
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int g = lane >> 4, r16 = lane & 15, jj = r16 >> 2, m = r16 & 3;
+    const int H = a.H, W = a.W, TH = t.TH, TW = W + 2;
+
+    // earlier launches' weight-gradient partials, summed first (LDS is free until staging)
+    if (a.pend.nparts > 0) pending_reduce<NT>(a.pend, smem);
+    if (a.pend2.nparts > 0) pending_reduce<NT>(a.pend2, smem);
+    if (tid < 16) reinterpret_cast<uint32_t*>(zero)[tid] = 0u;
+    // the dt window: its padding columns are never written
+    for (int j = tid; j < t.dt_bytes / 16; j += NT) reinterpret_cast<uint4*>(dtw)[j] = make_uint4(0, 0, 0, 0);
+    // the t and x windows' guard pixels (read only against zero dy / dt, never staged)
+    if (tid < PX / 4) {
+        reinterpret_cast<uint32_t*>(tw - PX)[tid] = 0u;
+        reinterpret_cast<uint32_t*>(tw + t.tx_guard)[tid] = 0u;
+        reinterpret_cast<uint32_t*>(xw - PX)[tid] = 0u;
+        reinterpret_cast<uint32_t*>(xw + t.tx_guard)[tid] = 0u;
+    }
+
+    // ---- input-gradient A fragments of both convs: A[o][k] = w[8 - tap][o][co] with k = tap * 16 + co
+    // (zero past the 9 taps; loads clamped)
+    const int ci0 = g * 4;   // the lane's first output channel
+    uint4 wfa[KSD], wfb[KSD];
+    auto load_w = [&](const float* w, uint4 (&wf)[KSD]) CB_INLINE_LAMBDA {
+#pragma unroll
+        for (int ks = 0; ks < KSD; ++ks) {
+            const int tap = 2 * ks + (g >> 1);
+            const float* p = w + ((tap < 9 ? 8 - tap : 0) * C + r16) * C + (g & 1) * 8;
+            const float4 u = load_f4(p), v = load_f4(p + 4);
+            wf[ks] = make_uint4(pack2bf(u.x, u.y), pack2bf(u.z, u.w), pack2bf(v.x, v.y), pack2bf(v.z, v.w));
+            if (tap >= 9) wf[ks] = make_uint4(0, 0, 0, 0);
+        }
+    };
+    load_w(a.wa, wfa);
+    load_w(a.wb, wfb);
+    // B-fragment byte offsets from the lane's tap-(0,0) pixel of a dy-like window: a k-step spans
+    // two taps; past the ninth the lanes re-read tap 8 against zero weights
+    int dboff[KSD];
+#pragma unroll
+    for (int ks = 0; ks < KSD; ++ks) {
+        const int tap = 2 * ks + (g >> 1), tp = tap < 9 ? tap : 8;
+        dboff[ks] = ((tp / 3) * TW + tp % 3) * PX + (g & 1) * 16;
+    }
+    // weight-gradient column blocks nb = wg + NWG * i (one tap, or the bias block) of conv_b
+    // (grp 0) or conv_a (grp 1)
+    const int wg = wave % NWG, grp = wave / NWG;
+    int wboff[TPW];
+#pragma unroll
+    for (int i = 0; i < TPW; ++i) {
+        const int nb = wg + NWG * i;
+        wboff[i] = nb < NB ? ((nb / 3) * TW + nb % 3) * PX + 8 * m : 0;
+    }
+    cb_f32x4 wacc[TPW];
+#pragma unroll
+    for (int i = 0; i < TPW; ++i) wacc[i] = cb_f32x4{0.f, 0.f, 0.f, 0.f};
+    const uint4 ones = make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u);
+
+    // ---- staging offsets, tile-invariant per lane (slot k of this wave: j = (wave + NW*k)*64
+    // + lane: pixel j / 2, half j % 2), relative to the window's first row at image row 0; a tile
+    // adds that row's image row. Rows off the frame fall outside the frame's buffer resource and
+    // read zero, as do padding columns (kOOB).
+    const int nsd = (TH + 4) * TW * 2, nsx = (TH + 2) * TW * 2;
+    auto win_off = [&](int j, int ns) CB_INLINE_LAMBDA {
+        const int p = j >> 1, rr = qdiv(p, t.inv_TW), col = p - rr * TW;
+        const uint32_t off = uint32_t(((rr * W + col - 1) * C + (j & 1) * 8) * 2);
+        return (j < ns) & (uint32_t(col - 1) < uint32_t(W)) ? off : kOOB;
+    };
+    uint32_t od[G::MAXS], ox[G::MAXS];
+#pragma unroll
+    for (int k = 0; k < G::MAXS; ++k) {
+        od[k] = win_off((wave + NW * k) * 64 + lane, nsd);
+        ox[k] = win_off((wave + NW * k) * 64 + lane, nsx);
+    }
+
+    // ---- one weight gradient over the band's own rows: dy-like window dwin (own row 0 at
+    // window row drow0) against the relu'd window bwin (row 0 = image row h0-1): pixel idx of
+    // the own rows pairs with bwin pixel idx - 1 + tap offset. Lane (g, 4jj+m) takes pixels
+    // o = 16*half + 4g + jj (channels 4m ..).
+    auto wgrad = [&](const unsigned char* dwin, int drow0, const unsigned char* bwin, const unsigned char* bguard, int L) {
+        // specialised per wave, so that each column block's kind (loaded or bias) is known at
+        // compile time and the k-step loop carries no branches
+        auto run = [&](auto wv) {
+            constexpr int WG = decltype(wv)::value;
+            const int nfull = L >> 5, o0 = 4 * g + jj;
+            const unsigned char* ap = dwin + (drow0 * TW + o0) * PX + 8 * m;
+            const unsigned char* bp = bwin + (o0 - 1) * PX;
+            auto kstep = [&](const unsigned char* a0, const unsigned char* a1, const unsigned char* b0, const unsigned char* b1) {
+                const uint2 alo = lds_read_tr16(a0), ahi = lds_read_tr16(a1);   // a0, a1: zero past L
+                const uint4 af = make_uint4(alo.x, alo.y, ahi.x, ahi.y);
+#pragma unroll
+                for (int i = 0; i < TPW; ++i) {
+                    const int nb = WG + NWG * i;
+                    if (nb < NB) {
+                        const uint2 lo = lds_read_tr16(b0 + wboff[i]), hi = lds_read_tr16(b1 + wboff[i]);
+                        wacc[i] = PrecBF16::mma(af, make_uint4(lo.x, lo.y, hi.x, hi.y), wacc[i]);
+                    } else if (nb == NB) {   // the bias block: a column of ones
+                        wacc[i] = PrecBF16::mma(af, ones, wacc[i]);
+                    }
+                }
+            };
+            int ks = 0;
+            for (; ks + 2 <= nfull; ks += 2) {   // two k-steps per trip: half the pointer updates
+                kstep(ap, ap + 16 * PX, bp, bp + 16 * PX);
+                kstep(ap + 32 * PX, ap + 48 * PX, bp + 32 * PX, bp + 48 * PX);
+                ap += 64 * PX;
+                bp += 64 * PX;
+            }
+            if (ks < nfull) {
+                kstep(ap, ap + 16 * PX, bp, bp + 16 * PX);
+                ap += 32 * PX;
+                bp += 32 * PX;
+            }
+            if (L & 31) {   // the last, partial k-step
+                const int o = nfull * 32 + o0;
+                const bool ok0 = o < L, ok1 = o + 16 < L;
+                kstep(ok0 ? ap : zero, ok1 ? ap + 16 * PX : zero, ok0 ? bp : bguard, ok1 ? bp + 16 * PX : bguard);
+            }
+        };
+        static_assert(NWG == 4, "one specialisation per wave of a group");
+        switch (wg) {
+            case 0: run(std::integral_constant<int, 0>{}); break;
+            case 1: run(std::integral_constant<int, 1>{}); break;
+            case 2: run(std::integral_constant<int, 2>{}); break;
+            default: run(std::integral_constant<int, 3>{}); break;
+        }
+    };
+
+    int lg = blockIdx.x;   // neighbouring bands (which share halo rows) on one XCD
+    if ((gridDim.x & 7) == 0) lg = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+
+    for (int tile = lg; tile < t.ntiles; tile += gridDim.x) {
+        const int band = tile % t.nbands, f = tile / t.nbands;
+        const int h0 = band * TH, the = H - h0 < TH ? H - h0 : TH;
+        const int64_t fo = int64_t(f) * H * W * C;   // the frame's first element
+        __syncthreads();   // the previous tile's LDS reads are done
+
+        // ---- stage dy (rows h0-2 ..), t and x (rows h0-1 ..)
+        {
+            const uint32_t fb = uint32_t(H) * W * C * 2;
+            const auto rd = buf_rsrc(static_cast<const uint16_t*>(a.dy) + fo, fb);
+            const auto rt = buf_rsrc(static_cast<const uint16_t*>(a.t) + fo, fb);
+            const auto rx = buf_rsrc(static_cast<const uint16_t*>(a.x) + fo, fb);
+            const uint32_t hd = uint32_t((h0 - 2) * W * C * 2);   // wraps above the frame: reads zero
+            const uint32_t hx = uint32_t((h0 - 1) * W * C * 2);
+#pragma unroll
+            for (int k = 0; k < G::MAXS; ++k)
+                if ((wave + NW * k) * 64 < nsd) dma16_to_lds(rd, dyw + (wave + NW * k) * 1024, od[k] + hd);
+#pragma unroll
+            for (int k = 0; k < G::MAXS; ++k)
+                if ((wave + NW * k) * 64 < nsx) {
+                    dma16_to_lds(rt, tw + (wave + NW * k) * 1024, ox[k] + hx);
+                    dma16_to_lds(rx, xw + (wave + NW * k) * 1024, ox[k] + hx);
+                }
+        }
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        {
+            // both convs read relu'd inputs; relu(v) > 0 exactly where v > 0, so the masks
+            // read the same windows
+            uint4* t4 = reinterpret_cast<uint4*>(tw);
+            uint4* x4 = reinterpret_cast<uint4*>(xw);
+            for (int j = tid; j < nsx; j += NT) {
+                const uint4 u = t4[j], v = x4[j];
+                t4[j] = relu8(u);
+                x4[j] = relu8(v);
+            }
+        }
+        __syncthreads();
+
+        // ---- conv_b's input gradient dt on window rows r = 0 .. the+1 (image rows h0-1+r;
+        // zero off the frame), 16-pixel column tiles, into the dt window
+        {
+            const int npx = (the + 2) * W;
+            for (int nt = wave; nt * 16 < npx; nt += NW) {
+                const int q = nt * 16 + r16;
+                const int qc = q < npx ? q : npx - 1;   // past npx: computed, not stored
+                const int row = qdiv(qc, t.inv_W), col = qc - row * W;
+                const unsigned char* xb = dyw + (row * TW + col) * PX;
+                cb_f32x4 acc = cb_f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int ks = 0; ks < KSD; ++ks) acc = PrecBF16::mma(wfb[ks], *reinterpret_cast<const uint4*>(xb + dboff[ks]), acc);
+                if (q < npx) {
+                    const int h = h0 - 1 + row;
+                    uint2 o = make_uint2(0u, 0u);
+                    if (h >= 0 && h < H) {
+                        float mk[4];
+                        load4(reinterpret_cast<const uint16_t*>(tw + (row * TW + col + 1) * PX + ci0 * 2), mk);
+                        o = make_uint2(pack2bf(mk[0] > 0.f ? acc[0] : 0.f, mk[1] > 0.f ? acc[1] : 0.f),
+                                       pack2bf(mk[2] > 0.f ? acc[2] : 0.f, mk[3] > 0.f ? acc[3] : 0.f));
+                    }
+                    *reinterpret_cast<uint2*>(dtw + (row * TW + col + 1) * PX + ci0 * 2) = o;
+                }
+            }
+        }
+        __syncthreads();   // the dt window is complete
+
+        // ---- dx = conv_a^T(dt) * [x > 0] + dy on the band's rows
+        {
+            const int npx = the * W;
+            uint16_t* dxt = static_cast<uint16_t*>(a.dx) + fo + int64_t(h0) * W * C;
+            for (int nt = wave; nt * 16 < npx; nt += NW) {
+                const int q = nt * 16 + r16;
+                const int qc = q < npx ? q : npx - 1;
+                const int row = qdiv(qc, t.inv_W), col = qc - row * W;
+                const unsigned char* xb = dtw + (row * TW + col) * PX;
+                cb_f32x4 acc = cb_f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int ks = 0; ks < KSD; ++ks) acc = PrecBF16::mma(wfa[ks], *reinterpret_cast<const uint4*>(xb + dboff[ks]), acc);
+                if (q < npx) {
+                    float mk[4], sk[4];
+                    load4(reinterpret_cast<const uint16_t*>(xw + ((row + 1) * TW + col + 1) * PX + ci0 * 2), mk);
+                    load4(reinterpret_cast<const uint16_t*>(dyw + ((row + 2) * TW + col + 1) * PX + ci0 * 2), sk);
+                    float v[4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) v[j] = (mk[j] > 0.f ? acc[j] : 0.f) + sk[j];
+                    store4(dxt + uint32_t(q * C + ci0), v[0], v[1], v[2], v[3]);
+                }
+            }
+        }
+        // ---- the weight gradients: conv_b's, dy (own rows from dy-window row 2) against
+        // relu(t), by the first half of the waves; conv_a's, dt (own rows from dt-window row
+        // 1) against relu(x), by the second
+        if (grp == 0) wgrad(dyw, 2, tw, tw - PX, the * TW);
+        else wgrad(dtw, 1, xw, xw - PX, the * TW);
+    }
+
+    // ---- this workgroup's partials: conv_b's set, then conv_a's, each [nb][co 16][ci 16]
+    float* part = a.partial + (grp == 0 ? 0 : t.pset) + int64_t(blockIdx.x) * G::PSTRIDE;
+#pragma unroll
+    for (int i = 0; i < TPW; ++i) {
+        const int nb = wg + NWG * i;
+        if (nb < G::NBB)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) part[nb * 256 + (4 * g + e) * 16 + r16] = wacc[i][e];
+    }
+}
+
 namespace {
 
 // Scratch: both partial sets. The kernels use one partial per CU at most (256).
@@ -550,9 +810,13 @@ constexpr size_t rbw_partial_floats() {
     return 2 * (cap < 256 ? 256 : (cap > 1024 ? 1024 : cap)) * size_t(G::PSTRIDE);
 }
 
-// Launches kernel(std::integral_constant<int, R>) on the tile shape that walkplan.h chooses.
-template <class G, class Launch>
-hipError_t rbw_launch(const ResBwdArgs& a, hipStream_t s, PendingReduce out[2], Launch&& launch) {
+void rbw_pending(const ResBwdArgs& a, int C, int parts, int pstride, int pset, PendingReduce out[2]) {
+    out[0] = PendingReduce{a.partial, a.dwb, a.dbb, parts, pstride, C, C, 0, 1.f};
+    out[1] = PendingReduce{a.partial + pset, a.dwa, a.dba, parts, pstride, C, C, 0, 1.f};
+}
+
+hipError_t rb32_launch(const ResBwdArgs& a, hipStream_t s, PendingReduce out[2]) {
+    using G = RbwGeom;
     const int H = a.H, W = a.W, cus = std::min(device_cus(), 256);
     if (int64_t(H) * W * G::C * 2 >= (int64_t(1) << 31)) return hipErrorInvalidValue;
     static thread_local WalkPlans<RbwTile> plans;
@@ -567,10 +831,43 @@ hipError_t rbw_launch(const ResBwdArgs& a, hipStream_t s, PendingReduce out[2], 
     const int parts = plan->t.pset / G::PSTRIDE;
     walk_dispatch<G::MAXR>(plan->t.R, [&](auto r) {
         ProfScope ps(s, [&] { return cb_key("resblock_bwd", 0, cb_dims(G::C, G::C) + "/" + cb_dims(H, W)); });
-        launch(r, dim3(unsigned(parts)), dim3(G::NT), plan->lds, plan->t);
+        hipLaunchKernelGGL(resblock_bwd_walk_kernel<decltype(r)::value>, dim3(unsigned(parts)), dim3(G::NT), plan->lds, s, a, plan->t);
     });
-    out[0] = PendingReduce{a.partial, a.dwb, a.dbb, parts, G::PSTRIDE, G::C, G::C, 0, 1.f};
-    out[1] = PendingReduce{a.partial + plan->t.pset, a.dwa, a.dba, parts, G::PSTRIDE, G::C, G::C, 0, 1.f};
+    rbw_pending(a, G::C, parts, G::PSTRIDE, plan->t.pset, out);
+    return hipGetLastError();
+}
+
+hipError_t rb16_launch(const ResBwdArgs& a, hipStream_t s, PendingReduce out[2]) {
+    using G = Rbw16Geom;
+    const int H = a.H, W = a.W, cus = std::min(device_cus(), 256);
+    if (int64_t(H) * W * G::C * 2 >= (int64_t(1) << 31)) return hipErrorInvalidValue;
+    static thread_local WalkPlans<Rb16Plan> plans;
+    const auto* plan = plans.find(a.n, H, W, cus);
+    if (!plan) {
+        const size_t limit = std::min<size_t>(lds_limit(), 160 * 1024);
+        Rb16Plan p{};
+        size_t L = 0;
+        if (!rb16_choose(a.n, H, W, cus, limit, p, L)) return hipErrorInvalidValue;
+        if (p.tiles) {
+            const void* fn = reinterpret_cast<const void*>(&resblock_bwd16_tile_kernel);
+            const int room = int(resblock_bwd_partial_floats(G::C) / (2 * size_t(G::PSTRIDE)));
+            p.u.pset = std::min({std::max(1, resident_blocks(fn, RbtGeom::NT, L)), room, p.u.ntiles}) * G::PSTRIDE;
+        }
+        plan = plans.put({a.n, H, W, cus, p, L});
+    }
+    const Rb16Plan& p = plan->t;
+    const int pset = p.tiles ? p.u.pset : p.t.pset, parts = pset / G::PSTRIDE;
+    auto scope = [&] { return cb_key("resblock_bwd", 0, cb_dims(G::C, G::C) + "/" + cb_dims(H, W)); };
+    if (p.tiles) {
+        ProfScope ps(s, scope);
+        hipLaunchKernelGGL(resblock_bwd16_tile_kernel, dim3(unsigned(parts)), dim3(RbtGeom::NT), plan->lds, s, a, p.u);
+    } else {
+        walk_dispatch<G::MAXR>(p.t.R, [&](auto r) {
+            ProfScope ps(s, scope);
+            hipLaunchKernelGGL(resblock_bwd16_walk_kernel<decltype(r)::value>, dim3(unsigned(parts)), dim3(G::NT), plan->lds, s, a, p.t);
+        });
+    }
+    rbw_pending(a, G::C, parts, G::PSTRIDE, pset, out);
     return hipGetLastError();
 }
 
@@ -595,14 +892,8 @@ hipError_t resblock_bwd(int C, const ResBwdArgs& a, hipStream_t s, PendingReduce
     if (a.n <= 0) {
         return flush_pending_reduces(a.pend, a.pend2, s);
     }
-    if (C == 16)
-        return rbw_launch<Rbw16Geom>(a, s, out, [&](auto r, dim3 grid, dim3 block, size_t lds, const RbwTile& t) {
-            hipLaunchKernelGGL(resblock_bwd16_walk_kernel<decltype(r)::value>, grid, block, lds, s, a, t);
-        });
-    if (C == 32)
-        return rbw_launch<RbwGeom>(a, s, out, [&](auto r, dim3 grid, dim3 block, size_t lds, const RbwTile& t) {
-            hipLaunchKernelGGL(resblock_bwd_walk_kernel<decltype(r)::value>, grid, block, lds, s, a, t);
-        });
+    if (C == 16) return rb16_launch(a, s, out);
+    if (C == 32) return rb32_launch(a, s, out);
     return hipErrorInvalidValue;
 }
 

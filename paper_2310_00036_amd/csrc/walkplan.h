@@ -43,6 +43,17 @@ constexpr int kWalkMaxF = 16;    // frames per tile
 inline int walk_frames(int64_t n, int nb) { return nb > 1 ? 1 : int(std::min<int64_t>(n, kWalkMaxF)); }
 inline int walk_tiles(int64_t n, int F, int nb) { return int((n + F - 1) / F) * nb; }
 
+// The cheapest of the shapes that `shapes` offers; false where none fits.
+template <class Tile, class Shapes>
+inline bool walk_choose(Shapes&& shapes, Tile& t, size_t& lds, double* us = nullptr) {
+    double best = 1e30;
+    shapes([&](const Tile& c, size_t bytes, double cost) {
+        if (cost < best) { best = cost; t = c; lds = bytes; }
+    });
+    if (us) *us = best;
+    return best < 1e30;
+}
+
 // ---------------------------------------------------------------- 32-channel block forward
 struct RwGeom {
     static constexpr int C = 32, NW = 4, NT = 256, KS = 9, MAXR = 7;   // kernels exist for 1 .. MAXR rows per walk
@@ -157,6 +168,72 @@ inline void rbw_shapes(int64_t n, int H, int W, int cus, size_t limit, Fn&& f) {
     });
 }
 
+// ---------------------------------------------------------------- 16-channel block backward, tile by tile
+struct RbtGeom {
+    static constexpr int C = 16, NW = 8, NT = 512, PX = 32, NBB = Rbw16Geom::NBB, PSTRIDE = Rbw16Geom::PSTRIDE;
+    static constexpr int MAXS = 4;                           // staging slots per lane and window
+    static constexpr size_t LDS_TARGET = 80 * 1024;          // two workgroups per CU
+    static constexpr size_t MIN_LDS = NW * 4 * 17 * 16;      // earlier launches' reduces
+};
+struct RbtTile {
+    int TH, nbands, ntiles;
+    int dy_off, t_off, x_off, dt_off;   // LDS byte offsets; 64 zero bytes at offset 0
+    int tx_guard;                       // t / x windows: byte offset of the rear guard pixel
+    int dt_bytes;
+    int pset;                           // floats per partial set (the launcher's, from its grid)
+    float inv_W, inv_TW;
+};
+
+// The balanced bands of the fewest tiles that fit; false where none does (frames wider than 202). us:
+// the estimated time with its reduce, like the walks' (fitted over 170 problem sizes; two workgroups
+// per CU, a last round of one per CU counts 0.6).
+inline bool rbt_shape(int64_t n, int H, int W, int cus, size_t limit, RbtTile& t, size_t& lds, double& us) {
+    using G = RbtGeom;
+    const int TW = W + 2;
+    auto layout = [&](int th) {
+        const int dyb = ((th + 4) * TW * 2 + 63) / 64 * 1024;
+        const int txb = ((th + 2) * TW * 2 + 63) / 64 * 1024 + 2 * G::PX;   // + a guard pixel either side
+        t.dt_bytes = (th + 2) * TW * G::PX;
+        t.dy_off = 64; t.t_off = t.dy_off + dyb; t.x_off = t.t_off + txb; t.dt_off = t.x_off + txb;
+        t.tx_guard = txb - 2 * G::PX;
+        return size_t(t.dt_off) + t.dt_bytes;
+    };
+    auto fits = [&](int th) { return (th + 4) * TW * 2 <= G::MAXS * G::NT; };
+    int th = H;
+    while (th > 1 && (layout(th) > G::LDS_TARGET || !fits(th))) --th;
+    if (layout(th) > limit || !fits(th)) return false;
+    const int nb0 = (H + th - 1) / th;
+    t.TH = (H + nb0 - 1) / nb0;
+    t.nbands = (H + t.TH - 1) / t.TH;
+    t.ntiles = walk_tiles(n, 1, t.nbands);
+    t.inv_W = 1.f / float(W);
+    t.inv_TW = 1.f / float(TW);
+    lds = std::max(layout(t.TH), G::MIN_LDS);
+    const int full = t.ntiles / (2 * cus), rest = t.ntiles - full * 2 * cus;
+    const double rounds = full + (rest > cus ? 1.0 : rest > 0 ? 0.6 : 0.0);
+    auto groups = [&](int rows) { return ((rows * W + 15) / 16 + G::NW - 1) / G::NW; };
+    const double partials = 2.0 * std::min(2 * cus, t.ntiles) * G::PSTRIDE * 4 / 1e6;
+    const double wgrad = t.TH * TW / 32.0, traffic = double(W) * G::PX * (5 * t.TH + 8) / 1000;
+    us = 11.9 + 0.956 * partials + rounds * (0.112 * (groups(t.TH + 2) + groups(t.TH)) + 0.268 * wgrad + 0.0264 * traffic + 0.94);
+    return true;
+}
+
+// The 16-channel block backward's launch: whichever form's estimate is the shorter.
+struct Rb16Plan {
+    bool tiles;      // tile by tile (u), else column walks (t)
+    RbwTile t;
+    RbtTile u;
+};
+inline bool rb16_choose(int64_t n, int H, int W, int cus, size_t limit, Rb16Plan& p, size_t& lds) {
+    size_t walk_lds = 0, tile_lds = 0;
+    double walk_us = 0, tile_us = 0;
+    const bool walk = walk_choose([&](auto&& f) { rbw_shapes<Rbw16Geom>(n, H, W, cus, limit, f); }, p.t, walk_lds, &walk_us);
+    const bool tile = rbt_shape(n, H, W, cus, limit, p.u, tile_lds, tile_us);
+    p.tiles = tile && (!walk || tile_us < walk_us);
+    lds = p.tiles ? tile_lds : walk_lds;
+    return walk || tile;
+}
+
 // ---------------------------------------------------------------- 64-channel conv backward
 struct Cw64Geom {
     static constexpr int C = 64, NW = 8, NT = 512, NS = 4, MAXR = 7;   // NS: waves per role
@@ -200,16 +277,6 @@ inline void cw64_shapes(int64_t n, int H, int W, int cus, size_t limit, Fn&& f) 
             }
         }
     });
-}
-
-// The cheapest of the shapes that `shapes` offers; false where none fits.
-template <class Tile, class Shapes>
-inline bool walk_choose(Shapes&& shapes, Tile& t, size_t& lds) {
-    double best = 1e30;
-    shapes([&](const Tile& c, size_t bytes, double cost) {
-        if (cost < best) { best = cost; t = c; lds = bytes; }
-    });
-    return best < 1e30;
 }
 
 }  // namespace cb

@@ -15,6 +15,9 @@ torch = pytest.importorskip("torch")
 SHAPES = [(1, 1, 1), (2, 2, 5), (7, 3, 3), (33, 4, 7), (5, 11, 11), (17, 11, 11), (700, 11, 11), (33, 21, 21),
           (3, 21, 22), (9, 8, 15), (2, 42, 42), (515, 42, 42), (1, 43, 39), (600, 5, 7), (3, 64, 64), (1, 7, 97)]
 
+# 16 channels, taken tile by tile: whole bands and a ragged last one, whole frames, odd widths
+TILES16 = [(515, 9, 97), (900, 11, 82), (200, 43, 103), (900, 29, 34), (4096, 9, 49), (4096, 21, 22), (3001, 38, 33)]
+
 
 def _p():
     import paper_2310_00036_amd as P
@@ -54,9 +57,9 @@ def test_resblock32_forward_equals_two_convolutions(case, offset):
     assert torch.equal(_bits(y), _bits(y_ref))
 
 
-@pytest.mark.parametrize("case", SHAPES, ids=lambda c: "n%d_%dx%d" % c)
 @pytest.mark.parametrize("offset", [0, 2])
-@pytest.mark.parametrize("C", [16, 32])
+@pytest.mark.parametrize("C,case", [(C, c) for C in (16, 32) for c in SHAPES] + [(16, c) for c in TILES16],
+                         ids=lambda c: "n%d_%dx%d" % c if isinstance(c, tuple) else "c%d" % c)
 def test_resblock_backward_equals_two_conv_backwards(case, offset, C):
     P = _p()
     n, H, W = case

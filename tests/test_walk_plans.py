@@ -1,6 +1,7 @@
 """The tile shapes of the column-walk kernels, as walkplan.h chooses them from a problem's size: that
 header is plain C++, compiled here with the host's compiler. Kinds: f32 the 32-channel block forward,
-b32 / b16 the block backward, c64 the 64-channel conv backward."""
+b32 / b16 the block backward by walks, t16 the 16-channel one in the form that its launch takes (R = 0: tile
+by tile), c64 the 64-channel conv backward."""
 from __future__ import annotations
 
 import ctypes as C
@@ -74,3 +75,14 @@ def test_few_frames_leave_few_partials(plan, n, H, W, most):
 def test_block_backwards_on_few_frames_are_not_cut_into_single_rows(plan, kind, n, H, W, most):
     """128 frames of 11x11 with 32 channels: 18 us in 64 or 128 workgroups, 24 in 256."""
     assert plan(kind, n, H, W)["tiles"] <= most
+
+
+@pytest.mark.parametrize("n,H,W,tiles", [(8192, 30, 45, True), (8192, 32, 32, True), (8192, 38, 33, True), (8192, 48, 40, True),
+                                         (2048, 84, 84, True), (2048, 100, 60, True), (2048, 42, 42, False),
+                                         (640, 42, 42, False), (8192, 21, 21, False), (8192, 11, 11, False),
+                                         (300, 200, 200, False), (128, 42, 42, False), (8, 84, 84, False)])
+def test_the_16_channel_block_backward_takes_the_faster_form(plan, n, H, W, tiles):
+    """Where both forms were timed in turn and one is more than 3% faster."""
+    p = plan("t16", n, H, W)
+    assert (p["R"] == 0) == tiles, p
+    assert p["tiles"] == -(-n // p["F"]) * p["bands"] and p["bands"] * p["TH"] >= H
