@@ -598,13 +598,23 @@ __global__ __launch_bounds__(RbtGeom::NT, 4) void resblock_bwd16_tile_kernel(Res
     load_w(a.wa, wfa);
     load_w(a.wb, wfb);
     // B-fragment byte offsets from the lane's tap-(0,0) pixel of a dy-like window: a k-step spans
-    // two taps; past the ninth the lanes re-read tap 8 against zero weights
+    // two taps; past the ninth the lanes read the zero bytes (an infinite value times a zero weight
+    // would be NaN)
     int dboff[KSD];
 #pragma unroll
     for (int ks = 0; ks < KSD; ++ks) {
-        const int tap = 2 * ks + (g >> 1), tp = tap < 9 ? tap : 8;
-        dboff[ks] = ((tp / 3) * TW + tp % 3) * PX + (g & 1) * 16;
+        const int tap = 2 * ks + (g >> 1);
+        dboff[ks] = ((tap / 3) * TW + tap % 3) * PX + (g & 1) * 16;
     }
+    auto dgrad = [&](const uint4 (&wf)[KSD], const unsigned char* xb) CB_INLINE_LAMBDA {
+        cb_f32x4 acc = cb_f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < KSD; ++ks) {
+            const unsigned char* p = ks == KSD - 1 && g >= 2 ? zero : xb + dboff[ks];
+            acc = PrecBF16::mma(wf[ks], *reinterpret_cast<const uint4*>(p), acc);
+        }
+        return acc;
+    };
     // weight-gradient column blocks nb = wg + NWG * i (one tap, or the bias block) of conv_b
     // (grp 0) or conv_a (grp 1)
     const int wg = wave % NWG, grp = wave / NWG;
@@ -740,9 +750,7 @@ __global__ __launch_bounds__(RbtGeom::NT, 4) void resblock_bwd16_tile_kernel(Res
                 const int qc = q < npx ? q : npx - 1;   // past npx: computed, not stored
                 const int row = qdiv(qc, t.inv_W), col = qc - row * W;
                 const unsigned char* xb = dyw + (row * TW + col) * PX;
-                cb_f32x4 acc = cb_f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int ks = 0; ks < KSD; ++ks) acc = PrecBF16::mma(wfb[ks], *reinterpret_cast<const uint4*>(xb + dboff[ks]), acc);
+                const cb_f32x4 acc = dgrad(wfb, xb);
                 if (q < npx) {
                     const int h = h0 - 1 + row;
                     uint2 o = make_uint2(0u, 0u);
@@ -767,9 +775,7 @@ __global__ __launch_bounds__(RbtGeom::NT, 4) void resblock_bwd16_tile_kernel(Res
                 const int qc = q < npx ? q : npx - 1;
                 const int row = qdiv(qc, t.inv_W), col = qc - row * W;
                 const unsigned char* xb = dtw + (row * TW + col) * PX;
-                cb_f32x4 acc = cb_f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int ks = 0; ks < KSD; ++ks) acc = PrecBF16::mma(wfa[ks], *reinterpret_cast<const uint4*>(xb + dboff[ks]), acc);
+                const cb_f32x4 acc = dgrad(wfa, xb);
                 if (q < npx) {
                     float mk[4], sk[4];
                     load4(reinterpret_cast<const uint16_t*>(xw + ((row + 1) * TW + col + 1) * PX + ci0 * 2), mk);

@@ -202,7 +202,9 @@ template <int R, class Pre, class Emit>
 CB_DEV void walk_conv16(const unsigned char* win, int p0, int g, int rowb, const uint4 (&w)[5], Pre&& pre, Emit&& emit) {
     const uint32_t base = uint32_t(p0) * 32 + uint32_t(g & 1) * 16;
     const bool up = g >= 2;
-    uint32_t a01 = base + (up ? 32u : 0u), a12 = base + (up ? 64u : 32u), am = up ? base + rowb : base + 64u, a2 = base + 64u;
+    uint32_t a01 = base + (up ? 32u : 0u), a12 = base + (up ? 64u : 32u), am = up ? base + rowb : base + 64u;
+    uint32_t a2 = up ? uint32_t(g & 1) * 16 : base + 64u;
+    const uint32_t row2 = up ? 0u : uint32_t(rowb);
     uint4 x[2][4];
     cb_f32x4 acc[3];
     auto load = [&](uint4 (&dst)[4], int i) CB_INLINE_LAMBDA {
@@ -216,7 +218,7 @@ CB_DEV void walk_conv16(const unsigned char* win, int p0, int g, int rowb, const
     for (int i = 0; i < R + 2; ++i) {
         const uint4 (&cur)[4] = x[i & 1];
         if (i < R + 1) {
-            a01 += rowb; a12 += rowb; am += rowb; a2 += rowb;
+            a01 += rowb; a12 += rowb; am += rowb; a2 += row2;
             load(x[(i + 1) & 1], i + 1);
         }
         if (i >= 2) {

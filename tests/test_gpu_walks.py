@@ -85,6 +85,36 @@ def test_resblock_backward_equals_two_conv_backwards(case, offset, C):
         assert torch.allclose(got, want, rtol=1e-5, atol=2.0 ** -20 * scale * max(float(n * H * W) ** 0.5, 1.0))
 
 
+@pytest.mark.parametrize("C,case", [(16, (33, 21, 21)), (16, (5, 42, 42)), (16, (900, 29, 34)), (32, (17, 11, 11)), (32, (3, 21, 22))],
+                         ids=lambda c: "n%d_%dx%d" % c if isinstance(c, tuple) else "c%d" % c)
+def test_resblock_backward_of_infinities(case, C):
+    """dx equals two conv backwards' also where dy, t or x hold infinities and NaNs: neither padding nor the
+    k-values past the ninth tap (zero weights) may turn an infinite value into a NaN."""
+    P = _p()
+    n, H, W = case
+    g = torch.Generator(device="cuda:0").manual_seed(n * 7 + H * 3 + W)
+    dy, t, x = (_act(g, (n, H, W, C)) for _ in range(3))
+    bad = torch.tensor([float("inf"), -float("inf"), float("nan")], device="cuda:0").to(torch.bfloat16)
+    for q in (dy, t, x):
+        k = max(3, q.numel() // 20000)
+        at = torch.randint(0, q.numel(), (k,), generator=g, device="cuda:0")
+        q.view(-1)[at] = bad[torch.arange(k, device="cuda:0") % 3]
+        q[0, 0, 0, 0], q[-1, -1, -1, -1] = bad[0], bad[1]   # the first and the last pixel
+    wa, wb = (torch.randn((3, 3, C, C), generator=g, device="cuda:0") * 0.1 for _ in range(2))
+    dx, dt, dx_ref = (torch.empty_like(x) for _ in range(3))
+    gw = [torch.empty(s, device="cuda:0") for s in ((3, 3, C, C), (C,)) * 2]
+    ws = torch.empty(max(P.impala_resblock_bwd_workspace_bytes(0, C), P.impala_conv3x3_bwd_workspace_bytes(0, C, C)),
+                     dtype=torch.uint8, device="cuda:0")
+    P.impala_resblock_bwd(P.PREC_BF16, n, H, W, C, dy, t, x, wa, wb, dx, *gw, ws)
+    P.impala_conv3x3_bwd(P.PREC_BF16, n, H, W, C, C, dy, t, P.X_RELU, wb, None, dt, gw[0], gw[1], ws)
+    P.impala_conv3x3_bwd(P.PREC_BF16, n, H, W, C, C, dt, x, P.X_RELU, wa, dy, dx_ref, gw[0], gw[1], ws)
+    torch.cuda.synchronize()
+    nan = torch.isnan(dx_ref)
+    assert torch.isinf(dx_ref).any() and not nan.all()
+    assert torch.equal(torch.isnan(dx), nan)
+    assert torch.equal(_bits(dx)[~nan], _bits(dx_ref)[~nan])
+
+
 @pytest.mark.parametrize("n", [1, 7, 8, 63, 64, 65])
 def test_dense_layer_on_few_frames(n):
     """The dense GEMM at and around the frame count where its tiles are mostly empty: the
