@@ -278,7 +278,7 @@ __global__ __launch_bounds__(64 * NW, RbGeom<C>::WPS) void resblock_fwd_kernel(R
 // us, 2048 of 11x11 27.3 -> 20.4 us, 8 of 21x21 12.4 -> 9.9 us. What is left at 21x21: about
 // 2.6 us before the first row, then 70% of the matrix cores' time (vector ALU work of the
 // epilogues beside them) and the loads of a tile that the other workgroup does not cover.
-template <int R>
+template <int R, int MAXS>
 __global__ __launch_bounds__(RwGeom::NT, 2) void resblock_walk_fwd_kernel(ResBlockArgs a, RwTile t) {
     using G = RwGeom;
     constexpr int NT = G::NT, NW = G::NW, KS = G::KS, C = G::C;
@@ -319,9 +319,9 @@ __global__ __launch_bounds__(RwGeom::NT, 2) void resblock_walk_fwd_kernel(ResBlo
     // NW*k)*64 + lane: pixel j / 4, position j % 4), relative to the tile's first frame with the
     // window's first row at image row 0; a tile adds that row. Rows off the frame fall outside
     // the tile's buffer resource (F > 1: they are kOOB); padding columns are kOOB and read zero.
-    uint32_t ox[G::MAXS];
+    uint32_t ox[MAXS];
 #pragma unroll
-    for (int k = 0; k < G::MAXS; ++k) {
+    for (int k = 0; k < MAXS; ++k) {
         const int j = (wave + NW * k) * 64 + lane, p = j >> 2;
         const int fi = qdiv(p, t.inv_xpf), pr = p - fi * xpf, rr = qdiv(pr, t.inv_TW), col = pr - rr * TW;
         const int q = (j & 3) ^ ((col >> 1) & 2);
@@ -338,7 +338,7 @@ __global__ __launch_bounds__(RwGeom::NT, 2) void resblock_walk_fwd_kernel(ResBlo
         const auto rx = buf_rsrc(static_cast<const uint16_t*>(a.x) + int64_t(f) * H * W * C, uint32_t(nf) * H * W * C * 2);
         const uint32_t hr = ho ? uint32_t((band * TH - 2) * W * C * 2) : 0u;   // wraps for h0 < 2: rows off the frame
 #pragma unroll
-        for (int k = 0; k < G::MAXS; ++k)
+        for (int k = 0; k < MAXS; ++k)
             if ((wave + NW * k) * 64 < nsx) dma16_to_lds(rx, xw + (wave + NW * k) * 1024, ox[k] + hr);
     };
     if (lg < t.ntiles) stage_x(lg);
@@ -498,13 +498,15 @@ hipError_t rw_launch(const ResBlockArgs& a, hipStream_t s) {
         if (!walk_choose([&](auto&& f) { rw_shapes(a.n, H, W, cus, f); }, t, L)) return hipErrorInvalidValue;
         plan = plans.put({a.n, H, W, cus, t, L});
     }
-    walk_dispatch<G::MAXR>(plan->t.R, [&](auto r) {
-        constexpr int R = decltype(r)::value;
-        const void* fn = reinterpret_cast<const void*>(&resblock_walk_fwd_kernel<R>);
+    auto launch = [&](auto r, auto slots) {
+        constexpr int R = decltype(r)::value, MAXS = decltype(slots)::value;
+        const void* fn = reinterpret_cast<const void*>(&resblock_walk_fwd_kernel<R, MAXS>);
         const int gx = std::min(plan->t.ntiles, std::max(1, resident_blocks(fn, G::NT, plan->lds)));
         ProfScope ps(s, [&] { return cb_key("resblock_fwd", 0, cb_dims(G::C, G::C) + "/" + cb_dims(H, W)); });
-        hipLaunchKernelGGL(resblock_walk_fwd_kernel<R>, dim3(unsigned(gx)), dim3(G::NT), plan->lds, s, a, plan->t);
-    });
+        hipLaunchKernelGGL((resblock_walk_fwd_kernel<R, MAXS>), dim3(unsigned(gx)), dim3(G::NT), plan->lds, s, a, plan->t);
+    };
+    if (plan->t.wide) walk_dispatch<G::WIDE_MAXR>(plan->t.R, [&](auto r) { launch(r, std::integral_constant<int, G::WIDE_MAXS>{}); });
+    else walk_dispatch<G::MAXR>(plan->t.R, [&](auto r) { launch(r, std::integral_constant<int, G::MAXS>{}); });
     return hipGetLastError();
 }
 

@@ -38,21 +38,10 @@ CB_DEV WalkAnchor walk_anchor(int id, int cols, int W, int nseg, int R, int nrow
 }
 
 // Calls f(std::integral_constant<int, R>) for a run-time R of 1 .. MAXR.
-template <int MAXR, class F>
+template <int MAXR, int R0 = 1, class F>
 inline void walk_dispatch(int R, F&& f) {
-    switch (R) {
-        case 1: f(std::integral_constant<int, 1>{}); break;
-        case 2: f(std::integral_constant<int, 2>{}); break;
-        case 3: f(std::integral_constant<int, 3>{}); break;
-        case 4: f(std::integral_constant<int, 4>{}); break;
-        case 5: f(std::integral_constant<int, 5>{}); break;
-        case 6: f(std::integral_constant<int, 6>{}); break;
-        case 7: f(std::integral_constant<int, 7>{}); break;
-        case 8:
-            if constexpr (MAXR >= 8) f(std::integral_constant<int, 8>{});
-            break;
-        default: break;
-    }
+    if (R == R0) f(std::integral_constant<int, R0>{});
+    else if constexpr (R0 < MAXR) walk_dispatch<MAXR, R0 + 1>(R, f);
 }
 // The last tile shapes chosen, per thread (the choice takes some microseconds): a few entries by
 // problem size, overwritten in turn.

@@ -60,9 +60,13 @@ struct RwGeom {
     static constexpr int MAXS = 11;                  // x-window staging slots per lane
     static constexpr int WFRAG = 2 * KS * 1024;      // one convolution's A fragments (bytes)
     static constexpr size_t LDS_TARGET = 80 * 1024;  // two workgroups per CU
+    // frames of which neither a band of one row (wider than 139) nor the whole fits in that: one workgroup
+    // per CU, walks of a row or two (the slots' offsets cost every other launch 2%)
+    static constexpr int WIDE_MAXS = 20, WIDE_MAXR = 2;
 };
 
 struct RwTile {
+    int wide;                    // the kernel of wide frames
     int F, TH, nbands, ntiles;   // frames per tile (1 with several bands per frame), rows per band
     int ho;                      // 1: t has a halo row either side (several bands)
     int t_off;                   // LDS bytes of the t window (the x window is at 0)
@@ -83,21 +87,31 @@ struct RwTile {
 template <class Fn>
 inline void rw_shapes(int64_t n, int H, int W, int cus, Fn&& f) {
     using G = RwGeom;
+    auto windows = [&](int F, int TH, int ho, int& xb) {
+        xb = walk_win_bytes(64, F, TH + 2 + 2 * ho, W);
+        return size_t(xb) + std::max(walk_win_bytes(64, F, TH + 2, W), 2 * G::WFRAG);
+    };
+    auto fits = [&](int F, int TH, int ho, bool wide) {
+        int xb = 0;
+        return windows(F, TH, ho, xb) <= (wide ? 2 : 1) * G::LDS_TARGET && xb <= (wide ? G::WIDE_MAXS : G::MAXS) * G::NW * 1024;
+    };
+    const bool wide = !fits(1, 1, 1, false) && !fits(1, H, 0, false);
     walk_bands(H, [&](int nb, int TH) {
         const int ho = nb > 1;
         for (int F = 1; F <= walk_frames(n, nb); ++F) {
-            const int xb = walk_win_bytes(64, F, TH + 2 + 2 * ho, W), tb = std::max(walk_win_bytes(64, F, TH + 2, W), 2 * G::WFRAG);
-            if (size_t(xb) + tb > G::LDS_TARGET || xb > G::MAXS * G::NW * 1024) break;
+            if (!fits(F, TH, ho, wide)) break;
+            int xb = 0;
+            const size_t lds = windows(F, TH, ho, xb);
             RwTile c{};
-            c.F = F; c.TH = TH; c.ho = ho; c.nbands = nb; c.ntiles = walk_tiles(n, F, nb); c.t_off = xb;
+            c.wide = wide; c.F = F; c.TH = TH; c.ho = ho; c.nbands = nb; c.ntiles = walk_tiles(n, F, nb); c.t_off = xb;
             c.inv_W = 1.f / float(W); c.inv_c = 1.f / float(F * W);
             c.inv_TW = 1.f / float(walk_pitch(W)); c.inv_xpf = 1.f / float((TH + 2 + 2 * ho) * walk_pitch(W));
             const double traffic = double(F) * W * 64 * (3 * TH + 4 * ho) / 1000;
             const int full = c.ntiles / (2 * cus), rest = c.ntiles - full * 2 * cus;
             const double rounds = full + (rest > cus ? 1.0 : rest > 0 ? 0.6 : 0.0);
-            for (c.R = 1; c.R <= std::min(TH, G::MAXR); ++c.R) {
+            for (c.R = 1; c.R <= std::min(TH, wide ? G::WIDE_MAXR : G::MAXR); ++c.R) {
                 const double rows = walk_rows(TH + 2 * ho, F * W, 16, G::NW, c.R, c.nseg1) + walk_rows(TH, F * W, 16, G::NW, c.R, c.nseg2);
-                f(c, size_t(xb) + tb, rounds * (0.244 * rows + 0.0546 * traffic + 0.37));
+                f(c, lds, rounds * (0.244 * rows + 0.0546 * traffic + 0.37));
             }
         }
     });

@@ -18,6 +18,9 @@ SHAPES = [(1, 1, 1), (2, 2, 5), (7, 3, 3), (33, 4, 7), (5, 11, 11), (17, 11, 11)
 # 16 channels, taken tile by tile: whole bands and a ragged last one, whole frames, odd widths
 TILES16 = [(515, 9, 97), (900, 11, 82), (200, 43, 103), (900, 29, 34), (4096, 9, 49), (4096, 21, 22), (3001, 38, 33)]
 
+# the 32-channel forward: the widest that a walk's windows take, and wider
+WIDE32 = [(2, 9, 139), (1, 1, 200), (1200, 7, 150), (3, 2, 140), (2, 5, 151), (3, 3, 256), (2, 1, 256), (300, 6, 141)]
+
 
 def _p():
     import paper_2310_00036_amd as P
@@ -35,7 +38,7 @@ def _bits(x):
     return x.view(torch.int16)
 
 
-@pytest.mark.parametrize("case", SHAPES, ids=lambda c: "n%d_%dx%d" % c)
+@pytest.mark.parametrize("case", SHAPES + WIDE32, ids=lambda c: "n%d_%dx%d" % c)
 @pytest.mark.parametrize("offset", [0, 2])
 def test_resblock32_forward_equals_two_convolutions(case, offset):
     P = _p()

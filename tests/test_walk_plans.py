@@ -86,3 +86,13 @@ def test_the_16_channel_block_backward_takes_the_faster_form(plan, n, H, W, tile
     p = plan("t16", n, H, W)
     assert (p["R"] == 0) == tiles, p
     assert p["tiles"] == -(-n // p["F"]) * p["bands"] and p["bands"] * p["TH"] >= H
+
+
+@pytest.mark.parametrize("n", [1, 2048])
+def test_the_block_forward_takes_every_frame_of_the_layer_calls(plan, n):
+    """Sides up to 256, from 140 wide on in one workgroup per CU."""
+    for W in range(1, 257):
+        for H in (1, 2, 3, 7, 40, 256):
+            p = plan("f32", n, H, W)
+            assert p is not None, (n, H, W)
+            assert p["lds"] <= (80 if W < 140 else 160) * 1024, (n, H, W, p)
