@@ -62,7 +62,7 @@ struct RwGeom {
     static constexpr size_t LDS_TARGET = 80 * 1024;  // two workgroups per CU
     // frames of which neither a band of one row (wider than 139) nor the whole fits in that: one workgroup
     // per CU, walks of a row or two (the slots' offsets cost every other launch 2%)
-    static constexpr int WIDE_MAXS = 20, WIDE_MAXR = 2;
+    static constexpr int WIDE_MAXS = 21, WIDE_MAXR = 2;
 };
 
 struct RwTile {
