@@ -128,8 +128,7 @@ __global__ __launch_bounds__(64 * NW, (CbGeom<CI, CO>::WPS)) void conv_bwd_kerne
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             const int k = ks * 32 + g * 8 + j, tap = k / CO, co = k % CO;
-            const float w = a.w[((tap < 9 ? 8 - tap : 0) * CI + o) * CO + co];   // clamped, then selected: no branch
-                    v[j] = tap < 9 ? w : 0.f;
+            v[j] = tap < 9 ? a.w[((8 - tap) * CI + o) * CO + co] : 0.f;
         }
         wf[ks] = make_uint4(pack2bf(v[0], v[1]), pack2bf(v[2], v[3]), pack2bf(v[4], v[5]), pack2bf(v[6], v[7]));
     }
@@ -175,8 +174,10 @@ __global__ __launch_bounds__(64 * NW, (CbGeom<CI, CO>::WPS)) void conv_bwd_kerne
     uint32_t od[G::MAXD], ox[G::MAXX];
     auto win_off = [&](int j, int slots, int nreal, int cbytes) -> uint32_t {
         const int p = j / slots, c = j - p * slots;
-        const int rowi = qdiv(p, t.inv_TW), col = p - rowi * TW;
-        const int f = qdiv(rowi, t.inv_TR), rr = rowi - f * TR;
+        // (a float reciprocal with 16 channels; from 32 on the divisions, which leave the main loop's
+        // registers as they are: relu'd 32 -> 32 on 300 frames of 21x21 29.6 against 30.9 us)
+        const int rowi = CI < 32 ? qdiv(p, t.inv_TW) : p / TW, col = p - rowi * TW;
+        const int f = CI < 32 ? qdiv(rowi, t.inv_TR) : rowi / TR, rr = rowi - f * TR;
         const bool in = (j < FR * TR * TW * slots) & (c < nreal) & (uint32_t(col - 1) < uint32_t(W)) &
                         ((FR == 1) | (uint32_t(rr - 1) < uint32_t(TH)));
         const uint32_t o = uint32_t(((f * H + rr - 1) * W + col - 1) * cbytes + c * 16);
@@ -196,14 +197,14 @@ __global__ __launch_bounds__(64 * NW, (CbGeom<CI, CO>::WPS)) void conv_bwd_kerne
             const int j = (wave + NW * k) * 64 + lane, px = j / (CO / 8), c = j - px * (CO / 8);
             const int rr = qdiv(px, inv_PW2), col = px - rr * PW2;
             const uint32_t o = uint32_t((((rr - 1) * t.OW + col - 1) * CO + c * 8) * 2);
-            opd[k] = (j < nsp) & (uint32_t(col - 1) < uint32_t(t.OW)) ? o : kOOB;
+            opd[k] = ((j < nsp) & (uint32_t(col - 1) < uint32_t(t.OW))) ? o : kOOB;
         }
 #pragma unroll
         for (int k = 0; k < G::MAXG; ++k) {
             const int j = (wave + NW * k) * 64 + lane, px = j / (CO / 16), c = j - px * (CO / 16);
             const int rr = qdiv(px, inv_PW2), col = px - rr * PW2;
             const uint32_t o = uint32_t(((rr - 1) * t.OW + col - 1) * CO + c * 16);
-            oag[k] = (j < nsg) & (uint32_t(col - 1) < uint32_t(t.OW)) ? o : kOOB;
+            oag[k] = ((j < nsg) & (uint32_t(col - 1) < uint32_t(t.OW))) ? o : kOOB;
         }
     }
 #pragma unroll
@@ -633,14 +634,14 @@ __global__ __launch_bounds__(64 * NW, (CbGeom<CI, CO>::WPS)) void conv_bwd_spec_
             const int j = (wave + NW * k) * 64 + lane, px = j / (CO / 8), c = j - px * (CO / 8);
             const int rr = qdiv(px, inv_PW2), col = px - rr * PW2;
             const uint32_t o = uint32_t((((rr - 1) * t.OW + col - 1) * CO + c * 8) * 2);
-            opd[k] = (j < nsp) & (uint32_t(col - 1) < uint32_t(t.OW)) ? o : kOOB;
+            opd[k] = ((j < nsp) & (uint32_t(col - 1) < uint32_t(t.OW))) ? o : kOOB;
         }
 #pragma unroll
         for (int k = 0; k < G::MAXG; ++k) {
             const int j = (wave + NW * k) * 64 + lane, px = j / (CO / 16), c = j - px * (CO / 16);
             const int rr = qdiv(px, inv_PW2), col = px - rr * PW2;
             const uint32_t o = uint32_t(((rr - 1) * t.OW + col - 1) * CO + c * 16);
-            oag[k] = (j < nsg) & (uint32_t(col - 1) < uint32_t(t.OW)) ? o : kOOB;
+            oag[k] = ((j < nsg) & (uint32_t(col - 1) < uint32_t(t.OW))) ? o : kOOB;
         }
     }
 #pragma unroll
