@@ -160,10 +160,10 @@ def test_resblock_forward(case):
 @pytest.mark.parametrize("case", [(1024, 42, 42, 16), (2048, 21, 21, 32), (2053, 42, 42, 32)],
                          ids=lambda c: "n%d_%dx%d_c%d" % c)
 def test_resblock_forward_many_tiles_per_workgroup(case):
-    """The same checks at a frame count where every workgroup runs several tiles (each tile's
-    window is staged during the previous tile's conv2), on frames spread over the launch. At
-    2053 frames of 42x42 with 32 channels every workgroup runs 32 or 33 tiles, which selects the
-    kernel whose two wave roles run conv1 and conv2 of neighbouring tiles at once."""
+    """The same checks at a frame count where every workgroup runs several tiles (16 channels:
+    each tile's window is staged during the previous tile's conv2), on frames spread over the
+    launch: with 32 channels whole frames of 21x21, and bands of 42x42 frames of which every
+    workgroup runs 16 or more."""
     _resblock_fwd_check(case, sample=[0, 1, 517, case[0] - 1])
 
 
@@ -273,6 +273,9 @@ CONV_BWD_CASES = [
     (2, 42, 42, 32, 64, P.X_PLAIN, 0), (3, 7, 5, 32, 64, P.X_PLAIN, 0),
     # frame counts at which each workgroup runs several tiles (weight gradients accumulating)
     (300, 21, 21, 64, 64, P.X_RELU, 1), (400, 11, 11, 64, 64, P.X_RELU, 0), (300, 21, 21, 32, 32, P.X_RELU, 1),
+    # relu'd 64-channel frames too wide for the column walks' windows: the widest that the kernel with
+    # specialised waves takes
+    (1, 3, 134, 64, 64, P.X_RELU, 1), (2, 5, 127, 64, 64, P.X_RELU, 0),
 ]
 
 

@@ -13,8 +13,15 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 SHAPES = [(1, 1, 1), (2, 2, 5), (7, 3, 3), (33, 4, 7), (5, 11, 11), (17, 11, 11), (700, 11, 11), (33, 21, 21),
-          (3, 21, 22), (9, 8, 15), (2, 42, 42), (515, 42, 42), (1, 43, 39), (600, 5, 7), (3, 64, 64), (1, 7, 97)]
+          (3, 21, 22), (9, 8, 15), (2, 42, 42), (515, 42, 42), (1, 43, 39), (600, 5, 7), (3, 64, 64), (1, 7, 97),
+          # the networks' layers at an actor's and an IMPALA block's frames
+          (128, 21, 21), (150, 42, 42), (640, 21, 21), (640, 11, 11), (2048, 11, 11),
+          # the row counts per walk (each a kernel of its own) that those above leave out
+          (65, 19, 26), (111, 17, 22), (550, 7, 15), (57, 9, 27), (85, 12, 22), (212, 7, 22), (37, 9, 31), (134, 17, 34),
+          (77, 13, 30), (61, 4, 9), (48, 7, 22)]
 
+# 64 channels, too wide for the walk's windows: the conv backward with specialised waves
+WIDE64 = [(2, 5, 106), (1, 4, 107), (3, 9, 107)]
 # 16 channels, taken tile by tile: whole bands and a ragged last one, whole frames, odd widths
 TILES16 = [(515, 9, 97), (900, 11, 82), (200, 43, 103), (900, 29, 34), (4096, 9, 49), (4096, 21, 22), (3001, 38, 33)]
 
@@ -142,7 +149,41 @@ def test_dense_layer_on_few_frames(n):
     assert err <= 2.0 ** -8, err
 
 
-@pytest.mark.parametrize("case", SHAPES, ids=lambda c: "n%d_%dx%d" % c)
+@pytest.mark.parametrize("n", [1, 8, 63])
+@pytest.mark.parametrize("hidden", [1024, 2056])
+def test_dense_input_gradient_on_few_frames(n, hidden):
+    """A hidden layer of 1024 units or more: the dense layer's input gradient on fewer than 64 frames, against
+    the same frames among 128 whose other frames have no gradient."""
+    from types import SimpleNamespace
+    P = _p()
+    net = SimpleNamespace(in_h=32, in_w=36, in_c=4, ch=(16, 32, 32), hidden=hidden, num_actions=6)
+    g = torch.Generator(device="cuda:0").manual_seed(n + hidden)
+    params = torch.randn(P.impala_param_count(net), generator=g, device="cuda:0") * 0.05
+    obs = torch.randint(0, 256, (128, 32, 36, 4), generator=g, device="cuda:0", dtype=torch.int32).to(torch.uint8)
+    dz, dv = torch.randn((128, 6), generator=g, device="cuda:0"), torch.randn(128, generator=g, device="cuda:0")
+    dz[n:], dv[n:] = 0, 0
+    ws, grads = {}, {}
+    for k in (128, n):
+        ws[k] = torch.empty(P.impala_workspace_bytes(net, k, P.PREC_BF16, 1), dtype=torch.uint8, device="cuda:0")
+        z, v = torch.empty((k, 6), device="cuda:0"), torch.empty(k, device="cuda:0")
+        P.impala_cnn_fwd(net, P.PREC_BF16, params, obs, None, k, ws[k], 1, z, v)
+        grads[k] = torch.empty_like(params)
+    # one forward's activations serve both (a forward on n frames rounds h its own way)
+    for (name, off, _, _, _), (_, o, size, _, shape) in zip(P.impala_activation_layout(net, P.PREC_BF16, 128),
+                                                            P.impala_activation_layout(net, P.PREC_BF16, n)):
+        assert shape[0] == n, name
+        ws[n][o:o + size] = ws[128][off:off + size]
+    for k in (128, n):
+        P.impala_cnn_bwd(net, P.PREC_BF16, params, obs, None, k, ws[k], dz, dv, grads[k])
+    torch.cuda.synchronize()
+    # dx is bf16: its rounding turns where the float32 sums of another split differ, and travels through the
+    # trunk's bf16 gradients: each tensor within one part in 2^8
+    for name, shape, off in P.impala_param_layout(net):
+        a, b = (grads[k][off:off + int(np.prod(shape))].double() for k in (128, n))
+        assert (a - b).norm() <= 2.0 ** -8 * a.norm() + 1e-30, name
+
+
+@pytest.mark.parametrize("case", SHAPES + WIDE64, ids=lambda c: "n%d_%dx%d" % c)
 @pytest.mark.parametrize("add", [False, True])
 def test_conv64_backward_equals_input_and_weight_gradient(case, add):
     P = _p()

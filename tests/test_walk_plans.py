@@ -96,3 +96,20 @@ def test_the_block_forward_takes_every_frame_of_the_layer_calls(plan, n):
             p = plan("f32", n, H, W)
             assert p is not None, (n, H, W)
             assert p["lds"] <= (80 if W < 140 else 160) * 1024, (n, H, W, p)
+
+
+def test_every_kernel_instance_is_compared_on_the_gpu(plan):
+    """R is a constant of the kernels: the shapes of the bit-equality tests reach every compiled one."""
+    pytest.importorskip("torch")
+    from test_gpu_walks import SHAPES, TILES16, WIDE32, WIDE64
+
+    def rows(kind, shapes):
+        return {plan(kind, *c)["R"] for c in shapes}
+
+    wide = [c for c in WIDE32 if c[2] >= 140 and c[1] > 2]   # (two rows fit whole)
+    assert rows("f32", SHAPES) == set(range(1, 8))
+    assert rows("f32", wide) == {1, 2}
+    assert rows("b32", SHAPES) == set(range(1, 8))
+    assert rows("t16", SHAPES) >= set(range(1, 9)) and rows("t16", TILES16) == {0}
+    assert rows("c64", SHAPES) == set(range(1, 8))
+    assert all(plan("c64", *c) is None for c in WIDE64)
