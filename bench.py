@@ -18,6 +18,7 @@ import argparse
 import hashlib
 import json
 import os
+import re
 import sys
 import time
 
@@ -310,16 +311,29 @@ def roofline(work, avg_s, prec):
     return out
 
 
-def source_digest(key):
+def source_files(key):
+    """The kernel sources of a launch key's family and the headers they include (csrc/), sorted."""
     fam = key.split("/")[0]
-    src = {"conv_fwd": "conv.hip", "conv_dgrad": "conv.hip", "conv_pool": "conv.hip", "wgrad": "wgrad.hip",
-           "gemm": "gemm.hip", "adam": "adam.hip", "pool_fwd": "pool.hip", "pool_bwd": "pool.hip",
-           "resblock_fwd": "resblock.hip", "resblock_bwd": "resbwd.hip", "conv_bwd": "convbwd.hip",
-           "pool_wgrad": "poolwgrad.hip"}.get(fam)
-    if not src:
-        return None
-    path = os.path.join(ROOT, "paper_2310_00036_amd", "csrc", src)
-    return hashlib.sha256(open(path, "rb").read()).hexdigest()[:16]
+    todo = {"conv_fwd": ["conv.hip"], "conv_dgrad": ["conv.hip"], "conv_pool": ["conv.hip", "convpool.hip"],
+            "wgrad": ["wgrad.hip"], "gemm": ["gemm.hip"], "adam": ["adam.hip"], "pool_fwd": ["pool.hip"],
+            "pool_bwd": ["pool.hip"], "resblock_fwd": ["resblock.hip"], "resblock_bwd": ["resbwd.hip"],
+            "conv_bwd": ["convbwd.hip"], "pool_wgrad": ["poolwgrad.hip"]}.get(fam, [])
+    csrc, seen = os.path.join(ROOT, "paper_2310_00036_amd", "csrc"), set()
+    while todo:
+        f = todo.pop()
+        if f in seen or not os.path.exists(os.path.join(csrc, f)):
+            continue
+        seen.add(f)
+        todo += re.findall(r'^\s*#include "([^"/]+)"', open(os.path.join(csrc, f)).read(), flags=re.M)
+    return sorted(seen)
+
+
+def source_digest(key):
+    h = hashlib.sha256()
+    files = source_files(key)
+    for f in files:
+        h.update(open(os.path.join(ROOT, "paper_2310_00036_amd", "csrc", f), "rb").read())
+    return h.hexdigest()[:16] if files else None
 
 
 def traffic_for(key, n):

@@ -1014,10 +1014,11 @@ __global__ __launch_bounds__(64 * NW, (CbGeom<CI, CO>::WPS)) void conv_bwd_spec_
 // weight gradients, each a 32 x 32 channel block of all nine taps (152 registers), and stage the
 // next tile's windows into the other buffers. Each dy fragment read feeds the three dx rows it
 // touches (6 MFMAs instead of 2), each x fragment the three dy rows it meets. Measured against the
-// form that reads each fragment once per tap (conv_bwd_spec_kernel): 8192 frames of 21x21 with the
-// residual 830 -> 577 us (640 -> 925 TFLOP/s), of 11x11 254 -> 183 us, 640 of 21x21 98.7 -> 68.4 us, 5
-// of 21x21 25 -> 20 us. What bounds it: the MFMAs of a SIMD's two waves (230 us at the matrix cores' rate at
-// 21x21) and the vector instructions between them.
+// form that reads each fragment once per tap (conv_bwd_spec_kernel), with the residual and the reduce, graph
+// replays on one card: 8192 frames of 21x21 925 -> 565 us (576 -> 943 TFLOP/s), of 11x11 270 -> 174, 640 of
+// 21x21 91 -> 59, 40 of 11x11 26 -> 20, 5 of 21x21 26 -> 16. What bounds it: the MFMAs of a SIMD's two waves
+// (230 us at the matrix cores' rate at 21x21) and the vector instructions between them. (Tile shapes:
+// walkplan.h.)
 template <int R, int ADD>
 __global__ __launch_bounds__(Cw64Geom::NT, 2) void conv_bwd64_walk_kernel(ConvBwdArgs a, Cw64Tile t) {
     using G = Cw64Geom;
@@ -1218,9 +1219,7 @@ int cb_parts_cap() {
     return int(cap < 256 ? 256 : (cap > 1024 ? 1024 : cap));
 }
 
-// Tile shapes of the 64-channel column-walk kernel: rounds of tiles over the CUs times a tile's
-// estimated cycles (both roles' MFMAs on their shared SIMD, or its loads at 8 bytes per cycle and
-// CU). Returns hipErrorNotSupported where no tile fits two window pairs (widths above about 100).
+// Returns hipErrorNotSupported where no tile fits two window pairs (widths above 105).
 template <int ADD>
 hipError_t cw64_launch(const ConvBwdArgs& a, hipStream_t s, int& parts) {
     using G = Cw64Geom;

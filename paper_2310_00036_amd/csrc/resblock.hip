@@ -106,10 +106,9 @@ __global__ __launch_bounds__(64 * NW, RbGeom<C>::WPS) void resblock_fwd_kernel(R
         b1[j] = a.b1 ? a.b1[co0 + j] : 0.f;
         b2[j] = a.b2 ? a.b2[co0 + j] : 0.f;
     }
-    // Per-lane B-fragment offsets from the tap-(0,0) pixel. k-values 8g .. 8g+7 of a k-step are
-    // channels (8g % C) .. +7 of one tap: plane (8g % C) / 16, half (g & 1) of the pixel's 32
-    // bytes. With 16 channels a k-step spans two taps (table per k-step; lanes g >= 2 of the
-    // last k-step are past the 9 taps and read the zero word); with 32, one tap per k-step.
+    // Per-lane B-fragment offsets from the tap-(0,0) pixel: a k-step spans two taps, lane group g
+    // the half (g & 1) of tap 2 ks + g / 2's 32 bytes; groups g >= 2 of the last k-step are past the
+    // 9 taps and read the zero word.
     int boff[KSTEPS];
 #pragma unroll
     for (int ks = 0; ks < KSTEPS; ++ks) {
@@ -263,7 +262,8 @@ __global__ __launch_bounds__(64 * NW, RbGeom<C>::WPS) void resblock_fwd_kernel(R
 // walks its anchors down the rows: the three fragments of an input row (kx = 0, 1, 2) feed the
 // three output rows they touch, both 16-channel output blocks each, 18 MFMAs for 3 KB, and the
 // next row's three are read meanwhile. Each wave holds both convolutions' weights for both
-// output blocks (144 registers): two 4-wave workgroups per CU, each with its own windows.
+// output blocks (144 registers): two 4-wave workgroups per CU, each with its own windows (one, with windows
+// of twice the size, where a frame is too wide: MAXS slots per lane).
 // Sums keep the tap order of one output pixel's chain, so results are those of the per-layer
 // convolutions bit for bit.
 //   - One padding column serves both sides (the right neighbour of a row's last pixel is the next
@@ -273,11 +273,12 @@ __global__ __launch_bounds__(64 * NW, RbGeom<C>::WPS) void resblock_fwd_kernel(R
 //   - Output rows of the A operand are permuted so that lane group g receives channels 8g .. 8g+7:
 //     one 16-byte store per pixel, 1 KB contiguous per wave.
 //   - The weights are read once per workgroup, coalesced, and shared through LDS.
-// Measured against the tile-by-tile form (and, at 42x42, a two-role pipelined form of it):
-// 2048 frames of 21x21 75 -> 51 us (2.3 -> 3.4 TB/s of its three tensors), 8192 of 42x42 930 -> 825
-// us, 2048 of 11x11 27.3 -> 20.4 us, 8 of 21x21 12.4 -> 9.9 us. What is left at 21x21: about
-// 2.6 us before the first row, then 70% of the matrix cores' time (vector ALU work of the
-// epilogues beside them) and the loads of a tile that the other workgroup does not cover.
+// Measured against a tile-by-tile form (at 42x42 against a two-role pipelined form of it), graph
+// replays on one card: 2048 frames of 21x21 74 -> 43.6 us (2.3 -> 4.0 TB/s of its three tensors), 8192 260
+// -> 155, 640 28.9 -> 21.3, 128 12.7 -> 8.5, 8 11.7 -> 5.3; 8192 of 42x42 969 -> 765, 2048 of 11x11 25.8 ->
+// 17.9. With walks of one row, which reuse nothing, 21x21 takes 53 us. What is left at 21x21: about 2.6 us
+// before the first row; then a tile's work and its loads, which add up unless the other workgroup covers
+// them. (Tile shapes: walkplan.h.)
 template <int R, int MAXS>
 __global__ __launch_bounds__(RwGeom::NT, 2) void resblock_walk_fwd_kernel(ResBlockArgs a, RwTile t) {
     using G = RwGeom;

@@ -25,22 +25,6 @@
 
 namespace cb {
 
-// The 32-channel block backward by column walks (walk.h), in one 8-wave workgroup per CU with
-// two wave roles. Waves 0-3 form dt, then dx, for both channel blocks (both convolutions' weights:
-// 144 registers; each input fragment feeds 18 MFMAs); waves 4-7 form conv_b's weight gradient
-// while dt is formed and conv_a's beside dx, each wave one 16x16 channel block of all nine taps (18
-// tap tiles and the bias columns: 80 registers; each x fragment feeds three rows of dy). A tile (F
-// whole frames, or a band of one) has two phases:
-//   a: dt = conv_b^T(dy) * [t > 0] into the dt window; dWb from dy and t; x and dy's own pixels
-//      once more (for the skip term; an L2 hit) are being staged;
-//   b: dx = conv_a^T(dt) * [x > 0] + dy; dWa from dt and x; the next tile's dy and t are staged.
-// No phase reads what is being staged in it, so loads overlap all of the work with one set of
-// windows in LDS.
-// Measured against a form that read every fragment once per tap and block (its own two roles
-// bound by LDS and by the vector instructions beside the MFMAs): 2048 frames of 21x21 138 -> 101 us,
-// of 11x11 56 -> 45 us, 8192 of 42x42 1590 -> 1490 us, 640 of 11x11 with its reduce 36 -> 25 us.
-// What bounds it: a SIMD's MFMAs (about 270 of 16 cycles per phase at 21x21) and the vector
-// instructions of its two waves, which overlap 1.6 to 1; then staging and barriers.
 // One window of a tile, HBM -> LDS: block wave + NW*k of 64 16-byte slots from the lane's offset
 // off[k], shifted by `row` rows.
 template <int C, int N>
@@ -74,6 +58,23 @@ CB_DEV void rbw_landed(unsigned char* win, int ns, int wave, int lane) {
     }
 }
 
+// The 32-channel block backward by column walks (walk.h), in one 8-wave workgroup per CU with
+// two wave roles. Waves 0-3 form dt, then dx, for both channel blocks (both convolutions' weights:
+// 144 registers; each input fragment feeds 18 MFMAs); waves 4-7 form conv_b's weight gradient
+// while dt is formed and conv_a's beside dx, each wave one 16x16 channel block of all nine taps (18
+// tap tiles and the bias columns: 80 registers; each x fragment feeds three rows of dy). A tile (F
+// whole frames, or a band of one; walkplan.h) has two phases:
+//   a: dt = conv_b^T(dy) * [t > 0] into the dt window; dWb from dy and t; x and dy's own pixels
+//      once more (for the skip term; an L2 hit) are being staged;
+//   b: dx = conv_a^T(dt) * [x > 0] + dy; dWa from dt and x; the next tile's dy and t are staged.
+// No phase reads what is being staged in it, so loads overlap all of the work with one set of
+// windows in LDS.
+// Measured against a form that read every fragment once per tap and block (its own two roles
+// bound by LDS and by the vector instructions beside the MFMAs), with the reduce, graph replays on one
+// card: 2048 frames of 21x21 128 -> 87 us, of 11x11 56 -> 41, 8192 of 42x42 1637 -> 1469, 640 of 11x11 36 ->
+// 27, 128 of 11x11 26 -> 18.
+// What bounds it: a SIMD's MFMAs (about 270 of 16 cycles per phase at 21x21) and the vector
+// instructions of its two waves, which overlap 1.6 to 1; then staging and barriers.
 template <int R>
 __global__ __launch_bounds__(RbwGeom::NT, 2) void resblock_bwd_walk_kernel(ResBwdArgs a, RbwTile t) {
     using G = RbwGeom;
@@ -307,11 +308,10 @@ __global__ __launch_bounds__(RbwGeom::NT, 2) void resblock_bwd_walk_kernel(ResBw
 // The 16-channel block backward in the same form. One fragment of weight-gradient anchors fills a wave
 // (all nine taps of the one channel block: 40 registers a convolution), so the four waves share the
 // anchors and their sums are added at the end.
-// Measured against a form of two workgroups per CU that staged a tile, waited, and read every
-// fragment once per tap: 2048 frames of 42x42 152.5 -> 144.7 us, 640 of 42x42 60 -> 55.5 us, of 21x21
-// 31.5 -> 26 us, of 11x11 22.7 -> 17.8 us. Two workgroups of this form per CU (80 KB windows, 128
-// registers, which spill) were slower: 180 us on 2048 frames of 42x42. What bounds it: 462 MB at the
-// rate of a large copy are 97 us; the rest is a phase's loads that outlast its work, and barriers.
+// Measured against the tile-by-tile form below, with the reduce, graph replays on one card: 2048 frames of
+// 42x42 157 -> 146 us, 640 of 42x42 60 -> 52, of 21x21 35 -> 25, of 11x11 26.5 -> 16.7, 8192 of 21x21 150 -> 136.
+// Two workgroups of this form per CU (80 KB windows, 128 registers, which spill) were slower. What bounds it:
+// 462 MB at the rate of a large copy are 97 us; the rest is work and loads of a phase that add up, and barriers.
 template <int R>
 __global__ __launch_bounds__(Rbw16Geom::NT, 2) void resblock_bwd16_walk_kernel(ResBwdArgs a, RbwTile t) {
     using G = Rbw16Geom;
@@ -882,8 +882,8 @@ hipError_t rb16_launch(const ResBwdArgs& a, hipStream_t s, PendingReduce out[2])
 bool resblock_bwd_supported(int C) { return C == 16 || C == 32; }
 
 // The block backward beats the two conv backward launches at every shape the networks use (32
-// channels, 2048 frames: 11x11 45 against 75 us, 21x21 101 against 148 us; 8192 frames at 42x42:
-// 1.49 against 1.97 ms).
+// channels, 2048 frames: 11x11 41 against 75 us, 21x21 87 against 148 us; 8192 frames at 42x42:
+// 1.47 against 1.97 ms).
 bool resblock_bwd_preferred(int C, int H, int W) { return (C == 16 || C == 32) && H > 0 && W > 0; }
 
 size_t resblock_bwd_partial_floats(int C) {
