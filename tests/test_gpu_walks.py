@@ -237,3 +237,45 @@ def test_actor_step_samples_as_the_sampling_call_does(n, A, keep_logits):
         assert torch.equal(a, act_ref)
         assert torch.equal(lp.view(torch.int32), logp_ref.view(torch.int32))
         assert torch.equal(v.view(torch.int32), value.view(torch.int32))
+
+
+def test_network_backward_through_the_tile_by_tile_kernel():
+    """The whole backward on 1700 frames of 58x68, whose first-stage blocks (29x34) are taken tile by tile and sum
+    the launches' partials before them at their start, against the sum over two halves, which walk. A partial of
+    the launch before it left out would move its weight gradient by a few percent."""
+    from types import SimpleNamespace
+    P = _p()
+    n, half = 1700, 850
+    net = SimpleNamespace(in_h=58, in_w=68, in_c=4, ch=(16, 32, 32), hidden=256, num_actions=6)
+    g = torch.Generator(device="cuda:0").manual_seed(58)
+    params = torch.randn(P.impala_param_count(net), generator=g, device="cuda:0") * 0.05
+    obs = torch.randint(0, 256, (n, 58, 68, 4), generator=g, device="cuda:0", dtype=torch.int32).to(torch.uint8)
+    dz, dv = torch.randn((n, 6), generator=g, device="cuda:0"), torch.randn(n, generator=g, device="cuda:0")
+
+    def forward(o):
+        k = o.shape[0]
+        ws = torch.empty(P.impala_workspace_bytes(net, k, P.PREC_BF16, 1), dtype=torch.uint8, device="cuda:0")
+        P.impala_cnn_fwd(net, P.PREC_BF16, params, o, None, k, ws, 1, torch.empty((k, 6), device="cuda:0"),
+                         torch.empty(k, device="cuda:0"))
+        return ws
+
+    whole, want = torch.empty_like(params), torch.zeros(params.numel(), dtype=torch.float64, device="cuda:0")
+    ws = forward(obs)
+    for a in (0, half):
+        o, part = obs[a:a + half].contiguous(), torch.empty_like(params)
+        wh = forward(o)
+        # the whole's activations, which both differentiate (the dense layer's sums group by frame count)
+        for (name, off, size, _, _), (_, at, hsize, _, _) in zip(P.impala_activation_layout(net, P.PREC_BF16, n),
+                                                                 P.impala_activation_layout(net, P.PREC_BF16, half)):
+            assert size == 2 * hsize, name
+            wh[at:at + hsize] = ws[off + (a // half) * hsize:off + (a // half + 1) * hsize]
+        P.impala_cnn_bwd(net, P.PREC_BF16, params, o, None, half, wh, dz[a:a + half].contiguous(),
+                         dv[a:a + half].contiguous(), part)
+        want += part.double()
+    P.impala_cnn_bwd(net, P.PREC_BF16, params, obs, None, n, ws, dz, dv, whole)
+    torch.cuda.synchronize()
+    # the trunk's gradients are the same bit for bit where the dense input gradient is (its sums over 256 hidden
+    # units may round another way: one part in 2^8 of single values), the weight gradients float32 sums
+    for name, shape, off in P.impala_param_layout(net):
+        w, q = want[off:off + int(np.prod(shape))], whole[off:off + int(np.prod(shape))].double()
+        assert (w - q).norm() <= 2.0 ** -10 * w.norm() + 1e-30, (name, float((w - q).norm() / w.norm()))
