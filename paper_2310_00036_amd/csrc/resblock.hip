@@ -267,7 +267,7 @@ __global__ __launch_bounds__(64 * NW, RbGeom<C>::WPS) void resblock_fwd_kernel(R
 // Sums keep the tap order of one output pixel's chain, so results are those of the per-layer
 // convolutions bit for bit.
 //   - One padding column serves both sides (the right neighbour of a row's last pixel is the next
-//     row's padding), and the windows' layout (walk.h) is free of bank conflicts.
+//     row's padding); walk.h has the windows' layout.
 //   - The x window stays as loaded (the fragments are ReLU'd in registers), so the residual comes
 //     from LDS too, and nothing is read twice from memory but a band's halo rows.
 //   - Output rows of the A operand are permuted so that lane group g receives channels 8g .. 8g+7:

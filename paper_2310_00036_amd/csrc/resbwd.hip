@@ -65,16 +65,18 @@ CB_DEV void rbw_landed(unsigned char* win, int ns, int wave, int lane) {
 // tap tiles and the bias columns: 80 registers; each x fragment feeds three rows of dy). A tile (F
 // whole frames, or a band of one; walkplan.h) has two phases:
 //   a: dt = conv_b^T(dy) * [t > 0] into the dt window; dWb from dy and t; x and dy's own pixels
-//      once more (for the skip term; an L2 hit) are being staged;
+//      once more (for the skip term) are being staged;
 //   b: dx = conv_a^T(dt) * [x > 0] + dy; dWa from dt and x; the next tile's dy and t are staged.
-// No phase reads what is being staged in it, so loads overlap all of the work with one set of
-// windows in LDS.
+// No phase reads what is being staged in it, so one set of windows in LDS is enough for loads to be in
+// flight during all of the work.
 // Measured against a form that read every fragment once per tap and block (its own two roles
 // bound by LDS and by the vector instructions beside the MFMAs), with the reduce, graph replays on one
 // card: 2048 frames of 21x21 128 -> 87 us, of 11x11 56 -> 41, 8192 of 42x42 1637 -> 1469, 640 of 11x11 36 ->
 // 27, 128 of 11x11 26 -> 18.
-// What bounds it: a SIMD's MFMAs (about 270 of 16 cycles per phase at 21x21) and the vector
-// instructions of its two waves, which overlap 1.6 to 1; then staging and barriers.
+// Counters at 2048 frames of 21x21: 252 MB move where 231 have to (a third of dy's second reads miss the
+// L2), the matrix cores are busy 0.33 of the time. What bounds it: a SIMD's MFMAs (about 270 of 16 cycles
+// per phase) and the vector instructions of its two waves, and the loads of a phase, which add up with its
+// work (walkplan.h); then barriers.
 template <int R>
 __global__ __launch_bounds__(RbwGeom::NT, 2) void resblock_bwd_walk_kernel(ResBwdArgs a, RbwTile t) {
     using G = RbwGeom;
@@ -311,7 +313,8 @@ __global__ __launch_bounds__(RbwGeom::NT, 2) void resblock_bwd_walk_kernel(ResBw
 // Measured against the tile-by-tile form below, with the reduce, graph replays on one card: 2048 frames of
 // 42x42 157 -> 146 us, 640 of 42x42 60 -> 52, of 21x21 35 -> 25, of 11x11 26.5 -> 16.7, 8192 of 21x21 150 -> 136.
 // Two workgroups of this form per CU (80 KB windows, 128 registers, which spill) were slower. What bounds it:
-// 462 MB at the rate of a large copy are 97 us; the rest is work and loads of a phase that add up, and barriers.
+// 462 MB (468 move) at the rate of a large copy are 97 us; the rest is work and loads of a phase that add up,
+// and barriers.
 template <int R>
 __global__ __launch_bounds__(Rbw16Geom::NT, 2) void resblock_bwd16_walk_kernel(ResBwdArgs a, RbwTile t) {
     using G = Rbw16Geom;

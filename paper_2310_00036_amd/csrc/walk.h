@@ -5,7 +5,9 @@
 // neighbour of a row's last pixel the next row's column 0. A pixel's 32 channels take 64 bytes,
 // its four 16-byte slots permuted by XOR with 2 * bit 2 of its column: 16-byte reads of 16
 // consecutive pixels, and 8-byte transpose reads of 8, then fall on distinct banks, and a step of
-// one row is one constant.
+// one row is one constant. A group of anchors that goes on in the next segment or frame (every group of
+// an 11-column frame, half of a 21-column one's) jumps in between and folds some of its reads onto one
+// bank: 0.26 to 0.53 of the LDS-active cycles are conflicts (21x21 backward, 11x11 forward).
 //
 // The pixels of a fragment are anchors: a column of the tile, or one of nseg segments of it, R
 // rows each. All lanes walk down their anchors together.
