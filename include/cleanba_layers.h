@@ -90,8 +90,8 @@ impala_status_t impala_conv3x3_wgrad(impala_prec_t prec, int64_t n, int32_t H, i
  * dy: [n, H, W, cout] or pooled as above; x, add, dx: [n, H, W, cin] (all bf16); w: float
  * HWIO [3,3,cin,cout]; dw: float [3,3,cin,cout]; db: float [cout] (both overwritten); ws:
  * device scratch of impala_conv3x3_bwd_workspace_bytes() bytes. Supported: IMPALA_X_RELU
- * without pool_arg with cin == cout in {16, 32}; IMPALA_X_PLAIN without add for (cin, cout)
- * in {(16,16), (16,32), (32,32)}; anything else returns IMPALA_EUNSUPPORTED. */
+ * without pool_arg with cin == cout in {16, 32, 64}; IMPALA_X_PLAIN without add for (cin, cout)
+ * in {(16,16), (16,32), (32,32), (32,64), (64,64)}; anything else returns IMPALA_EUNSUPPORTED. */
 size_t impala_conv3x3_bwd_workspace_bytes(impala_prec_t prec, int32_t cin, int32_t cout);
 impala_status_t impala_conv3x3_bwd(impala_prec_t prec, int64_t n, int32_t H, int32_t W, int32_t cin,
                                    int32_t cout, const void* dy, const uint8_t* pool_arg, const void* x,

@@ -1,7 +1,7 @@
 """The column-walk kernels against the per-layer calls they stand for, at the edges of their tile
 shapes: rows and columns around a walk's group of 16 anchors, whole frames and bands, a ragged last
 tile, row pitches of both parities, windows near the LDS budget, and pointers that are aligned to
-the element only. A walk adds the products of one output in the per-layer kernels' order, so stored
+four bytes only. A walk adds the products of one output in the per-layer kernels' order, so stored
 outputs are equal bit for bit; weight gradients are float32 sums in another order."""
 from __future__ import annotations
 
