@@ -107,10 +107,10 @@ __global__ __launch_bounds__(64 * NW, (CpGeom<CIN, COUT, MODE>::WPS)) void conv_
                 if ((wave + NW * k) * 64 < ns) dma16_to_lds(rx, dst + (wave + NW * k) * 1024, ox[k] + hr);
         }
     };
-    // the first window: in flight while the weights are loaded, except with 64 outputs, where its loads are
-    // in the way of the weights' (64->64 on 640 frames of 21x21 36.1 against 35.3 us; 16->32 on 300 of 42x42
-    // 16.7 against 17.2)
-    if (COUT < 64 && lg < t.ntiles) stage(sdst, lg);
+    // the first window: in flight while the weights are loaded, except with 64 inputs, where its loads are
+    // in the way of the 147 KB of weights' (64->64 on 640 frames of 21x21 36.0 against 35.4 us, on 150 13.5
+    // against 13.3; but 16->32 on 300 of 42x42 16.7 against 17.2, 32->64 on 31 9.7 against 9.9)
+    if (CIN < 64 && lg < t.ntiles) stage(sdst, lg);
 
     // ---- weight fragments of this wave's output block: A[o][k] = w[k*COUT + o] (HWIO, k =
     // tap*CIN + i), zero past the 9 taps; biases of the lane's four output channels
@@ -177,7 +177,7 @@ __global__ __launch_bounds__(64 * NW, (CpGeom<CIN, COUT, MODE>::WPS)) void conv_
     for (int j = tid; j < t.THmax * TW * KPB / 16; j += NT) reinterpret_cast<uint4*>(keys)[j] = make_uint4(0, 0, 0, 0);
 
     __syncthreads();
-    if (COUT >= 64 && lg < t.ntiles) stage(sdst, lg);
+    if (CIN >= 64 && lg < t.ntiles) stage(sdst, lg);
 
     for (int tile = lg; tile < t.ntiles; tile += gridDim.x) {
         const int band = tile % t.nbands, f = tile / t.nbands;
