@@ -32,7 +32,7 @@ CB_DEV void rbw_stage(const ResBwdArgs& a, const RbwTile& t, const void* src, un
                       const uint32_t (&off)[N], int wave, int tile, int row) {
     constexpr int NW = RbwGeom::NW;
     const int band = tile % t.nbands, f = (tile / t.nbands) * t.F;
-    const int nf = a.n - f < t.F ? a.n - f : t.F, fel = a.H * a.W * C;
+    const int nf = std::max(std::min(a.n - f, t.F), 0), fel = a.H * a.W * C;
     const auto r = buf_rsrc(static_cast<const uint16_t*>(src) + int64_t(f) * fel, uint32_t(nf) * fel * 2);
     const uint32_t hr = uint32_t((band * t.TH - row) * a.W * C * 2);   // wraps above the frame
 #pragma unroll
@@ -82,6 +82,7 @@ __global__ __launch_bounds__(RbwGeom::NT, 2) void resblock_bwd_walk_kernel(ResBw
     using G = RbwGeom;
     constexpr int NT = G::NT, NW = G::NW, NS = G::NS, C = G::C;
     extern __shared__ __align__(16) unsigned char smem[];
+    const int G0 = t.pset / G::PSTRIDE;      // workgroups with tiles
     unsigned char* dyw = smem;               // dy [F][TH+2+2ho][TW], row 0 = image row h0-1-ho
     unsigned char* tw = smem + t.t_off;      // relu(t) [F][TH+2][TW], row 0 = image row h0-1
     unsigned char* xw = smem + t.x_off;      // relu(x), likewise
@@ -113,8 +114,8 @@ __global__ __launch_bounds__(RbwGeom::NT, 2) void resblock_bwd_walk_kernel(ResBw
     const int rd = ho ? 2 : 0, rx = ho ? 1 : 0;   // a window's first row above the band (whole frames: in the offsets)
 
     int lg = blockIdx.x;   // neighbouring bands (which share halo rows) on one XCD
-    if ((gridDim.x & 7) == 0) lg = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
-    const int G0 = int(gridDim.x);
+    if ((G0 & 7) == 0) lg = (blockIdx.x & 7) * (G0 >> 3) + (blockIdx.x >> 3);
+    if (int(blockIdx.x) >= G0) lg = t.ntiles;   // past the frames: stages zeros
 
     // ---- weights, loaded first and packed below: 4 k-values (output channels of the forward) of one
     // input channel o per unit; A[o][tap * 32 + co] = w[8 - tap][o][co]
@@ -139,8 +140,7 @@ __global__ __launch_bounds__(RbwGeom::NT, 2) void resblock_bwd_walk_kernel(ResBw
     rbw_stage<C>(a, t, a.dy, dyw, nsd, od, wave, lg, rd);
     rbw_stage<C>(a, t, a.t, tw, nsx, ox, wave, lg, rx);
     // earlier launches' weight-gradient partials
-    if (a.pend.nparts > 0) pending_reduce<NT>(a.pend, dtw);
-    if (a.pend2.nparts > 0) pending_reduce<NT>(a.pend2, dtw);
+    if (pending_reduces<NT>(a, G0, dtw)) return;
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
         const int id = tid + u * NT, cv = id >= UNITS / 2, r = id - cv * (UNITS / 2);
@@ -320,6 +320,7 @@ __global__ __launch_bounds__(Rbw16Geom::NT, 2) void resblock_bwd16_walk_kernel(R
     using G = Rbw16Geom;
     constexpr int NT = G::NT, NW = G::NW, NS = G::NS, C = G::C;
     extern __shared__ __align__(16) unsigned char smem[];
+    const int G0 = t.pset / G::PSTRIDE;      // workgroups with tiles
     unsigned char* dyw = smem;               // dy [F][TH+2+2ho][TW], row 0 = image row h0-1-ho
     unsigned char* tw = smem + t.t_off;      // relu(t) [F][TH+2][TW], row 0 = image row h0-1
     unsigned char* xw = smem + t.x_off;      // relu(x), likewise
@@ -350,8 +351,8 @@ __global__ __launch_bounds__(Rbw16Geom::NT, 2) void resblock_bwd16_walk_kernel(R
     const int rd = ho ? 2 : 0, rx = ho ? 1 : 0;   // a window's first row above the band (whole frames: in the offsets)
 
     int lg = blockIdx.x;   // neighbouring bands (which share halo rows) on one XCD
-    if ((gridDim.x & 7) == 0) lg = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
-    const int G0 = int(gridDim.x);
+    if ((G0 & 7) == 0) lg = (blockIdx.x & 7) * (G0 >> 3) + (blockIdx.x >> 3);
+    if (int(blockIdx.x) >= G0) lg = t.ntiles;   // past the frames: stages zeros
 
 #pragma unroll
     for (int k = 0; k < G::MAXD; ++k) od[k] = win_off((wave + NW * k) * 64 + lane, nsd, dpf, t.inv_dpf);
@@ -365,8 +366,7 @@ __global__ __launch_bounds__(Rbw16Geom::NT, 2) void resblock_bwd16_walk_kernel(R
     rbw_stage<C>(a, t, a.dy, dyw, nsd, od, wave, lg, rd);
     rbw_stage<C>(a, t, a.t, tw, nsx, ox, wave, lg, rx);
     // earlier launches' weight-gradient partials
-    if (a.pend.nparts > 0) pending_reduce<NT>(a.pend, dtw);
-    if (a.pend2.nparts > 0) pending_reduce<NT>(a.pend2, dtw);
+    if (pending_reduces<NT>(a, G0, dtw)) return;
     lds_barrier();
     // the dt window: its padding and, for whole frames, its rows off the frame are never written
     auto clear_dt = [&] {
@@ -559,6 +559,7 @@ __global__ __launch_bounds__(RbtGeom::NT, 4) void resblock_bwd16_tile_kernel(Res
     constexpr int NWG = NW / 2, TPW = (G::NBB + NWG - 1) / NWG;
 
     extern __shared__ __align__(16) unsigned char smem[];
+    const int G0 = t.pset / G::PSTRIDE;           // workgroups with tiles
     unsigned char* zero = smem;                   // 64 zero bytes
     unsigned char* dyw = smem + t.dy_off;         // dy [TH+4][W+2], row 0 = image row h0-2
     unsigned char* tw = smem + t.t_off + PX;      // relu(t) [TH+2][W+2], row 0 = h0-1, guard pixels
@@ -571,8 +572,7 @@ __global__ __launch_bounds__(RbtGeom::NT, 4) void resblock_bwd16_tile_kernel(Res
     const int H = a.H, W = a.W, TH = t.TH, TW = W + 2;
 
     // earlier launches' weight-gradient partials, summed first (LDS is free until staging)
-    if (a.pend.nparts > 0) pending_reduce<NT>(a.pend, smem);
-    if (a.pend2.nparts > 0) pending_reduce<NT>(a.pend2, smem);
+    if (pending_reduces<NT>(a, G0, smem)) return;
     if (tid < 16) reinterpret_cast<uint32_t*>(zero)[tid] = 0u;
     // the dt window: its padding columns are never written
     for (int j = tid; j < t.dt_bytes / 16; j += NT) reinterpret_cast<uint4*>(dtw)[j] = make_uint4(0, 0, 0, 0);
@@ -703,9 +703,9 @@ __global__ __launch_bounds__(RbtGeom::NT, 4) void resblock_bwd16_tile_kernel(Res
     };
 
     int lg = blockIdx.x;   // neighbouring bands (which share halo rows) on one XCD
-    if ((gridDim.x & 7) == 0) lg = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    if ((G0 & 7) == 0) lg = (blockIdx.x & 7) * (G0 >> 3) + (blockIdx.x >> 3);
 
-    for (int tile = lg; tile < t.ntiles; tile += gridDim.x) {
+    for (int tile = lg; tile < t.ntiles; tile += G0) {
         const int band = tile % t.nbands, f = tile / t.nbands;
         const int h0 = band * TH, the = H - h0 < TH ? H - h0 : TH;
         const int64_t fo = int64_t(f) * H * W * C;   // the frame's first element
@@ -837,10 +837,10 @@ hipError_t rb32_launch(const ResBwdArgs& a, hipStream_t s, PendingReduce out[2])
         if (!walk_choose([&](auto&& f) { rbw_shapes<G>(a.n, H, W, cus, limit, f); }, t, L)) return hipErrorInvalidValue;
         plan = plans.put({a.n, H, W, cus, t, L});
     }
-    const int parts = plan->t.pset / G::PSTRIDE;
+    const int parts = plan->t.pset / G::PSTRIDE, helpers = pending_helpers(a, parts, cus);
     walk_dispatch<G::MAXR>(plan->t.R, [&](auto r) {
         ProfScope ps(s, [&] { return cb_key("resblock_bwd", 0, cb_dims(G::C, G::C) + "/" + cb_dims(H, W)); });
-        hipLaunchKernelGGL(resblock_bwd_walk_kernel<decltype(r)::value>, dim3(unsigned(parts)), dim3(G::NT), plan->lds, s, a, plan->t);
+        hipLaunchKernelGGL(resblock_bwd_walk_kernel<decltype(r)::value>, dim3(unsigned(parts + helpers)), dim3(G::NT), plan->lds, s, a, plan->t);
     });
     rbw_pending(a, G::C, parts, G::PSTRIDE, plan->t.pset, out);
     return hipGetLastError();
@@ -860,20 +860,22 @@ hipError_t rb16_launch(const ResBwdArgs& a, hipStream_t s, PendingReduce out[2])
         if (p.tiles) {
             const void* fn = reinterpret_cast<const void*>(&resblock_bwd16_tile_kernel);
             const int room = int(resblock_bwd_partial_floats(G::C) / (2 * size_t(G::PSTRIDE)));
-            p.u.pset = std::min({std::max(1, resident_blocks(fn, RbtGeom::NT, L)), room, p.u.ntiles}) * G::PSTRIDE;
+            p.room = std::min(std::max(1, resident_blocks(fn, RbtGeom::NT, L)), room);
+            p.u.pset = std::min(p.room, p.u.ntiles) * G::PSTRIDE;
         }
         plan = plans.put({a.n, H, W, cus, p, L});
     }
     const Rb16Plan& p = plan->t;
     const int pset = p.tiles ? p.u.pset : p.t.pset, parts = pset / G::PSTRIDE;
+    const int helpers = pending_helpers(a, parts, p.tiles ? p.room : cus);
     auto scope = [&] { return cb_key("resblock_bwd", 0, cb_dims(G::C, G::C) + "/" + cb_dims(H, W)); };
     if (p.tiles) {
         ProfScope ps(s, scope);
-        hipLaunchKernelGGL(resblock_bwd16_tile_kernel, dim3(unsigned(parts)), dim3(RbtGeom::NT), plan->lds, s, a, p.u);
+        hipLaunchKernelGGL(resblock_bwd16_tile_kernel, dim3(unsigned(parts + helpers)), dim3(RbtGeom::NT), plan->lds, s, a, p.u);
     } else {
         walk_dispatch<G::MAXR>(p.t.R, [&](auto r) {
             ProfScope ps(s, scope);
-            hipLaunchKernelGGL(resblock_bwd16_walk_kernel<decltype(r)::value>, dim3(unsigned(parts)), dim3(G::NT), plan->lds, s, a, p.t);
+            hipLaunchKernelGGL(resblock_bwd16_walk_kernel<decltype(r)::value>, dim3(unsigned(parts + helpers)), dim3(G::NT), plan->lds, s, a, p.t);
         });
     }
     rbw_pending(a, G::C, parts, G::PSTRIDE, pset, out);

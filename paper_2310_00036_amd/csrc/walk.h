@@ -45,6 +45,12 @@ inline void walk_dispatch(int R, F&& f) {
     if (R == R0) f(std::integral_constant<int, R0>{});
     else if constexpr (R0 < MAXR) walk_dispatch<MAXR, R0 + 1>(R, f);
 }
+template <class A>
+inline int pending_helpers(const A& a, int parts, int room) {
+    const int blocks = (a.pend.nparts > 0 ? a.pend.pstride / 64 : 0) + (a.pend2.nparts > 0 ? a.pend2.pstride / 64 : 0);
+    return pend_helpers(blocks, parts, room);
+}
+
 // The last tile shapes chosen, per thread (the choice takes some microseconds): a few entries by
 // problem size, overwritten in turn.
 template <class Tile>

@@ -24,6 +24,17 @@ CB_HD inline int walk_win_bytes(int px, int F, int rows, int W) {
     return ((F * rows * walk_pitch(W) + 1) * px + 1023) / 1024 * 1024;
 }
 
+// Workgroups added to a launch whose own `parts` leave some of its `room` free, to do the pending
+// reduces (`blocks` blocks of 64 entries in all, about 2.3 us each; pending_reduces in common.h) beside
+// its tiles. Without them the tiles wait for ceil(blocks / parts) blocks in turn: 8 frames of 9x9 with
+// 32 channels 32 us a launch in a chain against 9, 116 of 21x21 24 against 18; 2 of 11x11 with 64
+// channels 132 against 10, 87 of 12x9 28 against 16. None where they would take more than twice as many
+// in turn, which shows: 119 of 42x42 with 16 channels, 5 blocks for each of 18 against 1, 23 us against 20.
+inline int pend_helpers(int blocks, int parts, int room) {
+    const int spare = std::min(room - parts, blocks);
+    return spare > 0 && blocks <= 2 * spare * ((blocks + parts - 1) / parts) ? spare : 0;
+}
+
 // Rows a wave walks (its filling counted as 0.7 rows per walk) where `waves` waves take groups of
 // gw anchors, segments of R <= rows rows; nseg: segments per column.
 inline double walk_rows(int rows, int cols, int gw, int waves, int R, int& nseg) {
@@ -235,6 +246,7 @@ inline bool rbt_shape(int64_t n, int H, int W, int cus, size_t limit, RbtTile& t
 // The 16-channel block backward's launch: whichever form's estimate is the shorter.
 struct Rb16Plan {
     bool tiles;      // tile by tile (u), else column walks (t)
+    int room;        // tile by tile: the most workgroups (the launcher's)
     RbwTile t;
     RbtTile u;
 };

@@ -239,17 +239,14 @@ def test_actor_step_samples_as_the_sampling_call_does(n, A, keep_logits):
         assert torch.equal(v.view(torch.int32), value.view(torch.int32))
 
 
-def test_network_backward_through_the_tile_by_tile_kernel():
-    """The whole backward on 1700 frames of 58x68, whose first-stage blocks (29x34) are taken tile by tile and sum
-    the launches' partials before them at their start, against the sum over two halves, which walk. A partial of
-    the launch before it left out would move its weight gradient by a few percent."""
+def _network_backward_against_two_halves(ch, n, H, W):
     from types import SimpleNamespace
     P = _p()
-    n, half = 1700, 850
-    net = SimpleNamespace(in_h=58, in_w=68, in_c=4, ch=(16, 32, 32), hidden=256, num_actions=6)
-    g = torch.Generator(device="cuda:0").manual_seed(58)
+    half = n // 2
+    net = SimpleNamespace(in_h=H, in_w=W, in_c=4, ch=ch, hidden=256, num_actions=6)
+    g = torch.Generator(device="cuda:0").manual_seed(H)
     params = torch.randn(P.impala_param_count(net), generator=g, device="cuda:0") * 0.05
-    obs = torch.randint(0, 256, (n, 58, 68, 4), generator=g, device="cuda:0", dtype=torch.int32).to(torch.uint8)
+    obs = torch.randint(0, 256, (n, H, W, 4), generator=g, device="cuda:0", dtype=torch.int32).to(torch.uint8)
     dz, dv = torch.randn((n, 6), generator=g, device="cuda:0"), torch.randn(n, generator=g, device="cuda:0")
 
     def forward(o):
@@ -259,10 +256,10 @@ def test_network_backward_through_the_tile_by_tile_kernel():
                          torch.empty(k, device="cuda:0"))
         return ws
 
-    whole, want = torch.empty_like(params), torch.zeros(params.numel(), dtype=torch.float64, device="cuda:0")
+    whole, want = torch.full_like(params, float("nan")), torch.zeros(params.numel(), dtype=torch.float64, device="cuda:0")
     ws = forward(obs)
     for a in (0, half):
-        o, part = obs[a:a + half].contiguous(), torch.empty_like(params)
+        o, part = obs[a:a + half].contiguous(), torch.full_like(params, float("nan"))
         wh = forward(o)
         # the whole's activations, which both differentiate (the dense layer's sums group by frame count)
         for (name, off, size, _, _), (_, at, hsize, _, _) in zip(P.impala_activation_layout(net, P.PREC_BF16, n),
@@ -279,3 +276,19 @@ def test_network_backward_through_the_tile_by_tile_kernel():
     for name, shape, off in P.impala_param_layout(net):
         w, q = want[off:off + int(np.prod(shape))], whole[off:off + int(np.prod(shape))].double()
         assert (w - q).norm() <= 2.0 ** -10 * w.norm() + 1e-30, (name, float((w - q).norm() / w.norm()))
+
+
+def test_network_backward_through_the_tile_by_tile_kernel():
+    """The whole backward on 1700 frames of 58x68, whose first-stage blocks (29x34) are taken tile by tile and sum
+    the launches' partials before them at their start, against the sum over two halves, which walk. A partial of
+    the launch before it left out would move its weight gradient by a few percent."""
+    _network_backward_against_two_halves((16, 32, 32), 1700, 58, 68)
+
+
+@pytest.mark.parametrize("ch,n,H,W", [((16, 32, 32), 2, 84, 84), ((16, 32, 32), 24, 84, 84), ((16, 32, 32), 116, 84, 84),
+                                      ((16, 32, 32), 250, 84, 84), ((16, 32, 32), 340, 45, 61), ((32, 64, 64), 2, 40, 44),
+                                      ((32, 64, 64), 88, 46, 36), ((32, 64, 64), 150, 84, 84), ((16, 16, 32), 400, 84, 84)])
+def test_network_backward_of_few_frames(ch, n, H, W):
+    """Launches that leave compute units idle, on which the partial sums of the launches before are added up: every
+    weight gradient is written, and is the sum of the halves'."""
+    _network_backward_against_two_halves(ch, n, H, W)

@@ -25,7 +25,8 @@ def plan(tmp_path_factory):
     so = str(tmp_path_factory.mktemp("walkplan") / "walkplan.so")
     subprocess.run([cxx, "-O1", "-std=c++17", "-Wall", "-Werror", "-shared", "-fPIC", "-o", so,
                     os.path.join(HERE, "walkplan_driver.cpp")], check=True)
-    fn = C.CDLL(so).walk_plan
+    lib = C.CDLL(so)
+    fn = lib.walk_plan
     fn.argtypes = [C.c_char_p, C.c_int64, C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int64)]
 
     def choose(kind, n, H, W):
@@ -34,6 +35,7 @@ def plan(tmp_path_factory):
             return None
         return dict(zip(("F", "TH", "bands", "tiles", "R", "lds"), out))
 
+    choose.pend_helpers = lib.walk_pend_helpers
     return choose
 
 
@@ -114,3 +116,19 @@ def test_every_kernel_instance_is_compared_on_the_gpu(plan):
     assert rows("c64", SHAPES) == set(range(1, 8))
     assert all(plan("c64", *c) is None for c in WIDE64)
     assert plan("t16", 1700, 29, 34)["R"] == 0 and plan("t16", 850, 29, 34)["R"] > 0   # (the network's backward)
+
+
+@pytest.mark.parametrize("blocks,kind,n,H,W,helped", [(304, "b32", 8, 9, 9, True), (304, "b32", 114, 21, 21, True), (304, "b32", 301, 11, 11, True),
+                                                      (304, "b32", 304, 21, 21, False), (592, "c64", 2, 11, 11, True), (592, "c64", 87, 12, 9, True),
+                                                      (592, "c64", 105, 22, 18, False), (80, "b16", 94, 42, 42, True), (80, "b16", 119, 42, 42, False),
+                                                      (0, "b32", 8, 9, 9, False)])
+def test_idle_units_take_the_pending_sums(plan, blocks, kind, n, H, W, helped):
+    """The partial sums of the launches before (152 blocks of 64 entries per 32-channel weight, 592 of 64, 40 of 16) are added up beside
+    the tiles where enough compute units have none: 8 frames of 9x9 waited 23 us for them. No launch grows past the units."""
+    parts = min(CUS, plan(kind, n, H, W)["tiles"])
+    k = plan.pend_helpers(blocks, parts, CUS)
+    assert (k > 0) == helped, (parts, k)
+    for parts in range(1, CUS + 1):
+        k = plan.pend_helpers(blocks, parts, CUS)
+        assert 0 <= k <= min(blocks, CUS - parts)
+        assert k == 0 or -(-blocks // k) <= 2 * -(-blocks // parts)

@@ -33,3 +33,5 @@ extern "C" int walk_plan(const char* kind, int64_t n, int H, int W, int cus, int
     }
     return 0;
 }
+
+extern "C" int walk_pend_helpers(int blocks, int parts, int room) { return pend_helpers(blocks, parts, room); }
