@@ -286,17 +286,19 @@ CB_DEV void sum_partials_x4(const float* __restrict__ partial, int nparts, int p
 // A pending weight-gradient reduce (PendingReduce, see kernels.h) done by the first work of a
 // kernel with NT threads: blocks of 64 entries (16 float4 lanes x NT/16 slices, each slice
 // adding the partials s, s + NT/16, ... in turn, then a fixed pairwise tree), of which this
-// workgroup does first, first + step, ..., scattered to HWIO weights (times scale) and the bias. `lds` holds NT/16 x 17 float4.
-// Ends with a barrier, so the caller may reuse the LDS.
-template <int NT, class R>
-CB_DEV void pending_reduce(const R& r, unsigned char* lds, int first, int step) {
+// workgroup does first(), first() + step(), ..., scattered to HWIO weights (times scale) and the
+// bias. `lds` holds NT/16 x 17 float4. Ends with a barrier, so the caller may reuse the LDS.
+// (Functions, evaluated where they stand: as values, blockIdx.x and gridDim.x stay in registers of
+// the callers' main loops, 121.5 against 123.5 us for 16 -> 32 channels on 2048 frames of 42x42.)
+template <int NT, class R, class F, class S>
+CB_DEV void pending_reduce(const R& r, unsigned char* lds, F first, S step) {
     constexpr int SL = NT / 16;
     float4* sh = reinterpret_cast<float4*>(lds);
     const int q = threadIdx.x & 15, sl = threadIdx.x >> 4;
     const int NB = r.u8 ? 3 : 9 * r.cin / 16, NBB = NB + 1, cb16 = r.cin / 16 > 0 ? r.cin / 16 : 1;
     const int nrb = r.pstride / 64;
     const int64_t st = r.pstride / 4;
-    for (int rb = first; rb < nrb; rb += step) {
+    for (int rb = first(); rb < nrb; rb += step()) {
         const int e = rb * 64 + 4 * q;
         const float4* p = reinterpret_cast<const float4*>(r.partial + e);
         float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -345,7 +347,7 @@ CB_DEV void pending_reduce(const R& r, unsigned char* lds, int first, int step) 
 }
 template <int NT, class R>
 CB_DEV void pending_reduce(const R& r, unsigned char* lds) {
-    pending_reduce<NT>(r, lds, blockIdx.x, gridDim.x);
+    pending_reduce<NT>(r, lds, [] { return blockIdx.x; }, [] { return gridDim.x; });
 }
 
 // Both pending reduces of a launch, `parts` of whose workgroups have tiles: the further ones do all of
@@ -358,11 +360,11 @@ CB_DEV bool pending_reduces(const A& a, int parts, unsigned char* lds) {
     const int step = helper ? int(gridDim.x) - parts : parts;
     int rank = helper ? int(blockIdx.x) - parts : int(blockIdx.x);
     if (a.pend.nparts > 0) {
-        pending_reduce<NT>(a.pend, lds, rank, step);
+        pending_reduce<NT>(a.pend, lds, [&] { return rank; }, [&] { return step; });
         rank -= a.pend.pstride / 64 % step;   // the second set's blocks go on where the first's end
         rank += rank < 0 ? step : 0;
     }
-    if (a.pend2.nparts > 0) pending_reduce<NT>(a.pend2, lds, rank, step);
+    if (a.pend2.nparts > 0) pending_reduce<NT>(a.pend2, lds, [&] { return rank; }, [&] { return step; });
     if (helper) __builtin_amdgcn_s_waitcnt(0);   // windows being staged land before their LDS is given back
     return helper;
 }
