@@ -1019,12 +1019,12 @@ __global__ __launch_bounds__(64 * NW, (CbGeom<CI, CO>::WPS)) void conv_bwd_spec_
 // 21x21 91 -> 59, 40 of 11x11 26 -> 20, 5 of 21x21 26 -> 16. What bounds it: the MFMAs of a SIMD's two waves
 // (230 us at the matrix cores' rate at 21x21) and the vector instructions between them. (Tile shapes:
 // walkplan.h.)
-template <int R, int ADD>
+template <int R, int ADD, bool HELP>
 __global__ __launch_bounds__(Cw64Geom::NT, 2) void conv_bwd64_walk_kernel(ConvBwdArgs a, Cw64Tile t) {
     using G = Cw64Geom;
     constexpr int NT = G::NT, NS = G::NS, C = G::C;
     extern __shared__ __align__(16) unsigned char smem[];
-    const int G0 = t.parts;   // workgroups with tiles
+    if (HELP && pending_helper<NT>(a, t.parts, smem)) return;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1033,7 +1033,10 @@ __global__ __launch_bounds__(Cw64Geom::NT, 2) void conv_bwd64_walk_kernel(ConvBw
     const int H = a.H, W = a.W, F = t.F, TH = t.TH, TW = walk_pitch(W);
     const int pf = (TH + 2) * TW, nsl = (F * pf + 1) * 8, rowb = TW * 128, cols = F * W;
 
-    if (pending_reduces<NT>(a, G0, smem)) return;
+    if constexpr (!HELP) {
+        if (a.pend.nparts > 0) pending_reduce<NT>(a.pend, smem);
+        if (a.pend2.nparts > 0) pending_reduce<NT>(a.pend2, smem);
+    }
     // ---- weights: A[o][tap * 64 + co] = w[8 - tap][o][co], packed into A fragments in LDS (73 KB):
     // fragment (o / 32, b, k-step), whose row 4 i + j is channel 32 (o / 32) + 8 i + 4 b + j
     {
@@ -1057,7 +1060,9 @@ __global__ __launch_bounds__(Cw64Geom::NT, 2) void conv_bwd64_walk_kernel(ConvBw
     __syncthreads();
 
     int lg = blockIdx.x;   // neighbouring bands (which share halo rows) on one XCD
-    if ((G0 & 7) == 0) lg = (blockIdx.x & 7) * (G0 >> 3) + (blockIdx.x >> 3);
+    const unsigned nwg = HELP ? t.parts : gridDim.x;   // workgroups with tiles
+    if ((nwg & 7) == 0) lg = (blockIdx.x & 7) * (nwg >> 3) + (blockIdx.x >> 3);
+    const int G0 = int(nwg);
 
     if (dgrad) {
         const int oh = rw & 1;
@@ -1237,7 +1242,8 @@ hipError_t cw64_launch(const ConvBwdArgs& a, hipStream_t s, int& parts) {
     const int helpers = pending_helpers(a, parts, cus);
     walk_dispatch<G::MAXR>(plan->t.R, [&](auto r) {
         ProfScope ps(s, [&] { return cb_key("conv_bwd", 0, cb_dims(64, 64) + "/" + cb_dims(H, W) + cb_flags(IN_RELU, false, ADD)); });
-        hipLaunchKernelGGL((conv_bwd64_walk_kernel<decltype(r)::value, ADD>), dim3(unsigned(parts + helpers)), dim3(G::NT), plan->lds, s, a, plan->t);
+        const auto kernel = helpers ? conv_bwd64_walk_kernel<decltype(r)::value, ADD, true> : conv_bwd64_walk_kernel<decltype(r)::value, ADD, false>;
+        hipLaunchKernelGGL(kernel, dim3(unsigned(parts + helpers)), dim3(G::NT), plan->lds, s, a, plan->t);
     });
     return hipGetLastError();
 }

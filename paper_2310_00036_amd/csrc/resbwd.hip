@@ -32,7 +32,7 @@ CB_DEV void rbw_stage(const ResBwdArgs& a, const RbwTile& t, const void* src, un
                       const uint32_t (&off)[N], int wave, int tile, int row) {
     constexpr int NW = RbwGeom::NW;
     const int band = tile % t.nbands, f = (tile / t.nbands) * t.F;
-    const int nf = std::max(std::min(a.n - f, t.F), 0), fel = a.H * a.W * C;
+    const int nf = a.n - f < t.F ? a.n - f : t.F, fel = a.H * a.W * C;
     const auto r = buf_rsrc(static_cast<const uint16_t*>(src) + int64_t(f) * fel, uint32_t(nf) * fel * 2);
     const uint32_t hr = uint32_t((band * t.TH - row) * a.W * C * 2);   // wraps above the frame
 #pragma unroll
@@ -77,12 +77,12 @@ CB_DEV void rbw_landed(unsigned char* win, int ns, int wave, int lane) {
 // L2), the matrix cores are busy 0.33 of the time. What bounds it: a SIMD's MFMAs (about 270 of 16 cycles
 // per phase) and the vector instructions of its two waves, and the loads of a phase, which add up with its
 // work (walkplan.h); then barriers.
-template <int R>
+template <int R, bool HELP>
 __global__ __launch_bounds__(RbwGeom::NT, 2) void resblock_bwd_walk_kernel(ResBwdArgs a, RbwTile t) {
     using G = RbwGeom;
     constexpr int NT = G::NT, NW = G::NW, NS = G::NS, C = G::C;
     extern __shared__ __align__(16) unsigned char smem[];
-    const int G0 = t.pset / G::PSTRIDE;      // workgroups with tiles
+    if (HELP && pending_helper<NT>(a, t.pset / G::PSTRIDE, smem)) return;
     unsigned char* dyw = smem;               // dy [F][TH+2+2ho][TW], row 0 = image row h0-1-ho
     unsigned char* tw = smem + t.t_off;      // relu(t) [F][TH+2][TW], row 0 = image row h0-1
     unsigned char* xw = smem + t.x_off;      // relu(x), likewise
@@ -114,8 +114,9 @@ __global__ __launch_bounds__(RbwGeom::NT, 2) void resblock_bwd_walk_kernel(ResBw
     const int rd = ho ? 2 : 0, rx = ho ? 1 : 0;   // a window's first row above the band (whole frames: in the offsets)
 
     int lg = blockIdx.x;   // neighbouring bands (which share halo rows) on one XCD
-    if ((G0 & 7) == 0) lg = (blockIdx.x & 7) * (G0 >> 3) + (blockIdx.x >> 3);
-    if (int(blockIdx.x) >= G0) lg = t.ntiles;   // past the frames: stages zeros
+    const unsigned nwg = HELP ? t.pset / G::PSTRIDE : gridDim.x;   // workgroups with tiles
+    if ((nwg & 7) == 0) lg = (blockIdx.x & 7) * (nwg >> 3) + (blockIdx.x >> 3);
+    const int G0 = int(nwg);
 
     // ---- weights, loaded first and packed below: 4 k-values (output channels of the forward) of one
     // input channel o per unit; A[o][tap * 32 + co] = w[8 - tap][o][co]
@@ -140,7 +141,10 @@ __global__ __launch_bounds__(RbwGeom::NT, 2) void resblock_bwd_walk_kernel(ResBw
     rbw_stage<C>(a, t, a.dy, dyw, nsd, od, wave, lg, rd);
     rbw_stage<C>(a, t, a.t, tw, nsx, ox, wave, lg, rx);
     // earlier launches' weight-gradient partials
-    if (pending_reduces<NT>(a, G0, dtw)) return;
+    if constexpr (!HELP) {
+        if (a.pend.nparts > 0) pending_reduce<NT>(a.pend, dtw);
+        if (a.pend2.nparts > 0) pending_reduce<NT>(a.pend2, dtw);
+    }
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
         const int id = tid + u * NT, cv = id >= UNITS / 2, r = id - cv * (UNITS / 2);
@@ -315,12 +319,12 @@ __global__ __launch_bounds__(RbwGeom::NT, 2) void resblock_bwd_walk_kernel(ResBw
 // Two workgroups of this form per CU (80 KB windows, 128 registers, which spill) were slower. What bounds it:
 // 462 MB (468 move) at the rate of a large copy are 97 us; the rest is work and loads of a phase that add up,
 // and barriers.
-template <int R>
+template <int R, bool HELP>
 __global__ __launch_bounds__(Rbw16Geom::NT, 2) void resblock_bwd16_walk_kernel(ResBwdArgs a, RbwTile t) {
     using G = Rbw16Geom;
     constexpr int NT = G::NT, NW = G::NW, NS = G::NS, C = G::C;
     extern __shared__ __align__(16) unsigned char smem[];
-    const int G0 = t.pset / G::PSTRIDE;      // workgroups with tiles
+    if (HELP && pending_helper<NT>(a, t.pset / G::PSTRIDE, smem)) return;
     unsigned char* dyw = smem;               // dy [F][TH+2+2ho][TW], row 0 = image row h0-1-ho
     unsigned char* tw = smem + t.t_off;      // relu(t) [F][TH+2][TW], row 0 = image row h0-1
     unsigned char* xw = smem + t.x_off;      // relu(x), likewise
@@ -351,8 +355,9 @@ __global__ __launch_bounds__(Rbw16Geom::NT, 2) void resblock_bwd16_walk_kernel(R
     const int rd = ho ? 2 : 0, rx = ho ? 1 : 0;   // a window's first row above the band (whole frames: in the offsets)
 
     int lg = blockIdx.x;   // neighbouring bands (which share halo rows) on one XCD
-    if ((G0 & 7) == 0) lg = (blockIdx.x & 7) * (G0 >> 3) + (blockIdx.x >> 3);
-    if (int(blockIdx.x) >= G0) lg = t.ntiles;   // past the frames: stages zeros
+    const unsigned nwg = HELP ? t.pset / G::PSTRIDE : gridDim.x;   // workgroups with tiles
+    if ((nwg & 7) == 0) lg = (blockIdx.x & 7) * (nwg >> 3) + (blockIdx.x >> 3);
+    const int G0 = int(nwg);
 
 #pragma unroll
     for (int k = 0; k < G::MAXD; ++k) od[k] = win_off((wave + NW * k) * 64 + lane, nsd, dpf, t.inv_dpf);
@@ -366,7 +371,10 @@ __global__ __launch_bounds__(Rbw16Geom::NT, 2) void resblock_bwd16_walk_kernel(R
     rbw_stage<C>(a, t, a.dy, dyw, nsd, od, wave, lg, rd);
     rbw_stage<C>(a, t, a.t, tw, nsx, ox, wave, lg, rx);
     // earlier launches' weight-gradient partials
-    if (pending_reduces<NT>(a, G0, dtw)) return;
+    if constexpr (!HELP) {
+        if (a.pend.nparts > 0) pending_reduce<NT>(a.pend, dtw);
+        if (a.pend2.nparts > 0) pending_reduce<NT>(a.pend2, dtw);
+    }
     lds_barrier();
     // the dt window: its padding and, for whole frames, its rows off the frame are never written
     auto clear_dt = [&] {
@@ -550,6 +558,7 @@ __global__ __launch_bounds__(Rbw16Geom::NT, 2) void resblock_bwd16_walk_kernel(R
 // whole segments of rows. Walks against tiles, in turn on one card: 2048 frames of 42x42 144 against 155
 // us, 8192 of 21x21 134 against 152; but 8192 of 30x45 469 against 411, 32x32 347 against 320, 48x40 614
 // against 569, 2048 of 84x84 658 against 593. walkplan.h estimates both and takes the shorter.
+template <bool HELP>
 __global__ __launch_bounds__(RbtGeom::NT, 4) void resblock_bwd16_tile_kernel(ResBwdArgs a, RbtTile t) {
     using G = RbtGeom;
     constexpr int C = G::C, NW = G::NW, NT = G::NT, PX = G::PX, NB = G::NBB - 1;
@@ -559,7 +568,7 @@ __global__ __launch_bounds__(RbtGeom::NT, 4) void resblock_bwd16_tile_kernel(Res
     constexpr int NWG = NW / 2, TPW = (G::NBB + NWG - 1) / NWG;
 
     extern __shared__ __align__(16) unsigned char smem[];
-    const int G0 = t.pset / G::PSTRIDE;           // workgroups with tiles
+    if (HELP && pending_helper<NT>(a, t.pset / G::PSTRIDE, smem)) return;
     unsigned char* zero = smem;                   // 64 zero bytes
     unsigned char* dyw = smem + t.dy_off;         // dy [TH+4][W+2], row 0 = image row h0-2
     unsigned char* tw = smem + t.t_off + PX;      // relu(t) [TH+2][W+2], row 0 = h0-1, guard pixels
@@ -572,7 +581,10 @@ __global__ __launch_bounds__(RbtGeom::NT, 4) void resblock_bwd16_tile_kernel(Res
     const int H = a.H, W = a.W, TH = t.TH, TW = W + 2;
 
     // earlier launches' weight-gradient partials, summed first (LDS is free until staging)
-    if (pending_reduces<NT>(a, G0, smem)) return;
+    if constexpr (!HELP) {
+        if (a.pend.nparts > 0) pending_reduce<NT>(a.pend, smem);
+        if (a.pend2.nparts > 0) pending_reduce<NT>(a.pend2, smem);
+    }
     if (tid < 16) reinterpret_cast<uint32_t*>(zero)[tid] = 0u;
     // the dt window: its padding columns are never written
     for (int j = tid; j < t.dt_bytes / 16; j += NT) reinterpret_cast<uint4*>(dtw)[j] = make_uint4(0, 0, 0, 0);
@@ -703,9 +715,10 @@ __global__ __launch_bounds__(RbtGeom::NT, 4) void resblock_bwd16_tile_kernel(Res
     };
 
     int lg = blockIdx.x;   // neighbouring bands (which share halo rows) on one XCD
-    if ((G0 & 7) == 0) lg = (blockIdx.x & 7) * (G0 >> 3) + (blockIdx.x >> 3);
+    const unsigned nwg = HELP ? t.pset / G::PSTRIDE : gridDim.x;   // workgroups with tiles
+    if ((nwg & 7) == 0) lg = (blockIdx.x & 7) * (nwg >> 3) + (blockIdx.x >> 3);
 
-    for (int tile = lg; tile < t.ntiles; tile += G0) {
+    for (int tile = lg; tile < t.ntiles; tile += nwg) {
         const int band = tile % t.nbands, f = tile / t.nbands;
         const int h0 = band * TH, the = H - h0 < TH ? H - h0 : TH;
         const int64_t fo = int64_t(f) * H * W * C;   // the frame's first element
@@ -840,7 +853,8 @@ hipError_t rb32_launch(const ResBwdArgs& a, hipStream_t s, PendingReduce out[2])
     const int parts = plan->t.pset / G::PSTRIDE, helpers = pending_helpers(a, parts, cus);
     walk_dispatch<G::MAXR>(plan->t.R, [&](auto r) {
         ProfScope ps(s, [&] { return cb_key("resblock_bwd", 0, cb_dims(G::C, G::C) + "/" + cb_dims(H, W)); });
-        hipLaunchKernelGGL(resblock_bwd_walk_kernel<decltype(r)::value>, dim3(unsigned(parts + helpers)), dim3(G::NT), plan->lds, s, a, plan->t);
+        const auto kernel = helpers ? resblock_bwd_walk_kernel<decltype(r)::value, true> : resblock_bwd_walk_kernel<decltype(r)::value, false>;
+        hipLaunchKernelGGL(kernel, dim3(unsigned(parts + helpers)), dim3(G::NT), plan->lds, s, a, plan->t);
     });
     rbw_pending(a, G::C, parts, G::PSTRIDE, plan->t.pset, out);
     return hipGetLastError();
@@ -858,7 +872,7 @@ hipError_t rb16_launch(const ResBwdArgs& a, hipStream_t s, PendingReduce out[2])
         size_t L = 0;
         if (!rb16_choose(a.n, H, W, cus, limit, p, L)) return hipErrorInvalidValue;
         if (p.tiles) {
-            const void* fn = reinterpret_cast<const void*>(&resblock_bwd16_tile_kernel);
+            const void* fn = reinterpret_cast<const void*>(&resblock_bwd16_tile_kernel<false>);
             const int room = int(resblock_bwd_partial_floats(G::C) / (2 * size_t(G::PSTRIDE)));
             p.room = std::min(std::max(1, resident_blocks(fn, RbtGeom::NT, L)), room);
             p.u.pset = std::min(p.room, p.u.ntiles) * G::PSTRIDE;
@@ -871,11 +885,13 @@ hipError_t rb16_launch(const ResBwdArgs& a, hipStream_t s, PendingReduce out[2])
     auto scope = [&] { return cb_key("resblock_bwd", 0, cb_dims(G::C, G::C) + "/" + cb_dims(H, W)); };
     if (p.tiles) {
         ProfScope ps(s, scope);
-        hipLaunchKernelGGL(resblock_bwd16_tile_kernel, dim3(unsigned(parts + helpers)), dim3(RbtGeom::NT), plan->lds, s, a, p.u);
+        const auto kernel = helpers ? resblock_bwd16_tile_kernel<true> : resblock_bwd16_tile_kernel<false>;
+        hipLaunchKernelGGL(kernel, dim3(unsigned(parts + helpers)), dim3(RbtGeom::NT), plan->lds, s, a, p.u);
     } else {
         walk_dispatch<G::MAXR>(p.t.R, [&](auto r) {
             ProfScope ps(s, scope);
-            hipLaunchKernelGGL(resblock_bwd16_walk_kernel<decltype(r)::value>, dim3(unsigned(parts + helpers)), dim3(G::NT), plan->lds, s, a, p.t);
+            const auto kernel = helpers ? resblock_bwd16_walk_kernel<decltype(r)::value, true> : resblock_bwd16_walk_kernel<decltype(r)::value, false>;
+            hipLaunchKernelGGL(kernel, dim3(unsigned(parts + helpers)), dim3(G::NT), plan->lds, s, a, p.t);
         });
     }
     rbw_pending(a, G::C, parts, G::PSTRIDE, pset, out);

@@ -25,7 +25,7 @@ CB_HD inline int walk_win_bytes(int px, int F, int rows, int W) {
 }
 
 // Workgroups added to a launch whose own `parts` leave some of its `room` free, to do the pending
-// reduces (`blocks` blocks of 64 entries in all, about 2.3 us each; pending_reduces in common.h) beside
+// reduces (`blocks` blocks of 64 entries in all, about 2.3 us each; pending_helper in common.h) beside
 // its tiles. Without them the tiles wait for ceil(blocks / parts) blocks in turn: 8 frames of 9x9 with
 // 32 channels 32 us a launch in a chain against 9, 116 of 21x21 24 against 18; 2 of 11x11 with 64
 // channels 132 against 10, 87 of 12x9 28 against 16. None where they would take more than twice as many
