@@ -558,7 +558,6 @@ __global__ __launch_bounds__(Rbw16Geom::NT, 2) void resblock_bwd16_walk_kernel(R
 // whole segments of rows. Walks against tiles, in turn on one card: 2048 frames of 42x42 144 against 155
 // us, 8192 of 21x21 134 against 152; but 8192 of 30x45 469 against 411, 32x32 347 against 320, 48x40 614
 // against 569, 2048 of 84x84 658 against 593. walkplan.h estimates both and takes the shorter.
-template <bool HELP>
 __global__ __launch_bounds__(RbtGeom::NT, 4) void resblock_bwd16_tile_kernel(ResBwdArgs a, RbtTile t) {
     using G = RbtGeom;
     constexpr int C = G::C, NW = G::NW, NT = G::NT, PX = G::PX, NB = G::NBB - 1;
@@ -568,7 +567,6 @@ __global__ __launch_bounds__(RbtGeom::NT, 4) void resblock_bwd16_tile_kernel(Res
     constexpr int NWG = NW / 2, TPW = (G::NBB + NWG - 1) / NWG;
 
     extern __shared__ __align__(16) unsigned char smem[];
-    if (HELP && pending_helper<NT>(a, t.pset / G::PSTRIDE, smem)) return;
     unsigned char* zero = smem;                   // 64 zero bytes
     unsigned char* dyw = smem + t.dy_off;         // dy [TH+4][W+2], row 0 = image row h0-2
     unsigned char* tw = smem + t.t_off + PX;      // relu(t) [TH+2][W+2], row 0 = h0-1, guard pixels
@@ -581,10 +579,8 @@ __global__ __launch_bounds__(RbtGeom::NT, 4) void resblock_bwd16_tile_kernel(Res
     const int H = a.H, W = a.W, TH = t.TH, TW = W + 2;
 
     // earlier launches' weight-gradient partials, summed first (LDS is free until staging)
-    if constexpr (!HELP) {
-        if (a.pend.nparts > 0) pending_reduce<NT>(a.pend, smem);
-        if (a.pend2.nparts > 0) pending_reduce<NT>(a.pend2, smem);
-    }
+    if (a.pend.nparts > 0) pending_reduce<NT>(a.pend, smem);
+    if (a.pend2.nparts > 0) pending_reduce<NT>(a.pend2, smem);
     if (tid < 16) reinterpret_cast<uint32_t*>(zero)[tid] = 0u;
     // the dt window: its padding columns are never written
     for (int j = tid; j < t.dt_bytes / 16; j += NT) reinterpret_cast<uint4*>(dtw)[j] = make_uint4(0, 0, 0, 0);
@@ -715,10 +711,9 @@ __global__ __launch_bounds__(RbtGeom::NT, 4) void resblock_bwd16_tile_kernel(Res
     };
 
     int lg = blockIdx.x;   // neighbouring bands (which share halo rows) on one XCD
-    const unsigned nwg = HELP ? t.pset / G::PSTRIDE : gridDim.x;   // workgroups with tiles
-    if ((nwg & 7) == 0) lg = (blockIdx.x & 7) * (nwg >> 3) + (blockIdx.x >> 3);
+    if ((gridDim.x & 7) == 0) lg = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
 
-    for (int tile = lg; tile < t.ntiles; tile += nwg) {
+    for (int tile = lg; tile < t.ntiles; tile += gridDim.x) {
         const int band = tile % t.nbands, f = tile / t.nbands;
         const int h0 = band * TH, the = H - h0 < TH ? H - h0 : TH;
         const int64_t fo = int64_t(f) * H * W * C;   // the frame's first element
@@ -872,22 +867,20 @@ hipError_t rb16_launch(const ResBwdArgs& a, hipStream_t s, PendingReduce out[2])
         size_t L = 0;
         if (!rb16_choose(a.n, H, W, cus, limit, p, L)) return hipErrorInvalidValue;
         if (p.tiles) {
-            const void* fn = reinterpret_cast<const void*>(&resblock_bwd16_tile_kernel<false>);
+            const void* fn = reinterpret_cast<const void*>(&resblock_bwd16_tile_kernel);
             const int room = int(resblock_bwd_partial_floats(G::C) / (2 * size_t(G::PSTRIDE)));
-            p.room = std::min(std::max(1, resident_blocks(fn, RbtGeom::NT, L)), room);
-            p.u.pset = std::min(p.room, p.u.ntiles) * G::PSTRIDE;
+            p.u.pset = std::min({std::max(1, resident_blocks(fn, RbtGeom::NT, L)), room, p.u.ntiles}) * G::PSTRIDE;
         }
         plan = plans.put({a.n, H, W, cus, p, L});
     }
     const Rb16Plan& p = plan->t;
     const int pset = p.tiles ? p.u.pset : p.t.pset, parts = pset / G::PSTRIDE;
-    const int helpers = pending_helpers(a, parts, p.tiles ? p.room : cus);
     auto scope = [&] { return cb_key("resblock_bwd", 0, cb_dims(G::C, G::C) + "/" + cb_dims(H, W)); };
     if (p.tiles) {
         ProfScope ps(s, scope);
-        const auto kernel = helpers ? resblock_bwd16_tile_kernel<true> : resblock_bwd16_tile_kernel<false>;
-        hipLaunchKernelGGL(kernel, dim3(unsigned(parts + helpers)), dim3(RbtGeom::NT), plan->lds, s, a, p.u);
+        hipLaunchKernelGGL(resblock_bwd16_tile_kernel, dim3(unsigned(parts)), dim3(RbtGeom::NT), plan->lds, s, a, p.u);
     } else {
+        const int helpers = pending_helpers(a, parts, cus);   // (tiles are taken one by one only where they are many)
         walk_dispatch<G::MAXR>(p.t.R, [&](auto r) {
             ProfScope ps(s, scope);
             const auto kernel = helpers ? resblock_bwd16_walk_kernel<decltype(r)::value, true> : resblock_bwd16_walk_kernel<decltype(r)::value, false>;

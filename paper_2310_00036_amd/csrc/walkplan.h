@@ -246,7 +246,6 @@ inline bool rbt_shape(int64_t n, int H, int W, int cus, size_t limit, RbtTile& t
 // The 16-channel block backward's launch: whichever form's estimate is the shorter.
 struct Rb16Plan {
     bool tiles;      // tile by tile (u), else column walks (t)
-    int room;        // tile by tile: the most workgroups (the launcher's)
     RbwTile t;
     RbtTile u;
 };

@@ -287,7 +287,9 @@ def test_network_backward_through_the_tile_by_tile_kernel():
 
 @pytest.mark.parametrize("ch,n,H,W", [((16, 32, 32), 2, 84, 84), ((16, 32, 32), 24, 84, 84), ((16, 32, 32), 116, 84, 84),
                                       ((16, 32, 32), 250, 84, 84), ((16, 32, 32), 340, 45, 61), ((32, 64, 64), 2, 40, 44),
-                                      ((32, 64, 64), 88, 46, 36), ((32, 64, 64), 150, 84, 84), ((16, 16, 32), 400, 84, 84)])
+                                      ((32, 64, 64), 88, 46, 36), ((32, 64, 64), 150, 84, 84), ((16, 16, 32), 400, 84, 84),
+                                      # the row counts per walk that those above leave out
+                                      ((32, 64, 64), 40, 80, 105), ((16, 16, 32), 148, 29, 110)])
 def test_network_backward_of_few_frames(ch, n, H, W):
     """Launches that leave compute units idle, on which the partial sums of the launches before are added up: every
     weight gradient is written, and is the sum of the halves'."""

@@ -132,3 +132,11 @@ def test_idle_units_take_the_pending_sums(plan, blocks, kind, n, H, W, helped):
         k = plan.pend_helpers(blocks, parts, CUS)
         assert 0 <= k <= min(blocks, CUS - parts)
         assert k == 0 or -(-blocks // k) <= 2 * -(-blocks // parts)
+
+
+def test_tiles_are_taken_one_by_one_only_where_they_are_many(plan):
+    """The tile-by-tile kernel sums the launches before it in its own workgroups only: its launches leave no unit idle."""
+    for n in range(1, 512, 3):
+        for H, W in ((1, 64), (2, 3), (21, 21), (29, 34), (42, 42), (48, 40), (64, 64), (64, 17)):
+            p = plan("t16", n, H, W)
+            assert p["R"] or p["tiles"] >= 2 * CUS, (n, H, W, p)
